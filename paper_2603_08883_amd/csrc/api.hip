@@ -6,6 +6,7 @@
 #include <cstring>
 #include <string>
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <vector>
 
@@ -37,7 +38,9 @@ struct iqcc_ctx {
   int64_t inplace_cap = 0;                 // 0: as many stash entries as the LDS holds
   int64_t inplace_region_rows = 0;         // 0: regions share the arena minus the pool
   // device scratch
-  double* lut = nullptr;        // 8192: 3-qubit (4 x 22 x 64) or 4-qubit (2 x 16 x 256) tables
+  double* lut = nullptr;        // kLutDoubles: 3-qubit group table (4 x 22 x 64)
+  double* slots = nullptr;      // kFinishSlots finish slots, taken in turn
+  unsigned next_slot = 0;
   double* partial = nullptr;    // n_partial
   int64_t n_partial = 0;
   int64_t* scratch = nullptr;   // n_scratch
@@ -96,6 +99,16 @@ int fail(iqcc_ctx* ctx, int code, const char* fmt, ...) {
   } while (0)
 
 hipStream_t as_stream(void* s) { return (hipStream_t)s; }
+
+// Finish slots of a context: consecutive calls take them in turn, so calls
+// that overlap on different streams have partial sums and a counter of their
+// own as long as fewer than kFinishSlots are in flight.
+constexpr int kFinishSlots = 32;
+constexpr int kLutDoubles = kMaxWords * kGroupsPerWord * kLutEntries;
+
+double* take_slot(iqcc_ctx* ctx) {
+  return ctx->slots + (size_t)(ctx->next_slot++ % kFinishSlots) * kFinishSlot;
+}
 
 int ensure_scratch(iqcc_ctx* ctx, int64_t n) {
   if (n <= ctx->n_scratch) return IQCC_OK;
@@ -352,17 +365,15 @@ void inplace_geometry(const iqcc_ctx* ctx, const iqcc_store* st, int& m, int64_t
 }
 
 // ---- allocation-free QMF energy ----------------------------------------------
-// Device scratch of iqcc_qmf_energy_noalloc: the 3-qubit group table of the
-// QMF state (kMaxWords * 22 * 64 doubles) followed by the per-workgroup
-// partial sums (at most kNoAllocPartials).  Every device the library runs on
-// holds its own copy until the process ends; host code reaches it only
-// through the per-device address from hipGetSymbolAddress.
-constexpr int kNoAllocLut = 8192;   // energy table: 2 words x 16 nibbles x 256, or 4 x 22 x 64
-static_assert(kNoAllocLut >= 2 * 16 * 256 && kNoAllocLut >= kMaxWords * kGroupsPerWord * kLutEntries,
-              "the allocation-free energy table holds every table layout");
-constexpr int kNoAllocPartials = 8192;
+// Device scratch of iqcc_qmf_energy_noalloc: kNoAllocSlots finish slots, taken
+// in turn, zero at start (the state finish_arrive leaves).  Every device the
+// library runs on holds its own copy until the process ends; host code reaches
+// it only through the per-device address from hipGetSymbolAddress.
+constexpr int kNoAllocSlots = 8;
+constexpr int kNoAllocPartials = 8192;   // the largest grid the entry point accepts
 constexpr int kNoAllocDevices = 64;
-static __device__ __align__(256) double scratch[kNoAllocLut + kNoAllocPartials];
+static __device__ __align__(256) double scratch[kNoAllocSlots * kFinishSlot];
+std::atomic<unsigned> g_scratch_next{0};
 double* g_scratch[kNoAllocDevices] = {};
 std::mutex g_scratch_mu;
 
@@ -409,7 +420,12 @@ int iqcc_ctx_create(iqcc_ctx** out, int device) {
       ctx->lds_per_cu = (size_t)v;
   }
   noalloc_setup(device);
-  if (hipMalloc(&ctx->lut, sizeof(double) * 8192) != hipSuccess) {   // every energy table layout
+  const size_t slot_bytes = sizeof(double) * kFinishSlots * kFinishSlot;
+  if (hipMalloc(&ctx->lut, sizeof(double) * kLutDoubles) != hipSuccess ||
+      hipMalloc(&ctx->slots, slot_bytes) != hipSuccess || hipMemset(ctx->slots, 0, slot_bytes) != hipSuccess ||
+      hipDeviceSynchronize() != hipSuccess) {
+    if (ctx->lut) hipFree(ctx->lut);
+    if (ctx->slots) hipFree(ctx->slots);
     delete ctx;
     return IQCC_ERR_HIP;
   }
@@ -422,6 +438,7 @@ int iqcc_ctx_destroy(iqcc_ctx* ctx) {
   hipSetDevice(ctx->device);
   hipDeviceSynchronize();
   if (ctx->lut) hipFree(ctx->lut);
+  if (ctx->slots) hipFree(ctx->slots);
   if (ctx->partial) hipFree(ctx->partial);
   if (ctx->scratch) hipFree(ctx->scratch);
   delete ctx;
@@ -670,6 +687,12 @@ int iqcc_store_export(iqcc_ctx* ctx, const iqcc_store* st, uint64_t* x, uint64_t
 
 // ---- dressing ---------------------------------------------------------------
 
+// *out = <h>; the caller checks the launch
+static void energy_sum(iqcc_ctx* ctx, const iqcc_store* h, const double* theta, const double* phi, double* slot,
+                       double* out, hipStream_t s) {
+  launch_energy(h->W, h->nq, h->d, ctx->n_cu, (int)ctx->energy_grid_per_cu, ctx->lds_per_cu, theta, phi, slot, out, s);
+}
+
 static int dress_impl(iqcc_ctx* ctx, const iqcc_store* in, const uint64_t* px, const uint64_t* pz,
                       double tau, double eps, const double* theta, const double* phi,
                       const double* energy_in, double* energy, iqcc_store* out,
@@ -708,7 +731,7 @@ static int dress_impl(iqcc_ctx* ctx, const iqcc_store* in, const uint64_t* px, c
   cfg.split_thr = ctx->split_bucket_terms;
   cfg.anti_cap = (int)ctx->anti_cap;
   cfg.grid = grid;
-  if (want_e) {
+  if (fused) {
     launch_build_lut(W, in->nq, theta, phi, ctx->lut, s);
     LAUNCH_CHECK(ctx);
   }
@@ -725,8 +748,8 @@ static int dress_impl(iqcc_ctx* ctx, const iqcc_store* in, const uint64_t* px, c
   out->floor = eps;
   out->regions = false;
   if (want_e) {
-    if (!fused) launch_energy(W, out->d, grid, ctx->lut, ctx->partial, s);
-    launch_finalize_sum(ctx->partial, grid, nullptr, energy, s, delta ? energy_in : nullptr);
+    if (fused) launch_finalize_sum(ctx->partial, grid, nullptr, energy, s, delta ? energy_in : nullptr);
+    else energy_sum(ctx, out, theta, phi, take_slot(ctx), energy, s);
     LAUNCH_CHECK(ctx);
   }
   return IQCC_OK;
@@ -797,12 +820,7 @@ int iqcc_dress_inplace(iqcc_ctx* ctx, iqcc_store* st, const uint64_t* px, const 
   LAUNCH_CHECK(ctx);
   st->floor = eps;
   if (want_e && !fused) {
-    const int eg = (int)(ctx->n_cu * ctx->energy_grid_per_cu);
-    rc = ensure_partial(ctx, eg);
-    if (rc) return rc;
-    launch_build_lut(W, st->nq, theta, phi, ctx->lut, s);
-    launch_energy(W, st->d, eg, ctx->lut, ctx->partial, s);
-    launch_finalize_sum(ctx->partial, eg, nullptr, energy_out, s);
+    energy_sum(ctx, st, theta, phi, take_slot(ctx), energy_out, s);
     LAUNCH_CHECK(ctx);
   }
   return IQCC_OK;
@@ -1125,12 +1143,7 @@ int iqcc_qmf_energy(iqcc_ctx* ctx, const iqcc_store* h, const double* theta, con
   int rc = check_ctx(ctx);
   if (rc) return rc;
   if (!h || !theta || !phi || !energy) return fail(ctx, IQCC_ERR_INVALID_ARG, "null argument");
-  hipStream_t s = as_stream(stream);
-  const int grid = (int)(ctx->n_cu * ctx->energy_grid_per_cu);
-  rc = ensure_partial(ctx, grid);
-  if (rc) return rc;
-  launch_energy_table(h->W, h->nq, h->d, grid, theta, phi, ctx->lut, ctx->partial, s);
-  launch_finalize_sum(ctx->partial, grid, nullptr, energy, s);
+  energy_sum(ctx, h, theta, phi, take_slot(ctx), energy, as_stream(stream));
   LAUNCH_CHECK(ctx);
   return IQCC_OK;
 }
@@ -1147,9 +1160,8 @@ int iqcc_qmf_energy_noalloc(iqcc_ctx* ctx, const iqcc_store* h, const double* th
     return fail(ctx, IQCC_ERR_CAPACITY,
                 "allocation-free energy holds %d workgroup partials, the grid needs %lld "
                 "(lower energy_grid_per_cu)", kNoAllocPartials, (long long)grid);
-  hipStream_t s = as_stream(stream);
-  launch_energy_table(h->W, h->nq, h->d, (int)grid, theta, phi, base, base + kNoAllocLut, s);
-  launch_finalize_sum(base + kNoAllocLut, (int)grid, nullptr, energy, s);
+  double* slot = base + (size_t)(g_scratch_next.fetch_add(1, std::memory_order_relaxed) % kNoAllocSlots) * kFinishSlot;
+  energy_sum(ctx, h, theta, phi, slot, energy, as_stream(stream));
   LAUNCH_CHECK(ctx);
   return IQCC_OK;
 }

@@ -202,6 +202,38 @@ __device__ __forceinline__ FixedSum block_fixed_sum(FixedSum f, long long* tmp_h
   return t;
 }
 
+// Finish slot of a launch: kFinishSlot doubles of device memory.  The first
+// kFinishHead hold arrival counters, zero between launches (a root and
+// kFinishFan leaves, each on a 128-byte line of its own), the rest one partial
+// sum per arriving workgroup.  finish_arrive (one thread of each of `count`
+// workgroups) leaves the partial and returns whether it was the last to
+// arrive; that workgroup then reads all of them with finish_partial.  The last
+// arrivals reset the counters for the next launch that uses the slot.  Up to
+// 2 kFinishFan workgroups meet at the root; more meet at the leaves first,
+// because arrivals at one address take their turns one by one.
+constexpr int kFinishFan = 16;
+constexpr int kFinishHead = 16 * (kFinishFan + 1);
+constexpr int kFinishSlot = 2048;
+constexpr int kFinishPartials = kFinishSlot - kFinishHead;
+
+__device__ __forceinline__ bool finish_count(unsigned* counter, unsigned count) {
+  const bool last = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == count - 1;
+  if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return last;
+}
+
+__device__ __forceinline__ bool finish_arrive(double* slot, unsigned index, double value, unsigned count) {
+  __hip_atomic_store(&slot[kFinishHead + index], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (count <= 2 * kFinishFan) return finish_count((unsigned*)slot, count);
+  const unsigned leaf = index % kFinishFan;
+  if (!finish_count((unsigned*)(slot + 16 * (1 + leaf)), (count - leaf + kFinishFan - 1) / kFinishFan)) return false;
+  return finish_count((unsigned*)slot, kFinishFan);
+}
+
+__device__ __forceinline__ double finish_partial(const double* slot, unsigned index) {
+  return __hip_atomic_load(&slot[kFinishHead + index], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Block-wide sum of doubles in a fixed order (lane tree, then waves in order).
 __device__ __forceinline__ double block_sum(double v, double* tmp) {
   const int lane = threadIdx.x & 63;
@@ -683,14 +715,10 @@ void launch_flip_rows(int W, const StoreDev& st, int w_max, uint64_t* ox, uint64
                       int64_t ld, unsigned long long* count, int grid, hipStream_t s);
 void launch_energy_anti(int W, const StoreDev& st, const PauliKey& P, int grid, const double* lut,
                         double* partial, hipStream_t s);
-// Stand-alone energy: builds the table (4-qubit groups for keys of up to two
-// words, else 3-qubit groups) into `lut` (energy_lut_doubles(W) doubles) and
-// writes grid partial sums.
-int energy_lut_doubles(int W);
-void launch_energy_table(int W, int nq, const StoreDev& st, int grid, const double* theta,
-                         const double* phi, double* lut, double* partial, hipStream_t s);
-void launch_energy(int W, const StoreDev& st, int grid, const double* lut, double* e_partial,
-                   hipStream_t s);
+// Stand-alone energy, one launch: *out = <st>.  per_cu: upper bound of the
+// workgroups per CU; slot: a finish slot (see finish_arrive).
+void launch_energy(int W, int nq, const StoreDev& st, int n_cu, int per_cu, size_t lds_per_cu, const double* theta,
+                   const double* phi, double* slot, double* out, hipStream_t s);
 int energy_bwd_blocks_per_cu(int W);
 void launch_energy_backward(int W, int nq, const StoreDev& st, int grid, const double* theta,
                             const double* phi, const double* lut, const double* dE,

@@ -3,8 +3,8 @@
 //
 // <K> of the product state is prod_j b_j(sigma_j) with b(I) = 1,
 // b(X) = sin t cos f, b(Y) = sin t sin f, b(Z) = cos t.  Terms are streamed
-// once; the product uses a 3-qubit-group table in LDS and skips identity
-// groups.  Partial sums are per workgroup and reduced in a fixed order.
+// once; the product uses a table per group of 4 (or 3) qubits in LDS.  Partial
+// sums are per workgroup and reduced in a fixed order.
 #include <cfloat>
 
 #include "iqcc_internal.h"
@@ -78,173 +78,156 @@ void launch_finalize_fixed(const double* parts, int n, double* out, hipStream_t 
   hipLaunchKernelGGL(k_finalize_fixed, dim3(1), dim3(kBlock), 0, s, parts, n, out);
 }
 
-// <K> from every 3-qubit group of every half word, identity groups included
-// (their table entry 0 is 1.0): a fixed, branch-free sequence of independent
-// lookups whose addresses take two VALU operations each.
-template <int W>
-__device__ __forceinline__ double expect_dense(const double* lut, const uint64_t* x,
-                                               const uint64_t* z) {
-  double p[4] = {1.0, 1.0, 1.0, 1.0};
-#pragma unroll
-  for (int h = 0; h < 2 * W; ++h) {
-    const uint32_t xh = (uint32_t)(x[h >> 1] >> (32 * (h & 1)));
-    const uint32_t zh = (uint32_t)(z[h >> 1] >> (32 * (h & 1)));
-    const double* lh = lut + h * kGroupsPerHalf * kLutEntries;
-#pragma unroll
-    for (int g = 0; g < kGroupsPerHalf; ++g) {
-      const uint32_t code = __builtin_amdgcn_ubfe(xh, 3 * g, 3) | (__builtin_amdgcn_ubfe(zh, 3 * g, 3) << 3);
-      p[g & 3] *= lh[g * kLutEntries + code];
-    }
-  }
-  return (p[0] * p[1]) * (p[2] * p[3]);
-}
-
 // ---------------------------------------------------------------------------
-// Energy of a store.  Workgroup g takes the groups of G consecutive buckets
-// g, g + grid, ... (G = 1 .. 256 so that every workgroup has a group); the
-// rows of a group's buckets are streamed as one flat range, kEItems terms per
-// thread and pass, so small buckets do not each cost a round trip.
+// Energy of a store in one launch.  Workgroup g takes the groups of G
+// consecutive buckets g, g + grid, ... (G = 1 .. 512 so that every workgroup
+// has a group); the rows of a group's buckets are streamed as one flat range,
+// kEItems terms per thread and pass, so small buckets do not each cost a round
+// trip.
+//
+// The product of a term comes from a table in LDS that every workgroup builds
+// from the angles.  Keys of one or two words: 4-qubit groups ("nibbles"), 16
+// per key word, 256 entries each (32 KB per word).  A byte of x and the same
+// byte of z hold two nibbles; two bit-field inserts per 32-bit half word put
+// the codes of its eight groups into the bytes of two registers, and each
+// lookup takes one byte extraction.  A code holds the four z bits below the
+// four x bits: most groups of a Jordan-Wigner string are Z strings (x = 0),
+// whose 16 codes then lie next to each other, in different LDS banks (with
+// the x bits low they were 16 entries apart and met in two banks: 156 us
+// against XXX us on 1.6e7 two-word terms).  Wider keys: 3-qubit groups, 22 per
+// word and 64 entries each, because nibble tables would leave one workgroup
+// per CU.
+//
+// The grid holds what the CUs keep resident (more workgroups would only build
+// more tables), and of it only as many workgroups take part ("active") as
+// there are passes of kEMinRows rows: below that a workgroup would spend its
+// time on its table and its arrival (17.1 us a call over the stores of a
+// 32-Hamiltonian batch with one workgroup per bucket, 12.3 us with this rule).
+// The active workgroups leave their sums in the finish slot; the last of them
+// to arrive adds them in a fixed order, so a call is one launch.
+//
+// Bound: HBM for large stores (40 bytes a two-word term), the chain of
+// latencies (bucket table, rows, table build, arrival) for small ones.
+// 1.6e7 two-word terms: 128 us, 5.0 TB/s (table, sums and reduction in three
+// launches: 168 us); 361 terms: 6.6 us (23 us).
 // ---------------------------------------------------------------------------
 constexpr int kEItems = 4;
-
-template <int W>
-__global__ __launch_bounds__(kBlock) void k_energy(StoreDev st, const double* lut_g, double* partial) {
-  __shared__ double lut[W * kGroupsPerWord * kLutEntries];
-  __shared__ double red[kWaves];
-  __shared__ uint64_t scan_tmp[kWaves];
-  __shared__ int64_t s_pre[kBlock + 1];
-  __shared__ int64_t s_off[kBlock];
-  for (int i = threadIdx.x; i < W * kGroupsPerWord * kLutEntries; i += kBlock) lut[i] = lut_g[i];
-  const int64_t B = 1ll << *st.m;
-  int64_t G = B / gridDim.x;
-  G = G < 1 ? 1 : (G > kBlock ? kBlock : G);
-  const int64_t ngroups = (B + G - 1) / G;
-  double acc = 0.0;
-  __syncthreads();
-  for (int64_t grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
-    const int64_t b = grp * G + threadIdx.x;
-    const bool mine = threadIdx.x < G && b < B;
-    const int64_t cnt = mine ? st.cnt[b] : 0;
-    const int64_t off = mine ? st.off[b] : 0;
-    uint64_t total;
-    const uint64_t ex = block_exclusive_scan((uint64_t)cnt, scan_tmp, total);
-    s_pre[threadIdx.x] = (int64_t)ex;
-    s_off[threadIdx.x] = off;
-    if (threadIdx.x == 0) s_pre[kBlock] = (int64_t)total;
-    __syncthreads();
-    const int64_t n = (int64_t)total;
-    for (int64_t i0 = 0; i0 < n; i0 += kBlock * kEItems) {
-      uint64_t kx[kEItems][W], kz[kEItems][W];
-      double kc[kEItems];
-#pragma unroll
-      for (int r = 0; r < kEItems; ++r) {
-        const int64_t i = i0 + r * kBlock + threadIdx.x;
-        kc[r] = 0.0;
-#pragma unroll
-        for (int w = 0; w < W; ++w) kx[r][w] = kz[r][w] = 0;
-        if (i < n) {
-          int lo = 0;   // the last bucket of the group whose first row is <= i
-#pragma unroll
-          for (int step = kBlock / 2; step; step >>= 1)
-            if (s_pre[lo + step] <= i) lo += step;
-          const int64_t row = s_off[lo] + (i - s_pre[lo]);
-#pragma unroll
-          for (int w = 0; w < W; ++w) {
-            kx[r][w] = __builtin_nontemporal_load(&st.x[w * st.cap + row]);
-            kz[r][w] = __builtin_nontemporal_load(&st.z[w * st.cap + row]);
-          }
-          kc[r] = __builtin_nontemporal_load(&st.c[row]);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < kEItems; ++r) acc += kc[r] * expect_dense<W>(lut, kx[r], kz[r]);
-    }
-    __syncthreads();
-  }
-  const double s = block_sum(acc, red);
-  if (threadIdx.x == 0) partial[blockIdx.x] = s;
-}
-
-void launch_energy(int W, const StoreDev& st, int grid, const double* lut, double* e_partial,
-                   hipStream_t s) {
-  switch (W) {
-    case 1: hipLaunchKernelGGL(k_energy<1>, dim3(grid), dim3(kBlock), 0, s, st, lut, e_partial); break;
-    case 2: hipLaunchKernelGGL(k_energy<2>, dim3(grid), dim3(kBlock), 0, s, st, lut, e_partial); break;
-    case 3: hipLaunchKernelGGL(k_energy<3>, dim3(grid), dim3(kBlock), 0, s, st, lut, e_partial); break;
-    default: hipLaunchKernelGGL(k_energy<4>, dim3(grid), dim3(kBlock), 0, s, st, lut, e_partial); break;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Stand-alone energy with a table per 4-qubit group ("nibble"): 16 groups per
-// key word, 256 entries each (4 x bits, 4 z bits), 32 KB per word in LDS, so
-// keys of up to two words.  A byte of x and the same byte of z hold two
-// nibbles; two bit-field inserts per 32-bit half word put the codes of its
-// eight groups into the bytes of two registers, and each lookup takes one byte
-// extraction: 32 lookups per two-word term instead of 44, at about a third of
-// the address arithmetic.
-// ---------------------------------------------------------------------------
+constexpr int64_t kEMinRows = 2048;
 constexpr int kNibbleEntries = 256;
 constexpr int kNibblesPerWord = 16;
 constexpr int kE4Block = 512;
 
-__global__ void k_build_lut4(int W, int nq, const double* theta, const double* phi, double* lut) {
-  const int n = W * kNibblesPerWord * kNibbleEntries;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
-    const int code = e % kNibbleEntries;
-    const int gi = e / kNibbleEntries;   // qubits 4 gi .. 4 gi + 3
-    double p = 1.0;
-    for (int r = 0; r < 4; ++r) {
-      const int q = 4 * gi + r;
-      if (q >= nq) continue;
-      const int op = ((code >> r) & 1) | (((code >> (4 + r)) & 1) << 1);
-      if (op == 0) continue;
-      double st, ct, sp, cp;
+template <int W>
+struct EnergyTable {
+  static constexpr bool kNibble = W <= 2;
+  static constexpr int kEntries = kNibble ? W * kNibblesPerWord * kNibbleEntries : W * kGroupsPerWord * kLutEntries;
+  // scratch of the build: the qubits' factors and, for nibbles, the products
+  // of the two qubits of every even/odd pair
+  static constexpr int kBuild = 64 * W * 4 + (kNibble ? 32 * W * 16 : 0);
+};
+
+// Builds the table (the whole workgroup; ends with a barrier).  Multiplying by
+// the identity's factor 1.0 is exact.
+template <int W>
+__device__ void build_energy_table(double* lut, double* tmp, int nq, const double* theta, const double* phi) {
+  double* fac = tmp;   // [64 W][4]: I, X, Z, Y
+  for (int q = threadIdx.x; q < 64 * W; q += kE4Block) {
+    double st = 0.0, ct = 1.0, sp = 0.0, cp = 1.0;
+    const bool live = q < nq;
+    if (live) {
       sincos(theta[q], &st, &ct);
       sincos(phi[q], &sp, &cp);
-      p *= bloch_factor(op, st, ct, sp, cp);
     }
-    lut[e] = p;
+#pragma unroll
+    for (int op = 0; op < 4; ++op) fac[4 * q + op] = live ? bloch_factor(op, st, ct, sp, cp) : 1.0;
   }
+  __syncthreads();
+  if constexpr (EnergyTable<W>::kNibble) {
+    double* pair = fac + 64 * W * 4;   // [32 W][16]: z bits low, x bits high
+    for (int e = threadIdx.x; e < 32 * W * 16; e += kE4Block) {
+      const int q = 2 * (e >> 4), z = e & 3, x = (e >> 2) & 3;
+      pair[e] = fac[4 * q + ((x & 1) | ((z & 1) << 1))] * fac[4 * (q + 1) + ((x >> 1) | ((z >> 1) << 1))];
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < EnergyTable<W>::kEntries; e += kE4Block) {
+      const int z = e & 15, x = (e >> 4) & 15, gi = e >> 8;
+      lut[e] = pair[(2 * gi) * 16 + ((z & 3) | ((x & 3) << 2))] * pair[(2 * gi + 1) * 16 + ((z >> 2) | ((x >> 2) << 2))];
+    }
+  } else {
+    for (int e = threadIdx.x; e < EnergyTable<W>::kEntries; e += kE4Block) {
+      const int code = e % kLutEntries, gi = e / kLutEntries;
+      const int h = gi / kGroupsPerHalf, g = gi % kGroupsPerHalf;
+      double p = 1.0;
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        const int bit = 3 * g + r;
+        if (bit < 32) p *= fac[4 * (32 * h + bit) + (((code >> (3 + r)) & 1) | (((code >> r) & 1) << 1))];
+      }
+      lut[e] = p;
+    }
+  }
+  __syncthreads();
 }
 
 template <int W>
-__device__ __forceinline__ double expect_nibble(const double* lut, const uint64_t* x, const uint64_t* z) {
+__device__ __forceinline__ double expect_table(const double* lut, const uint64_t* x, const uint64_t* z) {
   double p[4] = {1.0, 1.0, 1.0, 1.0};
 #pragma unroll
   for (int h = 0; h < 2 * W; ++h) {
     const uint32_t xh = (uint32_t)(x[h >> 1] >> (32 * (h & 1)));
     const uint32_t zh = (uint32_t)(z[h >> 1] >> (32 * (h & 1)));
-    // byte k: code of nibble 2k (lo) and of nibble 2k + 1 (hi), x bits low
-    const uint32_t lo = ((zh << 4) & 0xF0F0F0F0u) | (xh & 0x0F0F0F0Fu);
-    const uint32_t hi = ((xh >> 4) & 0x0F0F0F0Fu) | (zh & 0xF0F0F0F0u);
-    const double* lh = lut + 8 * h * kNibbleEntries;
+    if constexpr (EnergyTable<W>::kNibble) {
+      // byte k: code of nibble 2k (lo) and of nibble 2k + 1 (hi), z bits low
+      const uint32_t lo = ((xh << 4) & 0xF0F0F0F0u) | (zh & 0x0F0F0F0Fu);
+      const uint32_t hi = ((zh >> 4) & 0x0F0F0F0Fu) | (xh & 0xF0F0F0F0u);
+      const double* lh = lut + 8 * h * kNibbleEntries;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      p[k] *= lh[(2 * k) * kNibbleEntries + ((lo >> (8 * k)) & 0xFFu)];
-      p[k] *= lh[(2 * k + 1) * kNibbleEntries + ((hi >> (8 * k)) & 0xFFu)];
+      for (int k = 0; k < 4; ++k) {
+        p[k] *= lh[(2 * k) * kNibbleEntries + ((lo >> (8 * k)) & 0xFFu)];
+        p[k] *= lh[(2 * k + 1) * kNibbleEntries + ((hi >> (8 * k)) & 0xFFu)];
+      }
+    } else {
+      const double* lh = lut + h * kGroupsPerHalf * kLutEntries;
+#pragma unroll
+      for (int g = 0; g < kGroupsPerHalf; ++g) {
+        const uint32_t code = __builtin_amdgcn_ubfe(zh, 3 * g, 3) | (__builtin_amdgcn_ubfe(xh, 3 * g, 3) << 3);
+        p[g & 3] *= lh[g * kLutEntries + code];
+      }
     }
   }
   return (p[0] * p[1]) * (p[2] * p[3]);
 }
 
 template <int W>
-__global__ __launch_bounds__(kE4Block) void k_energy4(StoreDev st, const double* lut_g, double* partial) {
-  constexpr int NE = W * kNibblesPerWord * kNibbleEntries;
-  extern __shared__ __align__(16) unsigned char smem_e4[];
-  double* lut = (double*)smem_e4;
-  int64_t* s_pre = (int64_t*)(lut + NE);     // [kE4Block + 1]
-  int64_t* s_off = s_pre + kE4Block + 1;     // [kE4Block]
+size_t energy_lds_bytes() {
+  // table, its build's scratch, first rows and row prefix sums of a group
+  return (size_t)(EnergyTable<W>::kEntries + EnergyTable<W>::kBuild) * 8 + (size_t)kE4Block * 8 +
+         (size_t)(kE4Block + 1) * 4;
+}
+
+template <int W>
+__global__ __launch_bounds__(kE4Block) void k_energy(StoreDev st, int nq, const double* theta, const double* phi,
+                                                     double* slot, double* out) {
+  extern __shared__ __align__(16) unsigned char smem_en[];
+  double* lut = (double*)smem_en;
+  double* tmp = lut + EnergyTable<W>::kEntries;                  // [kBuild]
+  int64_t* s_off = (int64_t*)(tmp + EnergyTable<W>::kBuild);     // [kE4Block]
+  uint32_t* s_pre = (uint32_t*)(s_off + kE4Block);               // [kE4Block + 1]
   __shared__ double red[kE4Block / 64];
   __shared__ uint64_t scan_tmp[kE4Block / 64];
-  for (int i = threadIdx.x; i < NE; i += kE4Block) lut[i] = lut_g[i];
+  __shared__ int s_last;
   const int64_t B = 1ll << *st.m;
-  int64_t G = B / gridDim.x;
-  G = G < 1 ? 1 : (G > kE4Block ? kE4Block : G);
+  // at least kEMinRows rows per workgroup (one pass) where the store has them
+  int64_t want = (*st.total + kEMinRows - 1) / kEMinRows;
+  want = want < 1 ? 1 : (want > gridDim.x ? gridDim.x : want);
+  int64_t G = (B + want - 1) / want;
+  G = G > kE4Block ? kE4Block : G;
   const int64_t ngroups = (B + G - 1) / G;
+  const unsigned active = ngroups < want ? (unsigned)ngroups : (unsigned)want;
+  if (blockIdx.x >= active) return;
+  bool table = false;
   double acc = 0.0;
-  __syncthreads();
-  for (int64_t grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
+  for (int64_t grp = blockIdx.x; grp < ngroups; grp += active) {
     const int64_t b = grp * G + threadIdx.x;
     const bool mine = threadIdx.x < G && b < B;
     const int64_t cnt = mine ? st.cnt[b] : 0;
@@ -252,26 +235,35 @@ __global__ __launch_bounds__(kE4Block) void k_energy4(StoreDev st, const double*
     uint64_t total;
     // (the scan's barriers also order the previous group's reads of s_pre)
     const uint64_t ex = block_exclusive_scan_n<kE4Block / 64>((uint64_t)cnt, scan_tmp, total);
-    s_pre[threadIdx.x] = (int64_t)ex;
+    s_pre[threadIdx.x] = (uint32_t)ex;
     s_off[threadIdx.x] = off;
-    if (threadIdx.x == 0) s_pre[kE4Block] = (int64_t)total;
+    if (threadIdx.x == 0) s_pre[kE4Block] = (uint32_t)total;
     __syncthreads();
-    const int64_t n = (int64_t)total;
-    for (int64_t i0 = 0; i0 < n; i0 += kE4Block * kEItems) {
+    // the group's rows are one range when every bucket starts where the one
+    // before it ends (a loaded store); then row = base + i, the row the search
+    // below would find (thread 0 holds the group's first bucket)
+    const int64_t base = s_off[0];
+    const bool contig = __syncthreads_and(!mine || off - (int64_t)ex == base) != 0;
+    const uint32_t n = (uint32_t)total;
+    uint32_t i0 = 0;
+    do {
       uint64_t kx[kEItems][W], kz[kEItems][W];
       double kc[kEItems];
 #pragma unroll
       for (int r = 0; r < kEItems; ++r) {
-        const int64_t i = i0 + r * kE4Block + threadIdx.x;
+        const uint32_t i = i0 + r * kE4Block + threadIdx.x;
         kc[r] = 0.0;
 #pragma unroll
         for (int w = 0; w < W; ++w) kx[r][w] = kz[r][w] = 0;
         if (i < n) {
-          int lo = 0;   // the last bucket of the group whose first row is <= i
+          int64_t row = base + i;
+          if (!contig) {
+            int lo = 0;   // the last bucket of the group whose first row is <= i
 #pragma unroll
-          for (int step = kE4Block / 2; step; step >>= 1)
-            if (s_pre[lo + step] <= i) lo += step;
-          const int64_t row = s_off[lo] + (i - s_pre[lo]);
+            for (int step = kE4Block / 2; step; step >>= 1)
+              if (s_pre[lo + step] <= i) lo += step;
+            row = s_off[lo] + (i - s_pre[lo]);
+          }
 #pragma unroll
           for (int w = 0; w < W; ++w) {
             kx[r][w] = __builtin_nontemporal_load(&st.x[w * st.cap + row]);
@@ -280,33 +272,50 @@ __global__ __launch_bounds__(kE4Block) void k_energy4(StoreDev st, const double*
           kc[r] = __builtin_nontemporal_load(&st.c[row]);
         }
       }
+      if (!table) {   // built while the first rows are on their way
+        build_energy_table<W>(lut, tmp, nq, theta, phi);
+        table = true;
+      }
 #pragma unroll
-      for (int r = 0; r < kEItems; ++r) acc += kc[r] * expect_nibble<W>(lut, kx[r], kz[r]);
-    }
+      for (int r = 0; r < kEItems; ++r) acc += kc[r] * expect_table<W>(lut, kx[r], kz[r]);
+      i0 += kE4Block * kEItems;
+    } while (i0 < n);
   }
   const double s = block_sum_n<kE4Block / 64>(acc, red);
-  if (threadIdx.x == 0) partial[blockIdx.x] = s;
-}
-
-int energy_lut_doubles(int W) {
-  return W <= 2 ? W * kNibblesPerWord * kNibbleEntries : W * kGroupsPerWord * kLutEntries;
-}
-
-void launch_energy_table(int W, int nq, const StoreDev& st, int grid, const double* theta,
-                         const double* phi, double* lut, double* partial, hipStream_t s) {
-  if (W > 2) {
-    launch_build_lut(W, nq, theta, phi, lut, s);
-    launch_energy(W, st, grid, lut, partial, s);
+  if (active == 1) {
+    if (threadIdx.x == 0) *out = s;
     return;
   }
-  hipLaunchKernelGGL(k_build_lut4, dim3(16), dim3(kBlock), 0, s, W, nq, theta, phi, lut);
-  const size_t lds = (size_t)W * kNibblesPerWord * kNibbleEntries * 8 + (size_t)(2 * kE4Block + 1) * 8;
-  if (W == 1) {
-    (void)hipFuncSetAttribute((const void*)k_energy4<1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k_energy4<1>, dim3(grid), dim3(kE4Block), lds, s, st, lut, partial);
-  } else {
-    (void)hipFuncSetAttribute((const void*)k_energy4<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k_energy4<2>, dim3(grid), dim3(kE4Block), lds, s, st, lut, partial);
+  if (threadIdx.x == 0) s_last = finish_arrive(slot, blockIdx.x, s, active);
+  __syncthreads();
+  if (s_last) {
+    double t = 0.0;
+    for (unsigned k = threadIdx.x; k < active; k += kE4Block) t += finish_partial(slot, k);
+    t = block_sum_n<kE4Block / 64>(t, red);
+    if (threadIdx.x == 0) *out = t;
+  }
+}
+
+template <int W>
+static void launch_energy_w(int nq, const StoreDev& st, int n_cu, int per_cu, size_t lds_per_cu, const double* theta,
+                            const double* phi, double* slot, double* out, hipStream_t s) {
+  const size_t lds = energy_lds_bytes<W>();
+  // resident workgroups per CU: LDS (with the static part), 2048 threads
+  int fit = (int)(lds_per_cu / (lds + 256));
+  fit = fit < 1 ? 1 : (fit > 2048 / kE4Block ? 2048 / kE4Block : fit);
+  int grid = n_cu * (per_cu < fit ? per_cu : fit);
+  if (grid > kFinishPartials) grid = kFinishPartials;
+  (void)hipFuncSetAttribute((const void*)k_energy<W>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL(k_energy<W>, dim3(grid), dim3(kE4Block), lds, s, st, nq, theta, phi, slot, out);
+}
+
+void launch_energy(int W, int nq, const StoreDev& st, int n_cu, int per_cu, size_t lds_per_cu, const double* theta,
+                   const double* phi, double* slot, double* out, hipStream_t s) {
+  switch (W) {
+    case 1: launch_energy_w<1>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s); break;
+    case 2: launch_energy_w<2>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s); break;
+    case 3: launch_energy_w<3>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s); break;
+    default: launch_energy_w<4>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s); break;
   }
 }
 
