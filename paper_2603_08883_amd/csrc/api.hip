@@ -1196,25 +1196,23 @@ int iqcc_dis_gradients(iqcc_ctx* ctx, const iqcc_store* h, const double* theta, 
   if (mode != IQCC_DIS_BATCHED && mode != IQCC_DIS_PLAIN) return fail(ctx, IQCC_ERR_INVALID_ARG, "bad mode");
   if (n_cand == 0) return IQCC_OK;
   hipStream_t s = as_stream(stream);
-  launch_build_lut(h->W, h->nq, theta, phi, ctx->lut, s);
   if (mode == IQCC_DIS_BATCHED) {
-    // candidate tiles x bucket ranges: about 8 workgroups per CU in total
-    // unless "dis_bucket_ranges" fixes the number of ranges
-    const int64_t tiles = (n_cand + ctx->dis_tile - 1) / ctx->dis_tile;
+    // room for the ranges' partial sums: about 8 workgroups per CU over the
+    // candidate tiles unless "dis_bucket_ranges" fixes the number of ranges
+    const int64_t tiles = (n_cand + dis_tile() - 1) / dis_tile();
     int64_t gt = ctx->dis_bucket_ranges ? ctx->dis_bucket_ranges : (ctx->n_cu * 8 + tiles - 1) / tiles;
     if (gt < 1) gt = 1;
     if (gt > 4096) gt = 4096;
-    const int64_t n_part = (gt * n_cand + 1) & ~int64_t(1);   // tables start 16-byte aligned
-    rc = ensure_partial(ctx, n_part + dis_tables_doubles(h->W));
+    rc = ensure_partial(ctx, gt * n_cand);
     if (rc) return rc;
-    launch_dis(h->W, h->d, ctx->lut, cx, cz, n_cand, ld_cand, 0, (int)ctx->dis_tile, 0,
-               ctx->partial, (int)gt, g, s, theta, phi, h->nq, ctx->partial + n_part);
+    launch_dis_batched(h->W, h->d, theta, phi, h->nq, cx, cz, n_cand, ld_cand, (int)ctx->dis_tile, ctx->n_cu,
+                       (int)gt, ctx->dis_bucket_ranges != 0, ctx->partial, g, s);
   } else {
     const int grid = (int)(ctx->n_cu * dis_one_blocks_per_cu(h->W));
     rc = ensure_partial(ctx, grid + 1);   // per-workgroup sums and a finish counter
     if (rc) return rc;
-    launch_dis(h->W, h->d, ctx->lut, cx, cz, n_cand, ld_cand, 1, 1, grid, ctx->partial, 0, g, s,
-               theta, phi, h->nq, nullptr);
+    launch_build_lut(h->W, h->nq, theta, phi, ctx->lut, s);
+    launch_dis_plain(h->W, h->d, ctx->lut, cx, cz, n_cand, ld_cand, grid, ctx->partial, g, s);
   }
   LAUNCH_CHECK(ctx);
   return IQCC_OK;

@@ -729,12 +729,14 @@ void launch_backward_finalize(int nq, int grid, const double* acc, const double*
                               hipStream_t s);
 
 int dis_one_blocks_per_cu(int W);
-void launch_dis(int W, const StoreDev& st, const double* lut, const uint64_t* cx,
-                const uint64_t* cz, int64_t n_cand, int64_t ld_cand, int mode, int tile,
-                int grid, double* partial /*[grid_terms][n_cand]*/, int grid_terms,
-                double* g, hipStream_t s, const double* theta, const double* phi, int nq,
-                double* tables /*dis_tables_doubles(W), batched mode*/);
-int64_t dis_tables_doubles(int W);
+// max_ranges x n_cand doubles of partial; fixed: exactly max_ranges term
+// ranges (a knob), else as many as the terms fill.
+void launch_dis_batched(int W, const StoreDev& st, const double* theta, const double* phi, int nq, const uint64_t* cx,
+                        const uint64_t* cz, int64_t n_cand, int64_t ld_cand, int tile, int n_cu, int max_ranges,
+                        int fixed, double* partial, double* g, hipStream_t s);
+// partial: grid + 1 doubles
+void launch_dis_plain(int W, const StoreDev& st, const double* lut, const uint64_t* cx, const uint64_t* cz,
+                      int64_t n_cand, int64_t ld_cand, int grid, double* partial, double* g, hipStream_t s);
 int64_t dis_tile();   // candidates per workgroup of the batched kernel
 
 void launch_dress_backward(int W, const StoreDev& in, double C, double S,

@@ -5,69 +5,27 @@
 //
 // Batched form: the QMF state is a product state, so for a term K and a
 // candidate P_a the ratio <Q>/<K> (Q = K P_a) only involves the qubits in the
-// support of P_a, and so does the phase e (a sum of per-qubit parts).  A table
-// per (qubit, Pauli of P_a there, Pauli of K there) gives the factor ratio
-// b_q(Q)/b_q(K), the qubit's share of e and whether b_q(K) is exactly zero.
-// Each term carries PK = product of its non-zero qubit factors and ZK = the
-// number of zero factors; then <Q> = PK * prod(ratios) when every zero factor
-// of K lies in the support of P_a, else 0.  One table lookup per support qubit
-// and term, no division in the loop and no special case at zero factors.
-// A workgroup holds a tile of candidates and a contiguous range of buckets;
-// lanes hold terms (kR per lane, pre-split into 2-bit qubit codes) and the
-// candidate loop is uniform, so the support of P_a is walked in scalar
-// registers.  Sums over lanes and waves, then over bucket ranges, are taken in
-// a fixed order.
-// Plain form: one launch per candidate streaming all terms (reference form).
+// support of P_a.  A table per (qubit, Pauli of P_a there, Pauli of K there)
+// gives the factor ratio b_q(Q)/b_q(K), with the sign of the qubit's phase that
+// counting leaves open (below); each term carries PK = the product of its
+// non-zero qubit factors, and where a state has factors that are exactly zero
+// also which of its qubits have one: then <Q> = PK * prod(ratios) when every
+// zero factor of K lies in the support of P_a, else 0.  One table lookup per
+// support qubit and term, no division in the loop and no special case at zero
+// factors.  Plain form: one launch per candidate streaming all terms
+// (reference form).
 #include "iqcc_internal.h"
 
 #pragma clang fp contract(off)
 
 namespace iqcc {
 
-constexpr int kDisB = 512;          // threads per workgroup of the batched kernel
+constexpr int kDisB = 256;          // threads per workgroup of the batched kernel
 constexpr int kDisWaves = kDisB / 64;
-constexpr int kDisR = 4;            // terms per lane
-constexpr int kDisTile = 256;       // candidates per workgroup
+constexpr int kDisR = 8;            // terms per lane of a full pass
+constexpr int kDisTile = 256;       // candidates staged at once
 constexpr int kDisChunk = kDisB;    // buckets whose prefix sums are staged at once
-
-// Per-qubit tables for the batched kernel, q < 64 W:
-//   ent[(q * 4 + p) * 4 + k] = {ratio, meta} for the Pauli k of K and p of P
-//   (bit 0 = x, bit 1 = z): ratio = b_q(k ^ p) / b_q(k) (b_q(k ^ p) when
-//   b_q(k) = 0), meta = [b_q(k) == 0] | (phase part << 12);
-//   fac[q * 4 + k] = b_q(k).
-struct DisEnt {
-  double ratio;
-  uint32_t meta;
-  uint32_t pad;
-};
-
-__global__ void k_dis_tables(int W, int nq, const double* theta, const double* phi,
-                             DisEnt* ent, double* fac) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= 64 * W) return;
-  double b[4] = {1.0, 1.0, 1.0, 1.0};
-  if (q < nq) {
-    double st, ct, sp, cp;
-    sincos(theta[q], &st, &ct);
-    sincos(phi[q], &sp, &cp);
-    b[1] = st * cp;   // X
-    b[2] = ct;        // Z
-    b[3] = st * sp;   // Y
-  }
-  for (int k = 0; k < 4; ++k) fac[q * 4 + k] = b[k];
-  for (int p = 0; p < 4; ++p) {
-    for (int k = 0; k < 4; ++k) {
-      const int x1 = k & 1, z1 = k >> 1, x2 = p & 1, z2 = p >> 1;
-      const int ph = (x1 * z1 + x2 * z2 + 2 * z1 * x2 - (x1 ^ x2) * (z1 ^ z2)) & 3;
-      const bool zero = b[k] == 0.0;
-      DisEnt e;
-      e.ratio = zero ? b[k ^ p] : b[k ^ p] / b[k];
-      e.meta = (zero ? 1u : 0u) | ((uint32_t)ph << 12);
-      e.pad = 0;
-      ent[(q * 4 + p) * 4 + k] = e;
-    }
-  }
-}
+constexpr int kDisPass = kDisB * kDisR;
 
 // Spread the 16 bits of v to the even bits of a 32-bit word.
 __device__ __forceinline__ uint32_t spread16(uint32_t v) {
@@ -111,156 +69,303 @@ __device__ __forceinline__ double wave_sum_to_lane63(double v) {
   return v;
 }
 
-template <int W>
-__global__ __launch_bounds__(kDisB) void k_dis_batched(StoreDev st, const DisEnt* __restrict__ ent_g,
-                                                       const double* __restrict__ fac_g,
-                                                       const uint64_t* __restrict__ cx,
-                                                       const uint64_t* __restrict__ cz,
-                                                       int64_t n_cand, int64_t ld_cand,
-                                                       int tile_size,
-                                                       double* __restrict__ partial) {
-  constexpr int R = kDisR;
-  constexpr int NQ = 64 * W;
-  constexpr int NS = 4 * W;   // 16-qubit slots
-  __shared__ DisEnt ent[NQ * 16];
-  __shared__ double fac[NQ * 4];
-  __shared__ double acc[kDisWaves][kDisTile];
-  __shared__ int64_t pre[kDisChunk + 1];
-  __shared__ int64_t boff[kDisChunk];
-  __shared__ uint64_t scan_tmp[kDisWaves];
-  for (int i = threadIdx.x; i < NQ * 16; i += kDisB) ent[i] = ent_g[i];
-  for (int i = threadIdx.x; i < NQ * 4; i += kDisB) fac[i] = fac_g[i];
-  for (int i = threadIdx.x; i < kDisWaves * kDisTile; i += kDisB) (&acc[0][0])[i] = 0.0;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int64_t a0 = (int64_t)blockIdx.x * tile_size;   // tile_size <= kDisTile
-  const int tile = (int)((n_cand - a0) < tile_size ? (n_cand - a0) : tile_size);
-  const int64_t B = 1ll << *st.m;
-  const int64_t b_lo = B * blockIdx.y / gridDim.y, b_hi = B * (blockIdx.y + 1) / gridDim.y;
-  const char* ent_base = reinterpret_cast<const char*>(ent);
+// Buckets per term range of a batched launch: as many as fill one pass (with
+// 2 % to spare, so that uneven buckets seldom spill a few terms into a second
+// pass: on 1e6 terms in 4096 buckets, ranges of 8.4 buckets took 2320 us, of 8
+// 1902 us), but no more than max_ranges ranges; `fixed`: max_ranges ranges.
+__device__ __forceinline__ int64_t dis_range_buckets(int64_t total, int64_t buckets, int max_ranges, int fixed) {
+  const int64_t least = (buckets + max_ranges - 1) / max_ranges;
+  if (fixed || total <= 0) return least;
+  const int64_t fill = (int64_t)((double)buckets * (kDisPass / 1.02) / (double)total);
+  return fill < least ? least : (fill > buckets ? buckets : fill);
+}
 
-  for (int64_t cb = b_lo; cb < b_hi; cb += kDisChunk) {
-    const int nb = (int)((b_hi - cb) < kDisChunk ? (b_hi - cb) : kDisChunk);
-    __syncthreads();   // tables ready / previous chunk done with pre, boff
-    uint64_t total;
-    const uint64_t n_b = threadIdx.x < nb ? (uint64_t)st.cnt[cb + threadIdx.x] : 0ull;
-    const uint64_t ex = block_exclusive_scan_n<kDisWaves>(n_b, scan_tmp, total);
-    if (threadIdx.x < nb) {
-      pre[threadIdx.x] = (int64_t)ex;
-      boff[threadIdx.x] = st.off[cb + threadIdx.x];
-    }
-    if (threadIdx.x == 0) pre[nb] = (int64_t)total;
-    __syncthreads();
-    const int64_t n_chunk = (int64_t)total;
-    for (int64_t j0 = 0; j0 < n_chunk; j0 += (int64_t)kDisB * R) {
-      // --- stage R terms per lane: 2-bit qubit codes, c * PK and ZK ---
-      uint32_t code[R][NS];
-      double cpk[R];
-      uint32_t zk[R];
+template <int W>
+struct DisShared {
+  static constexpr int NQ = 64 * W, NS = 4 * W;   // NS: 16-qubit slots
+  double ent[NQ * 16];       // [q][p][k]: signed factor ratios (p, k below)
+  double pair[NQ / 2 * 16];  // [q / 2][codes of q, q + 1]: product of the non-zero factors
+  uint32_t sw[kDisTile * NS];   // candidates as slot words
+  double acc[kDisWaves][kDisTile];   // first the factors b_q(k), [q][k]
+  int64_t boff[kDisChunk];
+  int64_t pre[kDisChunk + 1];
+  uint64_t scan_tmp[kDisWaves];
+  uint32_t zero[3][NS];      // qubits (even bits of a slot word) whose X, Z, Y factor is exactly 0
+};
+
+// Terms r * kDisB + threadIdx.x (r < R) of a pass against `ncand` staged
+// candidates.  A term is held as slot words: 16 qubits each, bit 2j the x bit
+// and bit 2j + 1 the z bit of qubit j; a candidate's slot words hold its z bit
+// at 2j and its x bit at 2j + 1, so that code & sw has one bit per
+// anticommuting factor (and two where both are Y, whose ratio carries the sign
+// -1 that the second bit would wrongly bring).  With n such bits and the signs
+// in the ratios, i^e = i^n, so the pair counts with +1 for n = 1 and -1 for
+// n = 3 (mod 4).
+// The candidate loop is uniform: slot words sit in scalar registers, the
+// support is walked with s_ff1, and every step issues R independent lookups.
+template <int W, int R, bool ZERO>
+__device__ __forceinline__ void dis_pass(const StoreDev& st, DisShared<W>& sh, int64_t j0, int64_t n_chunk, int nb,
+                                         int ncand) {
+  constexpr int NS = DisShared<W>::NS;
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t code[R][NS];
+  uint32_t zq[ZERO ? R : 1][NS / 2];   // zero factors: qubits of slots 2i (even bits) and 2i + 1 (odd bits)
+  double cpk[R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int64_t j = j0 + (int64_t)r * kDisB + threadIdx.x;
-        uint64_t kx[W], kz[W];
-        double c = 0.0;
-        if (j < n_chunk) {
-          int lo = 0, hi = nb - 1;   // last bucket with pre <= j (pre[0] = 0)
-          while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (pre[mid] <= j) lo = mid; else hi = mid - 1;
-          }
-          const int64_t i = boff[lo] + (j - pre[lo]);
+  for (int r = 0; r < R; ++r) {
+    const int64_t j = j0 + (int64_t)r * kDisB + threadIdx.x;
+    uint64_t kx[W], kz[W];
+    double c = 0.0;
 #pragma unroll
-          for (int w = 0; w < W; ++w) {
-            kx[w] = st.x[w * st.cap + i];
-            kz[w] = st.z[w * st.cap + i];
-          }
-          c = st.c[i];
-        } else {
-#pragma unroll
-          for (int w = 0; w < W; ++w) kx[w] = kz[w] = 0ull;
-        }
-        double pk = 1.0;
-        uint32_t nz = 0;
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-          for (uint64_t t = kx[w] | kz[w]; t; t &= t - 1) {
-            const int bq = __builtin_ctzll(t);
-            const int k = (int)((kx[w] >> bq) & 1) | (int)(((kz[w] >> bq) & 1) << 1);
-            const double f = fac[(64 * w + bq) * 4 + k];
-            if (f == 0.0) ++nz; else pk *= f;
-          }
-#pragma unroll
-          for (int s4 = 0; s4 < 4; ++s4) {
-            const uint32_t xs = (uint32_t)(kx[w] >> (16 * s4)), zs = (uint32_t)(kz[w] >> (16 * s4));
-            code[r][4 * w + s4] = spread16(xs) | (spread16(zs) << 1);
-          }
-        }
-        cpk[r] = c * pk;
-        zk[r] = nz | (1u << 12);   // meta sum of a live pair with e = 1; e = 3 adds 2 << 12
+    for (int w = 0; w < W; ++w) kx[w] = kz[w] = 0ull;
+    if (j < n_chunk) {
+      int lo = 0, hi = nb - 1;   // last bucket with pre <= j (pre[0] = 0)
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (sh.pre[mid] <= j) lo = mid; else hi = mid - 1;
       }
-      // --- candidates of the tile (uniform loop) ---
-      for (int t = 0; t < tile; ++t) {
-        const int64_t a = a0 + t;
-        double prod[R];
-        uint32_t msum[R];
+      const int64_t i = sh.boff[lo] + (j - sh.pre[lo]);
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          prod[r] = 1.0;
-          msum[r] = 0;
-        }
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-          const uint64_t ax = cx[w * ld_cand + a], az = cz[w * ld_cand + a];
-#pragma unroll
-          for (int s4 = 0; s4 < 4; ++s4) {
-            const uint32_t xs = (uint32_t)(ax >> (16 * s4)) & 0xffffu;
-            const uint32_t zs = (uint32_t)(az >> (16 * s4)) & 0xffffu;
-            for (uint32_t m = xs | zs; m; m &= m - 1) {
-              const uint32_t qb = (uint32_t)__builtin_ctz(m);
-              const uint32_t q = 64 * w + 16 * s4 + qb;
-              const uint32_t p = ((xs >> qb) & 1u) | (((zs >> qb) & 1u) << 1);
-              const char* row = ent_base + (size_t)((q * 4 + p) * 4) * sizeof(DisEnt);
-#pragma unroll
-              for (int r = 0; r < R; ++r) {
-                const uint32_t k = __builtin_amdgcn_ubfe(code[r][4 * w + s4], 2 * qb, 2);
-                const DisEnt e = *reinterpret_cast<const DisEnt*>(row + k * sizeof(DisEnt));
-                prod[r] *= e.ratio;
-                msum[r] += e.meta;
-              }
-            }
-          }
-        }
-        double v = 0.0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          // live: every zero factor of K in the support, and e odd (+ for 1, - for 3)
-          const uint32_t m = msum[r] & 0x3fffu;
-          const double f = m == zk[r] ? 1.0 : (m == zk[r] + (2u << 12) ? -1.0 : 0.0);
-          v = fma(f, cpk[r] * prod[r], v);   // exact product by +-1 or 0
-        }
-        v = wave_sum_to_lane63(v);
-        if (lane == 63) acc[wid][t] += v;
+      for (int w = 0; w < W; ++w) {
+        kx[w] = st.x[w * st.cap + i];
+        kz[w] = st.z[w * st.cap + i];
       }
+      c = st.c[i];
     }
+    double p0 = 1.0, p1 = 1.0;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const uint32_t xs = (uint32_t)(kx[s >> 2] >> (16 * (s & 3))), zs = (uint32_t)(kz[s >> 2] >> (16 * (s & 3)));
+      const uint32_t cd = spread16(xs) | (spread16(zs) << 1);
+      code[r][s] = cd;
+#pragma unroll
+      for (int i = 0; i < 8; i += 2) {
+        p0 *= sh.pair[(8 * s + i) * 16 + ((cd >> (4 * i)) & 15)];
+        p1 *= sh.pair[(8 * s + i + 1) * 16 + ((cd >> (4 * i + 4)) & 15)];
+      }
+      if (ZERO) {
+        const uint32_t x = cd & 0x55555555u, z = (cd >> 1) & 0x55555555u;
+        uint32_t m = (x & ~z & sh.zero[0][s]) | (z & ~x & sh.zero[1][s]) | (x & z & sh.zero[2][s]);
+        asm volatile("" : "+v"(m));
+        if (s & 1) zq[ZERO ? r : 0][s >> 1] |= m << 1; else zq[ZERO ? r : 0][s >> 1] = m;
+      }
+      // the products are needed here: left alone, the compiler holds every
+      // looked-up value until the candidate loop and spills
+      asm volatile("" : "+v"(p0), "+v"(p1));
+    }
+    cpk[r] = c * (p0 * p1);
   }
-  __syncthreads();
-  for (int t = threadIdx.x; t < tile; t += kDisB) {
-    double s = 0.0;
+  uint32_t next[NS];
 #pragma unroll
-    for (int w = 0; w < kDisWaves; ++w) s += acc[w][t];
-    partial[(int64_t)blockIdx.y * n_cand + a0 + t] = s;
+  for (int s = 0; s < NS; ++s) next[s] = sh.sw[s];
+  for (int t = 0; t < ncand; ++t) {
+    uint32_t sw[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) sw[s] = (uint32_t)__builtin_amdgcn_readfirstlane((int)next[s]);
+    const int tn = t + 1 < ncand ? t + 1 : t;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) next[s] = sh.sw[tn * NS + s];
+    double prod[R];
+    uint32_t n[R], dead[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      prod[r] = cpk[r];
+      n[r] = dead[r] = 0;
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      if (sw[s]) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) n[r] += __popc(code[r][s] & sw[s]);
+        uint32_t m = (sw[s] | (sw[s] >> 1)) & 0x55555555u;
+        const char* slot = reinterpret_cast<const char*>(sh.ent) + s * 2048;
+        do {
+          const uint32_t b = (uint32_t)__builtin_ctz(m);
+          m &= m - 1;
+          const char* row = slot + b * 64 + ((sw[s] >> b) & 3u) * 32;
+          double e[R];
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+            e[r] = *reinterpret_cast<const double*>(row + __builtin_amdgcn_ubfe(code[r][s], b, 2) * 8);
+          // all R reads in flight before the first product waits for its own
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int r = 0; r < R; ++r) prod[r] *= e[r];
+        } while (m);
+      }
+      if (ZERO && (s & 1)) {
+        const uint32_t sup = ((sw[s - 1] | (sw[s - 1] >> 1)) & 0x55555555u) | ((sw[s] | (sw[s] << 1)) & 0xAAAAAAAAu);
+#pragma unroll
+        for (int r = 0; r < R; ++r) dead[r] |= zq[ZERO ? r : 0][s >> 1] & ~sup;
+      }
+    }
+    double v = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      // +1 for n = 1, -1 for n = 3 (mod 4), else 0 as a factor: products by it are exact
+      uint32_t f = (((n[r] >> 1) << 31) | 0x3FF00000u) & (uint32_t)-(int)(n[r] & 1u);
+      if (ZERO) f = dead[r] ? 0u : f;
+      v = fma(__hiloint2double((int)f, 0), prod[r], v);
+    }
+    v = wave_sum_to_lane63(v);
+    if (lane == 63) sh.acc[wid][t] += v;
   }
 }
 
-int64_t dis_tables_doubles(int W) { return 64 * W * 16 * 2 + 64 * W * 4; }
+// The (range, candidate) pairs are numbered range by range and every workgroup
+// takes an equal run of them, so a range's terms are staged once for all the
+// candidates of the run and few terms or few candidates still fill the chip.
+//
+// Bound: VALU issue.  1e6 two-word terms x 1000 candidates of 10.8 support
+// qubits: 53 VALU instructions per 64 pairs (3 per support qubit, 2 per
+// touched slot, 11 for the sign and the sum), 1.68 ms; the former kernel (a
+// second lookup per qubit for the phase, 4 terms per lane, ranges of buckets
+// by tiles) took 2.38 ms plus 0.13 ms for the sum over ranges.  12,007 one-word
+// terms x 13,472 candidates: 1113 -> 196 us (its ranges held 307 of 2048
+// terms).  233,001 terms x 5 candidates: 298 -> 22 us.
+template <int W>
+__global__ __launch_bounds__(kDisB, W <= 2 ? 3 : 2) void k_dis_batched(StoreDev st, int nq, const double* __restrict__ theta,
+                                                       const double* __restrict__ phi,
+                                                       const uint64_t* __restrict__ cx,
+                                                       const uint64_t* __restrict__ cz, int64_t n_cand,
+                                                       int64_t ld_cand, int tile_size, int max_ranges, int fixed,
+                                                       double* __restrict__ partial) {
+  constexpr int NQ = 64 * W, NS = 4 * W;
+  extern __shared__ __align__(16) unsigned char smem_dis[];
+  DisShared<W>& sh = *reinterpret_cast<DisShared<W>*>(smem_dis);
+  const int64_t B = 1ll << *st.m;
+  const int64_t per = dis_range_buckets(*st.total, B, max_ranges, fixed);
+  const int64_t nr = (B + per - 1) / per;
+  int64_t run = (nr * n_cand + gridDim.x - 1) / gridDim.x;
+  const int64_t least = n_cand < 16 ? n_cand : 16;
+  if (run < least) run = least;
+  int64_t at = blockIdx.x * run;
+  int64_t end = at + run < nr * n_cand ? at + run : nr * n_cand;
+  if (at >= end) return;
+  // tables
+  double* fac = &sh.acc[0][0];
+  static_assert(NQ * 4 <= kDisWaves * kDisTile, "the factors fit the accumulators");
+  bool zero = false;
+  for (int i = threadIdx.x; i < 3 * NS; i += kDisB) (&sh.zero[0][0])[i] = 0u;
+  __syncthreads();
+  for (int q = threadIdx.x; q < NQ; q += kDisB) {
+    double b[4] = {1.0, 1.0, 1.0, 1.0};
+    if (q < nq) {
+      double st_, ct, sp, cp;
+      sincos(theta[q], &st_, &ct);
+      sincos(phi[q], &sp, &cp);
+#pragma unroll
+      for (int op = 1; op < 4; ++op) b[op] = bloch_factor(op, st_, ct, sp, cp);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      fac[4 * q + k] = b[k];
+      if (b[k] == 0.0) {
+        zero = true;
+        atomicOr(&sh.zero[k == 1 ? 0 : k == 2 ? 1 : 2][q >> 4], 1u << (2 * (q & 15)));
+      }
+    }
+  }
+  const bool any_zero = __syncthreads_or(zero) != 0;
+  for (int i = threadIdx.x; i < NQ * 16; i += kDisB) {
+    const int k = i & 3, q = i >> 4;
+    const int x1 = k & 1, z1 = k >> 1, z2 = (i >> 2) & 1, x2 = (i >> 3) & 1;
+    const int ph = (x1 * z1 + x2 * z2 + 2 * z1 * x2 - (x1 ^ x2) * (z1 ^ z2)) & 3;
+    const int bits = (x1 & z2) + (z1 & x2);   // bits of this qubit in code & sw
+    const double bk = fac[4 * q + k], bq = fac[4 * q + (k ^ (x2 | (z2 << 1)))];
+    const double ratio = bk == 0.0 ? bq : bq / bk;
+    sh.ent[i] = ((ph - bits) & 2) ? -ratio : ratio;
+  }
+  for (int i = threadIdx.x; i < NQ / 2 * 16; i += kDisB) {
+    const double f0 = fac[8 * (i >> 4) + (i & 3)], f1 = fac[8 * (i >> 4) + 4 + ((i >> 2) & 3)];
+    sh.pair[i] = (f0 == 0.0 ? 1.0 : f0) * (f1 == 0.0 ? 1.0 : f1);
+  }
+  while (at < end) {
+    const int64_t range = at / n_cand, a_lo = at - range * n_cand;
+    const int64_t left = end - at, room = n_cand - a_lo;
+    const int64_t a_hi = a_lo + (left < room ? left : room);
+    at += a_hi - a_lo;
+    const int64_t b_lo = range * per, b_hi = b_lo + per < B ? b_lo + per : B;
+    for (int64_t a0 = a_lo; a0 < a_hi; a0 += tile_size) {
+      const int ncand = (int)(a_hi - a0 < tile_size ? a_hi - a0 : tile_size);   // tile_size <= kDisTile
+      __syncthreads();   // tables ready / previous tile written out
+      for (int i = threadIdx.x; i < ncand * NS; i += kDisB) {
+        const int t = i / NS, s = i % NS;
+        const uint32_t xs = (uint32_t)(cx[(s >> 2) * ld_cand + a0 + t] >> (16 * (s & 3)));
+        const uint32_t zs = (uint32_t)(cz[(s >> 2) * ld_cand + a0 + t] >> (16 * (s & 3)));
+        sh.sw[i] = spread16(zs) | (spread16(xs) << 1);
+      }
+      for (int i = threadIdx.x; i < kDisWaves * ncand; i += kDisB) sh.acc[i / ncand][i % ncand] = 0.0;
+      for (int64_t cb = b_lo; cb < b_hi; cb += kDisChunk) {
+        const int nb = (int)((b_hi - cb) < kDisChunk ? (b_hi - cb) : kDisChunk);
+        __syncthreads();   // candidates staged / previous chunk done with pre, boff
+        uint64_t total;
+        const uint64_t n_b = threadIdx.x < nb ? (uint64_t)st.cnt[cb + threadIdx.x] : 0ull;
+        const uint64_t ex = block_exclusive_scan_n<kDisWaves>(n_b, sh.scan_tmp, total);
+        if (threadIdx.x < nb) {
+          sh.pre[threadIdx.x] = (int64_t)ex;
+          sh.boff[threadIdx.x] = st.off[cb + threadIdx.x];
+        }
+        if (threadIdx.x == 0) sh.pre[nb] = (int64_t)total;
+        __syncthreads();
+        const int64_t n_chunk = (int64_t)total;
+        // full passes, then the rest with as few idle lanes as the terms per
+        // lane of a pass allow
+        for (int64_t j = 0; j < n_chunk;) {
+          const int64_t rest = n_chunk - j;
+          if (any_zero) {
+            if (rest > 2 * kDisB) { dis_pass<W, 4, true>(st, sh, j, n_chunk, nb, ncand); j += 4 * kDisB; }
+            else { dis_pass<W, 2, true>(st, sh, j, n_chunk, nb, ncand); j += 2 * kDisB; }
+          } else if (rest > 4 * kDisB) {
+            dis_pass<W, kDisR, false>(st, sh, j, n_chunk, nb, ncand); j += kDisR * kDisB;
+          } else if (rest > 2 * kDisB) {
+            dis_pass<W, 4, false>(st, sh, j, n_chunk, nb, ncand); j += 4 * kDisB;
+          } else {
+            dis_pass<W, 2, false>(st, sh, j, n_chunk, nb, ncand); j += 2 * kDisB;
+          }
+        }
+      }
+      __syncthreads();
+      for (int t = threadIdx.x; t < ncand; t += kDisB) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < kDisWaves; ++w) s += sh.acc[w][t];
+        partial[range * n_cand + a0 + t] = s;
+      }
+    }
+  }
+}
 
 int64_t dis_tile() { return kDisTile; }   // the largest tile the batched kernel holds
 
-__global__ void k_dis_reduce(const double* partial, int rows, int64_t n_cand, double* g) {
-  for (int64_t a = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; a < n_cand;
-       a += (int64_t)gridDim.x * blockDim.x) {
-    double s = 0.0;
-    for (int r = 0; r < rows; ++r) s += partial[(int64_t)r * n_cand + a];
-    g[a] = s;
+// Sums the ranges' partials of 16 candidates per workgroup: 16 threads take
+// every 16th range of a candidate (reads of 128 bytes), then their sums in
+// order.  (One thread per candidate walked all ranges alone: 243 us for 2048
+// ranges of 5 candidates.)
+__global__ __launch_bounds__(kBlock) void k_dis_reduce(StoreDev st, const double* partial, int max_ranges, int fixed,
+                                                       int64_t n_cand, double* g) {
+  __shared__ double red[16][17];
+  const int64_t B = 1ll << *st.m, per = dis_range_buckets(*st.total, B, max_ranges, fixed);
+  const int64_t nr = (B + per - 1) / per;
+  const int t = threadIdx.x & 15, l = threadIdx.x >> 4;
+  const int64_t a = blockIdx.x * 16ll + t;
+  double s = 0.0;
+  if (a < n_cand) {
+    int64_t r = l;
+    for (; r + 48 < nr; r += 64) {   // four loads in flight, added in order
+      const double v0 = partial[r * n_cand + a], v1 = partial[(r + 16) * n_cand + a];
+      const double v2 = partial[(r + 32) * n_cand + a], v3 = partial[(r + 48) * n_cand + a];
+      s += v0; s += v1; s += v2; s += v3;
+    }
+    for (; r < nr; r += 16) s += partial[r * n_cand + a];
+  }
+  red[l][t] = s;
+  __syncthreads();
+  if (threadIdx.x < 16 && a < n_cand) {
+    double v = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v += red[i][t];
+    g[a] = v;
   }
 }
 
@@ -436,38 +541,47 @@ int dis_one_blocks_per_cu(int W) {
   return (e == hipSuccess && nb > 0) ? nb : 1;
 }
 
-void launch_dis(int W, const StoreDev& st, const double* lut, const uint64_t* cx,
-                const uint64_t* cz, int64_t n_cand, int64_t ld_cand, int mode, int tile,
-                int grid, double* partial, int grid_terms, double* g, hipStream_t s,
-                const double* theta, const double* phi, int nq, double* tables) {
+template <int W>
+static void launch_dis_w(const StoreDev& st, const double* theta, const double* phi, int nq, const uint64_t* cx,
+                         const uint64_t* cz, int64_t n_cand, int64_t ld_cand, int tile, int n_cu, int max_ranges,
+                         int fixed, double* partial, hipStream_t s) {
+  const size_t lds = sizeof(DisShared<W>);
+  (void)hipFuncSetAttribute((const void*)k_dis_batched<W>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  // three workgroups per CU are resident (two for wide keys; registers); four
+  // times as many even out ranges that need a second pass (1e6 terms x 1000
+  // candidates: 1903 us with the resident ones alone, 1678 us with four times,
+  // 1731 us with eight times as many: each builds its tables)
+  hipLaunchKernelGGL(k_dis_batched<W>, dim3(n_cu * (W <= 2 ? 12 : 8)), dim3(kDisB), lds, s, st, nq, theta, phi, cx, cz,
+                     n_cand, ld_cand, tile, max_ranges, fixed, partial);
+}
+
+void launch_dis_batched(int W, const StoreDev& st, const double* theta, const double* phi, int nq, const uint64_t* cx,
+                        const uint64_t* cz, int64_t n_cand, int64_t ld_cand, int tile, int n_cu, int max_ranges,
+                        int fixed, double* partial, double* g, hipStream_t s) {
   if (n_cand <= 0) return;
   if (tile < 1 || tile > kDisTile) tile = kDisTile;
-  if (mode == 0) {
-    DisEnt* ent = reinterpret_cast<DisEnt*>(tables);
-    double* fac = tables + dis_tables_doubles(W) - 64 * W * 4;
-    hipLaunchKernelGGL(k_dis_tables, dim3((64 * W + 255) / 256), dim3(256), 0, s, W, nq, theta, phi,
-                       ent, fac);
-    const int64_t tiles = (n_cand + tile - 1) / tile;
-    dim3 gr((unsigned)tiles, (unsigned)grid_terms);
+  switch (W) {
+    case 1: launch_dis_w<1>(st, theta, phi, nq, cx, cz, n_cand, ld_cand, tile, n_cu, max_ranges, fixed, partial, s); break;
+    case 2: launch_dis_w<2>(st, theta, phi, nq, cx, cz, n_cand, ld_cand, tile, n_cu, max_ranges, fixed, partial, s); break;
+    case 3: launch_dis_w<3>(st, theta, phi, nq, cx, cz, n_cand, ld_cand, tile, n_cu, max_ranges, fixed, partial, s); break;
+    default: launch_dis_w<4>(st, theta, phi, nq, cx, cz, n_cand, ld_cand, tile, n_cu, max_ranges, fixed, partial, s); break;
+  }
+  hipLaunchKernelGGL(k_dis_reduce, dim3((unsigned)((n_cand + 15) / 16)), dim3(kBlock), 0, s, st, partial, max_ranges,
+                     fixed, n_cand, g);
+}
+
+void launch_dis_plain(int W, const StoreDev& st, const double* lut, const uint64_t* cx, const uint64_t* cz,
+                      int64_t n_cand, int64_t ld_cand, int grid, double* partial, double* g, hipStream_t s) {
+  if (n_cand <= 0) return;
+  // partial[0, grid) per-workgroup sums, then the finish counter
+  unsigned int* done = reinterpret_cast<unsigned int*>(partial + grid);
+  hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, done);
+  for (int64_t a = 0; a < n_cand; ++a) {
     switch (W) {
-      case 1: hipLaunchKernelGGL(k_dis_batched<1>, gr, dim3(kDisB), 0, s, st, ent, fac, cx, cz, n_cand, ld_cand, tile, partial); break;
-      case 2: hipLaunchKernelGGL(k_dis_batched<2>, gr, dim3(kDisB), 0, s, st, ent, fac, cx, cz, n_cand, ld_cand, tile, partial); break;
-      case 3: hipLaunchKernelGGL(k_dis_batched<3>, gr, dim3(kDisB), 0, s, st, ent, fac, cx, cz, n_cand, ld_cand, tile, partial); break;
-      default: hipLaunchKernelGGL(k_dis_batched<4>, gr, dim3(kDisB), 0, s, st, ent, fac, cx, cz, n_cand, ld_cand, tile, partial); break;
-    }
-    int64_t blocks = (n_cand + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(k_dis_reduce, dim3((unsigned)blocks), dim3(kBlock), 0, s, partial, grid_terms, n_cand, g);
-  } else {
-    // partial[0, grid) per-workgroup sums, then the finish counter
-    unsigned int* done = reinterpret_cast<unsigned int*>(partial + grid);
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, done);
-    for (int64_t a = 0; a < n_cand; ++a) {
-      switch (W) {
-        case 1: hipLaunchKernelGGL(k_dis_one<1>, dim3(grid), dim3(kBlock), 0, s, st, lut, cx, cz, ld_cand, a, partial, done, g); break;
-        case 2: hipLaunchKernelGGL(k_dis_one<2>, dim3(grid), dim3(kBlock), 0, s, st, lut, cx, cz, ld_cand, a, partial, done, g); break;
-        case 3: hipLaunchKernelGGL(k_dis_one<3>, dim3(grid), dim3(kBlock), 0, s, st, lut, cx, cz, ld_cand, a, partial, done, g); break;
-        default: hipLaunchKernelGGL(k_dis_one<4>, dim3(grid), dim3(kBlock), 0, s, st, lut, cx, cz, ld_cand, a, partial, done, g); break;
-      }
+      case 1: hipLaunchKernelGGL(k_dis_one<1>, dim3(grid), dim3(kBlock), 0, s, st, lut, cx, cz, ld_cand, a, partial, done, g); break;
+      case 2: hipLaunchKernelGGL(k_dis_one<2>, dim3(grid), dim3(kBlock), 0, s, st, lut, cx, cz, ld_cand, a, partial, done, g); break;
+      case 3: hipLaunchKernelGGL(k_dis_one<3>, dim3(grid), dim3(kBlock), 0, s, st, lut, cx, cz, ld_cand, a, partial, done, g); break;
+      default: hipLaunchKernelGGL(k_dis_one<4>, dim3(grid), dim3(kBlock), 0, s, st, lut, cx, cz, ld_cand, a, partial, done, g); break;
     }
   }
 }
