@@ -415,11 +415,12 @@ int iqcc_qmf_energy_noalloc(iqcc_ctx *ctx, const iqcc_store *h, const double *th
  * iqcc_expectations computes it (same values up to the rounding of the
  * product; rows that hold no term are left untouched).  dtheta and dphi are
  * the same bits on every run and for any order of the rows within the
- * buckets: every per-term contribution is added as an exact 120-bit fixed-
- * point integer (resolution 2^-60), and the per-workgroup sums are reduced
- * in a fixed order.  The exact sums need every |c| < 2^31 and, per workgroup,
- * (largest |c|) * (terms) < 2^42; past those bounds, or with a non-finite
- * coefficient or angle, dtheta and dphi come out NaN. */
+ * buckets: the contributions are added as exact fixed-point integers
+ * (resolution 2^-186 before a division by one qubit factor, at least 2^-86
+ * after it; a contribution that holds a qubit factor below 2^-100 is left out),
+ * and the per-workgroup sums are reduced in a fixed order.  The exact sums need every |c| < 2^31; past
+ * that bound, or with a non-finite coefficient or angle, dtheta and dphi come
+ * out NaN. */
 int iqcc_qmf_energy_backward(iqcc_ctx *ctx, const iqcc_store *h, const double *theta,
                              const double *phi, const double *dE_scale, double *dtheta,
                              double *dphi, double *lambda, void *stream);

@@ -1173,12 +1173,10 @@ int iqcc_qmf_energy_backward(iqcc_ctx* ctx, const iqcc_store* h, const double* t
   if (rc) return rc;
   if (!h || !theta || !phi || !dtheta || !dphi) return fail(ctx, IQCC_ERR_INVALID_ARG, "null argument");
   hipStream_t s = as_stream(stream);
-  const int grid = (int)(ctx->n_cu * energy_bwd_blocks_per_cu(h->W));
+  const int grid = ctx->n_cu;   // the LDS of one CU holds one workgroup
   rc = ensure_partial(ctx, (int64_t)grid * 3 * h->nq);
   if (rc) return rc;
-  launch_build_lut(h->W, h->nq, theta, phi, ctx->lut, s);
-  launch_energy_backward(h->W, h->nq, h->d, grid, theta, phi, ctx->lut, dE, lambda, ctx->partial, s);
-  launch_backward_finalize(h->nq, grid, ctx->partial, theta, phi, dE, dtheta, dphi, s);
+  launch_energy_backward(h->W, h->nq, h->d, grid, theta, phi, dE, lambda, ctx->partial, dtheta, dphi, s);
   LAUNCH_CHECK(ctx);
   return IQCC_OK;
 }

@@ -719,15 +719,9 @@ void launch_energy_anti(int W, const StoreDev& st, const PauliKey& P, int grid, 
 // workgroups per CU; slot: a finish slot (see finish_arrive).
 void launch_energy(int W, int nq, const StoreDev& st, int n_cu, int per_cu, size_t lds_per_cu, const double* theta,
                    const double* phi, double* slot, double* out, hipStream_t s);
-int energy_bwd_blocks_per_cu(int W);
-void launch_energy_backward(int W, int nq, const StoreDev& st, int grid, const double* theta,
-                            const double* phi, const double* lut, const double* dE,
-                            double* lam /*null or [arena rows]*/, double* acc /*[grid][3*nq]*/,
-                            hipStream_t s);
-void launch_backward_finalize(int nq, int grid, const double* acc, const double* theta,
-                              const double* phi, const double* dE, double* dtheta, double* dphi,
-                              hipStream_t s);
-
+void launch_energy_backward(int W, int nq, const StoreDev& st, int grid, const double* theta, const double* phi,
+                            const double* dE, double* lam /*null or [arena rows]*/, double* acc /*[3*nq][grid]*/,
+                            double* dtheta, double* dphi, hipStream_t s);
 int dis_one_blocks_per_cu(int W);
 // max_ranges x n_cand doubles of partial; fixed: exactly max_ranges term
 // ranges (a knob), else as many as the terms fill.

@@ -126,12 +126,11 @@ struct EnergyTable {
   static constexpr int kBuild = 64 * W * 4 + (kNibble ? 32 * W * 16 : 0);
 };
 
-// Builds the table (the whole workgroup; ends with a barrier).  Multiplying by
-// the identity's factor 1.0 is exact.
-template <int W>
-__device__ void build_energy_table(double* lut, double* tmp, int nq, const double* theta, const double* phi) {
-  double* fac = tmp;   // [64 W][4]: I, X, Z, Y
-  for (int q = threadIdx.x; q < 64 * W; q += kE4Block) {
+// The qubits' factors [64 W][4] (I, X, Z, Y), 1.0 past the last qubit.  The
+// workgroup's NT threads.
+template <int W, int NT>
+__device__ __forceinline__ void build_factors(double* fac, int nq, const double* theta, const double* phi) {
+  for (int q = threadIdx.x; q < 64 * W; q += NT) {
     double st = 0.0, ct = 1.0, sp = 0.0, cp = 1.0;
     const bool live = q < nq;
     if (live) {
@@ -141,20 +140,27 @@ __device__ void build_energy_table(double* lut, double* tmp, int nq, const doubl
 #pragma unroll
     for (int op = 0; op < 4; ++op) fac[4 * q + op] = live ? bloch_factor(op, st, ct, sp, cp) : 1.0;
   }
-  __syncthreads();
+}
+
+// Builds the table from the factors in tmp (the whole workgroup; a barrier has
+// to lie between the factors and this, and it ends with one).  Multiplying by
+// the identity's factor 1.0 is exact.
+template <int W, int NT>
+__device__ void build_energy_table(double* lut, double* tmp) {
+  const double* fac = tmp;
   if constexpr (EnergyTable<W>::kNibble) {
-    double* pair = fac + 64 * W * 4;   // [32 W][16]: z bits low, x bits high
-    for (int e = threadIdx.x; e < 32 * W * 16; e += kE4Block) {
+    double* pair = tmp + 64 * W * 4;   // [32 W][16]: z bits low, x bits high
+    for (int e = threadIdx.x; e < 32 * W * 16; e += NT) {
       const int q = 2 * (e >> 4), z = e & 3, x = (e >> 2) & 3;
       pair[e] = fac[4 * q + ((x & 1) | ((z & 1) << 1))] * fac[4 * (q + 1) + ((x >> 1) | ((z >> 1) << 1))];
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < EnergyTable<W>::kEntries; e += kE4Block) {
+    for (int e = threadIdx.x; e < EnergyTable<W>::kEntries; e += NT) {
       const int z = e & 15, x = (e >> 4) & 15, gi = e >> 8;
       lut[e] = pair[(2 * gi) * 16 + ((z & 3) | ((x & 3) << 2))] * pair[(2 * gi + 1) * 16 + ((z >> 2) | ((x >> 2) << 2))];
     }
   } else {
-    for (int e = threadIdx.x; e < EnergyTable<W>::kEntries; e += kE4Block) {
+    for (int e = threadIdx.x; e < EnergyTable<W>::kEntries; e += NT) {
       const int code = e % kLutEntries, gi = e / kLutEntries;
       const int h = gi / kGroupsPerHalf, g = gi % kGroupsPerHalf;
       double p = 1.0;
@@ -273,7 +279,9 @@ __global__ __launch_bounds__(kE4Block) void k_energy(StoreDev st, int nq, const 
         }
       }
       if (!table) {   // built while the first rows are on their way
-        build_energy_table<W>(lut, tmp, nq, theta, phi);
+        build_factors<W, kE4Block>(tmp, nq, theta, phi);
+        __syncthreads();
+        build_energy_table<W, kE4Block>(lut, tmp);
         table = true;
       }
 #pragma unroll
@@ -325,230 +333,271 @@ void launch_energy(int W, int nq, const StoreDev& st, int n_cu, int per_cu, size
 // S[q][sigma] adds, over the terms with sigma on qubit q, c times the product
 // of the term's other factors.
 //
-// The product of a term runs over its 3-qubit groups (the energy table L), so
-// the derivative is first formed per group table entry:
-//   T[g][e] = sum over the terms whose group g has code e != 0 of
-//             c * prod_{g' != g} L_g',
-// and once per workgroup S[q][sigma] = sum over the codes e of q's group with
-// sigma at q's position of T[g][e] * (product of the group's other qubit
-// factors of that code).  The product of a term's other groups comes from
-// prefix and suffix products -- inside each 32-bit half word over its 11
-// groups, and across the half words over their products -- with no division,
-// so vanishing factors need no special case.
+// All terms of S[q][sigma] miss the same factor b = b_q(sigma), so
+//   S[q][sigma] = (sum of v_k over the terms with sigma on q) / b,
+//   v_k = c_k times the product of all of the term's factors,
+// with one division at the end.  Factors that are zero or below 2^-100 ("null")
+// are left out of v_k instead: a term with one null factor, on qubit q, counts
+// only for q and its sigma there (undivided), a term with several counts
+// nowhere -- what it would add holds a null factor and is below 2^-69.
 //
-// Summation order does not change the result.  Each value is split into two
-// integers, round(v * 2^20) and round((v - that * 2^-20) * 2^60), and added
-// to two 64-bit integer tables with LDS atomics, which are exact; per
-// workgroup the two sums turn into one double, and the per-workgroup S are
-// reduced in a fixed order, so dE/dtheta and dE/dphi are the same on every
-// run.  The split is exact for |v| < 2^31 and the sums cannot overflow while
-// (largest |c| of the workgroup's terms) * (its term count) < 2^42 and the
-// count is below 2^23; a workgroup past these bounds, or one that meets a
-// non-finite coefficient or angle, writes NaN instead of its S.  Resolution:
-// 2^-61 per added value.
-// acc layout per workgroup: [3 * nq] with sigma order X, Z, Y.
+// The sums are a contraction of the 0/1 matrix (x bits, z bits, x and z bits
+// of the keys) with the v_k, and they are made exactly, so that they do not
+// depend on the order of the rows: v_k is taken as a fixed-point number
+// (resolution 2^-186, |v| < 2^31) of 32 digits of 7 bits, and the matrix cores
+// add the digits of all terms per key bit (v_mfma_i32_32x32x32_i8: 32 qubits x
+// 32 terms x 32 digits), exactly in 32-bit integers for up to 2^24 terms per
+// workgroup.  Sums over exactly one of X, Z, Y are integer differences of
+// those.  Per workgroup the 32 digit sums turn into one double, and the
+// workgroups' doubles are added in a fixed order.  A workgroup that meets a
+// non-finite coefficient or angle, |c| >= 2^31, or 2^24 terms writes NaN.
+//
+// Work split: a team of TW waves takes 64 TW terms at a time.  Each wave makes
+// v, its digits and, by a 64 x 64 bit transposition in registers, the bits of
+// 64 terms per qubit; after a barrier each wave multiplies the bits of "its"
+// 32 qubits with the digits of the team's terms (of half of them for one-word
+// keys).  The 32 terms of one matrix product may come in any order as long as
+// bits and digits agree, so a dword of the bit operand is (bits >> s) &
+// 0x01010101 -- terms s, s + 8, s + 16, s + 24 -- and a term's digits are
+// stored at the byte that this order gives it.
+//
+// A workgroup holds three teams (one for wide keys), one wave of each per SIMD,
+// and a team has a barrier of its own, so that one team's matrix products run
+// beside another's vector work (4e6 two-word terms: four teams of 128 registers
+// 117 us, spilling; three 113 us; a workgroup per team with a 3-qubit table 131
+// us; the workgroup's barrier in place of the teams' 117 us).
+//
+// Bound: VALU issue (about 590 instructions per 64 two-word terms: 128 for the
+// product, 190 for digits and transposition, 216 for the bit operands), and 24
+// matrix products of 32 cycles.  4e6 two-word terms: 112 us; the former kernel,
+// which added every (term, group) value to integer tables in LDS with two
+// 64-bit atomics, took 203 us.  1.1e6 one-word terms: 27 us (67 us).
+// acc layout: [3 * nq][workgroups] with sigma order X, Z, Y.
 // ---------------------------------------------------------------------------
-constexpr int kBwdBlock = 512;
-constexpr int kBwdGroup = 256;   // most buckets per group of one flat range
-// LDS tables of the backward hold each 3-qubit group's 64 entries at a stride
-// of 65, so that equal codes of different groups fall in different banks.
-constexpr int kBwdStride = kLutEntries + 1;
-
-size_t energy_bwd_lds_bytes(int W) {
-  // energy table, the two integer tables (the per-qubit factors of the
-  // epilogue reuse the first), bucket-group scan
-  return (size_t)3 * W * kGroupsPerWord * kBwdStride * 8 + (size_t)(2 * kBwdGroup + 1) * 8;
-}
-
-// Workgroups per CU that the LDS of one CU holds (160 KiB), at most 2048
-// threads (32 waves) in all.
-int energy_bwd_blocks_per_cu(int W) {
-  const int k = (int)((size_t)160 * 1024 / (energy_bwd_lds_bytes(W) + 512));
-  const int kmax = 2048 / kBwdBlock;
-  return k < 1 ? 1 : k > kmax ? kmax : k;
-}
-
-// v as round(v * 2^20) * 2^-20 + round(r * 2^60) * 2^-60 (r the remainder),
-// both added to their integer tables.  Adding 1.5 * 2^32 (resp. 1.5 * 2^-8)
-// rounds to a multiple of 2^-20 (2^-60), and the difference of the bit
-// patterns is that multiple as an integer (both sums stay in the binade of the
-// constant, whose low 32 bits are zero).
-__device__ __forceinline__ void add_fixed(unsigned long long* hi, unsigned long long* lo, int e, double v) {
-  const double k1 = 0x1.8p32, k0 = 0x1.8p-8;
-  const double a1 = v + k1;
-  const double r = v - (a1 - k1);
-  const double a0 = r + k0;
-  atomicAdd(&hi[e], (unsigned long long)(__double_as_longlong(a1) - __double_as_longlong(k1)));
-  atomicAdd(&lo[e], (unsigned long long)(__double_as_longlong(a0) - __double_as_longlong(k0)));
-}
-
-// One term of the backward: T contributions of its non-identity groups and,
-// when lam is given, its cotangent.
 template <int W>
-__device__ __forceinline__ void bwd_term(const double* lut, unsigned long long* thi,
-                                         unsigned long long* tlo, const uint64_t* kx,
-                                         const uint64_t* kz, double c, double* lam_row,
-                                         double scale) {
-  constexpr int NH = kGroupsPerHalf * kBwdStride;
-  // products of the 2W half words (identity groups read entry 0 = 1.0)
-  double hp[2 * W];
-#pragma unroll
-  for (int h = 0; h < 2 * W; ++h) {
-    const uint32_t xh = (uint32_t)(kx[h >> 1] >> (32 * (h & 1)));
-    const uint32_t zh = (uint32_t)(kz[h >> 1] >> (32 * (h & 1)));
-    const double* lh = lut + h * NH;
-    double p0 = 1.0, p1 = 1.0;
-#pragma unroll
-    for (int g = 0; g < kGroupsPerHalf; ++g) {
-      const uint32_t code = __builtin_amdgcn_ubfe(xh, 3 * g, 3) | (__builtin_amdgcn_ubfe(zh, 3 * g, 3) << 3);
-      if (g & 1) p1 *= lh[g * kBwdStride + code]; else p0 *= lh[g * kBwdStride + code];
-    }
-    hp[h] = p0 * p1;
-  }
-  // <K> for the coefficient cotangent
-  if (lam_row) {
-    double all = hp[0];
-#pragma unroll
-    for (int h = 1; h < 2 * W; ++h) all *= hp[h];
-    *lam_row = scale * all;
-  }
-  // c times the product of the other half words, per half word
-  double ho[2 * W];
-  double pre = c;
-#pragma unroll
-  for (int h = 0; h < 2 * W; ++h) { ho[h] = pre; pre *= hp[h]; }
-  double suf = 1.0;
-#pragma unroll
-  for (int h = 2 * W - 1; h >= 0; --h) { ho[h] *= suf; suf *= hp[h]; }
-  // each half word: prefix and suffix over its groups.  A term visits its
-  // half words, and the groups of each, starting at ones picked from its own
-  // key bits, so that the lanes of a wave add into different groups' tables
-  // at a time (fewer lanes on one LDS address or bank); the values do not
-  // depend on where the term sits in the store.
-  const uint32_t mix = ((uint32_t)kx[0] ^ (uint32_t)(kz[0] >> 29) ^ (uint32_t)(kx[W - 1] >> 35)) * 0x9E3779B1u;
-  const int rot = (int)__umulhi(mix, 2u * W);
-#pragma unroll 1
-  for (int j = 0; j < 2 * W; ++j) {
-    int h = rot + j;
-    h = h >= 2 * W ? h - 2 * W : h;
-    uint64_t xw = kx[0], zw = kz[0];
-    double oh = ho[0];
-#pragma unroll
-    for (int u = 1; u < 2 * W; ++u) {
-      if (u == h) oh = ho[u];
-      if ((u & 1) == 0 && u == (h & ~1)) { xw = kx[u >> 1]; zw = kz[u >> 1]; }
-    }
-    const uint32_t xh = (uint32_t)(xw >> (32 * (h & 1)));
-    const uint32_t zh = (uint32_t)(zw >> (32 * (h & 1)));
-    const int rg = (int)__umulhi(mix * 0x85EBCA6Bu, (uint32_t)kGroupsPerHalf);
-    const uint64_t xr = ((uint64_t)xh | ((uint64_t)xh << 33)) >> (3 * rg);
-    const uint64_t zr = ((uint64_t)zh | ((uint64_t)zh << 33)) >> (3 * rg);
-    double L[kGroupsPerHalf];
-    uint32_t code[kGroupsPerHalf];
-    int idx[kGroupsPerHalf];
-    // group rg + g of the half, wrapped: the base before and after the wrap
-    const int base_lo = h * NH + rg * kBwdStride;
-    const int base_hi = base_lo - kGroupsPerHalf * kBwdStride;
-#pragma unroll
-    for (int g = 0; g < kGroupsPerHalf; ++g) {
-      code[g] = (uint32_t)((xr >> (3 * g)) & 7) | ((uint32_t)((zr >> (3 * g)) & 7) << 3);
-      idx[g] = (rg < kGroupsPerHalf - g ? base_lo : base_hi) + g * kBwdStride + (int)code[g];
-      L[g] = lut[idx[g]];
-    }
-    double sf[kGroupsPerHalf];
-    sf[kGroupsPerHalf - 1] = 1.0;
-#pragma unroll
-    for (int g = kGroupsPerHalf - 1; g > 0; --g) sf[g - 1] = sf[g] * L[g];
-    double pg = oh;
-#pragma unroll
-    for (int g = 0; g < kGroupsPerHalf; ++g) {
-      if (code[g] != 0) add_fixed(thi, tlo, idx[g], pg * sf[g]);
-      pg *= L[g];
-    }
-  }
-}
+struct BwdGeom {
+  static constexpr int kBlocks = 2 * W;                 // 32-qubit blocks
+  static constexpr int kTeamWaves = W == 1 ? 4 : 2 * W;
+  static constexpr int kTeams = W <= 2 ? 3 : 1;
+  static constexpr int kThreads = 64 * kTeamWaves * kTeams;
+  static constexpr int kSplit = kTeamWaves / kBlocks;   // waves that share a block's terms
+};
+constexpr int kBwdGroup = 256;     // most buckets per group of one flat range
+constexpr int kDigits = 32;
+constexpr int kDigitStride = 80;   // bytes per digit row of 64 terms (padded: 16-byte reads of 8 lanes hit all banks)
+constexpr int kDigitBase = -186;   // log2 of the lowest digit's weight
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
 
 template <int W>
-__global__ __launch_bounds__(kBwdBlock, 4) void k_energy_bwd(StoreDev st, int nq, const double* theta,
-                                                             const double* phi, const double* lut_g,
-                                                             const double* dE, double* lam,
-                                                             double* acc_g) {
-  constexpr int NE = W * kGroupsPerWord * kBwdStride;
-  constexpr int NH = kGroupsPerHalf * kBwdStride;   // entries per half word
+struct BwdShared {
+  using T = EnergyTable<W>;
+  using B = BwdGeom<W>;
+  double lut[T::kEntries];                            // afterwards the digit sums
+  double fac[64 * W * 4];
+  uint64_t bits[2][B::kTeams][B::kTeamWaves][64 * W];   // x, z: 64 terms per qubit
+  alignas(16) uint8_t dig[B::kTeams][B::kTeamWaves][kDigits * kDigitStride];
+  int64_t s_off[kBwdGroup];
+  uint32_t s_pre[kBwdGroup + 1];
+  uint64_t null_mask[3][W];                           // qubits whose X, Z, Y factor is null
+  uint64_t scan_tmp[B::kThreads / 64];
+  unsigned arrived[B::kTeams];
+  int bad;
+  static_assert(sizeof(bits) + sizeof(dig) >= sizeof(double) * T::kBuild, "the table is built there");
+  static_assert(sizeof(lut) + sizeof(fac) + sizeof(bits) + sizeof(dig) >= sizeof(int) * 96 * B::kBlocks * kDigits,
+                "the digit sums fit");
+};
+
+// Workgroups that take part: one per kThreads rows, at most grid and one per bucket.
+__device__ __forceinline__ int64_t bwd_active(int64_t total, int64_t buckets, int grid, int threads) {
+  int64_t a = (total + threads - 1) / threads;
+  a = a < 1 ? 1 : (a > grid ? grid : a);
+  return a > buckets ? buckets : a;
+}
+
+// Transposition of the 64 x 64 bit matrix of a wave: lane l holds row l in
+// (lo, hi) and afterwards bit l of every lane's row, lane order.  Step s swaps
+// the bits with index bit s set in lanes without it against those without it
+// in lanes with it.
+__device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b) {   // one v_bfi_b32
+  return b ^ (m & (a ^ b));
+}
+
+// N rows of 32 bits per lane, one step for all of them at a time (lane moves
+// need wait states after the write of their source).
+template <int N>
+__device__ __forceinline__ void transpose32(uint32_t (&a)[N], int lane) {
+  uint32_t t[N];
+  const uint32_t p16 = (lane & 16) ? 0x07060302u : 0x05040100u;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {   // 16: (own, other row's) and (other row's, own)
+    auto r = __builtin_amdgcn_permlane16_swap(a[i], a[i], false, false);
+    a[i] = r[0];
+    t[i] = r[1];
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) a[i] = __builtin_amdgcn_perm(t[i], a[i], p16);
+  const uint32_t p8 = (lane & 8) ? 0x03070105u : 0x06020400u;
+#pragma unroll
+  for (int i = 0; i < N; ++i) t[i] = (uint32_t)__builtin_amdgcn_mov_dpp((int)a[i], 0x128, 0xF, 0xF, false);   // row_ror:8
+#pragma unroll
+  for (int i = 0; i < N; ++i) a[i] = __builtin_amdgcn_perm(t[i], a[i], p8);
+  // 4: row_shl:4 for the lanes without bit 2, row_shr:4 for the others
+#pragma unroll
+  for (int i = 0; i < N; ++i) t[i] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a[i], 0x104, 0xF, 0x5, false);
+#pragma unroll
+  for (int i = 0; i < N; ++i) t[i] = (uint32_t)__builtin_amdgcn_update_dpp((int)t[i], (int)a[i], 0x114, 0xF, 0xA, false);
+  const uint32_t r4 = (lane & 4) ? 4 : 28, m4 = (lane & 4) ? 0xF0F0F0F0u : 0x0F0F0F0Fu;
+#pragma unroll
+  for (int i = 0; i < N; ++i) a[i] = bit_select(m4, a[i], __builtin_amdgcn_alignbit(t[i], t[i], r4));
+  const uint32_t r2 = (lane & 2) ? 2 : 30, m2 = (lane & 2) ? 0xCCCCCCCCu : 0x33333333u;
+#pragma unroll
+  for (int i = 0; i < N; ++i) t[i] = (uint32_t)__builtin_amdgcn_mov_dpp((int)a[i], 0x4E, 0xF, 0xF, false);   // quad_perm 2,3,0,1
+#pragma unroll
+  for (int i = 0; i < N; ++i) a[i] = bit_select(m2, a[i], __builtin_amdgcn_alignbit(t[i], t[i], r2));
+  const uint32_t r1 = (lane & 1) ? 1 : 31, m1 = (lane & 1) ? 0xAAAAAAAAu : 0x55555555u;
+#pragma unroll
+  for (int i = 0; i < N; ++i) t[i] = (uint32_t)__builtin_amdgcn_mov_dpp((int)a[i], 0xB1, 0xF, 0xF, false);   // quad_perm 1,0,3,2
+#pragma unroll
+  for (int i = 0; i < N; ++i) a[i] = bit_select(m1, a[i], __builtin_amdgcn_alignbit(t[i], t[i], r1));
+}
+
+// The 64 x 64 bits of x and of z (word w) of the wave's lanes, transposed in place.
+__device__ __forceinline__ void transpose64(uint64_t& x, uint64_t& z, int lane) {
+  auto rx = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)(x >> 32), false, false);
+  auto rz = __builtin_amdgcn_permlane32_swap((uint32_t)z, (uint32_t)(z >> 32), false, false);
+  uint32_t r[4] = {rx[0], rx[1], rz[0], rz[1]};
+  transpose32<4>(r, lane);
+  x = (uint64_t)r[0] | ((uint64_t)r[1] << 32);
+  z = (uint64_t)r[2] | ((uint64_t)r[3] << 32);
+}
+
+// Digits of v (|v| < 2^31) into the wave's digit rows, at this lane's term.
+__device__ __forceinline__ void put_digits(uint8_t* dig, int lane, double v) {
+  const v4i zero = {0, 0, 0, 0};
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {   // 32 rows of 64 bytes
+    const int k = lane + 64 * i;
+    *reinterpret_cast<v4i*>(dig + (k >> 2) * kDigitStride + (k & 3) * 16) = zero;
+  }
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const int e = (int)(u >> 52) & 0x7FF;
+  uint64_t mant = (u & 0xFFFFFFFFFFFFFull) | (e ? 1ull << 52 : 0ull);
+  int p = e - 1075 - kDigitBase;   // bit position of the lowest mantissa bit, at most 164
+  if (p < 0) {
+    mant = p > -64 ? mant >> -p : 0ull;
+    p = 0;
+  }
+  const int d0 = (p * 293) >> 11;   // p / 7, at most 23
+  int64_t m = (int64_t)(mant << (p - 7 * d0));
+  m = (int64_t)u < 0 ? -m : m;      // two's complement: the last digit carries the sign
+  uint8_t* at = dig + d0 * kDigitStride + (lane & 32) + ((lane >> 2) & 1) * 16 + (lane & 3) * 4 + ((lane >> 3) & 3);
+  const uint32_t lo = (uint32_t)m, hi = (uint32_t)((uint64_t)m >> 32);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) at[j * kDigitStride] = (uint8_t)__builtin_amdgcn_ubfe(lo, 7 * j, 7);
+  at[4 * kDigitStride] = (uint8_t)(__builtin_amdgcn_alignbit(hi, lo, 28) & 127u);
+#pragma unroll
+  for (int j = 5; j < 8; ++j) at[j * kDigitStride] = (uint8_t)__builtin_amdgcn_ubfe(hi, 7 * j - 32, 7);
+  at[8 * kDigitStride] = (uint8_t)(hi >> 24);
+}
+
+// Barrier of one team's `waves` waves: an arrival counter in LDS that only
+// grows (`target` is the wave's own count of what it has to reach).  All waves
+// of a workgroup are resident, and every wave of a team passes the same
+// barriers, so each wait ends.
+__device__ __forceinline__ void team_barrier(unsigned* arrived, unsigned& target, unsigned waves) {
+  target += waves;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // this wave's LDS accesses are done
+  if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  while ((int)(target - __hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) > 0)
+    __builtin_amdgcn_s_sleep(1);
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+template <int W>
+__global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st, int nq, const double* theta,
+                                                                     const double* phi, const double* dE,
+                                                                     double* lam, double* acc_g) {
+  using BG = BwdGeom<W>;
+  constexpr int NT = BG::kThreads, NB = BG::kBlocks, TW = BG::kTeamWaves;
   extern __shared__ __align__(16) unsigned char smem_bwd[];
-  double* lut = (double*)smem_bwd;                                     // [NE] L per group entry
-  unsigned long long* thi = (unsigned long long*)(lut + NE);           // [NE] sums of round(v 2^20)
-  unsigned long long* tlo = thi + NE;                                  // [NE] sums of the remainders
-  double* fac = (double*)thi;   // epilogue: per qubit, factor of I, X, Z, Y (4 * 64W <= NE)
-  int64_t* s_pre = (int64_t*)(tlo + NE);                               // [kBwdGroup + 1] group scan
-  int64_t* s_off = s_pre + kBwdGroup + 1;                              // [kBwdGroup] first rows
-  __shared__ double s_cmax[kBwdBlock / 64];
-  __shared__ long long s_cnt[kBwdBlock / 64];
-  __shared__ uint64_t scan_tmp[kBwdBlock / 64];
-  __shared__ int s_bad;
-  if (threadIdx.x == 0) s_bad = 0;
+  BwdShared<W>& sh = *reinterpret_cast<BwdShared<W>*>(smem_bwd);
+  const int64_t B = 1ll << *st.m;
+  const int64_t active = bwd_active(*st.total, B, (int)gridDim.x, NT);
+  if (blockIdx.x >= active) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int team = wave / TW, tw = wave % TW, block = tw % NB, part = tw / NB;
+  // factors, their null masks, and the table of the factors without the null ones
+  double* tmp = reinterpret_cast<double*>(sh.bits);
+  if (threadIdx.x == 0) sh.bad = 0;
+  if (threadIdx.x < BG::kTeams) sh.arrived[threadIdx.x] = 0u;
+  unsigned target = 0;
+  for (int i = threadIdx.x; i < 3 * W; i += NT) (&sh.null_mask[0][0])[i] = 0ull;
+  build_factors<W, NT>(sh.fac, nq, theta, phi);
   __syncthreads();
-  for (int i = threadIdx.x; i < NE; i += kBwdBlock) {
-    const int k = i % kBwdStride;
-    lut[i] = k < kLutEntries ? lut_g[i / kBwdStride * kLutEntries + k] : 0.0;
-    thi[i] = tlo[i] = 0ull;
+  bool null_here = false;
+  for (int i = threadIdx.x; i < 64 * W * 4; i += NT) {
+    const int q = i >> 2, op = i & 3;
+    const double f = sh.fac[i];
+    const bool null = fabs(f) < 0x1p-100;
+    if (null) {
+      atomicOr((unsigned long long*)&sh.null_mask[op == 1 ? 0 : op == 2 ? 1 : 2][q >> 6], 1ull << (q & 63));
+      null_here = true;
+    }
+    tmp[i] = null ? 1.0 : f;
+    if (op == 0 && q < nq && !(fabs(theta[q]) <= DBL_MAX && fabs(phi[q]) <= DBL_MAX)) sh.bad = 1;
   }
-  for (int q = threadIdx.x; q < nq; q += kBwdBlock)
-    if (!(fabs(theta[q]) <= DBL_MAX && fabs(phi[q]) <= DBL_MAX)) s_bad = 1;
+  const bool any_null = __syncthreads_or(null_here) != 0;
+  build_energy_table<W, NT>(sh.lut, tmp);
   const double scale = dE ? *dE : 1.0;
   bool ok = true;   // every coefficient finite and below 2^31 in magnitude
-  double cmax = 0.0;
-  long long nmine = 0;
-  // Workgroup g takes the groups of G consecutive buckets g, g + grid, ...;
+  int64_t nwg = 0;   // terms of the workgroup
+  v16i sx, sz, sy;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) sx[i] = sz[i] = sy[i] = 0;
+  // Workgroup g takes the groups of G consecutive buckets g, g + active, ...;
   // a group's rows are one flat range, one term per thread and pass, the next
   // pass's term loaded while this one is processed.
-  const int64_t B = 1ll << *st.m;
-  int64_t G = B / gridDim.x;
-  G = G < 1 ? 1 : (G > kBwdGroup ? kBwdGroup : G);
+  int64_t G = (B + active - 1) / active;
+  G = G > kBwdGroup ? kBwdGroup : G;
   const int64_t ngroups = (B + G - 1) / G;
-  for (int64_t grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
+  for (int64_t grp = blockIdx.x; grp < ngroups; grp += active) {
     const int64_t b = grp * G + threadIdx.x;
     const bool mine = threadIdx.x < G && b < B;
     const int64_t cnt = mine ? st.cnt[b] : 0;
     const int64_t off = mine ? st.off[b] : 0;
     uint64_t total;
     // (the scan's barriers also order the previous group's reads of s_pre)
-    const uint64_t ex = block_exclusive_scan_n<kBwdBlock / 64>((uint64_t)cnt, scan_tmp, total);
+    const uint64_t ex = block_exclusive_scan_n<NT / 64>((uint64_t)cnt, sh.scan_tmp, total);
     if (threadIdx.x < kBwdGroup) {
-      s_pre[threadIdx.x] = (int64_t)ex;
-      s_off[threadIdx.x] = off;
+      sh.s_pre[threadIdx.x] = (uint32_t)ex;
+      sh.s_off[threadIdx.x] = off;
     }
-    if (threadIdx.x == 0) s_pre[kBwdGroup] = (int64_t)total;
+    if (threadIdx.x == 0) sh.s_pre[kBwdGroup] = (uint32_t)total;
     __syncthreads();
-    const int64_t n = (int64_t)total;
-    auto row_of = [&](int64_t i) {
-      int lo = 0;   // the last bucket of the group whose first row is <= i
-#pragma unroll
-      for (int step = kBwdGroup / 2; step; step >>= 1)
-        if (s_pre[lo + step] <= i) lo += step;
-      return s_off[lo] + (i - s_pre[lo]);
-    };
-    uint64_t cx[W], cz[W], nx[W], nz[W];
-    double cc = 0.0, nc = 0.0;
-    int64_t crow = 0, nrow = 0;
-#pragma unroll
-    for (int w = 0; w < W; ++w) cx[w] = cz[w] = 0;
-    if (threadIdx.x < n) {
-      crow = row_of(threadIdx.x);
-#pragma unroll
-      for (int w = 0; w < W; ++w) {
-        cx[w] = __builtin_nontemporal_load(&st.x[w * st.cap + crow]);
-        cz[w] = __builtin_nontemporal_load(&st.z[w * st.cap + crow]);
-      }
-      cc = __builtin_nontemporal_load(&st.c[crow]);
-    }
-    for (int64_t i0 = 0; i0 < n; i0 += kBwdBlock) {
-      const int64_t in = i0 + kBwdBlock + threadIdx.x;
+    const int64_t base = sh.s_off[0];   // one range of rows, as in the energy
+    const bool contig = __syncthreads_and(!mine || off - (int64_t)ex == base) != 0;
+    const uint32_t n = (uint32_t)total;
+    nwg += n;
+    uint64_t nx[W], nz[W];
+    double nc;
+    int64_t nrow;
+    auto load = [&](uint32_t i) {
+      nc = 0.0;
+      nrow = 0;
 #pragma unroll
       for (int w = 0; w < W; ++w) nx[w] = nz[w] = 0;
-      nc = 0.0;
-      if (in < n) {
-        nrow = row_of(in);
+      if (i < n) {
+        nrow = base + i;
+        if (!contig) {
+          int lo = 0;   // the last bucket of the group whose first row is <= i
+#pragma unroll
+          for (int step = kBwdGroup / 2; step; step >>= 1)
+            if (sh.s_pre[lo + step] <= i) lo += step;
+          nrow = sh.s_off[lo] + (i - sh.s_pre[lo]);
+        }
 #pragma unroll
         for (int w = 0; w < W; ++w) {
           nx[w] = __builtin_nontemporal_load(&st.x[w * st.cap + nrow]);
@@ -556,132 +605,176 @@ __global__ __launch_bounds__(kBwdBlock, 4) void k_energy_bwd(StoreDev st, int nq
         }
         nc = __builtin_nontemporal_load(&st.c[nrow]);
       }
-      if (i0 + threadIdx.x < n) {
-        ++nmine;
-        ok = ok && fabs(cc) < 0x1p31;
-        cmax = fmax(cmax, fabs(cc));
-        bwd_term<W>(lut, thi, tlo, cx, cz, cc, lam ? lam + crow : nullptr, scale);
-      }
+    };
+    load(threadIdx.x);
+    for (uint32_t i0 = 0; i0 < n; i0 += NT) {
+      uint64_t kx[W], kz[W];
 #pragma unroll
-      for (int w = 0; w < W; ++w) { cx[w] = nx[w]; cz[w] = nz[w]; }
-      cc = nc;
-      crow = nrow;
-    }
-  }
-  // bounds of the exact integer sums (see above), over the workgroup
+      for (int w = 0; w < W; ++w) { kx[w] = nx[w]; kz[w] = nz[w]; }
+      const double c = nc;
+      const int64_t row = nrow;
+      const bool live = i0 + threadIdx.x < n;
+      load(i0 + NT + threadIdx.x);
+      if (i0 + 64 * wave < n) {   // the wave has terms
+        const double pk = expect_table<W>(sh.lut, kx, kz);
+        double v = c * pk, all = pk;
+        if (any_null) {
+          uint64_t nm[W];
+          int nn = 0;
 #pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    cmax = fmax(cmax, __shfl_xor(cmax, d, 64));
-    nmine += __shfl_xor(nmine, d, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    s_cmax[threadIdx.x >> 6] = cmax;
-    s_cnt[threadIdx.x >> 6] = nmine;
-  }
-  if (!ok) s_bad = 1;
-  __syncthreads();
-  double cm = 0.0;
-  long long nwg = 0;
-  for (int k = 0; k < kBwdBlock / 64; ++k) {
-    cm = fmax(cm, s_cmax[k]);
-    nwg += s_cnt[k];
-  }
-  const bool in_range = s_bad == 0 && nwg < (1ll << 23) && cm * (double)nwg < 0x1p42;
-  // the sums as doubles, over the energy table (no longer needed), then the
-  // per-qubit factors over the first integer table
-  for (int i = threadIdx.x; i < NE; i += kBwdBlock)
-    lut[i] = (double)(long long)thi[i] * 0x1p-20 + (double)(long long)tlo[i] * 0x1p-60;
-  __syncthreads();
-  for (int q = threadIdx.x; q < 64 * W; q += kBwdBlock) {
-    double st_ = 0, ct = 1, sp = 0, cp = 1;
-    if (q < nq) {
-      sincos(theta[q], &st_, &ct);
-      sincos(phi[q], &sp, &cp);
-    }
-    for (int op = 0; op < 4; ++op) fac[4 * q + op] = bloch_factor(op, st_, ct, sp, cp);
-  }
-  __syncthreads();
-  // S[q][sigma] from T: the codes of q's group with sigma at q's position,
-  // each weighted by the product of the group's other factors of that code
-  for (int k = threadIdx.x; k < 3 * nq; k += kBwdBlock) {
-    const int q = k / 3, op = k % 3 + 1;   // op: 1 = X, 2 = Z, 3 = Y
-    const int h = q >> 5, bit = q & 31;
-    const int g = (int)div3_small((uint32_t)bit), r = bit - 3 * g;
-    const double* tg = lut + h * NH + g * kBwdStride;
-    double s = 0.0;
-    for (int code = 1; code < kLutEntries; ++code) {
-      if ((((code >> r) & 1) | (((code >> (3 + r)) & 1) << 1)) != op) continue;
-      double other = 1.0;
-      bool valid = true;
-      for (int r2 = 0; r2 < 3; ++r2) {
-        if (r2 == r) continue;
-        const int o2 = ((code >> r2) & 1) | (((code >> (3 + r2)) & 1) << 1);
-        if (3 * g + r2 >= 32) {   // position past the half word: no qubit
-          valid = valid && o2 == 0;
-          continue;
+          for (int w = 0; w < W; ++w) {
+            nm[w] = (kx[w] & ~kz[w] & sh.null_mask[0][w]) | (kz[w] & ~kx[w] & sh.null_mask[1][w]) |
+                    (kx[w] & kz[w] & sh.null_mask[2][w]);
+            nn += __popcll(nm[w]);
+          }
+          if (nn) {
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+              for (uint64_t t = nm[w]; t; t &= t - 1) {
+                const int q = __builtin_ctzll(t);
+                all *= sh.fac[4 * (64 * w + q) + ((int)((kx[w] >> q) & 1) | ((int)((kz[w] >> q) & 1) << 1))];
+              }
+            }
+#pragma unroll
+            for (int w = 0; w < W; ++w) { kx[w] &= nm[w]; kz[w] &= nm[w]; }
+            if (nn > 1) v = 0.0;
+          }
         }
-        other *= fac[4 * (32 * h + 3 * g + r2) + o2];
+        ok = ok && fabs(c) < 0x1p31;
+        if (lam && live) lam[row] = scale * all;
+        put_digits(sh.dig[team][tw], lane, fabs(v) < 0x1p31 ? v : 0.0);   // (c = 0 past the last row)
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          transpose64(kx[w], kz[w], lane);
+          sh.bits[0][team][tw][64 * w + lane] = kx[w];
+          sh.bits[1][team][tw][64 * w + lane] = kz[w];
+        }
       }
-      if (valid) s += tg[code] * other;
+      team_barrier(&sh.arrived[team], target, TW);
+#pragma unroll 1
+      for (int p = part; p < TW; p += BG::kSplit) {
+        if (i0 + 64 * (team * TW + p) >= n) break;
+        const uint64_t xm = sh.bits[0][team][p][32 * block + (lane & 31)];
+        const uint64_t zm = sh.bits[1][team][p][32 * block + (lane & 31)];
+        const uint8_t* dg = sh.dig[team][p] + (lane & 31) * kDigitStride + (lane >> 5) * 16;
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+          const v4i bd = *reinterpret_cast<const v4i*>(dg + 32 * kb);
+          const uint32_t xw = (uint32_t)(xm >> (32 * kb)) >> ((lane >> 5) * 4);
+          const uint32_t zw = (uint32_t)(zm >> (32 * kb)) >> ((lane >> 5) * 4);
+          v4i ax, az, ay;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            ax[i] = (int)((xw >> i) & 0x01010101u);
+            az[i] = (int)((zw >> i) & 0x01010101u);
+            ay[i] = ax[i] & az[i];
+          }
+          sx = __builtin_amdgcn_mfma_i32_32x32x32_i8(ax, bd, sx, 0, 0, 0);
+          sz = __builtin_amdgcn_mfma_i32_32x32x32_i8(az, bd, sz, 0, 0, 0);
+          sy = __builtin_amdgcn_mfma_i32_32x32x32_i8(ay, bd, sy, 0, 0, 0);
+        }
+      }
+      team_barrier(&sh.arrived[team], target, TW);
     }
-    acc_g[(int64_t)blockIdx.x * 3 * nq + k] = in_range ? s : __builtin_nan("");
+  }
+  if (!ok) sh.bad = 1;
+  __syncthreads();
+  const bool in_range = sh.bad == 0 && nwg < (1ll << 24);
+  // digit sums of all waves (x or z alone: less the sums over both), over the
+  // table and what follows it; then one double per (qubit, sigma).  Column d of
+  // row r sits at d ^ (r mod 32): both the adds (one row, all columns) and the
+  // reads (one column, all rows) touch every bank once.
+  int* sums = reinterpret_cast<int*>(sh.lut);   // [3][32 NB][kDigits]
+  for (int i = threadIdx.x; i < 3 * 32 * NB * kDigits; i += NT) sums[i] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int r = 32 * block + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
+    const int at = r * kDigits + ((lane & 31) ^ (r & 31));
+    atomicAdd(&sums[at], sx[i] - sy[i]);
+    atomicAdd(&sums[32 * NB * kDigits + at], sz[i] - sy[i]);
+    atomicAdd(&sums[64 * NB * kDigits + at], sy[i]);
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < 3 * 32 * NB; k += NT) {
+    const int sg = k / (32 * NB), q = k % (32 * NB);
+    if (q >= nq) continue;
+    int dg[kDigits];
+#pragma unroll
+    for (int d = 0; d < kDigits; ++d) dg[d] = sums[k * kDigits + (d ^ (k & 31))];
+    // carries moved up, then the digits from the top (a negative sum has a
+    // negative carry out of the top digit)
+    int carry = 0;
+#pragma unroll
+    for (int d = 0; d < kDigits; ++d) {
+      const int t = dg[d] + carry;   // below 2^31: 127 * 2^24 + 2^24
+      dg[d] = t & 127;
+      carry = t >> 7;
+    }
+    double s = (double)carry;
+#pragma unroll
+    for (int d = kDigits - 1; d >= 0; --d) s = s * 128.0 + (double)dg[d];
+    acc_g[(int64_t)(3 * q + sg) * gridDim.x + blockIdx.x] = in_range ? s * 0x1p-186 : __builtin_nan("");
   }
 }
 
 template <int W>
-static void launch_bwd_w(int nq, const StoreDev& st, int grid, const double* theta,
-                         const double* phi, const double* lut, const double* dE, double* lam,
-                         double* acc, hipStream_t s) {
-  const size_t lds = energy_bwd_lds_bytes(W);
-  (void)hipFuncSetAttribute((const void*)k_energy_bwd<W>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds);
-  hipLaunchKernelGGL(k_energy_bwd<W>, dim3(grid), dim3(kBwdBlock), lds, s, st, nq, theta, phi,
-                     lut, dE, lam, acc);
+static int launch_bwd_w(int nq, const StoreDev& st, int grid, const double* theta, const double* phi,
+                        const double* dE, double* lam, double* acc, hipStream_t s) {
+  const size_t lds = sizeof(BwdShared<W>);
+  (void)hipFuncSetAttribute((const void*)k_energy_bwd<W>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL(k_energy_bwd<W>, dim3(grid), dim3(BwdGeom<W>::kThreads), lds, s, st, nq, theta, phi, dE, lam,
+                     acc);
+  return BwdGeom<W>::kThreads;
 }
 
-void launch_energy_backward(int W, int nq, const StoreDev& st, int grid, const double* theta,
-                            const double* phi, const double* lut, const double* dE, double* lam,
-                            double* acc, hipStream_t s) {
-  switch (W) {
-    case 1: launch_bwd_w<1>(nq, st, grid, theta, phi, lut, dE, lam, acc, s); break;
-    case 2: launch_bwd_w<2>(nq, st, grid, theta, phi, lut, dE, lam, acc, s); break;
-    case 3: launch_bwd_w<3>(nq, st, grid, theta, phi, lut, dE, lam, acc, s); break;
-    default: launch_bwd_w<4>(nq, st, grid, theta, phi, lut, dE, lam, acc, s); break;
-  }
-}
-
-// One workgroup per qubit: S[q][sigma] summed over the per-workgroup
-// partials in a fixed order, then the chain rule through the Bloch factors.
-__global__ void k_backward_finalize(int nq, int grid, const double* acc, const double* theta,
-                                    const double* phi, const double* dE, double* dtheta,
-                                    double* dphi) {
+// One workgroup per qubit: S[q][sigma] summed over the workgroups in a fixed
+// order and divided by the factor it misses, then the chain rule through the
+// Bloch factors.
+__global__ __launch_bounds__(kBlock) void k_backward_finalize(StoreDev st, int threads, int grid, const double* acc,
+                                                              const double* theta, const double* phi,
+                                                              const double* dE, double* dtheta, double* dphi) {
   __shared__ double red[kWaves];
   const int q = blockIdx.x;
-  double S[3];
-  for (int k = 0; k < 3; ++k) {
-    double v = 0.0;
-    for (int g = threadIdx.x; g < grid; g += kBlock) v += acc[(int64_t)g * 3 * nq + 3 * q + k];
-    S[k] = block_sum(v, red);   // valid in thread 0
+  const int active = (int)bwd_active(*st.total, 1ll << *st.m, grid, threads);
+  double S[3] = {0.0, 0.0, 0.0};
+  for (int g = threadIdx.x; g < active; g += kBlock) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) S[k] += acc[(int64_t)(3 * q + k) * grid + g];
   }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) S[k] = block_sum(S[k], red);   // valid in thread 0
   if (threadIdx.x == 0) {
-    double st, ct, sp, cp;
-    sincos(theta[q], &st, &ct);
+    double sn, ct, sp, cp;
+    sincos(theta[q], &sn, &ct);
     sincos(phi[q], &sp, &cp);
     // sigma order X, Z, Y
-    const double dt = S[0] * (ct * cp) + S[1] * (-st) + S[2] * (ct * sp);
-    const double dp = S[0] * (-st * sp) + S[2] * (st * cp);
+    const int ops[3] = {1, 2, 3};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const double b = bloch_factor(ops[k], sn, ct, sp, cp);
+      if (!(fabs(b) < 0x1p-100)) S[k] /= b;
+    }
+    const double dt = S[0] * (ct * cp) + S[1] * (-sn) + S[2] * (ct * sp);
+    const double dp = S[0] * (-sn * sp) + S[2] * (sn * cp);
     const double sc = dE ? *dE : 1.0;
     dtheta[q] = sc * dt;
     dphi[q] = sc * dp;
   }
 }
 
-void launch_backward_finalize(int nq, int grid, const double* acc, const double* theta,
-                              const double* phi, const double* dE, double* dtheta, double* dphi,
-                              hipStream_t s) {
+void launch_energy_backward(int W, int nq, const StoreDev& st, int grid, const double* theta, const double* phi,
+                            const double* dE, double* lam, double* acc, double* dtheta, double* dphi, hipStream_t s) {
   if (nq <= 0) return;
-  hipLaunchKernelGGL(k_backward_finalize, dim3(nq), dim3(kBlock), 0, s, nq, grid, acc, theta, phi,
-                     dE, dtheta, dphi);
+  int threads = 0;
+  switch (W) {
+    case 1: threads = launch_bwd_w<1>(nq, st, grid, theta, phi, dE, lam, acc, s); break;
+    case 2: threads = launch_bwd_w<2>(nq, st, grid, theta, phi, dE, lam, acc, s); break;
+    case 3: threads = launch_bwd_w<3>(nq, st, grid, theta, phi, dE, lam, acc, s); break;
+    default: threads = launch_bwd_w<4>(nq, st, grid, theta, phi, dE, lam, acc, s); break;
+  }
+  hipLaunchKernelGGL(k_backward_finalize, dim3(nq), dim3(kBlock), 0, s, st, threads, grid, acc, theta, phi, dE,
+                     dtheta, dphi);
 }
 
 }  // namespace iqcc
