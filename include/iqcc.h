@@ -396,12 +396,12 @@ int iqcc_qmf_energy(iqcc_ctx *ctx, const iqcc_store *h, const double *theta,
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * energy as iqcc_qmf_energy, from the same kernel, with no allocation of any
- * kind.  Its scratch (eight sets of per-workgroup partial sums and arrival
+ * kind.  Its scratch (six sets of per-workgroup partial sums and arrival
  * counters, taken in turn) is a fixed array of device memory inside the
- * library, 128 KB per device, held until the process ends.  A grid (n_cu *
+ * library, 120 KB per device, held until the process ends.  A grid (n_cu *
  * energy_grid_per_cu workgroups) above 8192 is refused with IQCC_ERR_CAPACITY
  * before any launch.  All calls on one device share that scratch, so more
- * than eight calls that overlap on a device (other streams, other contexts or
+ * than six calls that overlap on a device (other streams, other contexts or
  * threads) may race; calls in one stream are ordered.  Each call rewrites all
  * the partial sums it reads and leaves the counters zero. */
 int iqcc_qmf_energy_noalloc(iqcc_ctx *ctx, const iqcc_store *h, const double *theta,

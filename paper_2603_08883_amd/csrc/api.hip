@@ -369,7 +369,7 @@ void inplace_geometry(const iqcc_ctx* ctx, const iqcc_store* st, int& m, int64_t
 // in turn, zero at start (the state finish_arrive leaves).  Every device the
 // library runs on holds its own copy until the process ends; host code reaches
 // it only through the per-device address from hipGetSymbolAddress.
-constexpr int kNoAllocSlots = 8;
+constexpr int kNoAllocSlots = 6;
 constexpr int kNoAllocPartials = 8192;   // the largest grid the entry point accepts
 constexpr int kNoAllocDevices = 64;
 static __device__ __align__(256) double scratch[kNoAllocSlots * kFinishSlot];
@@ -798,11 +798,7 @@ int iqcc_dress_inplace(iqcc_ctx* ctx, iqcc_store* st, const uint64_t* px, const 
   if (ctx->inplace_cap && ctx->inplace_cap < cap) cap = (int)ctx->inplace_cap;
   if (cap < 16 || inplace_lds_bytes(W, cap, fused) > budget)
     return fail(ctx, IQCC_ERR_UNSUPPORTED, "the in-place step does not fit the LDS of a workgroup");
-  const int grid = ctx->n_cu;
-  const int nparts = grid * inplace_waves_per_block();
-  // energy partials, then five counts per wavefront
-  rc = ensure_partial(ctx, 6 * (int64_t)nparts);
-  if (rc) return rc;
+  const int grid = ctx->n_cu < kInplaceGrid ? ctx->n_cu : kInplaceGrid;
   InplaceConfig cfg{};
   cfg.C = std::cos(tau);
   cfg.S = std::sin(tau);
@@ -814,9 +810,10 @@ int iqcc_dress_inplace(iqcc_ctx* ctx, iqcc_store* st, const uint64_t* px, const 
   cfg.nq = st->nq;
   const bool delta = fused && energy_in;
   cfg.delta = delta ? 1 : 0;
-  cfg.e_partial = ctx->partial;
-  cfg.counts = reinterpret_cast<int64_t*>(ctx->partial + nparts);
-  launch_dress_inplace(W, st->d, P, cfg, grid, delta ? energy_in : nullptr, fused ? energy_out : nullptr, s);
+  cfg.slot = take_slot(ctx);
+  cfg.energy_in = delta ? energy_in : nullptr;
+  cfg.energy_out = fused ? energy_out : nullptr;
+  launch_dress_inplace(W, st->d, P, cfg, grid, s);
   LAUNCH_CHECK(ctx);
   st->floor = eps;
   if (want_e && !fused) {

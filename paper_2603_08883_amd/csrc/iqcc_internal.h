@@ -204,34 +204,54 @@ __device__ __forceinline__ FixedSum block_fixed_sum(FixedSum f, long long* tmp_h
 
 // Finish slot of a launch: kFinishSlot doubles of device memory.  The first
 // kFinishHead hold arrival counters, zero between launches (a root and
-// kFinishFan leaves, each on a 128-byte line of its own), the rest one partial
-// sum per arriving workgroup.  finish_arrive (one thread of each of `count`
-// workgroups) leaves the partial and returns whether it was the last to
-// arrive; that workgroup then reads all of them with finish_partial.  The last
-// arrivals reset the counters for the next launch that uses the slot.  Up to
-// 2 kFinishFan workgroups meet at the root; more meet at the leaves first,
-// because arrivals at one address take their turns one by one.
+// kFinishFan leaves, each on a 128-byte line of its own), the rest what the
+// workgroups leave for the last of them.  A wave leaves its words with
+// finish_put (any of its lanes) and arrives with finish_arrive (the whole wave
+// calls; one wave of each of `count` workgroups); the workgroup that arrives
+// last gets true and reads all words with finish_get.  The last arrivals reset
+// the counters for the next launch that uses the slot.  Up to 2 kFinishFan
+// workgroups meet at the root; more meet at the leaves first, because arrivals
+// at one address take their turns one by one.
+//
+// The words are agent-scope atomics, which go past the caches that other
+// workgroups do not share, and the arrival waits until they are written; it is
+// no release of everything else the workgroup wrote, which the end of the
+// kernel brings anyway (a release writes back every dirty line of the L2).
 constexpr int kFinishFan = 16;
 constexpr int kFinishHead = 16 * (kFinishFan + 1);
-constexpr int kFinishSlot = 2048;
-constexpr int kFinishPartials = kFinishSlot - kFinishHead;
+constexpr int kFinishSlot = 2560;
+constexpr int kFinishWords = kFinishSlot - kFinishHead;
+
+__device__ __forceinline__ void finish_put(double* slot, unsigned index, double value) {
+  __hip_atomic_store(&slot[kFinishHead + index], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ double finish_get(const double* slot, unsigned index) {
+  return __hip_atomic_load(&slot[kFinishHead + index], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 __device__ __forceinline__ bool finish_count(unsigned* counter, unsigned count) {
-  const bool last = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == count - 1;
+  const bool last = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == count - 1;
   if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return last;
 }
 
-__device__ __forceinline__ bool finish_arrive(double* slot, unsigned index, double value, unsigned count) {
-  __hip_atomic_store(&slot[kFinishHead + index], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (count <= 2 * kFinishFan) return finish_count((unsigned*)slot, count);
-  const unsigned leaf = index % kFinishFan;
-  if (!finish_count((unsigned*)(slot + 16 * (1 + leaf)), (count - leaf + kFinishFan - 1) / kFinishFan)) return false;
-  return finish_count((unsigned*)slot, kFinishFan);
-}
-
-__device__ __forceinline__ double finish_partial(const double* slot, unsigned index) {
-  return __hip_atomic_load(&slot[kFinishHead + index], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// True for every lane of the wave that arrives last.
+__device__ __forceinline__ bool finish_arrive(double* slot, unsigned index, unsigned count) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the wave's words are written
+  int last = 0;
+  if ((threadIdx.x & 63) == 0) {
+    if (count <= 2 * kFinishFan) {
+      last = finish_count((unsigned*)slot, count);
+    } else {
+      const unsigned leaf = index % kFinishFan;
+      last = finish_count((unsigned*)(slot + 16 * (1 + leaf)), (count - leaf + kFinishFan - 1) / kFinishFan) &&
+             finish_count((unsigned*)slot, kFinishFan);
+    }
+  }
+  last = __builtin_amdgcn_readfirstlane(last);
+  asm volatile("" ::: "memory");
+  return last != 0;
 }
 
 // Block-wide sum of doubles in a fixed order (lane tree, then waves in order).
@@ -615,19 +635,19 @@ struct InplaceConfig {
   const double* theta;  // null: no energy; else the QMF angles (the group
   const double* phi;    //   table is built in each workgroup's LDS)
   int nq;
-  int delta;            // 1: e_partial accumulates only the change of the energy
-  double* e_partial;    // [grid * inplace_waves_per_block()]
-  int64_t* counts;      // [grid * inplace_waves_per_block()][5]: anticommuting
-                        //   inputs, new keys, change of the term count,
-                        //   relocated items, freed rows, per wavefront
+  int delta;            // 1: only the change of the energy is accumulated
+  double* slot;         // finish slot: [6][grid] words, per workgroup the anticommuting inputs,
+                        //   new keys, change of the term count, relocated items, freed rows
+                        //   (the bits of 64-bit integers), and the energy
+  const double* energy_in;   // added to the energy, or null
+  double* energy_out;   // null: no energy
 };
 size_t inplace_lds_bytes(int W, int cap, bool energy);
 int inplace_cap(int W, bool energy, size_t lds_budget);
-int inplace_waves_per_block();
-// The step and its finishing kernel (counters of the store, and the energy
-// into energy_out, plus *energy_in when given, if energy_out is not null).
+// At most this many workgroups (their words fit a finish slot).
+constexpr int kInplaceGrid = kFinishWords / 6;
 void launch_dress_inplace(int W, const StoreDev& st, const Entangler& P, const InplaceConfig& cfg, int grid,
-                          const double* energy_in, double* energy_out, hipStream_t s);
+                          hipStream_t s);
 // Bucket regions: bucket b gets max(R, 2 cnt_b rounded up to 16) rows; the
 // pool starts after the last region.  Load of flat rows (as launch_store_load;
 // scratch 3 B + B/1024 + 16 + n) and copy of a store (deterministic: each

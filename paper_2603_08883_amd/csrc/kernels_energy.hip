@@ -294,11 +294,15 @@ __global__ __launch_bounds__(kE4Block) void k_energy(StoreDev st, int nq, const 
     if (threadIdx.x == 0) *out = s;
     return;
   }
-  if (threadIdx.x == 0) s_last = finish_arrive(slot, blockIdx.x, s, active);
+  if (threadIdx.x < 64) {
+    if (threadIdx.x == 0) finish_put(slot, blockIdx.x, s);
+    const bool last = finish_arrive(slot, blockIdx.x, active);
+    if (threadIdx.x == 0) s_last = last;
+  }
   __syncthreads();
   if (s_last) {
     double t = 0.0;
-    for (unsigned k = threadIdx.x; k < active; k += kE4Block) t += finish_partial(slot, k);
+    for (unsigned k = threadIdx.x; k < active; k += kE4Block) t += finish_get(slot, k);
     t = block_sum_n<kE4Block / 64>(t, red);
     if (threadIdx.x == 0) *out = t;
   }
@@ -312,7 +316,7 @@ static void launch_energy_w(int nq, const StoreDev& st, int n_cu, int per_cu, si
   int fit = (int)(lds_per_cu / (lds + 256));
   fit = fit < 1 ? 1 : (fit > 2048 / kE4Block ? 2048 / kE4Block : fit);
   int grid = n_cu * (per_cu < fit ? per_cu : fit);
-  if (grid > kFinishPartials) grid = kFinishPartials;
+  if (grid > kFinishWords) grid = kFinishWords;
   (void)hipFuncSetAttribute((const void*)k_energy<W>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(k_energy<W>, dim3(grid), dim3(kE4Block), lds, s, st, nq, theta, phi, slot, out);
 }

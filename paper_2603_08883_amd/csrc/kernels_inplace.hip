@@ -20,8 +20,9 @@
 // Work split: one wavefront per work item, with no workgroup barrier after
 // the table load.  A work item is a bucket pair {b, b ^ f} (the single-device
 // form of the pairwise exchange between partitions, App. B/C), or up to 32
-// consecutive pairs while buckets are small.  Wave g of the grid takes items
-// g, g + waves, g + 2 waves, ..., and loads the bucket table of its next item
+// consecutive pairs while buckets are small and there are items enough for
+// every wave.  Wave g of the grid takes items g, g + waves, g + 2 waves, ...
+// (waves numbered across the CUs), and loads the bucket table of its next item
 // while it works on the current one.  Every row position, every sum and the
 // energy partials are the same on every run.  Inside an item the
 // anticommuting terms are staged in the wave's LDS segment, joined on one
@@ -39,6 +40,7 @@ namespace iqcc {
 #endif
 constexpr int kIPW = IQCC_INPLACE_WAVES;   // waves per workgroup (one workgroup per CU)
 constexpr int kIPB = 64 * kIPW;
+static_assert(kIPW >= 6, "six waves add the six fields of the records");
 constexpr int kIPSlots = 64;      // buckets per work item (one per lane)
 #ifndef IQCC_INPLACE_UNROLL
 #define IQCC_INPLACE_UNROLL 2
@@ -835,7 +837,7 @@ __global__ __launch_bounds__(kIPB) void k_dress_inplace(StoreDev st, Entangler P
   }
   __syncthreads();
   const Seg<W> g = carve_seg<W>(smem + lut_bytes + (size_t)wave * seg_bytes(W, cfg.cap), cfg.cap);
-  const int64_t gw = (int64_t)blockIdx.x * kIPW + wave;
+  const int64_t gw = (int64_t)wave * gridDim.x + blockIdx.x;   // few items: one per CU first
   double eacc = 0.0;
   WaveCounts wc;
   if (*st.err == 0) {
@@ -850,11 +852,18 @@ __global__ __launch_bounds__(kIPB) void k_dress_inplace(StoreDev st, Entangler P
     const int64_t mean = (n_in >> m) > 0 ? (n_in >> m) : 1;
     const int64_t pair_terms = G.selfp ? mean : 2 * mean;
     const int maxp = G.selfp ? kIPSlots : kIPSlots / 2;
+    const int64_t nw = (int64_t)gridDim.x * kIPW;
+    // Pairs per item: what the stash holds, but at least two items a wave, since
+    // a wave's chain of loads, join and stores takes about as long for 6 terms
+    // as for 192 (4096 buckets of 3 terms: 64 items of 32 pairs on 64 waves 24
+    // to 38 us a step, 2048 of one pair 13 us; 2^18 buckets of 4 terms: 92 us
+    // with 4096 items for 3072 waves, 80 us with 8192)
     int ppi = 1;
-    while (ppi * 2 <= maxp && (int64_t)ppi * 2 * pair_terms <= cfg.item_terms) ppi *= 2;
+    while (ppi * 2 <= maxp && (int64_t)ppi * 2 * pair_terms <= cfg.item_terms &&
+           G.npairs / (ppi * 2) >= 2 * nw)
+      ppi *= 2;
     G.ppi = ppi;
     G.nitems = (G.npairs + ppi - 1) / ppi;
-    const int64_t nw = (int64_t)gridDim.x * kIPW;
     // bucket tables two items ahead, term slices one item ahead
     SlotDesc d_next;
     if (gw + nw < G.nitems) d_next = load_desc(st, G, gw + nw);
@@ -873,67 +882,66 @@ __global__ __launch_bounds__(kIPB) void k_dress_inplace(StoreDev st, Entangler P
       I = In;
     }
   }
-  // per-wavefront counts (summed by k_inplace_end, no atomics)
-  if (lane == 0) {
-    int64_t* c = cfg.counts + 5 * gw;
-    c[0] = wc.anti;
-    c[1] = wc.fresh;
-    c[2] = wc.delta;
-    c[3] = wc.reloc;
-    c[4] = wc.freed;
-  }
+  // The workgroup's counts and energy go to the finish slot, over the table's
+  // memory; the workgroup that arrives last adds the counts into the store's
+  // counters (integer sums) and the energy in a fixed order, so a step is one
+  // launch (a second one that added 3072 wavefronts' records took 12 to 14 us,
+  // this takes 2 us).
   if (ENERGY) {
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) eacc += __shfl_down(eacc, d, 64);
-    if (lane == 0) cfg.e_partial[gw] = eacc;
   }
-}
-
-// Finishes a step in one workgroup: sums the per-wavefront counts into the
-// store's counters (integer sums) and the energy partials in a fixed order
-// (each thread a strided share, then the lane tree and the waves in order).
-__global__ __launch_bounds__(kBlock) void k_inplace_end(StoreDev st, const int64_t* counts,
-                                                        const double* e_partial, int nparts,
-                                                        const double* energy_in, double* energy_out) {
-  __shared__ double red[kWaves];
-  __shared__ unsigned long long s_cnt[5];
-  if (threadIdx.x < 5) s_cnt[threadIdx.x] = 0ull;
   __syncthreads();
-  unsigned long long mine[5] = {0ull, 0ull, 0ull, 0ull, 0ull};
-  double e = 0.0;
-  // four strided partials per round, their loads issued together; the
-  // energy adds stay in increasing partial order
-  constexpr int kU = 4;
-  for (int i0 = threadIdx.x; i0 < nparts; i0 += kU * kBlock) {
-    int64_t cv[kU][5];
-    double ev[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int i = i0 + u * kBlock;
-      const bool ok = i < nparts;
-#pragma unroll
-      for (int k = 0; k < 5; ++k) cv[u][k] = ok ? counts[5 * i + k] : 0;
-      ev[u] = (ok && energy_out) ? e_partial[i] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-#pragma unroll
-      for (int k = 0; k < 5; ++k) mine[k] += (unsigned long long)cv[u][k];
-      if (i0 + u * kBlock < nparts && energy_out) e += ev[u];
-    }
+  double* rec = (double*)smem;             // [kIPW][6], later [6]
+  int* s_last = (int*)(rec + 6 * kIPW);
+  if (lane == 0) {
+    rec[6 * wave] = __longlong_as_double(wc.anti);
+    rec[6 * wave + 1] = __longlong_as_double(wc.fresh);
+    rec[6 * wave + 2] = __longlong_as_double(wc.delta);
+    rec[6 * wave + 3] = __longlong_as_double(wc.reloc);
+    rec[6 * wave + 4] = __longlong_as_double(wc.freed);
+    rec[6 * wave + 5] = eacc;
   }
+  __syncthreads();
+  if (wave == 0) {
+    if (lane < 5) {
+      long long v = 0;
+      for (int k = 0; k < kIPW; ++k) v += __double_as_longlong(rec[6 * k + lane]);
+      finish_put(cfg.slot, lane * gridDim.x + blockIdx.x, __longlong_as_double(v));
+    } else if (lane == 5) {
+      double v = 0.0;
+      for (int k = 0; k < kIPW; ++k) v += rec[6 * k + 5];
+      finish_put(cfg.slot, 5 * gridDim.x + blockIdx.x, v);
+    }
+    const bool last = finish_arrive(cfg.slot, blockIdx.x, gridDim.x);
+    if (lane == 0) *s_last = last;
+  }
+  __syncthreads();
+  if (!*s_last) return;
+  // wave k sums field k over the workgroups
+  if (wave < 6) {
+    long long v = 0;
+    double e = 0.0;
+    for (unsigned i = lane; i < gridDim.x; i += 64) {
+      const double w = finish_get(cfg.slot, wave * gridDim.x + i);
+      if (wave < 5) v += __double_as_longlong(w); else e += w;
+    }
 #pragma unroll
-  for (int k = 0; k < 5; ++k)
-    if (mine[k]) atomicAdd(&s_cnt[k], mine[k]);
-  const double es = block_sum(e, red);   // also orders the LDS adds above
-  if (threadIdx.x == 0) {
-    st.stats[0] = (int64_t)s_cnt[0];
-    st.stats[1] = (int64_t)s_cnt[1];
-    st.aux[0] = (int64_t)s_cnt[2];
-    st.aux[3] = (int64_t)s_cnt[3];
-    st.aux[4] = (int64_t)s_cnt[4];
-    *st.total += (int64_t)s_cnt[2];
-    if (energy_out) *energy_out = energy_in ? *energy_in + es : es;
+    for (int d = 32; d >= 1; d >>= 1) {
+      v += __shfl_down(v, d, 64);
+      e += __shfl_down(e, d, 64);
+    }
+    if (lane == 0) {
+      if (wave == 0) st.stats[0] = v;
+      if (wave == 1) st.stats[1] = v;
+      if (wave == 2) {
+        st.aux[0] = v;
+        *st.total += v;
+      }
+      if (wave == 3) st.aux[3] = v;
+      if (wave == 4) st.aux[4] = v;
+      if (wave == 5 && cfg.energy_out) *cfg.energy_out = cfg.energy_in ? *cfg.energy_in + e : e;
+    }
   }
 }
 
@@ -947,7 +955,7 @@ static void launch_inplace_t(const StoreDev& st, const Entangler& P, const Inpla
 }
 
 void launch_dress_inplace(int W, const StoreDev& st, const Entangler& P, const InplaceConfig& cfg, int grid,
-                          const double* energy_in, double* energy_out, hipStream_t s) {
+                          hipStream_t s) {
   const bool e = cfg.theta != nullptr;
   switch (W) {
     case 1: e ? launch_inplace_t<1, true>(st, P, cfg, grid, s) : launch_inplace_t<1, false>(st, P, cfg, grid, s); break;
@@ -955,10 +963,6 @@ void launch_dress_inplace(int W, const StoreDev& st, const Entangler& P, const I
     case 3: e ? launch_inplace_t<3, true>(st, P, cfg, grid, s) : launch_inplace_t<3, false>(st, P, cfg, grid, s); break;
     default: e ? launch_inplace_t<4, true>(st, P, cfg, grid, s) : launch_inplace_t<4, false>(st, P, cfg, grid, s); break;
   }
-  hipLaunchKernelGGL(k_inplace_end, dim3(1), dim3(kBlock), 0, s, st, cfg.counts, cfg.e_partial,
-                     grid * kIPW, energy_in, energy_out);
 }
-
-int inplace_waves_per_block() { return kIPW; }
 
 }  // namespace iqcc
