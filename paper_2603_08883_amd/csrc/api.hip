@@ -106,8 +106,11 @@ hipStream_t as_stream(void* s) { return (hipStream_t)s; }
 constexpr int kFinishSlots = 32;
 constexpr int kLutDoubles = kMaxWords * kGroupsPerWord * kLutEntries;
 
+constexpr int kCtxSlot = kFinishHead + 4 * kDressGrid;   // words of the largest dressing grid
+static_assert(4 * kDressGrid >= kFinishWords && 4 * kDressGrid >= 6 * kInplaceGrid, "a slot holds every kernel's words");
+
 double* take_slot(iqcc_ctx* ctx) {
-  return ctx->slots + (size_t)(ctx->next_slot++ % kFinishSlots) * kFinishSlot;
+  return ctx->slots + (size_t)(ctx->next_slot++ % kFinishSlots) * kCtxSlot;
 }
 
 int ensure_scratch(iqcc_ctx* ctx, int64_t n) {
@@ -420,7 +423,7 @@ int iqcc_ctx_create(iqcc_ctx** out, int device) {
       ctx->lds_per_cu = (size_t)v;
   }
   noalloc_setup(device);
-  const size_t slot_bytes = sizeof(double) * kFinishSlots * kFinishSlot;
+  const size_t slot_bytes = sizeof(double) * kFinishSlots * kCtxSlot;
   if (hipMalloc(&ctx->lut, sizeof(double) * kLutDoubles) != hipSuccess ||
       hipMalloc(&ctx->slots, slot_bytes) != hipSuccess || hipMemset(ctx->slots, 0, slot_bytes) != hipSuccess ||
       hipDeviceSynchronize() != hipSuccess) {
@@ -721,9 +724,8 @@ static int dress_impl(iqcc_ctx* ctx, const iqcc_store* in, const uint64_t* px, c
   if (lds > ctx->lds_per_block)
     return fail(ctx, IQCC_ERR_INVALID_ARG, "anti_cap %d needs more LDS than a workgroup has",
                 (int)ctx->anti_cap);
-  const int grid = dress_grid(ctx, lds);
-  rc = ensure_partial(ctx, grid);
-  if (rc) return rc;
+  int grid = dress_grid(ctx, lds);
+  if (grid > kDressGrid) grid = kDressGrid;
   DressConfig cfg{};
   cfg.C = std::cos(tau);
   cfg.S = std::sin(tau);
@@ -732,24 +734,23 @@ static int dress_impl(iqcc_ctx* ctx, const iqcc_store* in, const uint64_t* px, c
   cfg.anti_cap = (int)ctx->anti_cap;
   cfg.grid = grid;
   if (fused) {
-    launch_build_lut(W, in->nq, theta, phi, ctx->lut, s);
-    LAUNCH_CHECK(ctx);
+    cfg.theta = theta;
+    cfg.phi = phi;
+    cfg.nq = in->nq;
+    // with the input's energy known, the fused pass accumulates only the change
+    cfg.delta = energy_in ? 1 : 0;
+    cfg.energy_in = energy_in;
+    cfg.energy_out = energy;
   }
-  cfg.lut = fused ? ctx->lut : nullptr;
-  // with the input's energy known, the fused pass accumulates only the change
-  const bool delta = fused && energy_in;
-  cfg.delta = delta ? 1 : 0;
-  cfg.e_partial = ctx->partial;
+  cfg.slot = take_slot(ctx);
   cfg.tape_self = tape_self;
   cfg.tape_partner = tape_partner;
-  launch_zero_counters(out->d, s);
   launch_dress(W, in->d, out->d, P, cfg, s);
   LAUNCH_CHECK(ctx);
   out->floor = eps;
   out->regions = false;
-  if (want_e) {
-    if (fused) launch_finalize_sum(ctx->partial, grid, nullptr, energy, s, delta ? energy_in : nullptr);
-    else energy_sum(ctx, out, theta, phi, take_slot(ctx), energy, s);
+  if (want_e && !fused) {
+    energy_sum(ctx, out, theta, phi, take_slot(ctx), energy, s);
     LAUNCH_CHECK(ctx);
   }
   return IQCC_OK;

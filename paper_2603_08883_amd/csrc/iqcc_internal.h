@@ -219,8 +219,8 @@ __device__ __forceinline__ FixedSum block_fixed_sum(FixedSum f, long long* tmp_h
 // kernel brings anyway (a release writes back every dirty line of the L2).
 constexpr int kFinishFan = 16;
 constexpr int kFinishHead = 16 * (kFinishFan + 1);
-constexpr int kFinishSlot = 2560;
-constexpr int kFinishWords = kFinishSlot - kFinishHead;
+constexpr int kFinishWords = 2288;
+constexpr int kFinishSlot = kFinishHead + kFinishWords;
 
 __device__ __forceinline__ void finish_put(double* slot, unsigned index, double value) {
   __hip_atomic_store(&slot[kFinishHead + index], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -362,6 +362,37 @@ __device__ __forceinline__ double expect_lut(const double* lut, const uint64_t* 
 __device__ __forceinline__ double bloch_factor(int op, double st, double ct, double sp,
                                                double cp) {
   return op == 0 ? 1.0 : op == 1 ? st * cp : op == 2 ? ct : st * sp;
+}
+
+// The 3-qubit group table (entries as expect_lut reads them) from the angles,
+// by the whole workgroup of NT threads; fq: 256 W doubles of LDS that it may
+// overwrite.  Ends with a barrier.
+template <int W, int NT>
+__device__ __forceinline__ void build_group_table(double* lut, double* fq, int nq, const double* theta,
+                                                  const double* phi) {
+  for (int q = threadIdx.x; q < 64 * W; q += NT) {
+    double st_ = 0.0, ct = 1.0, sp = 0.0, cp = 1.0;
+    if (q < nq) {
+      sincos(theta[q], &st_, &ct);
+      sincos(phi[q], &sp, &cp);
+    }
+#pragma unroll
+    for (int op = 0; op < 4; ++op) fq[4 * q + op] = bloch_factor(op, st_, ct, sp, cp);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < W * kGroupsPerWord * kLutEntries; i += NT) {
+    const int code = i % kLutEntries, gi = i / kLutEntries;
+    const int h = gi / kGroupsPerHalf, gg = gi % kGroupsPerHalf;
+    double p = 1.0;
+    for (int r = 0; r < 3; ++r) {
+      const int bit = 3 * gg + r, q = 32 * h + bit;
+      if (bit >= 32 || q >= nq) continue;
+      const int op = ((code >> r) & 1) | (((code >> (3 + r)) & 1) << 1);
+      if (op != 0) p *= fq[4 * q + op];
+    }
+    lut[i] = p;
+  }
+  __syncthreads();
 }
 
 // Anticommutation of K with P: parity of |xK & zP| + |zK & xP|.
@@ -615,15 +646,23 @@ struct DressConfig {
   int64_t split_thr;
   int anti_cap;
   int grid;
-  const double* lut;   // null: no fused energy
-  int delta;           // 1: e_partial accumulates only the change of the energy
-  double* e_partial;   // [grid]
+  const double* theta; // null: no fused energy; else the QMF angles (the group
+  const double* phi;   //   table is built in each workgroup's LDS)
+  int nq;
+  int delta;           // 1: only the change of the energy is accumulated
+  double* slot;        // finish slot: [4][grid] words, per workgroup the output terms, the
+                       //   anticommuting inputs, the new keys (the bits of 64-bit integers)
+                       //   and the energy; see also dress_top and dress_err
+  const double* energy_in;   // added to the energy, or null
+  double* energy_out;  // null: no energy
   int32_t* tape_self;     // null, or per input arena row: output row of K (-1 dropped)
   int32_t* tape_partner;  //   and -1 for a commuting row; for an anticommuting row
                           //   2 * (output row of K^P + 1) + [s_K = +1], where the
                           //   output row is -1 when K^P is absent or dropped
   int unit_pairs;         // batched dressing: consecutive bucket pairs per work unit
 };
+// At most this many workgroups (their words fit a context's finish slot).
+constexpr int kDressGrid = 4096;
 void launch_dress(int W, const StoreDev& in, const StoreDev& out, const Entangler& P,
                   const DressConfig& cfg, hipStream_t s);
 
@@ -645,7 +684,7 @@ struct InplaceConfig {
 size_t inplace_lds_bytes(int W, int cap, bool energy);
 int inplace_cap(int W, bool energy, size_t lds_budget);
 // At most this many workgroups (their words fit a finish slot).
-constexpr int kInplaceGrid = kFinishWords / 6;
+constexpr int kInplaceGrid = 4 * kDressGrid / 6;
 void launch_dress_inplace(int W, const StoreDev& st, const Entangler& P, const InplaceConfig& cfg, int grid,
                           hipStream_t s);
 // Bucket regions: bucket b gets max(R, 2 cnt_b rounded up to 16) rows; the

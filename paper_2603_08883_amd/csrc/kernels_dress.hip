@@ -48,8 +48,16 @@ size_t dress_lds_bytes(int W, int cap, bool energy, bool tape) {
   o += ((size_t)cap + 7) & ~(size_t)7;           // side
   o += 8 * 8 + 8 * 8 + 8 * 8 + 256 * 4 + 4 * 8;  // scan, reduce, misc, round stack, counters
   if (tape) o += (size_t)cap * 8 * 2;            // tape: input row, own output row
-  return o;
+  // the energy table's build keeps the qubits' factors after the table
+  const size_t build = energy ? (size_t)W * (kGroupsPerWord * kLutEntries + 64 * 4) * 8 : 0;
+  return o > build ? o : build;
 }
+
+// Row reservation counter and error flags of a running step: in the head of
+// its finish slot, zero between launches, copied to the output store and reset
+// by the workgroup that arrives last.
+__device__ __forceinline__ int64_t* dress_top(double* slot) { return (int64_t*)(slot + 2); }
+__device__ __forceinline__ int* dress_err(double* slot) { return (int*)(slot + 4); }
 
 template <int W>
 struct Smem {
@@ -390,12 +398,22 @@ __device__ int64_t reserve_rows(const StoreDev& in, const StoreDev& out, int64_t
   return base;
 }
 
-// Per-workgroup totals of one step, flushed to the output store's device
-// counters once at the end (same-address global atomics serialise in L2).
+// Totals of one workgroup (of one unit of a batch).
 struct StepCounts {
   int64_t produced = 0, anti = 0;   // thread 0 of the workgroup
-  int64_t fresh = 0;                // per wave (lane 0 flushes)
+  int64_t fresh = 0;                // per wave (the same in every lane)
 };
+
+// New keys of the workgroup, valid in thread 0.  Ends with a barrier.
+__device__ __forceinline__ int64_t sum_fresh(const StepCounts& counts, uint64_t* tmp) {
+  if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = (uint64_t)counts.fresh;
+  __syncthreads();
+  int64_t v = 0;
+  if (threadIdx.x == 0)
+    for (int k = 0; k < kDW; ++k) v += (int64_t)tmp[k];
+  __syncthreads();
+  return v;
+}
 
 // Everything one workgroup does for bucket pair `pi` of one dressing step;
 // `base` is the first arena row reserved for it (-1: no room, write nothing).
@@ -509,42 +527,60 @@ __device__ void process_pair(const StoreDev& in, const StoreDev& out, const Enta
   __syncthreads();
 }
 
-__device__ __forceinline__ void flush_counts(const StoreDev& out, const StepCounts& counts) {
+// A batch's unit adds its totals to the output store (one atomic each: 8 waves
+// adding their own new keys queued at one address).
+__device__ __forceinline__ void flush_counts(const StoreDev& out, const StepCounts& counts, uint64_t* tmp) {
+  const int64_t fresh = sum_fresh(counts, tmp);
   if (threadIdx.x == 0) {
     if (counts.produced) atomicAdd((unsigned long long*)out.total, (unsigned long long)counts.produced);
     if (counts.anti) atomicAdd((unsigned long long*)&out.stats[0], (unsigned long long)counts.anti);
+    if (fresh) atomicAdd((unsigned long long*)&out.stats[1], (unsigned long long)fresh);
   }
-  if ((threadIdx.x & 63) == 0 && counts.fresh)
-    atomicAdd((unsigned long long*)&out.stats[1], (unsigned long long)counts.fresh);
 }
 
+// The output's counters of a step that produced nothing.
+__device__ __forceinline__ void empty_step(const StoreDev& out, const DressConfig& cfg, int err) {
+  *out.total = 0;
+  *out.top = 0;
+  *out.err = err;
+  out.stats[0] = out.stats[1] = 0;
+  if (cfg.energy_out) *cfg.energy_out = __builtin_nan("");
+}
+
+// One launch per step: every workgroup builds the energy table in its LDS, and
+// the one that arrives last writes the output's counters and the energy from
+// the words the others left.  (Clearing the counters, the table and the energy
+// sum were launches of their own, 4.5 us each, and 4096 wavefronts added their
+// new keys at one address: 233,001 to 1.1e6 40-qubit terms 68 + 14 us a step,
+// now 30 us.)
 template <int W, bool ENERGY>
-__global__ __launch_bounds__(kDB) __attribute__((amdgpu_waves_per_eu(4))) void k_dress(StoreDev in, StoreDev out, Entangler P,
+__global__ __launch_bounds__(kDB) __attribute__((amdgpu_waves_per_eu(4))) void k_dress(StoreDev in, StoreDev out_g, Entangler P,
                                                DressConfig cfg) {
   extern __shared__ __align__(16) unsigned char smem[];
   const Smem<W> sm = carve<W, ENERGY>(smem, cfg.anti_cap, cfg.tape_self != nullptr);
   const int tid = threadIdx.x;
   if (*in.err) {
     // the input is the invalid output of an earlier step: propagate, read nothing
-    if (blockIdx.x == 0 && tid == 0) atomicOr(out.err, *in.err);
+    if (blockIdx.x == 0 && tid == 0) empty_step(out_g, cfg, *in.err);
     return;
   }
   const int m = *in.m;
   const int64_t n_in = *in.total;
-  const int split = (m < out.mcap) && (n_in > (cfg.split_thr << m)) ? 1 : 0;
-  if (m + split > out.mcap) {
-    if (blockIdx.x == 0 && tid == 0) atomicOr(out.err, 2);
+  const int split = (m < out_g.mcap) && (n_in > (cfg.split_thr << m)) ? 1 : 0;
+  if (m + split > out_g.mcap) {
+    if (blockIdx.x == 0 && tid == 0) empty_step(out_g, cfg, 2);
     return;
   }
+  StoreDev out = out_g;
+  out.top = dress_top(cfg.slot);
+  out.err = dress_err(cfg.slot);
   const uint32_t mask = (uint32_t)((1ull << m) - 1);
   const uint32_t f = P.hp & mask;
   const int64_t npairs = f ? (1ll << (m - 1)) : (1ll << m);
   const int thi = f ? 31 - __clz(f) : 0;
   if (blockIdx.x == 0 && tid == 0) *out.m = m + split;
-  if (ENERGY) {
-    for (int i = tid; i < W * kGroupsPerWord * kLutEntries; i += kDB) sm.lut[i] = cfg.lut[i];
-    __syncthreads();
-  }
+  if (ENERGY)   // (the factors go where the terms will be)
+    build_group_table<W, kDB>(sm.lut, sm.lut + W * kGroupsPerWord * kLutEntries, cfg.nq, cfg.theta, cfg.phi);
   double eacc = 0.0;
   StepCounts counts;
   int64_t base = reserve_rows(in, out, blockIdx.x, gridDim.x, npairs, f, thi, sm.scan, sm.misc);
@@ -552,10 +588,42 @@ __global__ __launch_bounds__(kDB) __attribute__((amdgpu_waves_per_eu(4))) void k
     process_pair<W, ENERGY>(in, out, P, cfg, sm, pi, m, split, f, thi, base, eacc, counts);
     if (base >= 0) base += pair_need(in, pi, f, thi);
   }
-  flush_counts(out, counts);
-  if (ENERGY) {
-    const double s = block_sum_n<kDW>(eacc, sm.red);
-    if (tid == 0) cfg.e_partial[blockIdx.x] = s;
+  const int64_t fresh = sum_fresh(counts, sm.scan);
+  const double es = ENERGY ? block_sum_n<kDW>(eacc, sm.red) : 0.0;
+  const unsigned grid = gridDim.x;
+  if (tid < 64) {
+    if (tid == 0) {
+      finish_put(cfg.slot, blockIdx.x, __longlong_as_double(counts.produced));
+      finish_put(cfg.slot, grid + blockIdx.x, __longlong_as_double(counts.anti));
+      finish_put(cfg.slot, 2 * grid + blockIdx.x, __longlong_as_double(fresh));
+      if (ENERGY) finish_put(cfg.slot, 3 * grid + blockIdx.x, es);
+    }
+    const bool last = finish_arrive(cfg.slot, blockIdx.x, grid);
+    if (tid == 0) sm.misc[0] = last;
+  }
+  __syncthreads();
+  if (!sm.misc[0]) return;
+  uint64_t sum[3] = {0, 0, 0};
+  double e = 0.0;
+  for (unsigned i = tid; i < grid; i += kDB) {
+#pragma unroll
+    for (unsigned k = 0; k < 3; ++k) sum[k] += (uint64_t)__double_as_longlong(finish_get(cfg.slot, k * grid + i));
+    if (ENERGY) e += finish_get(cfg.slot, 3 * grid + i);
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    uint64_t total;
+    block_exclusive_scan_n<kDW>(sum[k], sm.scan, total);
+    sum[k] = total;
+  }
+  if (ENERGY) e = block_sum_n<kDW>(e, sm.red);
+  if (tid == 0) {
+    *out_g.total = (int64_t)sum[0];
+    out_g.stats[0] = (int64_t)sum[1];
+    out_g.stats[1] = (int64_t)sum[2];
+    *out_g.top = __hip_atomic_exchange(out.top, (int64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *out_g.err = __hip_atomic_exchange(out.err, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (ENERGY) *cfg.energy_out = cfg.energy_in ? *cfg.energy_in + e : e;
   }
 }
 
@@ -665,7 +733,7 @@ __global__ __launch_bounds__(kDB) __attribute__((amdgpu_waves_per_eu(4))) void k
       process_pair<W, false>(in, out, P, c, sm, pi, p.m, p.split, p.f, p.thi, base, eacc, counts);
       if (base >= 0) base += pair_need(in, pi, p.f, p.thi);
     }
-    flush_counts(out, counts);
+    flush_counts(out, counts, sm.scan);
     __syncthreads();   // every thread is done with s_item before the next copy
   }
 }
@@ -706,7 +774,7 @@ static void launch_dress_t(const StoreDev& in, const StoreDev& out, const Entang
 
 void launch_dress(int W, const StoreDev& in, const StoreDev& out, const Entangler& P,
                   const DressConfig& cfg, hipStream_t s) {
-  const bool e = cfg.lut != nullptr;
+  const bool e = cfg.theta != nullptr;
   switch (W) {
     case 1: e ? launch_dress_t<1, true>(in, out, P, cfg, s) : launch_dress_t<1, false>(in, out, P, cfg, s); break;
     case 2: e ? launch_dress_t<2, true>(in, out, P, cfg, s) : launch_dress_t<2, false>(in, out, P, cfg, s); break;

@@ -809,33 +809,9 @@ __global__ __launch_bounds__(kIPB) void k_dress_inplace(StoreDev st, Entangler P
   const size_t lut_bytes = ENERGY ? (size_t)W * kGroupsPerWord * kLutEntries * 8 : 0;
   double* lut = (double*)smem;
   if (ENERGY) {
-    // the 3-qubit group table of the QMF state, built in LDS from the angles;
-    // the per-qubit factors sit in the (not yet used) wave segments
-    double* fq = (double*)(smem + lut_bytes);
-    for (int q = threadIdx.x; q < 64 * W; q += kIPB) {
-      double st_ = 0.0, ct = 1.0, sp = 0.0, cp = 1.0;
-      if (q < cfg.nq) {
-        sincos(cfg.theta[q], &st_, &ct);
-        sincos(cfg.phi[q], &sp, &cp);
-      }
-#pragma unroll
-      for (int op = 0; op < 4; ++op) fq[4 * q + op] = bloch_factor(op, st_, ct, sp, cp);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < W * kGroupsPerWord * kLutEntries; i += kIPB) {
-      const int code = i % kLutEntries, gi = i / kLutEntries;
-      const int h = gi / kGroupsPerHalf, gg = gi % kGroupsPerHalf;
-      double p = 1.0;
-      for (int r = 0; r < 3; ++r) {
-        const int bit = 3 * gg + r, q = 32 * h + bit;
-        if (bit >= 32 || q >= cfg.nq) continue;
-        const int op = ((code >> r) & 1) | (((code >> (3 + r)) & 1) << 1);
-        if (op != 0) p *= fq[4 * q + op];
-      }
-      lut[i] = p;
-    }
+    // (the per-qubit factors sit in the not yet used wave segments)
+    build_group_table<W, kIPB>(lut, (double*)(smem + lut_bytes), cfg.nq, cfg.theta, cfg.phi);
   }
-  __syncthreads();
   const Seg<W> g = carve_seg<W>(smem + lut_bytes + (size_t)wave * seg_bytes(W, cfg.cap), cfg.cap);
   const int64_t gw = (int64_t)wave * gridDim.x + blockIdx.x;   // few items: one per CU first
   double eacc = 0.0;
