@@ -867,12 +867,9 @@ int iqcc_dress_backward(iqcc_ctx* ctx, const iqcc_store* in, const uint64_t* px,
   if (!padding_clear(in->nq, in->W, px, pz))
     return fail(ctx, IQCC_ERR_INVALID_ARG, "entangler has bits beyond n_qubits");
   hipStream_t s = as_stream(stream);
-  const int grid = (int)(ctx->n_cu * 4);
-  rc = ensure_partial(ctx, 3 * (int64_t)grid);   // exact fixed-point parts
-  if (rc) return rc;
+  const int grid = (int)(ctx->n_cu * 4) < kDressGrid ? (int)(ctx->n_cu * 4) : kDressGrid;
   launch_dress_backward(in->W, in->d, std::cos(tau), std::sin(tau), tape_self, tape_partner,
-                        lambda_out, lambda_in, ctx->partial, grid, s);
-  launch_finalize_fixed(ctx->partial, grid, dtau, s);
+                        lambda_out, lambda_in, take_slot(ctx), dtau, grid, s);
   LAUNCH_CHECK(ctx);
   return IQCC_OK;
 }

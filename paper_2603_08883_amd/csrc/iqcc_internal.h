@@ -727,10 +727,6 @@ void launch_dress_raw(int W, const uint64_t* x, const uint64_t* z, const double*
 // *out = (base ? *base : 0) + (scale ? *scale : 1) * sum(partial[0..n)); out may alias base.
 void launch_finalize_sum(const double* partial, int n, const double* scale, double* out,
                          hipStream_t s, const double* base = nullptr);
-// *out = exact sum of n FixedSum parts stored as three 8-byte words each
-// (hi, lo, mag), NaN when the values were out of range.
-void launch_finalize_fixed(const double* parts, int n, double* out, hipStream_t s);
-
 // Device state of the term-limit selection (kernels_select.hip).
 struct SelState {
   uint64_t prefix;               // digits fixed so far
@@ -794,8 +790,8 @@ int64_t dis_tile();   // candidates per workgroup of the batched kernel
 
 void launch_dress_backward(int W, const StoreDev& in, double C, double S,
                            const int32_t* tape_self, const int32_t* tape_partner,
-                           const double* lam_out, double* lam_in, double* partial, int grid,
-                           hipStream_t s);
+                           const double* lam_out, double* lam_in, double* slot /*3 grid words*/, double* dtau,
+                           int grid, hipStream_t s);
 void launch_expectations(int W, const StoreDev& st, const double* lut, const double* scale,
                          double* out, int grid, hipStream_t s);
 int64_t merge_scratch_len(int W, int64_t n, int m);

@@ -14,7 +14,9 @@
 // The tape recorded by the forward kernel gives, for every input row, the
 // output rows of A and A^P and the sign s_A, so no key is read or looked up
 // here.  The step's dE/dt is an exact fixed-point sum, so it has the same
-// bits for any order of the rows.
+// bits for any order of the rows; the workgroup that arrives last adds the
+// workgroups' parts, so a step is one launch (a second one took 2.7 us and its
+// gap).
 #include "iqcc_internal.h"
 
 #pragma clang fp contract(off)
@@ -26,10 +28,13 @@ __global__ __launch_bounds__(kBlock) void k_dress_backward(StoreDev in, double C
                                                            double S, const int32_t* tape_self,
                                                            const int32_t* tape_partner,
                                                            const double* lam_out, double* lam_in,
-                                                           double* partial) {
+                                                           double* slot, double* dtau) {
   __shared__ long long red_hi[kWaves], red_lo[kWaves];
   __shared__ double red_mag[kWaves];
+  __shared__ int s_last;
   const int64_t B = 1ll << *in.m;
+  const unsigned active = B < gridDim.x ? (unsigned)B : gridDim.x;   // workgroups with a bucket
+  if (blockIdx.x >= active) return;
   // dE/dt as an exact fixed-point sum: the same bits for any row order
   FixedSum acc;
   for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
@@ -51,23 +56,37 @@ __global__ __launch_bounds__(kBlock) void k_dress_backward(StoreDev in, double C
       fixed_add(acc, __dadd_rn(-__dmul_rn(__dmul_rn(S, c), la), s * __dmul_rn(__dmul_rn(C, c), lp)));
     }
   }
-  const FixedSum t = block_fixed_sum<kWaves>(acc, red_hi, red_lo, red_mag);
-  if (threadIdx.x == 0) {
-    partial[3 * blockIdx.x] = __longlong_as_double(t.hi);
-    partial[3 * blockIdx.x + 1] = __longlong_as_double(t.lo);
-    partial[3 * blockIdx.x + 2] = t.mag;
+  FixedSum t = block_fixed_sum<kWaves>(acc, red_hi, red_lo, red_mag);
+  if (threadIdx.x < 64) {
+    if (threadIdx.x == 0) {
+      finish_put(slot, blockIdx.x, __longlong_as_double(t.hi));
+      finish_put(slot, active + blockIdx.x, __longlong_as_double(t.lo));
+      finish_put(slot, 2 * active + blockIdx.x, t.mag);
+    }
+    const bool last = finish_arrive(slot, blockIdx.x, active);
+    if (threadIdx.x == 0) s_last = last;
   }
+  __syncthreads();
+  if (!s_last) return;
+  FixedSum f;
+  for (unsigned i = threadIdx.x; i < active; i += kBlock) {
+    f.hi += __double_as_longlong(finish_get(slot, i));
+    f.lo += __double_as_longlong(finish_get(slot, active + i));
+    f.mag += finish_get(slot, 2 * active + i);
+  }
+  t = block_fixed_sum<kWaves>(f, red_hi, red_lo, red_mag);
+  if (threadIdx.x == 0) *dtau = fixed_value(t.hi, t.lo, t.mag);
 }
 
 void launch_dress_backward(int W, const StoreDev& in, double C, double S,
                            const int32_t* tape_self, const int32_t* tape_partner,
-                           const double* lam_out, double* lam_in, double* partial, int grid,
+                           const double* lam_out, double* lam_in, double* slot, double* dtau, int grid,
                            hipStream_t s) {
   switch (W) {
-    case 1: hipLaunchKernelGGL(k_dress_backward<1>, dim3(grid), dim3(kBlock), 0, s, in, C, S, tape_self, tape_partner, lam_out, lam_in, partial); break;
-    case 2: hipLaunchKernelGGL(k_dress_backward<2>, dim3(grid), dim3(kBlock), 0, s, in, C, S, tape_self, tape_partner, lam_out, lam_in, partial); break;
-    case 3: hipLaunchKernelGGL(k_dress_backward<3>, dim3(grid), dim3(kBlock), 0, s, in, C, S, tape_self, tape_partner, lam_out, lam_in, partial); break;
-    default: hipLaunchKernelGGL(k_dress_backward<4>, dim3(grid), dim3(kBlock), 0, s, in, C, S, tape_self, tape_partner, lam_out, lam_in, partial); break;
+    case 1: hipLaunchKernelGGL(k_dress_backward<1>, dim3(grid), dim3(kBlock), 0, s, in, C, S, tape_self, tape_partner, lam_out, lam_in, slot, dtau); break;
+    case 2: hipLaunchKernelGGL(k_dress_backward<2>, dim3(grid), dim3(kBlock), 0, s, in, C, S, tape_self, tape_partner, lam_out, lam_in, slot, dtau); break;
+    case 3: hipLaunchKernelGGL(k_dress_backward<3>, dim3(grid), dim3(kBlock), 0, s, in, C, S, tape_self, tape_partner, lam_out, lam_in, slot, dtau); break;
+    default: hipLaunchKernelGGL(k_dress_backward<4>, dim3(grid), dim3(kBlock), 0, s, in, C, S, tape_self, tape_partner, lam_out, lam_in, slot, dtau); break;
   }
 }
 

@@ -60,24 +60,6 @@ void launch_finalize_sum(const double* partial, int n, const double* scale, doub
   hipLaunchKernelGGL(k_finalize_sum, dim3(1), dim3(kBlock), 0, s, partial, n, scale, base, out);
 }
 
-// Exact sum of FixedSum parts (hi, lo, mag as three 8-byte words each).
-__global__ void k_finalize_fixed(const double* parts, int n, double* out) {
-  __shared__ long long red_hi[kWaves], red_lo[kWaves];
-  __shared__ double red_mag[kWaves];
-  FixedSum f;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    f.hi += __double_as_longlong(parts[3 * i]);
-    f.lo += __double_as_longlong(parts[3 * i + 1]);
-    f.mag += parts[3 * i + 2];
-  }
-  const FixedSum t = block_fixed_sum<kWaves>(f, red_hi, red_lo, red_mag);
-  if (threadIdx.x == 0) *out = fixed_value(t.hi, t.lo, t.mag);
-}
-
-void launch_finalize_fixed(const double* parts, int n, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_finalize_fixed, dim3(1), dim3(kBlock), 0, s, parts, n, out);
-}
-
 // ---------------------------------------------------------------------------
 // Energy of a store in one launch.  Workgroup g takes the groups of G
 // consecutive buckets g, g + grid, ... (G = 1 .. 512 so that every workgroup
