@@ -28,11 +28,15 @@ class DressingChain:
         self.nq = n_qubits
         self.eps = float(eps)
         self.ents = [(np.asarray(px, np.uint64), np.asarray(pz, np.uint64)) for px, pz in entanglers]
+        # the entanglers as the chain calls take them, (n_steps, n_words)
+        self._px = np.array([e[0].reshape(-1) for e in self.ents], np.uint64)
+        self._pz = np.array([e[1].reshape(-1) for e in self.ents], np.uint64)
         self.h0 = iqcc.Store(ctx, n_qubits, max(2 * len(c), 16)).load_numpy(x, z, c)
         self.h0_max = max(2 * len(c), 16)
         self.stores = [None] * len(self.ents)      # output store of step j
         self.caps = [0] * len(self.ents)
         self.tapes = [None] * len(self.ents)       # (tape_self, tape_partner) of step j
+        self._sized = False                        # stores and tapes fit a whole run
         self.version = 0                           # bumped by every run()
 
     def _input(self, j):
@@ -45,6 +49,24 @@ class DressingChain:
         the previous one; `version` identifies the current contents.
         """
         self.version += 1
+        if not self.ents:
+            return self.h0
+        taus = list(taus)[:len(self.ents)]
+        if self._sized:
+            # sized by an earlier run: all steps in one call and one look at the
+            # result (a count before every step waits for the one before: 836 us
+            # a gradient step over 8 steps on 40 qubits, 461 us without).  A step
+            # that does not fit this time marks every later store, and the
+            # sizing run below takes over.
+            iqcc.iqcc_chain_forward(self.ctx.handle, self.h0.handle, self._px, self._pz, taus, self.eps,
+                                    [s.handle for s in self.stores], *zip(*self.tapes))
+            try:
+                self.stores[-1].count()
+                return self.stores[-1]
+            except iqcc.IqccError as e:
+                if e.code != iqcc.IQCC_ERR_CAPACITY:
+                    raise
+        self._sized = False
         prev_cap = self.h0_max
         for j, ((px, pz), t) in enumerate(zip(self.ents, taus)):
             src = self._input(j)
@@ -64,22 +86,16 @@ class DressingChain:
             iqcc.iqcc_dress_taped(self.ctx.handle, src.handle, px, pz, float(t), self.eps,
                                   self.stores[j].handle, tp[0], tp[1])
             prev_cap = self.caps[j]
-        return self.stores[-1] if self.ents else self.h0
+        self._sized = True
+        return self.stores[-1]
 
     def backward_taus(self, taus, lam_final):
         """Reverse sweep: returns dE/dtau (device tensor) given dE/dc of the final rows."""
-        K = len(self.ents)
-        dtau = torch.zeros(K, dtype=torch.float64, device="cuda")
-        lam = lam_final
-        for j in reversed(range(K)):
-            src = self._input(j)
-            lam_in = torch.empty(iqcc.iqcc_store_rows(src.handle), dtype=torch.float64, device="cuda")
-            px, pz = self.ents[j]
-            iqcc.iqcc_dress_backward(self.ctx.handle, src.handle, px, pz, float(taus[j]),
-                                     self.tapes[j][0], self.tapes[j][1], lam, lam_in, dtau[j:j + 1],
-                                     store_out=self.stores[j].handle)
-            lam = lam_in
-        return dtau
+        if not self.ents:
+            return torch.zeros(0, dtype=torch.float64, device="cuda")
+        return iqcc.iqcc_chain_backward(self.ctx.handle, self.h0.handle, self._px, self._pz,
+                                        list(taus)[:len(self.ents)],
+                                        [s.handle for s in self.stores], *zip(*self.tapes), lam_final)
 
     def close(self):
         for s in self.stores:
