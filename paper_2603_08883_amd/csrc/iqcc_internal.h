@@ -766,10 +766,21 @@ hipError_t sortless_dress_run(int W, const uint64_t* x, const uint64_t* z, const
                               int64_t ld, const PauliKey& P, int nbits, double C, double S, double eps,
                               uint64_t* ox, uint64_t* oz, double* oc, int64_t cap, int64_t ld_out,
                               int64_t* n_out, hipStream_t s);
-void launch_flip_rows(int W, const StoreDev& st, int w_max, uint64_t* ox, uint64_t* oz, double* oc,
-                      int64_t ld, unsigned long long* count, int grid, hipStream_t s);
-void launch_energy_anti(int W, const StoreDev& st, const PauliKey& P, int grid, const double* lut,
-                        double* partial, hipStream_t s);
+// Distinct flip sets with 1 <= |F| <= w_max (planes fx of leading dimension
+// ld >= the live terms; table: a power of two above them); count[0] sets,
+// count[1] qubits in all, count[2] cleared.
+void launch_flip_unique(int W, const StoreDev& st, int w_max, unsigned long long* tab, int64_t table, uint64_t* fx,
+                        int64_t ld, unsigned long long* count, int grid, hipStream_t s);
+// One candidate per qubit of each of the nf sets, nc in all (planes of nc).
+void launch_candidates(int W, const uint64_t* fx, int64_t ld, int64_t nf, uint64_t* cx, uint64_t* cz, int64_t nc,
+                       unsigned long long* count, hipStream_t s);
+// The k <= nc candidates of largest |g|, as rows {g, x words, z words}.
+void launch_top_candidates(int W, const double* g, const uint64_t* cx, const uint64_t* cz, int64_t nc, int k,
+                           double* out, hipStream_t s);
+// Sums over the terms that anticommute with P: c <K>, and (c_out not null) the
+// DIS gradient of P.  2 grid words of the slot.
+void launch_anti_sums(int W, const StoreDev& st, const Entangler& P, int nq, int grid, const double* theta,
+                      const double* phi, double* slot, double* b_out, double* c_out, hipStream_t s);
 // Stand-alone energy, one launch: *out = <st>.  per_cu: upper bound of the
 // workgroups per CU; slot: a finish slot (see finish_arrive).
 void launch_energy(int W, int nq, const StoreDev& st, int n_cu, int per_cu, size_t lds_per_cu, const double* theta,
