@@ -75,10 +75,9 @@ void launch_finalize_sum(const double* partial, int n, const double* scale, doub
 // lookup takes one byte extraction.  A code holds the four z bits below the
 // four x bits: most groups of a Jordan-Wigner string are Z strings (x = 0),
 // whose 16 codes then lie next to each other, in different LDS banks (with
-// the x bits low they were 16 entries apart and met in two banks: 156 us
-// against XXX us on 1.6e7 two-word terms).  Wider keys: 3-qubit groups, 22 per
-// word and 64 entries each, because nibble tables would leave one workgroup
-// per CU.
+// the x bits low they were 16 entries apart and met in two banks).  Wider keys:
+// 3-qubit groups, 22 per word and 64 entries each, because nibble tables would
+// leave one workgroup per CU.
 //
 // The grid holds what the CUs keep resident (more workgroups would only build
 // more tables), and of it only as many workgroups take part ("active") as

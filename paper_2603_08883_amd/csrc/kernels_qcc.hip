@@ -144,66 +144,78 @@ void launch_candidates(int W, const uint64_t* fx, int64_t ld, int64_t nf, uint64
 // next.  The order is total (candidates are distinct), so "not taken" is
 // "after the last one taken".  out: k rows {g, x words, z words}.
 constexpr int kTopBlock = 1024;
+static_assert(kTopBlock / 64 == 16, "the second tree spans 16 waves");
 
 template <int W>
 __global__ __launch_bounds__(kTopBlock) void k_top_candidates(const double* g, const uint64_t* cx, const uint64_t* cz,
                                                               int64_t nc, int k, double* out) {
   __shared__ int64_t s_best[kTopBlock / 64];
+  __shared__ double s_val[kTopBlock / 64];
   __shared__ int64_t s_taken;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   auto rank = [&](int64_t i) {
     const double v = fabs(g[i]);
     return v == v ? v : -1.0;
   };
-  // candidate a comes before candidate b (indices; -1: none)
-  auto before = [&](int64_t a, int64_t b) {
-    if (a < 0 || b < 0) return a >= 0;
-    const double va = rank(a), vb = rank(b);
-    if (va != vb) return va > vb;
+  // candidate a of rank va comes before candidate b of rank vb (none: -1 of
+  // rank -2); keys are read only where the ranks are equal
+  auto before = [&](double va, int64_t a, double vb, int64_t b) {
+    if (va != vb || a < 0 || b < 0) return va > vb;
     for (int w = W - 1; w >= 0; --w)
       if (cx[w * nc + a] != cx[w * nc + b]) return cx[w * nc + a] < cx[w * nc + b];
     for (int w = W - 1; w >= 0; --w)
       if (cz[w * nc + a] != cz[w * nc + b]) return cz[w * nc + a] < cz[w * nc + b];
     return false;
   };
-  auto best_after = [&](int64_t last) {
+  int64_t mine = -1;
+  double vmine = -2.0;
+  auto best_after = [&](int64_t last, double vl) {   // last -1: the best of all
     int64_t best = -1;
     double vb = -2.0;
-    const double vl = last >= 0 ? rank(last) : 0.0;
     for (int64_t i = threadIdx.x; i < nc; i += kTopBlock) {
       const double v = rank(i);
-      if (v < vb || (last >= 0 && v > vl)) continue;
-      if (last >= 0 && v == vl && !before(last, i)) continue;
-      if (v > vb || before(i, best)) {
+      if (v < vb || (last >= 0 && !before(vl, last, v, i))) continue;
+      if (before(v, i, vb, best)) {
         best = i;
         vb = v;
       }
     }
-    return best;
+    mine = best;
+    vmine = vb;
   };
-  int64_t mine = best_after(-1);
+  best_after(-1, 0.0);
   for (int r = 0; r < k; ++r) {
     int64_t b = mine;
+    double vb = vmine;
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
       const int64_t o = (int64_t)__shfl_xor((long long)b, d, 64);
-      if (before(o, b)) b = o;
+      const double vo = __shfl_xor(vb, d, 64);
+      if (before(vo, o, vb, b)) { b = o; vb = vo; }
     }
-    if (lane == 0) s_best[wave] = b;
+    if (lane == 0) {
+      s_best[wave] = b;
+      s_val[wave] = vb;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int i = 1; i < kTopBlock / 64; ++i)
-        if (before(s_best[i], b)) b = s_best[i];
-      s_taken = b;
-      double* row = out + (int64_t)r * (1 + 2 * W);
-      row[0] = g[b];   // k <= nc: there is one
-      for (int w = 0; w < W; ++w) {
-        row[1 + w] = __longlong_as_double((long long)cx[w * nc + b]);
-        row[1 + W + w] = __longlong_as_double((long long)cz[w * nc + b]);
+    if (wave == 0) {
+      b = lane < kTopBlock / 64 ? s_best[lane] : -1;
+      vb = lane < kTopBlock / 64 ? s_val[lane] : -2.0;
+#pragma unroll
+      for (int d = 8; d >= 1; d >>= 1) {
+        const int64_t o = (int64_t)__shfl_xor((long long)b, d, 64);
+        const double vo = __shfl_xor(vb, d, 64);
+        if (before(vo, o, vb, b)) { b = o; vb = vo; }
       }
+      if (lane == 0) s_taken = b;   // k <= nc: there is one
+      double* row = out + (int64_t)r * (1 + 2 * W);
+      b = (int64_t)wave_bcast0((unsigned long long)b);
+      if (lane == 0) row[0] = g[b];
+      if (lane >= 1 && lane <= W) row[lane] = __longlong_as_double((long long)cx[(lane - 1) * nc + b]);
+      if (lane > W && lane <= 2 * W) row[lane] = __longlong_as_double((long long)cz[(lane - 1 - W) * nc + b]);
     }
     __syncthreads();
-    if (s_taken == mine) mine = best_after(mine);
+    if (s_taken == mine && mine >= 0) best_after(mine, vmine);
   }
 }
 
