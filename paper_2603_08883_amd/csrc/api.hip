@@ -41,6 +41,7 @@ struct iqcc_ctx {
   double* lut = nullptr;        // kLutDoubles: 3-qubit group table (4 x 22 x 64)
   double* slots = nullptr;      // kFinishSlots finish slots, taken in turn
   unsigned next_slot = 0;
+  unsigned* sel_hist = nullptr; // kSelHist digit counters, zero between calls, then a SelState
   double* partial = nullptr;    // n_partial
   int64_t n_partial = 0;
   int64_t* scratch = nullptr;   // n_scratch
@@ -437,12 +438,15 @@ int iqcc_ctx_create(iqcc_ctx** out, int device) {
       ctx->lds_per_cu = (size_t)v;
   }
   noalloc_setup(device);
+  const size_t sel_bytes = sizeof(unsigned) * kSelHist + sizeof(SelState);
   const size_t slot_bytes = sizeof(double) * kFinishSlots * kCtxSlot;
   if (hipMalloc(&ctx->lut, sizeof(double) * kLutDoubles) != hipSuccess ||
       hipMalloc(&ctx->slots, slot_bytes) != hipSuccess || hipMemset(ctx->slots, 0, slot_bytes) != hipSuccess ||
+      hipMalloc(&ctx->sel_hist, sel_bytes) != hipSuccess || hipMemset(ctx->sel_hist, 0, sel_bytes) != hipSuccess ||
       hipDeviceSynchronize() != hipSuccess) {
     if (ctx->lut) hipFree(ctx->lut);
     if (ctx->slots) hipFree(ctx->slots);
+    if (ctx->sel_hist) hipFree(ctx->sel_hist);
     delete ctx;
     return IQCC_ERR_HIP;
   }
@@ -456,6 +460,7 @@ int iqcc_ctx_destroy(iqcc_ctx* ctx) {
   hipDeviceSynchronize();
   if (ctx->lut) hipFree(ctx->lut);
   if (ctx->slots) hipFree(ctx->slots);
+  if (ctx->sel_hist) hipFree(ctx->sel_hist);
   if (ctx->partial) hipFree(ctx->partial);
   if (ctx->scratch) hipFree(ctx->scratch);
   if (ctx->work) hipFree(ctx->work);
@@ -1430,48 +1435,40 @@ int iqcc_truncate_top(iqcc_ctx* ctx, const iqcc_store* in, int64_t max_terms, iq
   if (rc) return rc;
   const int W = in->W;
   const int grid = (int)(ctx->n_cu * 4);
-  DevBuf dss, dhist;
-  HIP_TRY(ctx, hipMalloc(&dss.p, sizeof(SelState)));
-  HIP_TRY(ctx, hipMalloc(&dhist.p, 2048 * sizeof(unsigned)));
-  SelState* ss = (SelState*)dss.p;
-  SelState h{};
-  h.need = max_terms;
-  HIP_TRY(ctx, hipMemcpyAsync(ss, &h, sizeof(h), hipMemcpyHostToDevice, s));
-  HIP_TRY(ctx, hipMemsetAsync(dhist.p, 0, 2048 * sizeof(unsigned), s));
-  launch_zero_counters(out->d, s);
-  int keep_all = n <= max_terms ? 1 : max_terms == 0 ? -1 : 0;
+  SelState* ss = (SelState*)(ctx->sel_hist + kSelHist);
+  const int keep_all = n <= max_terms ? 1 : max_terms == 0 ? -1 : 0;
   DevBuf keys, kcount;
   if (keep_all == 0) {
-    launch_abs_select_first(W, in->d, ss, (unsigned*)dhist.p, grid, s);
+    // (the output's rows and bucket counts are scratch until the copy)
+    launch_abs_select(in->d, ss, ctx->sel_hist, ctx->n_cu, max_terms, out->d, take_slot(ctx), s);
     LAUNCH_CHECK(ctx);
+    SelState h{};
     HIP_TRY(ctx, hipMemcpyAsync(&h, ss, sizeof(h), hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
-    // the terms that share the first digit: their |c| bits go to the reused
-    // partial-sum buffer, followed by the append counter
-    const int64_t ncand = h.at > 0 ? h.at : 1;
-    rc = ensure_partial(ctx, ncand + 1);
-    if (rc) return rc;
-    uint64_t* cand = (uint64_t*)ctx->partial;
-    unsigned long long* ccount = (unsigned long long*)(ctx->partial + ncand);
-    HIP_TRY(ctx, hipMemsetAsync(ccount, 0, sizeof(unsigned long long), s));
-    launch_abs_select_rest(W, in->d, ss, (unsigned*)dhist.p, grid, cand, ncand, ccount, s);
-    LAUNCH_CHECK(ctx);
-    HIP_TRY(ctx, hipMemcpyAsync(&h, ss, sizeof(h), hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
+    if (!h.done) {
+      launch_abs_select_rest(in->d, ss, ctx->sel_hist, ctx->n_cu, out->d, take_slot(ctx), s);
+      LAUNCH_CHECK(ctx);
+      HIP_TRY(ctx, hipMemcpyAsync(&h, ss, sizeof(h), hipMemcpyDeviceToHost, s));
+      HIP_TRY(ctx, hipStreamSynchronize(s));
+    }
     if (h.need < h.ties) {
       // not every term equal to the threshold fits: the smaller canonical keys go first
-      HIP_TRY(ctx, hipMalloc(&keys.p, (size_t)h.ties * 2 * W * sizeof(uint64_t)));
-      HIP_TRY(ctx, hipMalloc(&kcount.p, 64));
+      if (hipMalloc(&keys.p, (size_t)h.ties * 2 * W * sizeof(uint64_t)) != hipSuccess ||
+          hipMalloc(&kcount.p, 64) != hipSuccess) {
+        launch_select_compact(W, in->d, out->d, ss, -1, 1, take_slot(ctx), s);   // leave a valid, empty store
+        return fail(ctx, IQCC_ERR_HIP, "out of device memory for the keys of equal terms");
+      }
       HIP_TRY(ctx, hipMemsetAsync(kcount.p, 0, 64, s));
       launch_collect_ties(W, in->d, ss, (uint64_t*)keys.p, h.ties, (unsigned long long*)kcount.p,
                           grid, s);
-      launch_key_select(W, (const uint64_t*)keys.p, h.ties, ss, (unsigned*)dhist.p, s);
+      launch_key_select(W, (const uint64_t*)keys.p, h.ties, ss, ctx->sel_hist, take_slot(ctx), s);
       const int one = 1;
       HIP_TRY(ctx, hipMemcpyAsync(&ss->key_mode, &one, sizeof(int), hipMemcpyHostToDevice, s));
       LAUNCH_CHECK(ctx);
     }
   }
-  launch_select_compact(W, in->d, out->d, ss, keep_all, grid, s);
+  const int cgrid = ctx->n_cu * 8 < 4 * kDressGrid ? ctx->n_cu * 8 : 4 * kDressGrid;
+  launch_select_compact(W, in->d, out->d, ss, keep_all, cgrid, take_slot(ctx), s);
   out->regions = false;
   LAUNCH_CHECK(ctx);
   HIP_TRY(ctx, hipStreamSynchronize(s));

@@ -735,25 +735,26 @@ struct SelState {
   uint64_t T;                    // |c| bits of the M-th largest term
   int64_t ties;                  // terms with |c| bits == T
   int64_t at;                    // terms in the digit picked last
+  int64_t listed;                // |c| values listed by the finish in one launch
   int key_mode;                  // 1: keep only ties with canonical key <= kthr
-  int pad;
+  int done;                      // T, ties and need are settled
   uint64_t kthr[2 * kMaxWords];  // canonical key threshold among the ties
 };
-// First |c| digit over every term (sets ss->at, the terms that share it);
-// then the remaining digits, copying the |c| bits of those terms to cand
-// (capacity >= ss->at) on the second pass and reading only them afterwards.
-void launch_abs_select_first(int W, const StoreDev& st, SelState* ss, unsigned* hist, int grid,
-                             hipStream_t s);
-void launch_abs_select_rest(int W, const StoreDev& st, SelState* ss, unsigned* hist, int grid,
-                            uint64_t* cand, int64_t cand_cap, unsigned long long* cand_count,
-                            hipStream_t s);
+constexpr int kSelHist = 2048;   // digit counters, zero between passes
+// The need-th largest |c| of st: T, ties and need (ties to take) of ss, if done
+// is set then; else launch_abs_select_rest settles them.  tmp: a store at least
+// as large, whose rows and bucket counts are scratch.
+void launch_abs_select(const StoreDev& st, SelState* ss, unsigned* hist, int n_cu, int64_t need, const StoreDev& tmp,
+                       double* slot, hipStream_t s);
+void launch_abs_select_rest(const StoreDev& st, SelState* ss, unsigned* hist, int n_cu, const StoreDev& tmp,
+                            double* slot, hipStream_t s);
 void launch_collect_ties(int W, const StoreDev& st, const SelState* ss, uint64_t* keys, int64_t cap,
                          unsigned long long* count, int grid, hipStream_t s);
-void launch_key_select(int W, const uint64_t* keys, int64_t n, SelState* ss, unsigned* hist,
+void launch_key_select(int W, const uint64_t* keys, int64_t n, SelState* ss, unsigned* hist, double* slot,
                        hipStream_t s);
-// keep_all: 1 every term, 0 the selection in ss, -1 none
-void launch_select_compact(int W, const StoreDev& in, const StoreDev& out, const SelState* ss,
-                           int keep_all, int grid, hipStream_t s);
+// keep_all: 1 every term, 0 the selection in ss, -1 none; grid words of the slot
+void launch_select_compact(int W, const StoreDev& in, const StoreDev& out, const SelState* ss, int keep_all, int grid,
+                           double* slot, hipStream_t s);
 
 // A Pauli key passed by value to a kernel.
 struct PauliKey {
