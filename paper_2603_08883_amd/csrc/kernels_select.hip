@@ -216,10 +216,9 @@ static const int kDigitWidth[6] = {11, 11, 11, 11, 11, 9};
 static const int kDigitShift[6] = {53, 42, 31, 20, 9, 0};
 
 // The other four digits at once if the first two left at most kSelList terms
-// (64 KB of LDS; four passes and one more synchronisation otherwise: 38 us against 16 on 3e6
-// terms): each workgroup lists its
-// matches, the one that arrives last reads the whole list back and selects
-// from it.
+// (64 KB of LDS; four passes and one more synchronisation otherwise: 38 us
+// against 16 on 3e6 terms): each workgroup lists its matches, the one that
+// arrives last reads the whole list back and selects from it.
 constexpr int kSelList = 8192;
 
 __global__ __launch_bounds__(kSelBlock) void k_cand_finish(StoreDev st, const uint64_t* cand, const int64_t* ncand,

@@ -434,38 +434,120 @@ int launch_store_load_regions(int W, StoreDev st, const uint64_t* x, const uint6
   return 0;
 }
 
-// One wave per destination bucket d (m bits): its terms are those of source
-// bucket d mod 2^ms whose hash has low bits d (m >= ms), or every term of the
-// source buckets d + k 2^m in order (m < ms).  COUNT: live rows only; else the
-// rows, in source order (ballot ranks).
+// Copy into regions of another bucket count.  COUNT: live rows only; else the
+// rows, in source order.
+//
+// More buckets in the destination (m >= ms): a source bucket splits by m - ms
+// more hash bits.  One wavefront streams it once and keeps a counter per
+// destination bucket in LDS; a term's row is the counter plus its rank among
+// the lanes of the slice with the same bits, from one ballot per bit.  A split
+// into more than kSplit parts is several work items, which each place their
+// part.  (With a wavefront per destination bucket that selected its terms, the
+// source was read 2^(m - ms) times: 112 us to count and 218 us to place 1.1e6
+// two-word terms from 8192 into 2^17 buckets, now @C and @R.)  Bound: HBM,
+// 40 bytes read a term and row writes shorter than a cache line.
+//
+// Fewer (m < ms): a wavefront per destination bucket d copies the source
+// buckets d + k 2^m in order.
+constexpr int kSplit = 512;
+
 template <int W, bool COUNT>
-__global__ void k_copy_regions(StoreDev src, StoreDev dst, int m) {
+__device__ __forceinline__ void copy_split(const StoreDev& src, const StoreDev& dst, int m, int ms, int32_t* ctr) {
+  constexpr int U = 2;
+  const int lane = threadIdx.x & 63;
+  const int bits = m - ms < 9 ? m - ms : 9;   // of one work item
+  static_assert(kSplit == 1 << 9, "counters of one work item");
+  const int parts = 1 << bits;
+  const int64_t B = 1ll << ms, items = 1ll << (m - bits);
+  const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
+  for (int64_t it = blockIdx.x * (int64_t)(blockDim.x >> 6) + (threadIdx.x >> 6); it < items; it += waves) {
+    const int64_t sb = it & (B - 1);              // source bucket
+    const uint32_t high = (uint32_t)(it >> ms);   // hash bits above the item's
+    const int64_t n = src.cnt[sb], off = src.off[sb];
+    for (int k = lane; k < parts; k += 64)
+      ctr[k] = COUNT ? 0 : (int32_t)dst.off[sb | ((int64_t)k << ms) | ((int64_t)high << (ms + bits))];
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // one wave's LDS operations complete in order
+    for (int64_t i0 = 0; i0 < n; i0 += 64 * U) {
+      uint64_t kx[U][W], kz[U][W];
+      double c[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t i = i0 + 64 * u + lane;
+        if (i < n) {
+          if constexpr (COUNT) {
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+              kx[u][w] = src.x[w * src.cap + off + i];
+              kz[u][w] = src.z[w * src.cap + off + i];
+            }
+          } else {
+            load_key<W>(src, off + i, kx[u], kz[u], c[u]);
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (i0 + 64 * u >= n) break;
+        bool sel = i0 + 64 * u + lane < n;
+        uint32_t part = 0;
+        if (sel) {
+          const uint32_t h = (uint32_t)(bucket_hash<W>(kx[u], kz[u]) & ((1ull << m) - 1)) >> ms;
+          part = h & (uint32_t)(parts - 1);
+          sel = h >> bits == high;
+        }
+        if constexpr (COUNT) {
+          if (sel) atomicAdd(&ctr[part], 1);
+        } else {
+          uint64_t same = __ballot(sel);
+          for (int k = 0; k < bits; ++k) {
+            const uint64_t one = __ballot((part >> k) & 1);
+            same &= (part >> k) & 1 ? one : ~one;
+          }
+          if (sel) {
+            const int32_t base = ctr[part];
+            store_key<W>(dst, (int64_t)base + lanes_below(same), kx[u], kz[u], c[u]);
+            ctr[part] = base + (int32_t)__popcll(same);   // (the same value from every lane of the part)
+          }
+          __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        }
+      }
+    }
+    if constexpr (COUNT) {
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      for (int k = lane; k < parts; k += 64)
+        dst.cnt[sb | ((int64_t)k << ms) | ((int64_t)high << (ms + bits))] = ctr[k];
+    }
+  }
+}
+
+template <int W, bool COUNT>
+__global__ __launch_bounds__(kBlock) void k_copy_regions(StoreDev src, StoreDev dst, int m) {
+  __shared__ int32_t counters[kWaves][kSplit];
   if (*src.err || (!COUNT && *dst.err)) return;   // an invalid source is not read
   const int lane = threadIdx.x & 63;
   const int ms = *src.m;
+  if (m >= ms) {
+    copy_split<W, COUNT>(src, dst, m, ms, counters[threadIdx.x >> 6]);
+    return;
+  }
   const int64_t B = 1ll << m;
-  const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
-  const uint32_t mask = (uint32_t)(B - 1);
-  const int64_t nsrc = m >= ms ? 1 : (1ll << (ms - m));
-  for (int64_t d = blockIdx.x * (int64_t)(blockDim.x >> 6) + (threadIdx.x >> 6); d < B; d += waves) {
+  const int64_t waves = (int64_t)gridDim.x * kWaves;
+  const int64_t nsrc = 1ll << (ms - m);
+  for (int64_t d = blockIdx.x * (int64_t)kWaves + (threadIdx.x >> 6); d < B; d += waves) {
     int64_t k = 0;
     const int64_t base = COUNT ? 0 : dst.off[d];
     for (int64_t t = 0; t < nsrc; ++t) {
-      const int64_t sb = m >= ms ? (d & ((1ll << ms) - 1)) : d + (t << m);
+      const int64_t sb = d + (t << m);
       const int64_t n = src.cnt[sb], off = src.off[sb];
-      for (int64_t i0 = 0; i0 < n; i0 += 64) {
-        const int64_t i = i0 + lane;
-        uint64_t kx[W], kz[W];
-        double c = 0.0;
-        bool sel = false;
-        if (i < n) {
+      if constexpr (!COUNT) {
+        for (int64_t i = lane; i < n; i += 64) {
+          uint64_t kx[W], kz[W];
+          double c;
           load_key<W>(src, off + i, kx, kz, c);
-          sel = m < ms || (bucket_hash<W>(kx, kz) & mask) == (uint32_t)d;
+          store_key<W>(dst, base + k + i, kx, kz, c);
         }
-        const uint64_t bm = __ballot(sel);
-        if (!COUNT && sel) store_key<W>(dst, base + k + (int64_t)lanes_below(bm), kx, kz, c);
-        k += __popcll(bm);
       }
+      k += n;
     }
     if (COUNT && lane == 0) dst.cnt[d] = k;
   }
