@@ -553,26 +553,44 @@ __device__ __forceinline__ void expect_split(const double* lut, const Entangler&
     }
   } else {
     // A: every group of every half word with P's groups masked to the identity
-    // (table entry 0 = 1.0); each iteration issues 4 independent lookups per
-    // half word, so the whole product takes three LDS round trips
-    uint32_t xa[2 * W], za[2 * W];
+    // (table entry 0 = 1.0).  Two bit-field inserts put the x and z bits of the
+    // half's even and of its odd groups next to each other, six bits each, so a
+    // lookup is one extraction and one shift.  (The energy's share of an in-place
+    // step from 2.0e7 to 2.6e7 two-word terms is 20 us so; with two extractions a
+    // lookup it was 60.)  4 W lookups are in flight.
+    uint32_t ev[2 * W], od[2 * W], last[2 * W];
 #pragma unroll
     for (int h = 0; h < 2 * W; ++h) {
-      xa[h] = (uint32_t)(x[h >> 1] >> (32 * (h & 1))) & ~P.gbits[h];
-      za[h] = (uint32_t)(z[h >> 1] >> (32 * (h & 1))) & ~P.gbits[h];
+      const uint32_t xa = (uint32_t)(x[h >> 1] >> (32 * (h & 1))) & ~P.gbits[h];
+      const uint32_t za = (uint32_t)(z[h >> 1] >> (32 * (h & 1))) & ~P.gbits[h];
+      constexpr uint32_t kX = 0x071C71C7u;   // three bits of every six
+      ev[h] = (xa & kX) | ((za << 3) & ~kX);
+      od[h] = ((xa >> 3) & kX) | (za & ~kX);
+      last[h] = (xa >> 30) | ((za >> 30) << 3);
     }
-#pragma unroll 1
-    for (int g = 0; g < 12; g += 4) {
-      const uint32_t s0 = 3 * g;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
 #pragma unroll
       for (int h = 0; h < 2 * W; ++h) {
-        const double* lg = lut + (h * kGroupsPerHalf + g) * kLutEntries;
-        p0 *= lg[__builtin_amdgcn_ubfe(xa[h], s0, 3) | (__builtin_amdgcn_ubfe(za[h], s0, 3) << 3)];
-        p1 *= lg[kLutEntries + (__builtin_amdgcn_ubfe(xa[h], s0 + 3, 3) | (__builtin_amdgcn_ubfe(za[h], s0 + 3, 3) << 3))];
-        p2 *= lg[2 * kLutEntries + (__builtin_amdgcn_ubfe(xa[h], s0 + 6, 3) | (__builtin_amdgcn_ubfe(za[h], s0 + 6, 3) << 3))];
-        if (g + 3 < kGroupsPerHalf)
-          p3 *= lg[3 * kLutEntries + (__builtin_amdgcn_ubfe(xa[h], s0 + 9, 3) | (__builtin_amdgcn_ubfe(za[h], s0 + 9, 3) << 3))];
+        const double* lg = lut + (h * kGroupsPerHalf + 2 * k) * kLutEntries;
+        const double e0 = lg[__builtin_amdgcn_ubfe(ev[h], 6 * k, 6)];
+        const double e1 = lg[kLutEntries + __builtin_amdgcn_ubfe(od[h], 6 * k, 6)];
+        if (h & 1) {
+          p2 *= e0;
+          p3 *= e1;
+        } else {
+          p0 *= e0;
+          p1 *= e1;
+        }
       }
+      // the products stay here: left to itself the compiler moves them behind
+      // the last lookup, which keeps all the factors in registers
+      asm volatile("" : "+v"(p0), "+v"(p1), "+v"(p2), "+v"(p3));
+    }
+#pragma unroll
+    for (int h = 0; h < 2 * W; ++h) {
+      const double e = lut[(h * kGroupsPerHalf + 10) * kLutEntries + last[h]];
+      if (h & 1) p1 *= e; else p0 *= e;
     }
   }
   // B and B' over P's groups, two per LDS round trip.  The groups come from

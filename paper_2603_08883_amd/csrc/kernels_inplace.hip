@@ -29,6 +29,14 @@
 // member of each {K, K^P} pair in an LDS hash table, and every output
 // position comes from ballots in stash order.  Lane s of the wave holds the
 // bucket table entry of the item's slot s.
+//
+// Bound: HBM.  A step from 2.0e7 to 2.6e7 two-word terms takes 437 us with the
+// energy and 420 without, on 8 waves a CU as on 12; the same reads and writes
+// alone (buckets of 150 rows in five planes, half the coefficients rewritten,
+// 52 rows appended) take 330.  Rows appended in five short runs, which end in
+// partial cache lines, are the dear part: 0.27 GB take 130 us of them.  With
+// the phase of a term looked up again in each pass, per-slot counters in LDS
+// and shuffled scans the step took 466 us.
 #include "iqcc_internal.h"
 
 #pragma clang fp contract(off)
@@ -47,7 +55,8 @@ constexpr int kIPSlots = 64;      // buckets per work item (one per lane)
 #endif
 constexpr int kIPU = IQCC_INPLACE_UNROLL;   // 64-term slices of the scan in flight per wave
 
-enum : uint8_t { kFComm = 1, kFHole = 2, kFNew = 4 };
+// kFPlus: P K = i^3 (K^P), so K^P enters with + sin tau (set by item_join).
+enum : uint8_t { kFComm = 1, kFHole = 2, kFNew = 4, kFPlus = 8 };
 
 // Per-wave LDS segment: the stash of up to `cap` entries, its join table and
 // per-slot counters of the item.
@@ -140,21 +149,22 @@ __device__ __forceinline__ bool sorted_contains(const int32_t* h, int n, int v) 
   return lo < n && h[lo] == v;
 }
 
+// Inclusive scan over the wave (all lanes active): within rows of 16 lanes,
+// then the last lane of a row into the next rows.  No LDS round trips, of
+// which a scan by shuffles takes six in a chain.
 __device__ __forceinline__ int wave_incl_scan(int v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int y = __shfl_up(v, d, 64);
-    if (lane >= d) v += y;
-  }
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15 -> rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31 -> rows 2, 3
   return v;
 }
 
-// Sum over the wave, returned as a wave-uniform (scalar) value.
+// Sum over the wave (all lanes active), as a wave-uniform (scalar) value.
 __device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  return __builtin_amdgcn_readfirstlane(v);
+  return __builtin_amdgcn_readlane(wave_incl_scan(v), 63);
 }
 
 struct Geo {
@@ -184,9 +194,11 @@ __device__ __forceinline__ SlotDesc load_desc(const StoreDev& st, const Geo& G, 
     uint32_t b0, b1;
     pair_buckets(q, G.f, G.thi, b0, b1);
     d.b = (!G.selfp && (lane & 1)) ? b1 : b0;
-    d.off = (int)st.off[d.b];
-    d.cnt = (int)st.cnt[d.b];
-    d.lim = (int)st.lim[d.b];
+    // (low words: a load of both would have to be waited for before the high
+    // word's register is used again)
+    d.off = ((const int*)st.off)[2 * (int64_t)d.b];
+    d.cnt = ((const int*)st.cnt)[2 * (int64_t)d.b];
+    d.lim = ((const int*)st.lim)[2 * (int64_t)d.b];
   }
   return d;
 }
@@ -197,9 +209,13 @@ struct Item {
   int noff;             // first row of the fresh region (relocated items)
   uint32_t b;
   int pre;              // flat index of the slot's first term
-  int pre1;             // flat index of slot 1 (wave-uniform)
-  int nslots, n;
+  int nslots, n;        // the same in every lane, as are the following
+  int pre1;             // flat index of slot 1
+  int off0, off1;       // first rows of slots 0 and 1
 };
+
+// Value v0 or v1 (wave-uniform) of slot s of an item of at most two slots.
+__device__ __forceinline__ int of_slot(int s, int v0, int v1) { return s ? v1 : v0; }
 
 // Slot of flat index i: the largest s < nslots with pre_s <= i, where lane s
 // holds pre_s (non-decreasing, pre_0 = 0).  Called by the whole wave.
@@ -226,8 +242,10 @@ __device__ __forceinline__ Item make_item(const SlotDesc& d) {
   I.noff = 0;
   const int incl = wave_incl_scan(I.cnt);
   I.pre = incl - I.cnt;
-  I.n = __shfl(incl, 63, 64);
-  I.pre1 = __shfl(I.pre, 1, 64);
+  I.n = __shfl(incl, 63, 64);   // (as a scalar the loops over it need more registers than there are)
+  I.pre1 = __builtin_amdgcn_readlane(I.pre, 1);
+  I.off0 = __builtin_amdgcn_readlane(I.off, 0);
+  I.off1 = __builtin_amdgcn_readlane(I.off, 1);
   return I;
 }
 
@@ -248,8 +266,9 @@ __device__ __forceinline__ void issue_slices(const StoreDev& st, const Item& I, 
     const int i = base + 64 * u + lane;
     const bool valid = i < I.n;
     const int sl = slot_of(I, i);
-    const int pre = __shfl(I.pre, sl, 64);
-    const int off = __shfl(I.off, sl, 64);
+    const bool two = I.nslots <= 2;
+    const int pre = two ? of_slot(sl, 0, I.pre1) : __shfl(I.pre, sl, 64);
+    const int off = two ? of_slot(sl, I.off0, I.off1) : __shfl(I.off, sl, 64);
     S.slot[u] = sl;
     S.rel[u] = i - pre;
     S.kc[u] = 0.0;
@@ -398,6 +417,7 @@ __device__ void item_join(const Entangler& P, const Seg<W>& g, int n) {
     if (g.aflag[i] & kFComm) continue;
     uint64_t kx[W], kz[W];
     entry_key<W>(g, i, kx, kz);
+    if (product_phase<W>(P.px, P.pz, kx, kz) == 3) g.aflag[i] |= kFPlus;
     if (pivot_of<W>(P, kx, kz)) continue;
     const uint32_t hk = table_hash<W>(kx, kz);
     const int32_t e = (int32_t)((hk << 16) | (uint32_t)i);
@@ -423,10 +443,11 @@ __device__ void item_join(const Entangler& P, const Seg<W>& g, int n) {
       if (e == -1) break;
       if (((uint32_t)e & 0xFFFF0000u) == fp) {
         const int j = e & 0xFFFF;
-        bool eq = true;
+        uint64_t jx[W], jz[W], diff = 0;
+        entry_key<W>(g, j, jx, jz);
 #pragma unroll
-        for (int w = 0; w < W; ++w) eq = eq && g.ax[w * g.cap + j] == kx[w] && g.az[w * g.cap + j] == kz[w];
-        if (eq) {
+        for (int w = 0; w < W; ++w) diff |= (jx[w] ^ kx[w]) | (jz[w] ^ kz[w]);
+        if (diff == 0) {
           g.partner[i] = (int16_t)j;
           g.partner[j] = (int16_t)i;
           break;
@@ -443,55 +464,76 @@ __device__ void item_join(const Entangler& P, const Seg<W>& g, int n) {
 // RN(cos tau a) together with the new term K^P of value s_K RN(sin tau a),
 // where s_A = +1 when P A = i^3 (A^P) and -1 when P A = i^1 (A^P).
 template <int W>
-__device__ __forceinline__ void entry_values(const Entangler& P, double C, double S, const Seg<W>& g, int i,
-                                             const uint64_t* kx, const uint64_t* kz, double& a,
+__device__ __forceinline__ void entry_values(double C, double S, const Seg<W>& g, int i, uint8_t fl, double& a,
                                              double& v_own, double& v_new, bool& paired) {
   a = g.ac[i];
   const int j = g.partner[i];
   const double rot = __dmul_rn(C, a);
   paired = j >= 0;
   if (paired) {
-    uint64_t jx[W], jz[W];
-    entry_key<W>(g, j, jx, jz);
-    const int ej = product_phase<W>(P.px, P.pz, jx, jz);
     const double sj = __dmul_rn(S, g.ac[j]);
-    v_own = __dadd_rn(rot, ej == 3 ? sj : -sj);
+    v_own = __dadd_rn(rot, (g.aflag[j] & kFPlus) ? sj : -sj);
     v_new = 0.0;
   } else {
     v_own = rot;
-    const int e = product_phase<W>(P.px, P.pz, kx, kz);
     const double si = __dmul_rn(S, a);
-    v_new = e == 3 ? si : -si;
+    v_new = (fl & kFPlus) ? si : -si;
   }
 }
 
 // In-place path, first emission pass: which entries free their row and which
-// add a new key, and how many per slot.
+// add a new key, and how many per slot (lane s: nn and nh of slot s; also in
+// the segment's counters).
 template <int W>
-__device__ void count_outputs(const Entangler& P, double C, double S, double eps, const Seg<W>& g, int n,
-                              int selfp) {
+__device__ void count_outputs(double C, double S, double eps, const Seg<W>& g, const Item& I, int n, int selfp,
+                              int& nn, int& nh) {
   const int lane = threadIdx.x & 63;
-  for (int i = lane; i < n; i += 64) {
-    uint8_t fl = g.aflag[i];
-    const int s = g.aslot[i];
-    if (fl & kFComm) {
-      fl |= kFHole;
-    } else {
-      uint64_t kx[W], kz[W];
-      entry_key<W>(g, i, kx, kz);
-      double a, vo, vn;
-      bool paired;
-      entry_values<W>(P, C, S, g, i, kx, kz, a, vo, vn, paired);
-      if (fabs(vo) < eps) fl |= kFHole;
-      if (!paired && !(fabs(vn) < eps)) {
-        fl |= kFNew;
-        atomicAdd(&g.s_nnew[selfp ? s : s ^ 1], 1);
+  int nn0 = 0, nn1 = 0, nh0 = 0, nh1 = 0;
+  for (int i0 = 0; i0 < n; i0 += 64) {
+    const int i = i0 + lane;
+    uint8_t fl = 0;
+    int s = 0;
+    if (i < n) {
+      fl = g.aflag[i];
+      s = g.aslot[i];
+      if (fl & kFComm) {
+        fl |= kFHole;
+      } else {
+        double a, vo, vn;
+        bool paired;
+        entry_values<W>(C, S, g, i, fl, a, vo, vn, paired);
+        if (fabs(vo) < eps) fl |= kFHole;
+        if (!paired && !(fabs(vn) < eps)) fl |= kFNew;
       }
+      g.aflag[i] = fl;
     }
-    if (fl & kFHole) atomicAdd(&g.s_nhole[s], 1);
-    g.aflag[i] = fl;
+    if (I.nslots <= 2) {   // a whole slice would add to one or two counters
+      const uint64_t mn = __ballot(fl & kFNew), mh = __ballot(fl & kFHole), m1 = __ballot(s);
+      nn0 += (int)__popcll(mn & ~m1);
+      nn1 += (int)__popcll(mn & m1);
+      nh0 += (int)__popcll(mh & ~m1);
+      nh1 += (int)__popcll(mh & m1);
+    } else {
+      if (fl & kFNew) atomicAdd(&g.s_nnew[selfp ? s : s ^ 1], 1);
+      if (fl & kFHole) atomicAdd(&g.s_nhole[s], 1);
+    }
   }
-  wave_sync();
+  nn = nh = 0;
+  if (I.nslots <= 2) {
+    if (lane < 2) {
+      nn = lane == (selfp ? 0 : 1) ? nn0 : nn1;   // new keys go to slot s ^ 1, or stay
+      nh = lane == 0 ? nh0 : nh1;
+      g.s_nnew[lane] = nn;
+      g.s_nhole[lane] = nh;
+    }
+    wave_sync();
+  } else {
+    wave_sync();
+    if (lane < I.nslots) {
+      nn = g.s_nnew[lane];
+      nh = g.s_nhole[lane];
+    }
+  }
 }
 
 // The freed rows of every slot, ascending within the slot (the stash is in
@@ -500,9 +542,9 @@ template <int W>
 __device__ int list_holes(const Seg<W>& g, const Item& I, int n) {
   const int lane = threadIdx.x & 63;
   const int h = lane < I.nslots ? g.s_nhole[lane] : 0;
+  if (__ballot(h) == 0) return 0;
   const int incl = wave_incl_scan(h);
-  const int total = __shfl(incl, 63, 64);
-  if (total == 0) return 0;
+  const int total = __builtin_amdgcn_readlane(incl, 63);
   if (lane < I.nslots) g.s_hfirst[lane] = incl - h;
   int k = 0;
   for (int i0 = 0; i0 < n; i0 += 64) {
@@ -520,16 +562,21 @@ __device__ int list_holes(const Seg<W>& g, const Item& I, int n) {
 // rows, new keys into the partner slot (freed rows first), energy.
 template <int W, bool ENERGY>
 __device__ void emit_inplace(const StoreDev& st, const Entangler& P, double C, double S, int delta,
-                             const double* lut, const Seg<W>& g, const Item& I, int n, int selfp,
+                             const double* lut, const Seg<W>& g, const Item& I, int n, int selfp, int nh,
                              double& eacc) {
   const int lane = threadIdx.x & 63;
+  const bool two = I.nslots <= 2;
+  // of the two slots: freed rows, the next row after the live ones, keys placed
+  const int nh0 = __builtin_amdgcn_readlane(nh, 0), nh1 = __builtin_amdgcn_readlane(nh, 1);
+  const int end0 = I.off0 + I.pre1, end1 = I.off1 + (I.n - I.pre1);
+  int put0 = 0, put1 = 0;
   for (int i0 = 0; i0 < n; i0 += 64) {
     const int i = i0 + lane;
     const bool valid = i < n;
     const uint8_t fl = valid ? g.aflag[i] : (uint8_t)0;
     const bool live = valid && !(fl & kFComm);
     const int s = valid ? g.aslot[i] : 0;
-    const int off = __shfl(I.off, s, 64);
+    const int off = two ? of_slot(s, I.off0, I.off1) : __shfl(I.off, s, 64);
     uint64_t kx[W], kz[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) kx[w] = kz[w] = 0;
@@ -537,7 +584,7 @@ __device__ void emit_inplace(const StoreDev& st, const Entangler& P, double C, d
     if (live) {
       entry_key<W>(g, i, kx, kz);
       bool paired;
-      entry_values<W>(P, C, S, g, i, kx, kz, a, vo, vn, paired);
+      entry_values<W>(C, S, g, i, fl, a, vo, vn, paired);
       if (!(fl & kFHole)) st.c[(int64_t)off + g.arel[i]] = vo;
       if (ENERGY) {
         double ek, ekp;
@@ -553,7 +600,23 @@ __device__ void emit_inplace(const StoreDev& st, const Entangler& P, double C, d
       qx[w] = kx[w] ^ P.px[w];
       qz[w] = kz[w] ^ P.pz[w];
     }
-    put_rows<W, 0>(st, g, I, live && (fl & kFNew), valid ? (selfp ? s : s ^ 1) : -1, qx, qz, vn);
+    const bool has = live && (fl & kFNew);
+    const int d = selfp ? s : s ^ 1;
+    if (two) {   // the rows of put_rows, from ballots alone
+      const uint64_t hm = __ballot(has), m1 = __ballot(d);
+      const uint64_t hm0 = hm & ~m1, hm1 = hm & m1;
+      if (has) {
+        const int rank = of_slot(d, put0, put1) + (int)lanes_below(d ? hm1 : hm0);
+        const int hd = of_slot(d, nh0, nh1);
+        int row = of_slot(d, end0, end1) + (rank - hd);
+        if (rank < hd) row = of_slot(d, I.off0, I.off1) + g.tab[of_slot(d, 0, nh0) + rank];
+        store_key<W>(st, row, qx, qz, vn);
+      }
+      put0 += (int)__popcll(hm0);
+      put1 += (int)__popcll(hm1);
+    } else {
+      put_rows<W, 0>(st, g, I, has, valid ? d : -1, qx, qz, vn);
+    }
   }
   wave_sync();
 }
@@ -569,8 +632,7 @@ __device__ void emit_inplace(const StoreDev& st, const Entangler& P, double C, d
 // Reads are at rows >= fin and writes below fin, so no row is read after it
 // is overwritten.
 template <int W>
-__device__ void refill(const StoreDev& st, const Entangler& P, double C, double S, const Seg<W>& g,
-                       const Item& I, int n) {
+__device__ void refill(const StoreDev& st, double C, double S, const Seg<W>& g, const Item& I, int n) {
   const int lane = threadIdx.x & 63;
   // lane s: the length of slot s's window and the slot's stash range
   // (the stash is slot-major: aslot is non-decreasing)
@@ -590,7 +652,7 @@ __device__ void refill(const StoreDev& st, const Entangler& P, double C, double 
   }
   const int incl = wave_incl_scan(len);
   const int pre = incl - len;
-  const int total = __shfl(incl, 63, 64);
+  const int total = __builtin_amdgcn_readlane(incl, 63);
   wave_sync();
   for (int f0 = 0; f0 < total; f0 += 64) {
     const int f = f0 + lane;
@@ -633,7 +695,7 @@ __device__ void refill(const StoreDev& st, const Entangler& P, double C, double 
         entry_key<W>(g, a0, kx, kz);
         double a, vn;
         bool paired;
-        entry_values<W>(P, C, S, g, a0, kx, kz, a, c, vn, paired);
+        entry_values<W>(C, S, g, a0, g.aflag[a0], a, c, vn, paired);
       } else {
         load_key<W>(st, (int64_t)off + r, kx, kz, c);
       }
@@ -654,7 +716,7 @@ __device__ bool relocate_item(const StoreDev& st, const Entangler& P, const Inpl
   const int cp = __shfl(I.cnt, selfp ? lane : (lane ^ 1), 64);
   const int need = lane < I.nslots ? ((I.cnt + cp + 15) & ~15) : 0;
   const int incl = wave_incl_scan(need);
-  const int total = __shfl(incl, 63, 64);
+  const int total = __builtin_amdgcn_readlane(incl, 63);
   unsigned long long base = 0;
   if (lane == 0) base = atomicAdd((unsigned long long*)st.top, (unsigned long long)total);
   base = wave_bcast0(base);
@@ -697,7 +759,7 @@ __device__ bool relocate_item(const StoreDev& st, const Entangler& P, const Inpl
         bool paired = true;
         if (valid) {
           entry_key<W>(g, i, kx, kz);
-          entry_values<W>(P, cfg.C, cfg.S, g, i, kx, kz, a, vo, vn, paired);
+          entry_values<W>(cfg.C, cfg.S, g, i, g.aflag[i], a, vo, vn, paired);
         }
         const bool keep_own = valid && !(fabs(vo) < cfg.eps);
         const bool keep_new = valid && !paired && !(fabs(vn) < cfg.eps);
@@ -775,30 +837,25 @@ __device__ void process_item(const StoreDev& st, const Entangler& P, const Inpla
     issue_slices<W, kIPU>(st, In, 0, S);
   }
   wc.anti += nanti;
-  if (nst > g.cap) {
-    relocate_item<W, ENERGY>(st, P, cfg, lut, g, I, G.selfp, nanti, eacc, wc);
-    return;
-  }
-  item_join<W>(P, g, nst);
-  count_outputs<W>(P, cfg.C, cfg.S, cfg.eps, g, nst, G.selfp);
+  bool fits = nst <= g.cap;
   int nn = 0, nh = 0;
-  bool fits = true;
-  if (lane < I.nslots) {
-    nn = g.s_nnew[lane];
-    nh = g.s_nhole[lane];
-    fits = I.cnt + (nn > nh ? nn - nh : 0) <= I.room;
+  if (fits) {
+    item_join<W>(P, g, nst);
+    count_outputs<W>(cfg.C, cfg.S, cfg.eps, g, I, nst, G.selfp, nn, nh);
+    fits = lane >= I.nslots || I.cnt + (nn > nh ? nn - nh : 0) <= I.room;
   }
   if (__ballot(!fits)) {
     relocate_item<W, ENERGY>(st, P, cfg, lut, g, I, G.selfp, nanti, eacc, wc);
     return;
   }
   const int freed = list_holes<W>(g, I, nst);
-  emit_inplace<W, ENERGY>(st, P, cfg.C, cfg.S, cfg.delta, lut, g, I, nst, G.selfp, eacc);
-  if (__ballot(nh > nn)) refill<W>(st, P, cfg.C, cfg.S, g, I, nst);
+  emit_inplace<W, ENERGY>(st, P, cfg.C, cfg.S, cfg.delta, lut, g, I, nst, G.selfp, nh, eacc);
+  if (__ballot(nh > nn)) refill<W>(st, cfg.C, cfg.S, g, I, nst);
   if (lane < I.nslots) st.cnt[I.b] = I.cnt + nn - nh;
-  wc.delta += wave_sum(nn - nh);
-  wc.fresh += wave_sum(nn);
-  wc.freed += __builtin_amdgcn_readfirstlane(freed);
+  const int fresh = wave_sum(nn);
+  wc.delta += fresh - freed;
+  wc.fresh += fresh;
+  wc.freed += freed;
 }
 
 template <int W, bool ENERGY>
