@@ -338,25 +338,30 @@ void launch_energy(int W, int nq, const StoreDev& st, int n_cu, int per_cu, size
 // non-finite coefficient or angle, |c| >= 2^31, or 2^24 terms writes NaN.
 //
 // Work split: a team of TW waves takes 64 TW terms at a time.  Each wave makes
-// v, its digits and, by a 64 x 64 bit transposition in registers, the bits of
-// 64 terms per qubit; after a barrier each wave multiplies the bits of "its"
-// 32 qubits with the digits of the team's terms (of half of them for one-word
-// keys).  The 32 terms of one matrix product may come in any order as long as
-// bits and digits agree, so a dword of the bit operand is (bits >> s) &
-// 0x01010101 -- terms s, s + 8, s + 16, s + 24 -- and a term's digits are
-// stored at the byte that this order gives it.
+// v and its digits, and writes the bytes of its 64 terms' keys to LDS by byte
+// and term (the four bytes of a dword change places within four lanes first);
+// after a barrier each wave multiplies the bits of "its" 32 qubits with the
+// digits of the team's terms (of half of them for one-word keys).  A dword read
+// back holds one byte of four terms' keys, so the lane of qubit q has its bit
+// operand as (dword >> (q & 7)) & 0x01010101, and the eight lanes of a byte
+// read the same address.  (With the keys transposed bit by bit in registers,
+// 130 instructions per 64 terms against 40, 4e6 two-word terms took 108 us.)
 //
 // A workgroup holds three teams (one for wide keys), one wave of each per SIMD,
 // and a team has a barrier of its own, so that one team's matrix products run
-// beside another's vector work (4e6 two-word terms: four teams of 128 registers
-// 117 us, spilling; three 113 us; a workgroup per team with a 3-qubit table 131
-// us; the workgroup's barrier in place of the teams' 117 us).
+// beside another's vector work (4e6 two-word terms: four teams of 128 registers,
+// some of them in memory, 109 us; three 94 us; a workgroup's barrier in place of
+// the teams' and a workgroup per team were 4 % and 16 % slower).  A wave
+// arrives at a barrier as soon as its part is done and waits only before it
+// needs the others': it makes the next terms' products between the end of its
+// matrix products and the wait for the team's, and loads terms between its
+// writes and the wait for the team's (one wait at each arrival: 101 us).
 //
-// Bound: VALU issue (about 590 instructions per 64 two-word terms: 128 for the
-// product, 190 for digits and transposition, 216 for the bit operands), and 24
-// matrix products of 32 cycles.  4e6 two-word terms: 112 us; the former kernel,
-// which added every (term, group) value to integer tables in LDS with two
-// 64-bit atomics, took 203 us.  1.1e6 one-word terms: 27 us (67 us).
+// Bound: VALU issue (about 510 instructions per 64 two-word terms: 128 for the
+// product, 100 for digits and bytes, 160 for the bit operands) and the waits of
+// three waves per SIMD; 24 matrix products of 32 cycles run beside.  4e6
+// two-word terms: 94 us; with every (term, group) value added to integer tables
+// in LDS by two 64-bit atomics 203 us.  1.1e6 one-word terms: 26 us (67 us).
 // acc layout: [3 * nq][workgroups] with sigma order X, Z, Y.
 // ---------------------------------------------------------------------------
 template <int W>
@@ -381,7 +386,7 @@ struct BwdShared {
   using B = BwdGeom<W>;
   double lut[T::kEntries];                            // afterwards the digit sums
   double fac[64 * W * 4];
-  uint64_t bits[2][B::kTeams][B::kTeamWaves][64 * W];   // x, z: 64 terms per qubit
+  alignas(16) uint8_t bytes[2][B::kTeams][B::kTeamWaves][8 * W * 64];   // x, z: byte of the key, term
   alignas(16) uint8_t dig[B::kTeams][B::kTeamWaves][kDigits * kDigitStride];
   int64_t s_off[kBwdGroup];
   uint32_t s_pre[kBwdGroup + 1];
@@ -389,8 +394,8 @@ struct BwdShared {
   uint64_t scan_tmp[B::kThreads / 64];
   unsigned arrived[B::kTeams];
   int bad;
-  static_assert(sizeof(bits) + sizeof(dig) >= sizeof(double) * T::kBuild, "the table is built there");
-  static_assert(sizeof(lut) + sizeof(fac) + sizeof(bits) + sizeof(dig) >= sizeof(int) * 96 * B::kBlocks * kDigits,
+  static_assert(sizeof(bytes) + sizeof(dig) >= sizeof(double) * T::kBuild, "the table is built there");
+  static_assert(sizeof(lut) + sizeof(fac) + sizeof(bytes) + sizeof(dig) >= sizeof(int) * 96 * B::kBlocks * kDigits,
                 "the digit sums fit");
 };
 
@@ -401,61 +406,22 @@ __device__ __forceinline__ int64_t bwd_active(int64_t total, int64_t buckets, in
   return a > buckets ? buckets : a;
 }
 
-// Transposition of the 64 x 64 bit matrix of a wave: lane l holds row l in
-// (lo, hi) and afterwards bit l of every lane's row, lane order.  Step s swaps
-// the bits with index bit s set in lanes without it against those without it
-// in lanes with it.
-__device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b) {   // one v_bfi_b32
-  return b ^ (m & (a ^ b));
+// Bytes of dword d (4 rows of 64 bytes, one byte per term) of every lane's key:
+// the 4 x 4 bytes of four lanes are transposed, and each lane writes the dword
+// of its row.  sel1, sel2: the lane's byte selectors (see byte_selectors).
+__device__ __forceinline__ void put_bytes(uint8_t* rows, int lane, uint32_t a, uint32_t sel1, uint32_t sel2) {
+  uint32_t t = (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0xB1, 0xF, 0xF, false);   // quad_perm 1,0,3,2
+  a = __builtin_amdgcn_perm(t, a, sel1);
+  t = (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0x4E, 0xF, 0xF, false);            // quad_perm 2,3,0,1
+  a = __builtin_amdgcn_perm(t, a, sel2);
+  *reinterpret_cast<uint32_t*>(rows + (lane & 3) * 64 + (lane & ~3)) = a;
 }
 
-// N rows of 32 bits per lane, one step for all of them at a time (lane moves
-// need wait states after the write of their source).
-template <int N>
-__device__ __forceinline__ void transpose32(uint32_t (&a)[N], int lane) {
-  uint32_t t[N];
-  const uint32_t p16 = (lane & 16) ? 0x07060302u : 0x05040100u;
-#pragma unroll
-  for (int i = 0; i < N; ++i) {   // 16: (own, other row's) and (other row's, own)
-    auto r = __builtin_amdgcn_permlane16_swap(a[i], a[i], false, false);
-    a[i] = r[0];
-    t[i] = r[1];
-  }
-#pragma unroll
-  for (int i = 0; i < N; ++i) a[i] = __builtin_amdgcn_perm(t[i], a[i], p16);
-  const uint32_t p8 = (lane & 8) ? 0x03070105u : 0x06020400u;
-#pragma unroll
-  for (int i = 0; i < N; ++i) t[i] = (uint32_t)__builtin_amdgcn_mov_dpp((int)a[i], 0x128, 0xF, 0xF, false);   // row_ror:8
-#pragma unroll
-  for (int i = 0; i < N; ++i) a[i] = __builtin_amdgcn_perm(t[i], a[i], p8);
-  // 4: row_shl:4 for the lanes without bit 2, row_shr:4 for the others
-#pragma unroll
-  for (int i = 0; i < N; ++i) t[i] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a[i], 0x104, 0xF, 0x5, false);
-#pragma unroll
-  for (int i = 0; i < N; ++i) t[i] = (uint32_t)__builtin_amdgcn_update_dpp((int)t[i], (int)a[i], 0x114, 0xF, 0xA, false);
-  const uint32_t r4 = (lane & 4) ? 4 : 28, m4 = (lane & 4) ? 0xF0F0F0F0u : 0x0F0F0F0Fu;
-#pragma unroll
-  for (int i = 0; i < N; ++i) a[i] = bit_select(m4, a[i], __builtin_amdgcn_alignbit(t[i], t[i], r4));
-  const uint32_t r2 = (lane & 2) ? 2 : 30, m2 = (lane & 2) ? 0xCCCCCCCCu : 0x33333333u;
-#pragma unroll
-  for (int i = 0; i < N; ++i) t[i] = (uint32_t)__builtin_amdgcn_mov_dpp((int)a[i], 0x4E, 0xF, 0xF, false);   // quad_perm 2,3,0,1
-#pragma unroll
-  for (int i = 0; i < N; ++i) a[i] = bit_select(m2, a[i], __builtin_amdgcn_alignbit(t[i], t[i], r2));
-  const uint32_t r1 = (lane & 1) ? 1 : 31, m1 = (lane & 1) ? 0xAAAAAAAAu : 0x55555555u;
-#pragma unroll
-  for (int i = 0; i < N; ++i) t[i] = (uint32_t)__builtin_amdgcn_mov_dpp((int)a[i], 0xB1, 0xF, 0xF, false);   // quad_perm 1,0,3,2
-#pragma unroll
-  for (int i = 0; i < N; ++i) a[i] = bit_select(m1, a[i], __builtin_amdgcn_alignbit(t[i], t[i], r1));
-}
-
-// The 64 x 64 bits of x and of z (word w) of the wave's lanes, transposed in place.
-__device__ __forceinline__ void transpose64(uint64_t& x, uint64_t& z, int lane) {
-  auto rx = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)(x >> 32), false, false);
-  auto rz = __builtin_amdgcn_permlane32_swap((uint32_t)z, (uint32_t)(z >> 32), false, false);
-  uint32_t r[4] = {rx[0], rx[1], rz[0], rz[1]};
-  transpose32<4>(r, lane);
-  x = (uint64_t)r[0] | ((uint64_t)r[1] << 32);
-  z = (uint64_t)r[2] | ((uint64_t)r[3] << 32);
+// Step 1 takes the even (odd) bytes of the even (odd) lane, step 2 the low
+// (high) halves of the lanes with bit 1 clear (set).
+__device__ __forceinline__ void byte_selectors(int lane, uint32_t& sel1, uint32_t& sel2) {
+  sel1 = (lane & 1) ? 0x03070105u : 0x06020400u;
+  sel2 = (lane & 2) ? 0x03020706u : 0x05040100u;
 }
 
 // Digits of v (|v| < 2^31) into the wave's digit rows, at this lane's term.
@@ -477,7 +443,7 @@ __device__ __forceinline__ void put_digits(uint8_t* dig, int lane, double v) {
   const int d0 = (p * 293) >> 11;   // p / 7, at most 23
   int64_t m = (int64_t)(mant << (p - 7 * d0));
   m = (int64_t)u < 0 ? -m : m;      // two's complement: the last digit carries the sign
-  uint8_t* at = dig + d0 * kDigitStride + (lane & 32) + ((lane >> 2) & 1) * 16 + (lane & 3) * 4 + ((lane >> 3) & 3);
+  uint8_t* at = dig + d0 * kDigitStride + lane;
   const uint32_t lo = (uint32_t)m, hi = (uint32_t)((uint64_t)m >> 32);
 #pragma unroll
   for (int j = 0; j < 4; ++j) at[j * kDigitStride] = (uint8_t)__builtin_amdgcn_ubfe(lo, 7 * j, 7);
@@ -487,14 +453,18 @@ __device__ __forceinline__ void put_digits(uint8_t* dig, int lane, double v) {
   at[8 * kDigitStride] = (uint8_t)(hi >> 24);
 }
 
-// Barrier of one team's `waves` waves: an arrival counter in LDS that only
-// grows (`target` is the wave's own count of what it has to reach).  All waves
-// of a workgroup are resident, and every wave of a team passes the same
-// barriers, so each wait ends.
-__device__ __forceinline__ void team_barrier(unsigned* arrived, unsigned& target, unsigned waves) {
+// Barrier of one team's `waves` waves, in two halves, between which a wave does
+// what needs no other wave: an arrival counter in LDS that only grows (`target`
+// is the wave's own count of what it has to reach).  All waves of a workgroup
+// are resident, and every wave of a team passes the same barriers in the same
+// order, so each wait ends.
+__device__ __forceinline__ void team_arrive(unsigned* arrived, unsigned& target, unsigned waves) {
   target += waves;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // this wave's LDS accesses are done
   if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+__device__ __forceinline__ void team_wait(const unsigned* arrived, unsigned target) {
   while ((int)(target - __hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) > 0)
     __builtin_amdgcn_s_sleep(1);
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -515,7 +485,7 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int team = wave / TW, tw = wave % TW, block = tw % NB, part = tw / NB;
   // factors, their null masks, and the table of the factors without the null ones
-  double* tmp = reinterpret_cast<double*>(sh.bits);
+  double* tmp = reinterpret_cast<double*>(sh.bytes);
   if (threadIdx.x == 0) sh.bad = 0;
   if (threadIdx.x < BG::kTeams) sh.arrived[threadIdx.x] = 0u;
   unsigned target = 0;
@@ -536,6 +506,8 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
   }
   const bool any_null = __syncthreads_or(null_here) != 0;
   build_energy_table<W, NT>(sh.lut, tmp);
+  uint32_t sel1, sel2;
+  byte_selectors(lane, sel1, sel2);
   const double scale = dE ? *dE : 1.0;
   bool ok = true;   // every coefficient finite and below 2^31 in magnitude
   int64_t nwg = 0;   // terms of the workgroup
@@ -544,7 +516,7 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
   for (int i = 0; i < 16; ++i) sx[i] = sz[i] = sy[i] = 0;
   // Workgroup g takes the groups of G consecutive buckets g, g + active, ...;
   // a group's rows are one flat range, one term per thread and pass, the next
-  // pass's term loaded while this one is processed.
+  // pass's term loaded while this one's bits are multiplied.
   int64_t G = (B + active - 1) / active;
   G = G > kBwdGroup ? kBwdGroup : G;
   const int64_t ngroups = (B + G - 1) / G;
@@ -566,43 +538,39 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
     const bool contig = __syncthreads_and(!mine || off - (int64_t)ex == base) != 0;
     const uint32_t n = (uint32_t)total;
     nwg += n;
-    uint64_t nx[W], nz[W];
-    double nc;
-    int64_t nrow;
+    uint64_t kx[W], kz[W];
+    double c;
+    int64_t row;
     auto load = [&](uint32_t i) {
-      nc = 0.0;
-      nrow = 0;
+      c = 0.0;
+      row = 0;
 #pragma unroll
-      for (int w = 0; w < W; ++w) nx[w] = nz[w] = 0;
+      for (int w = 0; w < W; ++w) kx[w] = kz[w] = 0;
       if (i < n) {
-        nrow = base + i;
+        row = base + i;
         if (!contig) {
           int lo = 0;   // the last bucket of the group whose first row is <= i
 #pragma unroll
           for (int step = kBwdGroup / 2; step; step >>= 1)
             if (sh.s_pre[lo + step] <= i) lo += step;
-          nrow = sh.s_off[lo] + (i - sh.s_pre[lo]);
+          row = sh.s_off[lo] + (i - sh.s_pre[lo]);
         }
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-          nx[w] = __builtin_nontemporal_load(&st.x[w * st.cap + nrow]);
-          nz[w] = __builtin_nontemporal_load(&st.z[w * st.cap + nrow]);
+          kx[w] = __builtin_nontemporal_load(&st.x[w * st.cap + row]);
+          kz[w] = __builtin_nontemporal_load(&st.z[w * st.cap + row]);
         }
-        nc = __builtin_nontemporal_load(&st.c[nrow]);
+        c = __builtin_nontemporal_load(&st.c[row]);
       }
     };
     load(threadIdx.x);
     for (uint32_t i0 = 0; i0 < n; i0 += NT) {
-      uint64_t kx[W], kz[W];
-#pragma unroll
-      for (int w = 0; w < W; ++w) { kx[w] = nx[w]; kz[w] = nz[w]; }
-      const double c = nc;
-      const int64_t row = nrow;
       const bool live = i0 + threadIdx.x < n;
-      load(i0 + NT + threadIdx.x);
-      if (i0 + 64 * wave < n) {   // the wave has terms
-        const double pk = expect_table<W>(sh.lut, kx, kz);
-        double v = c * pk, all = pk;
+      const bool has_terms = i0 + 64 * wave < n;   // of the wave
+      double v = 0.0, all = 1.0;
+      if (has_terms) {
+        all = expect_table<W>(sh.lut, kx, kz);
+        v = c * all;
         if (any_null) {
           uint64_t nm[W];
           int nn = 0;
@@ -627,31 +595,37 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
         }
         ok = ok && fabs(c) < 0x1p31;
         if (lam && live) lam[row] = scale * all;
+      }
+      team_wait(&sh.arrived[team], target);   // the team has read the last pass's digits
+      if (has_terms) {
         put_digits(sh.dig[team][tw], lane, fabs(v) < 0x1p31 ? v : 0.0);   // (c = 0 past the last row)
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-          transpose64(kx[w], kz[w], lane);
-          sh.bits[0][team][tw][64 * w + lane] = kx[w];
-          sh.bits[1][team][tw][64 * w + lane] = kz[w];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            put_bytes(sh.bytes[0][team][tw] + (2 * w + h) * 256, lane, (uint32_t)(kx[w] >> (32 * h)), sel1, sel2);
+            put_bytes(sh.bytes[1][team][tw] + (2 * w + h) * 256, lane, (uint32_t)(kz[w] >> (32 * h)), sel1, sel2);
+          }
         }
       }
-      team_barrier(&sh.arrived[team], target, TW);
+      team_arrive(&sh.arrived[team], target, TW);
+      load(i0 + NT + threadIdx.x);
+      team_wait(&sh.arrived[team], target);
 #pragma unroll 1
       for (int p = part; p < TW; p += BG::kSplit) {
         if (i0 + 64 * (team * TW + p) >= n) break;
-        const uint64_t xm = sh.bits[0][team][p][32 * block + (lane & 31)];
-        const uint64_t zm = sh.bits[1][team][p][32 * block + (lane & 31)];
+        const int at = (4 * block + ((lane >> 3) & 3)) * 64 + (lane >> 5) * 16;
         const uint8_t* dg = sh.dig[team][p] + (lane & 31) * kDigitStride + (lane >> 5) * 16;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
+          const v4i bx = *reinterpret_cast<const v4i*>(sh.bytes[0][team][p] + at + 32 * kb);
+          const v4i bz = *reinterpret_cast<const v4i*>(sh.bytes[1][team][p] + at + 32 * kb);
           const v4i bd = *reinterpret_cast<const v4i*>(dg + 32 * kb);
-          const uint32_t xw = (uint32_t)(xm >> (32 * kb)) >> ((lane >> 5) * 4);
-          const uint32_t zw = (uint32_t)(zm >> (32 * kb)) >> ((lane >> 5) * 4);
           v4i ax, az, ay;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            ax[i] = (int)((xw >> i) & 0x01010101u);
-            az[i] = (int)((zw >> i) & 0x01010101u);
+            ax[i] = (int)(((uint32_t)bx[i] >> (lane & 7)) & 0x01010101u);
+            az[i] = (int)(((uint32_t)bz[i] >> (lane & 7)) & 0x01010101u);
             ay[i] = ax[i] & az[i];
           }
           sx = __builtin_amdgcn_mfma_i32_32x32x32_i8(ax, bd, sx, 0, 0, 0);
@@ -659,7 +633,7 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
           sy = __builtin_amdgcn_mfma_i32_32x32x32_i8(ay, bd, sy, 0, 0, 0);
         }
       }
-      team_barrier(&sh.arrived[team], target, TW);
+      team_arrive(&sh.arrived[team], target, TW);
     }
   }
   if (!ok) sh.bad = 1;
