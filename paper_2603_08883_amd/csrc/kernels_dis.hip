@@ -153,7 +153,7 @@ __device__ __forceinline__ void dis_pass(const StoreDev& st, DisShared<W>& sh, i
       // looked-up value until the candidate loop and spills
       asm volatile("" : "+v"(p0), "+v"(p1));
     }
-    cpk[r] = c * (p0 * p1);
+    cpk[r] = 0.5 * (c * (p0 * p1));   // (half: the signs below are +-2)
   }
   uint32_t next[NS];
 #pragma unroll
@@ -202,8 +202,9 @@ __device__ __forceinline__ void dis_pass(const StoreDev& st, DisShared<W>& sh, i
     double v = 0.0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      // +1 for n = 1, -1 for n = 3 (mod 4), else 0 as a factor: products by it are exact
-      uint32_t f = (((n[r] >> 1) << 31) | 0x3FF00000u) & (uint32_t)-(int)(n[r] & 1u);
+      // +2 for n = 1, -2 for n = 3 (mod 4), else a zero: the low bits of n are the
+      // sign and the top exponent bit of the factor, and products by it are exact
+      uint32_t f = n[r] << 30;
       if (ZERO) f = dead[r] ? 0u : f;
       v = fma(__hiloint2double((int)f, 0), prod[r], v);
     }
@@ -216,12 +217,14 @@ __device__ __forceinline__ void dis_pass(const StoreDev& st, DisShared<W>& sh, i
 // takes an equal run of them, so a range's terms are staged once for all the
 // candidates of the run and few terms or few candidates still fill the chip.
 //
-// Bound: VALU issue.  1e6 two-word terms x 1000 candidates of 10.8 support
-// qubits: 53 VALU instructions per 64 pairs (3 per support qubit, 2 per
-// touched slot, 11 for the sign and the sum), 1.68 ms; the former kernel (a
-// second lookup per qubit for the phase, 4 terms per lane, ranges of buckets
-// by tiles) took 2.38 ms plus 0.13 ms for the sum over ranges.  12,007 one-word
-// terms x 13,472 candidates: 1113 -> 196 us (its ranges held 307 of 2048
+// Bound: VALU issue, and LDS reads close behind.  1e6 two-word terms x 1000
+// candidates of 10.8 support qubits: 50 VALU instructions per 64 pairs (3 per
+// support qubit, 2 per touched slot, 7 for the sign and the sum) over four
+// SIMDs against 11 reads of 512 bytes through one LDS, 1.63 ms (1.68 with the
+// sign put together from +-1 and a mask); the former kernel (a second lookup
+// per qubit for the phase, 4 terms per lane, ranges of buckets by tiles) took
+// 2.38 ms plus 0.13 ms for the sum over ranges.  12,007 one-word terms x 13,472
+// candidates: 1113 -> 193 us (its ranges held 307 of 2048
 // terms).  233,001 terms x 5 candidates: 298 -> 22 us.
 template <int W>
 __global__ __launch_bounds__(kDisB, W <= 2 ? 3 : 2) void k_dis_batched(StoreDev st, int nq, const double* __restrict__ theta,
