@@ -80,20 +80,22 @@ void launch_finalize_sum(const double* partial, int n, const double* scale, doub
 // leave one workgroup per CU.
 //
 // The grid holds what the CUs keep resident (more workgroups would only build
-// more tables), and of it only as many workgroups take part ("active") as
-// there are passes of kEMinRows rows: below that a workgroup would spend its
-// time on its table and its arrival (17.1 us a call over the stores of a
-// 32-Hamiltonian batch with one workgroup per bucket, 12.3 us with this rule).
+// more tables), and of it one workgroup per kEMinRows rows of the store takes
+// part ("active"): with fewer rows a workgroup would spend its
+// time on its table and its arrival, with more on another round of bucket
+// searches and loads (a call over the stores of a 32-Hamiltonian batch: 17.1 us
+// with one workgroup per bucket, 10.4 with 512 rows, 10.3 with 1024, 11.5 with
+// 2048, 16 with stores below 16384 rows on one workgroup).
 // The active workgroups leave their sums in the finish slot; the last of them
 // to arrive adds them in a fixed order, so a call is one launch.
 //
 // Bound: HBM for large stores (40 bytes a two-word term), the chain of
 // latencies (bucket table, rows, table build, arrival) for small ones.
-// 1.6e7 two-word terms: 128 us, 5.0 TB/s (table, sums and reduction in three
+// 1.6e7 two-word terms: 122 us, 5.2 TB/s (table, sums and reduction in three
 // launches: 168 us); 361 terms: 6.6 us (23 us).
 // ---------------------------------------------------------------------------
 constexpr int kEItems = 4;
-constexpr int64_t kEMinRows = 2048;
+constexpr int64_t kEMinRows = 1024;
 constexpr int kNibbleEntries = 256;
 constexpr int kNibblesPerWord = 16;
 constexpr int kE4Block = 512;
@@ -111,7 +113,7 @@ struct EnergyTable {
 // workgroup's NT threads.
 template <int W, int NT>
 __device__ __forceinline__ void build_factors(double* fac, int nq, const double* theta, const double* phi) {
-  for (int q = threadIdx.x; q < 64 * W; q += NT) {
+  for (int q = NT - 1 - (int)threadIdx.x; q < 64 * W; q += NT) {   // the last threads: the first ones have buckets
     double st = 0.0, ct = 1.0, sp = 0.0, cp = 1.0;
     const bool live = q < nq;
     if (live) {
@@ -204,7 +206,7 @@ __global__ __launch_bounds__(kE4Block) void k_energy(StoreDev st, int nq, const 
   __shared__ uint64_t scan_tmp[kE4Block / 64];
   __shared__ int s_last;
   const int64_t B = 1ll << *st.m;
-  // at least kEMinRows rows per workgroup (one pass) where the store has them
+  // at least kEMinRows rows per workgroup where the store has them
   int64_t want = (*st.total + kEMinRows - 1) / kEMinRows;
   want = want < 1 ? 1 : (want > gridDim.x ? gridDim.x : want);
   int64_t G = (B + want - 1) / want;
@@ -212,6 +214,8 @@ __global__ __launch_bounds__(kE4Block) void k_energy(StoreDev st, int nq, const 
   const int64_t ngroups = (B + G - 1) / G;
   const unsigned active = ngroups < want ? (unsigned)ngroups : (unsigned)want;
   if (blockIdx.x >= active) return;
+  // (the factors' chain of loads and sines beside that of the bucket table)
+  build_factors<W, kE4Block>(tmp, nq, theta, phi);
   bool table = false;
   double acc = 0.0;
   for (int64_t grp = blockIdx.x; grp < ngroups; grp += active) {
@@ -260,8 +264,6 @@ __global__ __launch_bounds__(kE4Block) void k_energy(StoreDev st, int nq, const 
         }
       }
       if (!table) {   // built while the first rows are on their way
-        build_factors<W, kE4Block>(tmp, nq, theta, phi);
-        __syncthreads();
         build_energy_table<W, kE4Block>(lut, tmp);
         table = true;
       }
