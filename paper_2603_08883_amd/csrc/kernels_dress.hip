@@ -237,7 +237,9 @@ __device__ void emit_anti(const StoreDev& out, const Entangler& P, const Smem<W>
   for (int i = tid; i < sm.ts; i += kDB) sm.tab[i] = -1;
   for (int i = tid; i < n; i += kDB) sm.partner[i] = -1;
   __syncthreads();
-  // insert the members whose pivot bit is 0
+  // insert the members whose pivot bit is 0 (the list holds at most 2^14 entries:
+  // the index and, above it, the hash's high half, which rejects most other keys
+  // without reading them; -1 is empty)
   for (int i = tid; i < n; i += kDB) {
     uint64_t kx[W], kz[W];
 #pragma unroll
@@ -246,8 +248,10 @@ __device__ void emit_anti(const StoreDev& out, const Entangler& P, const Smem<W>
       kz[w] = sm.az[w * sm.cap + i];
     }
     if (pivot_of<W>(P, kx, kz)) continue;
-    uint32_t h = table_hash<W>(kx, kz) & tmask;
-    while (atomicCAS(&sm.tab[h], -1, i) != -1) h = (h + 1) & tmask;
+    const uint32_t hk = table_hash<W>(kx, kz);
+    const int e = (int)((hk & 0xFFFF0000u) | (uint32_t)i);
+    uint32_t h = hk & tmask;
+    while (atomicCAS(&sm.tab[h], -1, e) != -1) h = (h + 1) & tmask;
   }
   __syncthreads();
   // the members whose pivot bit is 1 look up K ^ P
@@ -259,18 +263,21 @@ __device__ void emit_anti(const StoreDev& out, const Entangler& P, const Smem<W>
       kz[w] = sm.az[w * sm.cap + i] ^ P.pz[w];
     }
     if (pivot_of<W>(P, kx, kz)) continue;  // pivot of K was 0: K is in the table itself
-    uint32_t h = table_hash<W>(kx, kz) & tmask;
+    const uint32_t hk = table_hash<W>(kx, kz);
+    uint32_t h = hk & tmask;
     for (;;) {
-      const int j = sm.tab[h];
-      if (j < 0) break;
-      bool eq = true;
+      const int e = sm.tab[h];
+      if (e == -1) break;
+      if ((((uint32_t)e ^ hk) & 0xFFFF0000u) == 0) {
+        const int j = e & 0xFFFF;
+        uint64_t diff = 0;
 #pragma unroll
-      for (int w = 0; w < W; ++w)
-        eq = eq && (sm.ax[w * sm.cap + j] == kx[w]) && (sm.az[w * sm.cap + j] == kz[w]);
-      if (eq) {
-        sm.partner[i] = (int16_t)j;
-        sm.partner[j] = (int16_t)i;
-        break;
+        for (int w = 0; w < W; ++w) diff |= (sm.ax[w * sm.cap + j] ^ kx[w]) | (sm.az[w * sm.cap + j] ^ kz[w]);
+        if (diff == 0) {
+          sm.partner[i] = (int16_t)j;
+          sm.partner[j] = (int16_t)i;
+          break;
+        }
       }
       h = (h + 1) & tmask;
     }
@@ -373,15 +380,12 @@ __device__ __forceinline__ int64_t pair_need(const StoreDev& in, int64_t pi, uin
   return f ? 2 * (n0 + in.cnt[b1]) : 2 * n0;
 }
 
-// Rows for every pair this workgroup owns (pi = first, first + stride, ...),
-// reserved with one atomic; returns the base (block-uniform) or -1 when the
-// arena is too small.
-__device__ int64_t reserve_rows(const StoreDev& in, const StoreDev& out, int64_t first,
-                                int64_t stride, int64_t npairs, uint32_t f, int thi,
+// Rows for the pairs p0 .. p1 - 1, reserved with one atomic; returns the base
+// (block-uniform) or -1 when the arena is too small.
+__device__ int64_t reserve_rows(const StoreDev& in, const StoreDev& out, int64_t p0, int64_t p1, uint32_t f, int thi,
                                 uint64_t* scan_tmp, int64_t* misc) {
   int64_t mine = 0;
-  const int64_t count = first < npairs ? (npairs - first + stride - 1) / stride : 0;
-  for (int64_t k = threadIdx.x; k < count; k += kDB) mine += pair_need(in, first + k * stride, f, thi);
+  for (int64_t pi = p0 + threadIdx.x; pi < p1; pi += kDB) mine += pair_need(in, pi, f, thi);
   uint64_t total;
   block_exclusive_scan_n<kDW>((uint64_t)mine, scan_tmp, total);
   if (threadIdx.x == 0) {
@@ -396,6 +400,49 @@ __device__ int64_t reserve_rows(const StoreDev& in, const StoreDev& out, int64_t
   const int64_t base = misc[5];
   __syncthreads();
   return base;
+}
+
+// The same rows without the atomic: the pairs lie in the arena in order, so the
+// base is what the pairs before p0 need.  A few thousand counts are read from
+// the L2 in less time than several hundred workgroups take turns at one counter
+// (up to 7 us for 512): a step from 250,000 one-word terms takes 17.7 us so and
+// 20.9 with the counter, from 4e6 (8192 pairs) 104.5 and 104.9.  `last`: this
+// workgroup owns the last pair and leaves the sum for the output's counter.
+constexpr int64_t kOrderedPairs = 8192;
+
+__device__ int64_t ordered_rows(const StoreDev& in, const StoreDev& out, int64_t p0, int64_t p1, bool last, uint32_t f,
+                                int thi, uint64_t* scan_tmp) {
+  int64_t before = 0, mine = 0;
+  for (int64_t pi = threadIdx.x; pi < p1; pi += kDB) {
+    const int64_t need = pair_need(in, pi, f, thi);
+    before += pi < p0 ? need : 0;
+    mine += pi < p0 ? 0 : need;
+  }
+  uint64_t sum_before, sum_mine;
+  block_exclusive_scan_n<kDW>((uint64_t)before, scan_tmp, sum_before);
+  block_exclusive_scan_n<kDW>((uint64_t)mine, scan_tmp, sum_mine);
+  const int64_t base = (int64_t)sum_before, end = base + (int64_t)sum_mine;
+  if (threadIdx.x == 0) {
+    if (last) __hip_atomic_store(out.top, end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (end > out.cap) atomicOr(out.err, 1);
+  }
+  return end > out.cap ? -1 : base;
+}
+
+// Rows of a pair's two buckets.
+struct PairHead {
+  int64_t n0 = 0, off0 = 0, n1 = 0, off1 = 0;
+};
+
+__device__ __forceinline__ PairHead pair_head(const StoreDev& in, int64_t pi, uint32_t f, int thi) {
+  uint32_t b0, b1;
+  pair_buckets(pi, f, thi, b0, b1);
+  PairHead h;
+  h.n0 = in.cnt[b0];
+  h.off0 = in.off[b0];
+  h.n1 = f ? in.cnt[b1] : 0;
+  h.off1 = f ? in.off[b1] : 0;
+  return h;
 }
 
 // Totals of one workgroup (of one unit of a batch).
@@ -419,17 +466,17 @@ __device__ __forceinline__ int64_t sum_fresh(const StepCounts& counts, uint64_t*
 // `base` is the first arena row reserved for it (-1: no room, write nothing).
 template <int W, bool ENERGY>
 __device__ void process_pair(const StoreDev& in, const StoreDev& out, const Entangler& P,
-                             const DressConfig& cfg, const Smem<W>& sm, int64_t pi, int m,
+                             const DressConfig& cfg, const Smem<W>& sm, int64_t pi, const PairHead& head, int m,
                              int split, uint32_t f, int thi, int64_t base, double& eacc,
                              StepCounts& counts) {
   const int tid = threadIdx.x;
   PairState ps;
   pair_buckets(pi, f, thi, ps.b0, ps.b1);
   ps.self = (f == 0);
-  ps.n0 = in.cnt[ps.b0];
-  ps.off0 = in.off[ps.b0];
-  ps.n1 = ps.self ? 0 : in.cnt[ps.b1];
-  ps.off1 = ps.self ? 0 : in.off[ps.b1];
+  ps.n0 = head.n0;
+  ps.off0 = head.off0;
+  ps.n1 = head.n1;
+  ps.off1 = head.off1;
   ps.ntot = ps.n0 + ps.n1;
   ps.bound0 = ps.self ? 2 * ps.n0 : ps.n0 + ps.n1;
   ps.bound1 = ps.self ? 0 : ps.n0 + ps.n1;
@@ -552,7 +599,10 @@ __device__ __forceinline__ void empty_step(const StoreDev& out, const DressConfi
 // the words the others left.  (Clearing the counters, the table and the energy
 // sum were launches of their own, 4.5 us each, and 4096 wavefronts added their
 // new keys at one address: 233,001 to 1.1e6 40-qubit terms 68 + 14 us a step,
-// now 30 us.)
+// now 25 us; 30 us with all workgroups at one counter for their rows, idle ones
+// among the arrivals and the bucket table read after that.)
+// Bound: the chain of one pair (bucket table, rows, join, stores), since a step
+// of these sizes gives a workgroup one or two.
 template <int W, bool ENERGY>
 __global__ __launch_bounds__(kDB) __attribute__((amdgpu_waves_per_eu(4))) void k_dress(StoreDev in, StoreDev out_g, Entangler P,
                                                DressConfig cfg) {
@@ -579,18 +629,27 @@ __global__ __launch_bounds__(kDB) __attribute__((amdgpu_waves_per_eu(4))) void k
   const int64_t npairs = f ? (1ll << (m - 1)) : (1ll << m);
   const int thi = f ? 31 - __clz(f) : 0;
   if (blockIdx.x == 0 && tid == 0) *out.m = m + split;
+  // workgroups without a pair take no part
+  const int64_t active = npairs < gridDim.x ? npairs : gridDim.x;
+  if (blockIdx.x >= active) return;
+  const int64_t p0 = npairs * blockIdx.x / active, p1 = npairs * (blockIdx.x + 1) / active;
+  PairHead head = pair_head(in, p0, f, thi);
   if (ENERGY)   // (the factors go where the terms will be)
     build_group_table<W, kDB>(sm.lut, sm.lut + W * kGroupsPerWord * kLutEntries, cfg.nq, cfg.theta, cfg.phi);
   double eacc = 0.0;
   StepCounts counts;
-  int64_t base = reserve_rows(in, out, blockIdx.x, gridDim.x, npairs, f, thi, sm.scan, sm.misc);
-  for (int64_t pi = blockIdx.x; pi < npairs; pi += gridDim.x) {
-    process_pair<W, ENERGY>(in, out, P, cfg, sm, pi, m, split, f, thi, base, eacc, counts);
-    if (base >= 0) base += pair_need(in, pi, f, thi);
+  int64_t base = npairs <= kOrderedPairs
+                     ? ordered_rows(in, out, p0, p1, blockIdx.x == active - 1, f, thi, sm.scan)
+                     : reserve_rows(in, out, p0, p1, f, thi, sm.scan, sm.misc);
+  for (int64_t pi = p0; pi < p1; ++pi) {
+    const PairHead next = pi + 1 < p1 ? pair_head(in, pi + 1, f, thi) : PairHead();
+    process_pair<W, ENERGY>(in, out, P, cfg, sm, pi, head, m, split, f, thi, base, eacc, counts);
+    if (base >= 0) base += 2 * (head.n0 + head.n1);
+    head = next;
   }
   const int64_t fresh = sum_fresh(counts, sm.scan);
   const double es = ENERGY ? block_sum_n<kDW>(eacc, sm.red) : 0.0;
-  const unsigned grid = gridDim.x;
+  const unsigned grid = (unsigned)active;
   if (tid < 64) {
     if (tid == 0) {
       finish_put(cfg.slot, blockIdx.x, __longlong_as_double(counts.produced));
@@ -603,27 +662,23 @@ __global__ __launch_bounds__(kDB) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
   __syncthreads();
   if (!sm.misc[0]) return;
-  uint64_t sum[3] = {0, 0, 0};
-  double e = 0.0;
-  for (unsigned i = tid; i < grid; i += kDB) {
+  // waves 0 to 3 take a field each, wave 4 the reservation and the error
+  const int wave = tid >> 6, lane = tid & 63;
+  if (wave < 3) {
+    int64_t v = 0;
+    for (unsigned i = lane; i < grid; i += 64) v += __double_as_longlong(finish_get(cfg.slot, wave * grid + i));
 #pragma unroll
-    for (unsigned k = 0; k < 3; ++k) sum[k] += (uint64_t)__double_as_longlong(finish_get(cfg.slot, k * grid + i));
-    if (ENERGY) e += finish_get(cfg.slot, 3 * grid + i);
-  }
+    for (int d = 32; d >= 1; d >>= 1) v += __shfl_down(v, d, 64);
+    if (lane == 0) *(wave == 0 ? out_g.total : wave == 1 ? &out_g.stats[0] : &out_g.stats[1]) = v;
+  } else if (ENERGY && wave == 3) {
+    double e = 0.0;
+    for (unsigned i = lane; i < grid; i += 64) e += finish_get(cfg.slot, 3 * grid + i);
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    uint64_t total;
-    block_exclusive_scan_n<kDW>(sum[k], sm.scan, total);
-    sum[k] = total;
-  }
-  if (ENERGY) e = block_sum_n<kDW>(e, sm.red);
-  if (tid == 0) {
-    *out_g.total = (int64_t)sum[0];
-    out_g.stats[0] = (int64_t)sum[1];
-    out_g.stats[1] = (int64_t)sum[2];
-    *out_g.top = __hip_atomic_exchange(out.top, (int64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *out_g.err = __hip_atomic_exchange(out.err, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (ENERGY) *cfg.energy_out = cfg.energy_in ? *cfg.energy_in + e : e;
+    for (int d = 32; d >= 1; d >>= 1) e += __shfl_down(e, d, 64);
+    if (lane == 0) *cfg.energy_out = cfg.energy_in ? *cfg.energy_in + e : e;
+  } else if (wave == 4 && lane < 2) {
+    if (lane == 0) *out_g.top = __hip_atomic_exchange(out.top, (int64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *out_g.err = __hip_atomic_exchange(out.err, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -727,11 +782,15 @@ __global__ __launch_bounds__(kDB) __attribute__((amdgpu_waves_per_eu(4))) void k
     c.S = s_item.S;
     const int64_t p0 = (unit - p.item_start) * cfg.unit_pairs;
     const int64_t p1 = p0 + cfg.unit_pairs < p.npairs ? p0 + cfg.unit_pairs : p.npairs;
-    int64_t base = reserve_rows(in, out, p0, 1, p1, p.f, p.thi, sm.scan, sm.misc);
+    PairHead head = pair_head(in, p0, p.f, p.thi);
+    int64_t base = reserve_rows(in, out, p0, p1, p.f, p.thi, sm.scan, sm.misc);
     StepCounts counts;
     for (int64_t pi = p0; pi < p1; ++pi) {
-      process_pair<W, false>(in, out, P, c, sm, pi, p.m, p.split, p.f, p.thi, base, eacc, counts);
-      if (base >= 0) base += pair_need(in, pi, p.f, p.thi);
+      // (wider keys leave no registers to load the next pair's entries ahead)
+      const PairHead next = W == 1 && pi + 1 < p1 ? pair_head(in, pi + 1, p.f, p.thi) : PairHead();
+      process_pair<W, false>(in, out, P, c, sm, pi, head, p.m, p.split, p.f, p.thi, base, eacc, counts);
+      if (base >= 0) base += 2 * (head.n0 + head.n1);
+      head = W == 1 || pi + 1 >= p1 ? next : pair_head(in, pi + 1, p.f, p.thi);
     }
     flush_counts(out, counts, sm.scan);
     __syncthreads();   // every thread is done with s_item before the next copy
