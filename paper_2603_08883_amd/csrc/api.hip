@@ -622,6 +622,13 @@ int iqcc_store_copy(iqcc_ctx* ctx, const iqcc_store* src, iqcc_store* dst, void*
   return IQCC_OK;
 }
 
+static int store_error(iqcc_ctx* ctx, int err) {
+  if (err & 1) return fail(ctx, IQCC_ERR_CAPACITY, "dressing output exceeded the store arena");
+  if (err & 2) return fail(ctx, IQCC_ERR_CAPACITY, "dressing output exceeded the bucket table");
+  if (err & 4) return fail(ctx, IQCC_ERR_CAPACITY, "bucket pair beyond the hash-round limit");
+  return IQCC_OK;
+}
+
 int iqcc_store_count(iqcc_ctx* ctx, const iqcc_store* st, int64_t* n, void* stream) {
   int rc = check_ctx(ctx);
   if (rc) return rc;
@@ -635,10 +642,7 @@ int iqcc_store_count(iqcc_ctx* ctx, const iqcc_store* st, int64_t* n, void* stre
   std::memcpy(&total, buf, 8);
   std::memcpy(&err, buf + 20, 4);
   *n = total;
-  if (err & 1) return fail(ctx, IQCC_ERR_CAPACITY, "dressing output exceeded the store arena");
-  if (err & 2) return fail(ctx, IQCC_ERR_CAPACITY, "dressing output exceeded the bucket table");
-  if (err & 4) return fail(ctx, IQCC_ERR_CAPACITY, "bucket pair beyond the hash-round limit");
-  return IQCC_OK;
+  return store_error(ctx, err);
 }
 
 int iqcc_store_stats(iqcc_ctx* ctx, const iqcc_store* st, int64_t* n_anti, int64_t* n_new,
@@ -1430,21 +1434,20 @@ int iqcc_truncate_top(iqcc_ctx* ctx, const iqcc_store* in, int64_t max_terms, iq
   if (out->d.cap < in->d.cap || out->d.mcap < in->d.mcap)
     return fail(ctx, IQCC_ERR_CAPACITY, "output store is smaller than the input store");
   hipStream_t s = as_stream(stream);
-  int64_t n = 0;
-  rc = iqcc_store_count(ctx, in, &n, stream);
-  if (rc) return rc;
   const int W = in->W;
   const int grid = (int)(ctx->n_cu * 4);
   SelState* ss = (SelState*)(ctx->sel_hist + kSelHist);
-  const int keep_all = n <= max_terms ? 1 : max_terms == 0 ? -1 : 0;
   DevBuf keys, kcount;
+  // (the output's rows and bucket counts are scratch until the copy)
+  launch_abs_select(in->d, ss, ctx->sel_hist, ctx->n_cu, max_terms, out->d, take_slot(ctx), s);
+  LAUNCH_CHECK(ctx);
+  SelState h{};
+  HIP_TRY(ctx, hipMemcpyAsync(&h, ss, sizeof(h), hipMemcpyDeviceToHost, s));
+  HIP_TRY(ctx, hipStreamSynchronize(s));
+  rc = store_error(ctx, h.err);
+  if (rc) return rc;
+  const int keep_all = h.n <= max_terms ? 1 : max_terms == 0 ? -1 : 0;
   if (keep_all == 0) {
-    // (the output's rows and bucket counts are scratch until the copy)
-    launch_abs_select(in->d, ss, ctx->sel_hist, ctx->n_cu, max_terms, out->d, take_slot(ctx), s);
-    LAUNCH_CHECK(ctx);
-    SelState h{};
-    HIP_TRY(ctx, hipMemcpyAsync(&h, ss, sizeof(h), hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
     if (!h.done) {
       launch_abs_select_rest(in->d, ss, ctx->sel_hist, ctx->n_cu, out->d, take_slot(ctx), s);
       LAUNCH_CHECK(ctx);

@@ -756,11 +756,14 @@ struct SelState {
   int64_t listed;                // |c| values listed by the finish in one launch
   int key_mode;                  // 1: keep only ties with canonical key <= kthr
   int done;                      // T, ties and need are settled
+  int64_t n;                     // live terms of the store
+  int err, skip;                 // its error flag; nothing selected
   uint64_t kthr[2 * kMaxWords];  // canonical key threshold among the ties
 };
 constexpr int kSelHist = 2048;   // digit counters, zero between passes
 // The need-th largest |c| of st: T, ties and need (ties to take) of ss, if done
-// is set then; else launch_abs_select_rest settles them.  tmp: a store at least
+// is set then; else launch_abs_select_rest settles them.  skip: the store is
+// invalid (err), or need is 0 or not below its n terms.  tmp: a store at least
 // as large, whose rows and bucket counts are scratch.
 void launch_abs_select(const StoreDev& st, SelState* ss, unsigned* hist, int n_cu, int64_t need, const StoreDev& tmp,
                        double* slot, hipStream_t s);

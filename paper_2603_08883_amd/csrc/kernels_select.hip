@@ -173,9 +173,21 @@ __device__ __forceinline__ void each_value(const uint64_t* val, const int64_t* c
 
 __device__ __forceinline__ uint64_t magnitude(uint64_t bits) { return bits & 0x7fffffffffffffffull; }
 
-// First digit over every live term.
+// First digit over every live term.  An invalid store, and one that needs no
+// selection (all or none of its terms stay), is left alone: skip stands for
+// the following passes and the host, which reads it with the result instead of
+// the count before (one synchronisation less).
 __global__ __launch_bounds__(kSelBlock) void k_abs_hist(StoreDev st, int shift, PickArgs a) {
   __shared__ unsigned h[kSelBins];
+  const int64_t n = *st.total;
+  const int err = *st.err;
+  const bool skip = err || n <= a.need || a.need == 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    a.ss->n = n;
+    a.ss->err = err;
+    a.ss->skip = skip;
+  }
+  if (skip) return;
   for (int i = threadIdx.x; i < kSelBins; i += kSelBlock) h[i] = 0;
   __syncthreads();
   each_value((const uint64_t*)st.c, st.cnt, st.off, *st.m,
@@ -191,6 +203,7 @@ __global__ __launch_bounds__(kSelBlock) void k_abs_hist(StoreDev st, int shift, 
 __global__ __launch_bounds__(kSelBlock) void k_abs_collect(StoreDev st, int shift, uint64_t* cand, int64_t* ncand,
                                                            PickArgs a) {
   __shared__ unsigned h[kSelBins];
+  if (a.ss->skip) return;
   for (int i = threadIdx.x; i < kSelBins; i += kSelBlock) h[i] = 0;
   __syncthreads();
   const uint64_t prefix = a.ss->prefix;
@@ -228,7 +241,7 @@ __global__ __launch_bounds__(kSelBlock) void k_cand_finish(StoreDev st, const ui
   __shared__ unsigned n_mine;
   __shared__ unsigned long long base;
   SelState* ss = a.ss;
-  if (ss->at > kSelList) return;   // the same in every workgroup
+  if (ss->skip || ss->at > kSelList) return;   // the same in every workgroup
   if (threadIdx.x == 0) n_mine = 0;
   __syncthreads();
   uint64_t prefix = ss->prefix;
