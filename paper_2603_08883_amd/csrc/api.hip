@@ -583,7 +583,7 @@ int iqcc_store_load(iqcc_ctx* ctx, iqcc_store* st, const uint64_t* x, const uint
     int64_t R = 0;
     inplace_geometry(ctx, st, m, R);
     const int64_t Bi = 1ll << m;
-    rc = ensure_scratch(ctx, 3 * Bi + Bi / 1024 + 16 + n);
+    rc = ensure_scratch(ctx, 2 * Bi + Bi / 1024 + 16 + n);
     if (rc) return rc;
     launch_store_load_regions(st->W, st->d, x, z, c, n, ld, m, R, ctx->scratch, s);
     LAUNCH_CHECK(ctx);
@@ -611,7 +611,7 @@ int iqcc_store_copy(iqcc_ctx* ctx, const iqcc_store* src, iqcc_store* dst, void*
   int64_t R = 0;
   inplace_geometry(ctx, dst, m, R);
   const int64_t B = 1ll << m;
-  rc = ensure_scratch(ctx, B + B / 1024 + 16);
+  rc = ensure_scratch(ctx, B / 1024 + 16);
   if (rc) return rc;
   launch_store_copy_regions(dst->W, src->d, dst->d, m, R, ctx->scratch, as_stream(stream),
                             src->regions && src->region_m == m);

@@ -20,33 +20,37 @@ void launch_zero_counters(StoreDev out, hipStream_t s) {
   hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, s, out);
 }
 
-__global__ void k_fill_i64(int64_t* p, int64_t n, int64_t v) {
+__global__ void k_clear_i64(int64_t* p, int64_t* q, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    p[i] = 0;
+    q[i] = 0;
+  }
 }
 
-static void fill_i64(int64_t* p, int64_t n, int64_t v, hipStream_t s) {
+static void clear_i64(int64_t* p, int64_t* q, int64_t n, hipStream_t s) {
   int64_t blocks = (n + kBlock - 1) / kBlock;
   if (blocks > 4096) blocks = 4096;
   if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(k_fill_i64, dim3((unsigned)blocks), dim3(kBlock), 0, s, p, n, v);
+  hipLaunchKernelGGL(k_clear_i64, dim3((unsigned)blocks), dim3(kBlock), 0, s, p, q, n);
 }
 
 // ---------------------------------------------------------------------------
-// Exclusive scan of int64 (three passes: block sums, scan of sums, apply).
+// Exclusive scan of int64: tile sums, what lies before each tile, the elements.
 // scratch: ceil(n/1024) + 1 int64.
 // ---------------------------------------------------------------------------
 constexpr int kScanItems = 4;
 constexpr int kScanTile = kBlock * kScanItems;
 
-__global__ void k_scan_blocksum(const int64_t* in, int64_t n, int64_t* sums) {
+// V: get(i) the value of element i; put(i, exclusive, value) stores its result.
+template <class V>
+__global__ __launch_bounds__(kBlock) void k_scan_blocksum(V v, int64_t n, int64_t* sums) {
   __shared__ uint64_t tmp[kWaves];
   const int64_t base = (int64_t)blockIdx.x * kScanTile;
   int64_t s = 0;
   for (int r = 0; r < kScanItems; ++r) {
     int64_t i = base + (int64_t)threadIdx.x * kScanItems + r;
-    if (i < n) s += in[i];
+    if (i < n) s += v.get(i);
   }
   uint64_t total;
   block_exclusive_scan((uint64_t)s, tmp, total);
@@ -71,32 +75,64 @@ __global__ void k_scan_sums(int64_t* sums, int64_t nb) {
   }
 }
 
-__global__ void k_scan_apply(const int64_t* in, int64_t* out, int64_t n, const int64_t* sums) {
+// SUMMED: sums holds what lies before each tile, else the tiles' own sums.
+template <class V, bool SUMMED>
+__global__ __launch_bounds__(kBlock) void k_scan_apply(V f, int64_t n, const int64_t* sums) {
   __shared__ uint64_t tmp[kWaves];
   const int64_t base = (int64_t)blockIdx.x * kScanTile;
+  int64_t before = 0;
+  if (SUMMED) {
+    before = sums[blockIdx.x];
+  } else if (blockIdx.x) {
+    int64_t part = 0;
+    for (unsigned b = threadIdx.x; b < blockIdx.x; b += kBlock) part += sums[b];
+    uint64_t total;
+    block_exclusive_scan((uint64_t)part, tmp, total);
+    before = (int64_t)total;
+  }
   int64_t v[kScanItems];
   int64_t s = 0;
   for (int r = 0; r < kScanItems; ++r) {
     int64_t i = base + (int64_t)threadIdx.x * kScanItems + r;
-    v[r] = i < n ? in[i] : 0;
+    v[r] = i < n ? f.get(i) : 0;
     s += v[r];
   }
   uint64_t total;
-  int64_t ex = (int64_t)block_exclusive_scan((uint64_t)s, tmp, total) + sums[blockIdx.x];
+  int64_t ex = (int64_t)block_exclusive_scan((uint64_t)s, tmp, total) + before;
   for (int r = 0; r < kScanItems; ++r) {
     int64_t i = base + (int64_t)threadIdx.x * kScanItems + r;
-    if (i < n) out[i] = ex;
+    if (i < n) f.put(i, ex, v[r]);
     ex += v[r];
   }
 }
 
+// One launch for one tile, two while a workgroup adds up the tiles before its
+// own in a read or a few (a launch less is 4 us; 1e6 elements), three above.
+constexpr int64_t kScanDirect = 1024;
+
+template <class V>
+static void launch_scan(const V& v, int64_t n, int64_t* scratch, hipStream_t s) {
+  if (n <= 0) return;
+  const int64_t nb = (n + kScanTile - 1) / kScanTile;
+  if (nb > 1) hipLaunchKernelGGL(k_scan_blocksum<V>, dim3((unsigned)nb), dim3(kBlock), 0, s, v, n, scratch);
+  if (nb > kScanDirect) {
+    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kBlock), 0, s, scratch, nb);
+    hipLaunchKernelGGL((k_scan_apply<V, true>), dim3((unsigned)nb), dim3(kBlock), 0, s, v, n, scratch);
+  } else {
+    hipLaunchKernelGGL((k_scan_apply<V, false>), dim3((unsigned)nb), dim3(kBlock), 0, s, v, n, scratch);
+  }
+}
+
+struct PlainScan {
+  const int64_t* in;
+  int64_t* out;
+  __device__ int64_t get(int64_t i) const { return in[i]; }
+  __device__ void put(int64_t i, int64_t ex, int64_t) const { out[i] = ex; }
+};
+
 void launch_scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* scratch,
                      hipStream_t s) {
-  if (n <= 0) return;
-  int64_t nb = (n + kScanTile - 1) / kScanTile;
-  hipLaunchKernelGGL(k_scan_blocksum, dim3((unsigned)nb), dim3(kBlock), 0, s, in, n, scratch);
-  hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kBlock), 0, s, scratch, nb);
-  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(kBlock), 0, s, in, out, n, scratch);
+  launch_scan(PlainScan{in, out}, n, scratch, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -308,14 +344,17 @@ static void load_place_rows(int W, StoreDev st, const uint64_t* x, const uint64_
 }
 
 // Loaded buckets are packed: each bucket's region is exactly its rows.
-__global__ void k_set_packed_lim(StoreDev st, int64_t B) {
-  for (int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; b < B;
-       b += (int64_t)gridDim.x * blockDim.x)
-    st.lim[b] = st.off[b] + st.cnt[b];
-}
-
-__global__ void k_load_finish(StoreDev st, int m, int64_t n) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
+// The scan that packs the buckets: off and lim of each (no room to grow), and
+// the store's counters from the last one.
+struct PackedScan {
+  StoreDev st;
+  int64_t B, n;
+  int m;
+  __device__ int64_t get(int64_t b) const { return st.cnt[b]; }
+  __device__ void put(int64_t b, int64_t ex, int64_t cnt) const {
+    st.off[b] = ex;
+    st.lim[b] = ex + cnt;
+    if (b != B - 1) return;
     *st.m = m;
     *st.total = n;
     *st.top = n;
@@ -323,7 +362,7 @@ __global__ void k_load_finish(StoreDev st, int m, int64_t n) {
     st.stats[0] = 0;
     st.stats[1] = 0;
   }
-}
+};
 
 // scratch: B + ceil(B/1024) + 16 + n int64 (fill, scan, slot lists).
 int launch_store_load(int W, StoreDev st, const uint64_t* x, const uint64_t* z, const double* c,
@@ -333,8 +372,7 @@ int launch_store_load(int W, StoreDev st, const uint64_t* x, const uint64_t* z, 
   int64_t* fill = scratch;                       // B
   int64_t* scan_tmp = scratch + B;               // ceil(B/1024)+1
   int64_t* slots = scratch + B + B / 1024 + 16;  // n
-  fill_i64(st.cnt, B, 0, s);
-  fill_i64(fill, B, 0, s);
+  clear_i64(st.cnt, fill, B, s);
   const LoadGrid lg = load_grid(n, B);
   if (n > 0) {
     switch (W) {
@@ -344,15 +382,9 @@ int launch_store_load(int W, StoreDev st, const uint64_t* x, const uint64_t* z, 
       default: hipLaunchKernelGGL(k_load_hist<4>, dim3(lg.blocks), dim3(kBlock), 0, s, x, z, n, ld, mask, st.cnt, lg.lds); break;
     }
   }
-  launch_scan_i64(st.cnt, st.off, B, scan_tmp, s);
+  launch_scan(PackedScan{st, B, n, m}, B, scan_tmp, s);
   // packed rows: the slot lists and the rows share their offsets
   load_place_rows(W, st, x, z, c, n, ld, mask, B, st.off, fill, slots, false, s);
-  {
-    int64_t lb = (B + kBlock - 1) / kBlock;
-    if (lb > 4096) lb = 4096;
-    hipLaunchKernelGGL(k_set_packed_lim, dim3((unsigned)lb), dim3(kBlock), 0, s, st, B);
-  }
-  hipLaunchKernelGGL(k_load_finish, dim3(1), dim3(64), 0, s, st, m, n);
   return 0;
 }
 
@@ -362,25 +394,22 @@ int launch_store_load(int W, StoreDev st, const uint64_t* x, const uint64_t* z, 
 // can grow after its live rows; the pool for buckets that outgrow their
 // region starts after the last region.
 // ---------------------------------------------------------------------------
-__global__ void k_region_sizes(const int64_t* cnt, int64_t B, int64_t R, int64_t* reg) {
-  for (int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; b < B;
-       b += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r = (2 * cnt[b] + 15) & ~(int64_t)15;
-    reg[b] = r > R ? r : R;
+// The scan that lays the regions out: off and lim of every bucket, and the
+// store's counters from the last one.  n >= 0: the live terms; n < 0: take them
+// (and an error flag) from src.
+struct RegionScan {
+  StoreDev st, src;
+  int64_t B, R, n;
+  int m;
+  __device__ int64_t get(int64_t b) const {
+    const int64_t r = (2 * st.cnt[b] + 15) & ~(int64_t)15;
+    return r > R ? r : R;
   }
-}
-
-__global__ void k_region_lim(StoreDev st, const int64_t* reg, int64_t B) {
-  for (int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; b < B;
-       b += (int64_t)gridDim.x * blockDim.x)
-    st.lim[b] = st.off[b] + reg[b];
-}
-
-// n >= 0: the live terms; n < 0: take them (and an error flag) from src.
-__global__ void k_regions_finish(StoreDev st, const int64_t* reg, int64_t B, int m, int64_t R, int64_t n,
-                                 StoreDev src) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    const int64_t end = st.off[B - 1] + reg[B - 1];
+  __device__ void put(int64_t b, int64_t ex, int64_t reg) const {
+    const int64_t end = ex + reg;
+    st.off[b] = ex;
+    st.lim[b] = end;
+    if (b != B - 1) return;
     const int serr = n < 0 ? *src.err : 0;
     *st.m = m;
     *st.total = n < 0 ? *src.total : n;
@@ -394,31 +423,24 @@ __global__ void k_regions_finish(StoreDev st, const int64_t* reg, int64_t B, int
     st.aux[3] = 0;
     st.aux[4] = 0;
   }
-}
+};
 
 static void regions_from_counts(StoreDev st, int64_t B, int m, int64_t R, int64_t n, const StoreDev& src,
-                                int64_t* reg, int64_t* scan_tmp, hipStream_t s) {
-  int64_t lb = (B + kBlock - 1) / kBlock;
-  if (lb > 4096) lb = 4096;
-  hipLaunchKernelGGL(k_region_sizes, dim3((unsigned)lb), dim3(kBlock), 0, s, st.cnt, B, R, reg);
-  launch_scan_i64(reg, st.off, B, scan_tmp, s);
-  hipLaunchKernelGGL(k_region_lim, dim3((unsigned)lb), dim3(kBlock), 0, s, st, reg, B);
-  hipLaunchKernelGGL(k_regions_finish, dim3(1), dim3(64), 0, s, st, reg, B, m, R, n, src);
+                                int64_t* scan_tmp, hipStream_t s) {
+  launch_scan(RegionScan{st, src, B, R, n, m}, B, scan_tmp, s);
 }
 
-// scratch: 3 B + ceil(B/1024) + 16 + n int64 (fill, region sizes, scan,
-// packed slot offsets, slot lists).
+// scratch: 2 B + ceil(B/1024) + 16 + n int64 (fill, scan, packed slot offsets,
+// slot lists).
 int launch_store_load_regions(int W, StoreDev st, const uint64_t* x, const uint64_t* z, const double* c,
                               int64_t n, int64_t ld, int m, int64_t R, int64_t* scratch, hipStream_t s) {
   const int64_t B = 1ll << m;
   const uint32_t mask = (uint32_t)(B - 1);
   int64_t* fill = scratch;                           // B
-  int64_t* reg = scratch + B;                        // B
-  int64_t* scan_tmp = scratch + 2 * B;               // ceil(B/1024)+1
-  int64_t* poff = scratch + 2 * B + B / 1024 + 16;   // B
+  int64_t* scan_tmp = scratch + B;                   // ceil(B/1024)+1
+  int64_t* poff = scratch + B + B / 1024 + 16;       // B
   int64_t* slots = poff + B;                         // n
-  fill_i64(st.cnt, B, 0, s);
-  fill_i64(fill, B, 0, s);
+  clear_i64(st.cnt, fill, B, s);
   const LoadGrid lg = load_grid(n, B);
   if (n > 0) {
     switch (W) {
@@ -428,7 +450,7 @@ int launch_store_load_regions(int W, StoreDev st, const uint64_t* x, const uint6
       default: hipLaunchKernelGGL(k_load_hist<4>, dim3(lg.blocks), dim3(kBlock), 0, s, x, z, n, ld, mask, st.cnt, lg.lds); break;
     }
   }
-  regions_from_counts(st, B, m, R, n, st, reg, scan_tmp, s);
+  regions_from_counts(st, B, m, R, n, st, scan_tmp, s);
   launch_scan_i64(st.cnt, poff, B, scan_tmp, s);
   load_place_rows(W, st, x, z, c, n, ld, mask, B, poff, fill, slots, true, s);
   return 0;
@@ -603,13 +625,12 @@ __global__ void k_copy_rows_same(StoreDev src, StoreDev dst, int64_t B) {
 void launch_store_copy_regions(int W, const StoreDev& src, StoreDev dst, int m, int64_t R, int64_t* scratch,
                                hipStream_t s, bool same_m) {
   const int64_t B = 1ll << m;
-  int64_t* reg = scratch;               // B
-  int64_t* scan_tmp = scratch + B;      // ceil(B/1024)+1
+  int64_t* scan_tmp = scratch;          // ceil(B/1024)+1
   if (same_m) {
     int64_t lb = (B + kBlock - 1) / kBlock;
     if (lb > 4096) lb = 4096;
     hipLaunchKernelGGL(k_copy_counts_same, dim3((unsigned)lb), dim3(kBlock), 0, s, src, dst, B);
-    regions_from_counts(dst, B, m, R, -1, src, reg, scan_tmp, s);
+    regions_from_counts(dst, B, m, R, -1, src, scan_tmp, s);
     int64_t wb = (B / 64 + kWaves - 1) / kWaves;
     if (wb < 1) wb = 1;
     if (wb > 8192) wb = 8192;
@@ -629,7 +650,7 @@ void launch_store_copy_regions(int W, const StoreDev& src, StoreDev dst, int m, 
     case 3: hipLaunchKernelGGL((k_copy_regions<3, true>), dim3(blocks), dim3(kBlock), 0, s, src, dst, m); break;
     default: hipLaunchKernelGGL((k_copy_regions<4, true>), dim3(blocks), dim3(kBlock), 0, s, src, dst, m); break;
   }
-  regions_from_counts(dst, B, m, R, -1, src, reg, scan_tmp, s);
+  regions_from_counts(dst, B, m, R, -1, src, scan_tmp, s);
   switch (W) {
     case 1: hipLaunchKernelGGL((k_copy_regions<1, false>), dim3(blocks), dim3(kBlock), 0, s, src, dst, m); break;
     case 2: hipLaunchKernelGGL((k_copy_regions<2, false>), dim3(blocks), dim3(kBlock), 0, s, src, dst, m); break;
