@@ -62,7 +62,7 @@ void launch_finalize_sum(const double* partial, int n, const double* scale, doub
 
 // ---------------------------------------------------------------------------
 // Energy of a store in one launch.  Workgroup g takes the groups of G
-// consecutive buckets g, g + grid, ... (G = 1 .. 512 so that every workgroup
+// consecutive buckets g, g + grid, ... (G up to its threads, so that every workgroup
 // has a group); the rows of a group's buckets are streamed as one flat range,
 // kEItems terms per thread and pass, so small buckets do not each cost a round
 // trip.
@@ -77,7 +77,7 @@ void launch_finalize_sum(const double* partial, int n, const double* scale, doub
 // whose 16 codes then lie next to each other, in different LDS banks (with
 // the x bits low they were 16 entries apart and met in two banks).  Wider keys:
 // 3-qubit groups, 22 per word and 64 entries each, because nibble tables would
-// leave one workgroup per CU.
+// leave few waves per CU.
 //
 // The grid holds what the CUs keep resident (more workgroups would only build
 // more tables), and of it one workgroup per kEMinRows rows of the store takes
@@ -91,18 +91,21 @@ void launch_finalize_sum(const double* partial, int n, const double* scale, doub
 //
 // Bound: HBM for large stores (40 bytes a two-word term), the chain of
 // latencies (bucket table, rows, table build, arrival) for small ones.
-// 1.6e7 two-word terms: 122 us, 5.2 TB/s (table, sums and reduction in three
+// 1.6e7 two-word terms: 119 us, 5.4 TB/s (table, sums and reduction in three
 // launches: 168 us); 361 terms: 6.6 us (23 us).
 // ---------------------------------------------------------------------------
 constexpr int kEItems = 4;
 constexpr int64_t kEMinRows = 1024;
 constexpr int kNibbleEntries = 256;
 constexpr int kNibblesPerWord = 16;
-constexpr int kE4Block = 512;
 
 template <int W>
 struct EnergyTable {
   static constexpr bool kNibble = W <= 2;
+  // of a workgroup of k_energy: a CU's LDS holds one table of two-word keys, so
+  // its workgroup has the waves of two (5.4e7 terms in bucket regions 552 us with
+  // 512 threads, 499 with 1024; 1.6e7 loaded terms 122 us, 119)
+  static constexpr int kThreads = W == 2 ? 1024 : 512;
   static constexpr int kEntries = kNibble ? W * kNibblesPerWord * kNibbleEntries : W * kGroupsPerWord * kLutEntries;
   // scratch of the build: the qubits' factors and, for nibbles, the products
   // of the two qubits of every even/odd pair
@@ -190,32 +193,32 @@ __device__ __forceinline__ double expect_table(const double* lut, const uint64_t
 template <int W>
 size_t energy_lds_bytes() {
   // table, its build's scratch, first rows and row prefix sums of a group
-  return (size_t)(EnergyTable<W>::kEntries + EnergyTable<W>::kBuild) * 8 + (size_t)kE4Block * 8 +
-         (size_t)(kE4Block + 1) * 4;
+  return (size_t)(EnergyTable<W>::kEntries + EnergyTable<W>::kBuild) * 8 + (size_t)EnergyTable<W>::kThreads * 8 +
+         (size_t)(EnergyTable<W>::kThreads + 1) * 4;
 }
 
 template <int W>
-__global__ __launch_bounds__(kE4Block) void k_energy(StoreDev st, int nq, const double* theta, const double* phi,
+__global__ __launch_bounds__(EnergyTable<W>::kThreads) void k_energy(StoreDev st, int nq, const double* theta, const double* phi,
                                                      double* slot, double* out) {
   extern __shared__ __align__(16) unsigned char smem_en[];
   double* lut = (double*)smem_en;
   double* tmp = lut + EnergyTable<W>::kEntries;                  // [kBuild]
-  int64_t* s_off = (int64_t*)(tmp + EnergyTable<W>::kBuild);     // [kE4Block]
-  uint32_t* s_pre = (uint32_t*)(s_off + kE4Block);               // [kE4Block + 1]
-  __shared__ double red[kE4Block / 64];
-  __shared__ uint64_t scan_tmp[kE4Block / 64];
+  int64_t* s_off = (int64_t*)(tmp + EnergyTable<W>::kBuild);     // [EnergyTable<W>::kThreads]
+  uint32_t* s_pre = (uint32_t*)(s_off + EnergyTable<W>::kThreads);               // [EnergyTable<W>::kThreads + 1]
+  __shared__ double red[EnergyTable<W>::kThreads / 64];
+  __shared__ uint64_t scan_tmp[EnergyTable<W>::kThreads / 64];
   __shared__ int s_last;
   const int64_t B = 1ll << *st.m;
   // at least kEMinRows rows per workgroup where the store has them
   int64_t want = (*st.total + kEMinRows - 1) / kEMinRows;
   want = want < 1 ? 1 : (want > gridDim.x ? gridDim.x : want);
   int64_t G = (B + want - 1) / want;
-  G = G > kE4Block ? kE4Block : G;
+  G = G > EnergyTable<W>::kThreads ? EnergyTable<W>::kThreads : G;
   const int64_t ngroups = (B + G - 1) / G;
   const unsigned active = ngroups < want ? (unsigned)ngroups : (unsigned)want;
   if (blockIdx.x >= active) return;
   // (the factors' chain of loads and sines beside that of the bucket table)
-  build_factors<W, kE4Block>(tmp, nq, theta, phi);
+  build_factors<W, EnergyTable<W>::kThreads>(tmp, nq, theta, phi);
   bool table = false;
   double acc = 0.0;
   for (int64_t grp = blockIdx.x; grp < ngroups; grp += active) {
@@ -225,10 +228,10 @@ __global__ __launch_bounds__(kE4Block) void k_energy(StoreDev st, int nq, const 
     const int64_t off = mine ? st.off[b] : 0;
     uint64_t total;
     // (the scan's barriers also order the previous group's reads of s_pre)
-    const uint64_t ex = block_exclusive_scan_n<kE4Block / 64>((uint64_t)cnt, scan_tmp, total);
+    const uint64_t ex = block_exclusive_scan_n<EnergyTable<W>::kThreads / 64>((uint64_t)cnt, scan_tmp, total);
     s_pre[threadIdx.x] = (uint32_t)ex;
     s_off[threadIdx.x] = off;
-    if (threadIdx.x == 0) s_pre[kE4Block] = (uint32_t)total;
+    if (threadIdx.x == 0) s_pre[EnergyTable<W>::kThreads] = (uint32_t)total;
     __syncthreads();
     // the group's rows are one range when every bucket starts where the one
     // before it ends (a loaded store); then row = base + i, the row the search
@@ -242,7 +245,7 @@ __global__ __launch_bounds__(kE4Block) void k_energy(StoreDev st, int nq, const 
       double kc[kEItems];
 #pragma unroll
       for (int r = 0; r < kEItems; ++r) {
-        const uint32_t i = i0 + r * kE4Block + threadIdx.x;
+        const uint32_t i = i0 + r * EnergyTable<W>::kThreads + threadIdx.x;
         kc[r] = 0.0;
 #pragma unroll
         for (int w = 0; w < W; ++w) kx[r][w] = kz[r][w] = 0;
@@ -251,7 +254,7 @@ __global__ __launch_bounds__(kE4Block) void k_energy(StoreDev st, int nq, const 
           if (!contig) {
             int lo = 0;   // the last bucket of the group whose first row is <= i
 #pragma unroll
-            for (int step = kE4Block / 2; step; step >>= 1)
+            for (int step = EnergyTable<W>::kThreads / 2; step; step >>= 1)
               if (s_pre[lo + step] <= i) lo += step;
             row = s_off[lo] + (i - s_pre[lo]);
           }
@@ -264,15 +267,15 @@ __global__ __launch_bounds__(kE4Block) void k_energy(StoreDev st, int nq, const 
         }
       }
       if (!table) {   // built while the first rows are on their way
-        build_energy_table<W, kE4Block>(lut, tmp);
+        build_energy_table<W, EnergyTable<W>::kThreads>(lut, tmp);
         table = true;
       }
 #pragma unroll
       for (int r = 0; r < kEItems; ++r) acc += kc[r] * expect_table<W>(lut, kx[r], kz[r]);
-      i0 += kE4Block * kEItems;
+      i0 += EnergyTable<W>::kThreads * kEItems;
     } while (i0 < n);
   }
-  const double s = block_sum_n<kE4Block / 64>(acc, red);
+  const double s = block_sum_n<EnergyTable<W>::kThreads / 64>(acc, red);
   if (active == 1) {
     if (threadIdx.x == 0) *out = s;
     return;
@@ -285,8 +288,8 @@ __global__ __launch_bounds__(kE4Block) void k_energy(StoreDev st, int nq, const 
   __syncthreads();
   if (s_last) {
     double t = 0.0;
-    for (unsigned k = threadIdx.x; k < active; k += kE4Block) t += finish_get(slot, k);
-    t = block_sum_n<kE4Block / 64>(t, red);
+    for (unsigned k = threadIdx.x; k < active; k += EnergyTable<W>::kThreads) t += finish_get(slot, k);
+    t = block_sum_n<EnergyTable<W>::kThreads / 64>(t, red);
     if (threadIdx.x == 0) *out = t;
   }
 }
@@ -297,11 +300,11 @@ static void launch_energy_w(int nq, const StoreDev& st, int n_cu, int per_cu, si
   const size_t lds = energy_lds_bytes<W>();
   // resident workgroups per CU: LDS (with the static part), 2048 threads
   int fit = (int)(lds_per_cu / (lds + 256));
-  fit = fit < 1 ? 1 : (fit > 2048 / kE4Block ? 2048 / kE4Block : fit);
+  fit = fit < 1 ? 1 : (fit > 2048 / EnergyTable<W>::kThreads ? 2048 / EnergyTable<W>::kThreads : fit);
   int grid = n_cu * (per_cu < fit ? per_cu : fit);
   if (grid > kFinishWords) grid = kFinishWords;
   (void)hipFuncSetAttribute((const void*)k_energy<W>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(k_energy<W>, dim3(grid), dim3(kE4Block), lds, s, st, nq, theta, phi, slot, out);
+  hipLaunchKernelGGL(k_energy<W>, dim3(grid), dim3(EnergyTable<W>::kThreads), lds, s, st, nq, theta, phi, slot, out);
 }
 
 void launch_energy(int W, int nq, const StoreDev& st, int n_cu, int per_cu, size_t lds_per_cu, const double* theta,
