@@ -270,8 +270,8 @@ def angle_backward_leg(ctx, stream, final, tht, pht, bt, reps=5):
             "hbm_gbps_algorithmic": nbytes / (ms * 1e-3) / 1e9,
             "roofline_frac_hbm": nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBPS,
             "bit_identical_calls": same,
-            "bound": "VALU and LDS: 44 group lookups, prefix/suffix products and an exact "
-                     "fixed-point add per 3-qubit group of every term"}
+            "bound": "VALU issue: the product of every term, its digits, and the bit operands "
+                     "of the matrix products that add them"}
 
 
 def autograd_leg(ctx, stream, wl):
@@ -387,7 +387,7 @@ def autograd_leg(ctx, stream, wl):
             "ms": bwd_ms, "alg_bytes": int(bwd_bytes),
             "hbm_gbps_algorithmic": bwd_bytes / (bwd_ms * 1e-3) / 1e9,
             "roofline_frac_hbm": bwd_bytes / (bwd_ms * 1e-3) / 1e9 / HBM_PEAK_GBPS,
-            "bound": "valu (counters: VALU issue about 70% of SIMD time)"},
+            "bound": "valu (counters: VALU issue about 60% of SIMD time)"},
     }
 
 

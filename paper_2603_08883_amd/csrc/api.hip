@@ -113,7 +113,7 @@ constexpr int kCtxSlot = kFinishHead + 4 * kDressGrid;   // words of the largest
 static_assert(4 * kDressGrid >= kFinishWords && 4 * kDressGrid >= 6 * kInplaceGrid, "a slot holds every kernel's words");
 
 double* take_slot(iqcc_ctx* ctx) {
-  return ctx->slots + (size_t)(ctx->next_slot++ % kFinishSlots) * kCtxSlot;
+  return ctx->slots + (size_t)(__atomic_fetch_add(&ctx->next_slot, 1u, __ATOMIC_RELAXED) % kFinishSlots) * kCtxSlot;
 }
 
 int ensure_scratch(iqcc_ctx* ctx, int64_t n) {
@@ -717,7 +717,8 @@ int iqcc_store_export(iqcc_ctx* ctx, const iqcc_store* st, uint64_t* x, uint64_t
 // *out = <h>; the caller checks the launch
 static void energy_sum(iqcc_ctx* ctx, const iqcc_store* h, const double* theta, const double* phi, double* slot,
                        double* out, hipStream_t s) {
-  launch_energy(h->W, h->nq, h->d, ctx->n_cu, (int)ctx->energy_grid_per_cu, ctx->lds_per_cu, theta, phi, slot, out, s);
+  launch_energy(h->W, h->nq, h->d, h->regions, ctx->n_cu, (int)ctx->energy_grid_per_cu, ctx->lds_per_cu, theta, phi,
+                slot, out, s);
 }
 
 static int dress_impl(iqcc_ctx* ctx, const iqcc_store* in, const uint64_t* px, const uint64_t* pz,

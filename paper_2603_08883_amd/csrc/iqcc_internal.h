@@ -804,9 +804,10 @@ void launch_top_candidates(int W, const double* g, const uint64_t* cx, const uin
 void launch_anti_sums(int W, const StoreDev& st, const Entangler& P, int nq, int grid, const double* theta,
                       const double* phi, double* slot, double* b_out, double* c_out, hipStream_t s);
 // Stand-alone energy, one launch: *out = <st>.  per_cu: upper bound of the
-// workgroups per CU; slot: a finish slot (see finish_arrive).
-void launch_energy(int W, int nq, const StoreDev& st, int n_cu, int per_cu, size_t lds_per_cu, const double* theta,
-                   const double* phi, double* slot, double* out, hipStream_t s);
+// workgroups per CU; slot: a finish slot (see finish_arrive); regions: rows in
+// bucket regions.
+void launch_energy(int W, int nq, const StoreDev& st, bool regions, int n_cu, int per_cu, size_t lds_per_cu,
+                   const double* theta, const double* phi, double* slot, double* out, hipStream_t s);
 void launch_energy_backward(int W, int nq, const StoreDev& st, int grid, const double* theta, const double* phi,
                             const double* dE, double* lam /*null or [arena rows]*/, double* acc /*[3*nq][grid]*/,
                             double* dtheta, double* dphi, hipStream_t s);

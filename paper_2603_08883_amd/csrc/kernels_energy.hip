@@ -91,7 +91,7 @@ void launch_finalize_sum(const double* partial, int n, const double* scale, doub
 //
 // Bound: HBM for large stores (40 bytes a two-word term), the chain of
 // latencies (bucket table, rows, table build, arrival) for small ones.
-// 1.6e7 two-word terms: 119 us, 5.4 TB/s (table, sums and reduction in three
+// 1.6e7 two-word terms: 122 us, 5.2 TB/s (table, sums and reduction in three
 // launches: 168 us); 361 terms: 6.6 us (23 us).
 // ---------------------------------------------------------------------------
 constexpr int kEItems = 4;
@@ -102,10 +102,6 @@ constexpr int kNibblesPerWord = 16;
 template <int W>
 struct EnergyTable {
   static constexpr bool kNibble = W <= 2;
-  // of a workgroup of k_energy: a CU's LDS holds one table of two-word keys, so
-  // its workgroup has the waves of two (5.4e7 terms in bucket regions 552 us with
-  // 512 threads, 499 with 1024; 1.6e7 loaded terms 122 us, 119)
-  static constexpr int kThreads = W == 2 ? 1024 : 512;
   static constexpr int kEntries = kNibble ? W * kNibblesPerWord * kNibbleEntries : W * kGroupsPerWord * kLutEntries;
   // scratch of the build: the qubits' factors and, for nibbles, the products
   // of the two qubits of every even/odd pair
@@ -190,35 +186,35 @@ __device__ __forceinline__ double expect_table(const double* lut, const uint64_t
   return (p[0] * p[1]) * (p[2] * p[3]);
 }
 
-template <int W>
+template <int W, int NT>
 size_t energy_lds_bytes() {
   // table, its build's scratch, first rows and row prefix sums of a group
-  return (size_t)(EnergyTable<W>::kEntries + EnergyTable<W>::kBuild) * 8 + (size_t)EnergyTable<W>::kThreads * 8 +
-         (size_t)(EnergyTable<W>::kThreads + 1) * 4;
+  return (size_t)(EnergyTable<W>::kEntries + EnergyTable<W>::kBuild) * 8 + (size_t)NT * 8 +
+         (size_t)(NT + 1) * 4;
 }
 
-template <int W>
-__global__ __launch_bounds__(EnergyTable<W>::kThreads) void k_energy(StoreDev st, int nq, const double* theta, const double* phi,
+template <int W, int NT>
+__global__ __launch_bounds__(NT) void k_energy(StoreDev st, int nq, const double* theta, const double* phi,
                                                      double* slot, double* out) {
   extern __shared__ __align__(16) unsigned char smem_en[];
   double* lut = (double*)smem_en;
   double* tmp = lut + EnergyTable<W>::kEntries;                  // [kBuild]
-  int64_t* s_off = (int64_t*)(tmp + EnergyTable<W>::kBuild);     // [EnergyTable<W>::kThreads]
-  uint32_t* s_pre = (uint32_t*)(s_off + EnergyTable<W>::kThreads);               // [EnergyTable<W>::kThreads + 1]
-  __shared__ double red[EnergyTable<W>::kThreads / 64];
-  __shared__ uint64_t scan_tmp[EnergyTable<W>::kThreads / 64];
+  int64_t* s_off = (int64_t*)(tmp + EnergyTable<W>::kBuild);     // [NT]
+  uint32_t* s_pre = (uint32_t*)(s_off + NT);               // [NT + 1]
+  __shared__ double red[NT / 64];
+  __shared__ uint64_t scan_tmp[NT / 64];
   __shared__ int s_last;
   const int64_t B = 1ll << *st.m;
   // at least kEMinRows rows per workgroup where the store has them
   int64_t want = (*st.total + kEMinRows - 1) / kEMinRows;
   want = want < 1 ? 1 : (want > gridDim.x ? gridDim.x : want);
   int64_t G = (B + want - 1) / want;
-  G = G > EnergyTable<W>::kThreads ? EnergyTable<W>::kThreads : G;
+  G = G > NT ? NT : G;
   const int64_t ngroups = (B + G - 1) / G;
   const unsigned active = ngroups < want ? (unsigned)ngroups : (unsigned)want;
   if (blockIdx.x >= active) return;
   // (the factors' chain of loads and sines beside that of the bucket table)
-  build_factors<W, EnergyTable<W>::kThreads>(tmp, nq, theta, phi);
+  build_factors<W, NT>(tmp, nq, theta, phi);
   bool table = false;
   double acc = 0.0;
   for (int64_t grp = blockIdx.x; grp < ngroups; grp += active) {
@@ -228,10 +224,10 @@ __global__ __launch_bounds__(EnergyTable<W>::kThreads) void k_energy(StoreDev st
     const int64_t off = mine ? st.off[b] : 0;
     uint64_t total;
     // (the scan's barriers also order the previous group's reads of s_pre)
-    const uint64_t ex = block_exclusive_scan_n<EnergyTable<W>::kThreads / 64>((uint64_t)cnt, scan_tmp, total);
+    const uint64_t ex = block_exclusive_scan_n<NT / 64>((uint64_t)cnt, scan_tmp, total);
     s_pre[threadIdx.x] = (uint32_t)ex;
     s_off[threadIdx.x] = off;
-    if (threadIdx.x == 0) s_pre[EnergyTable<W>::kThreads] = (uint32_t)total;
+    if (threadIdx.x == 0) s_pre[NT] = (uint32_t)total;
     __syncthreads();
     // the group's rows are one range when every bucket starts where the one
     // before it ends (a loaded store); then row = base + i, the row the search
@@ -245,7 +241,7 @@ __global__ __launch_bounds__(EnergyTable<W>::kThreads) void k_energy(StoreDev st
       double kc[kEItems];
 #pragma unroll
       for (int r = 0; r < kEItems; ++r) {
-        const uint32_t i = i0 + r * EnergyTable<W>::kThreads + threadIdx.x;
+        const uint32_t i = i0 + r * NT + threadIdx.x;
         kc[r] = 0.0;
 #pragma unroll
         for (int w = 0; w < W; ++w) kx[r][w] = kz[r][w] = 0;
@@ -254,7 +250,7 @@ __global__ __launch_bounds__(EnergyTable<W>::kThreads) void k_energy(StoreDev st
           if (!contig) {
             int lo = 0;   // the last bucket of the group whose first row is <= i
 #pragma unroll
-            for (int step = EnergyTable<W>::kThreads / 2; step; step >>= 1)
+            for (int step = NT / 2; step; step >>= 1)
               if (s_pre[lo + step] <= i) lo += step;
             row = s_off[lo] + (i - s_pre[lo]);
           }
@@ -267,15 +263,15 @@ __global__ __launch_bounds__(EnergyTable<W>::kThreads) void k_energy(StoreDev st
         }
       }
       if (!table) {   // built while the first rows are on their way
-        build_energy_table<W, EnergyTable<W>::kThreads>(lut, tmp);
+        build_energy_table<W, NT>(lut, tmp);
         table = true;
       }
 #pragma unroll
       for (int r = 0; r < kEItems; ++r) acc += kc[r] * expect_table<W>(lut, kx[r], kz[r]);
-      i0 += EnergyTable<W>::kThreads * kEItems;
+      i0 += NT * kEItems;
     } while (i0 < n);
   }
-  const double s = block_sum_n<EnergyTable<W>::kThreads / 64>(acc, red);
+  const double s = block_sum_n<NT / 64>(acc, red);
   if (active == 1) {
     if (threadIdx.x == 0) *out = s;
     return;
@@ -288,32 +284,39 @@ __global__ __launch_bounds__(EnergyTable<W>::kThreads) void k_energy(StoreDev st
   __syncthreads();
   if (s_last) {
     double t = 0.0;
-    for (unsigned k = threadIdx.x; k < active; k += EnergyTable<W>::kThreads) t += finish_get(slot, k);
-    t = block_sum_n<EnergyTable<W>::kThreads / 64>(t, red);
+    for (unsigned k = threadIdx.x; k < active; k += NT) t += finish_get(slot, k);
+    t = block_sum_n<NT / 64>(t, red);
     if (threadIdx.x == 0) *out = t;
   }
 }
 
-template <int W>
+template <int W, int NT>
 static void launch_energy_w(int nq, const StoreDev& st, int n_cu, int per_cu, size_t lds_per_cu, const double* theta,
                             const double* phi, double* slot, double* out, hipStream_t s) {
-  const size_t lds = energy_lds_bytes<W>();
+  const size_t lds = energy_lds_bytes<W, NT>();
   // resident workgroups per CU: LDS (with the static part), 2048 threads
   int fit = (int)(lds_per_cu / (lds + 256));
-  fit = fit < 1 ? 1 : (fit > 2048 / EnergyTable<W>::kThreads ? 2048 / EnergyTable<W>::kThreads : fit);
+  fit = fit < 1 ? 1 : (fit > 2048 / NT ? 2048 / NT : fit);
   int grid = n_cu * (per_cu < fit ? per_cu : fit);
   if (grid > kFinishWords) grid = kFinishWords;
-  (void)hipFuncSetAttribute((const void*)k_energy<W>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(k_energy<W>, dim3(grid), dim3(EnergyTable<W>::kThreads), lds, s, st, nq, theta, phi, slot, out);
+  (void)hipFuncSetAttribute((const void*)k_energy<W, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((k_energy<W, NT>), dim3(grid), dim3(NT), lds, s, st, nq, theta, phi, slot, out);
 }
 
-void launch_energy(int W, int nq, const StoreDev& st, int n_cu, int per_cu, size_t lds_per_cu, const double* theta,
+// A CU's LDS holds one table of two-word keys.  Where the rows of a store lie in
+// bucket regions, each pass also searches its buckets, and the workgroup gets
+// 1024 threads, the waves of two (5.4e7 terms 552 us with 512, 499 with 1024);
+// loaded rows stream faster with 512 (1.6e7 terms 121 us, 125).
+void launch_energy(int W, int nq, const StoreDev& st, bool regions, int n_cu, int per_cu, size_t lds_per_cu, const double* theta,
                    const double* phi, double* slot, double* out, hipStream_t s) {
   switch (W) {
-    case 1: launch_energy_w<1>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s); break;
-    case 2: launch_energy_w<2>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s); break;
-    case 3: launch_energy_w<3>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s); break;
-    default: launch_energy_w<4>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s); break;
+    case 1: launch_energy_w<1, 512>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s); break;
+    case 2:
+      if (regions) launch_energy_w<2, 1024>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s);
+      else launch_energy_w<2, 512>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s);
+      break;
+    case 3: launch_energy_w<3, 512>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s); break;
+    default: launch_energy_w<4, 512>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s); break;
   }
 }
 
