@@ -26,6 +26,8 @@ constexpr int kDisR = 8;            // terms per lane of a full pass
 constexpr int kDisTile = 256;       // candidates staged at once
 constexpr int kDisChunk = kDisB;    // buckets whose prefix sums are staged at once
 constexpr int kDisPass = kDisB * kDisR;
+constexpr int kDisRun = 16;     // least candidates of a workgroup's run, if there are as many
+constexpr int kDisFill = 256;   // workgroups that give every CU one
 
 // Spread the 16 bits of v to the even bits of a 32-bit word.
 __device__ __forceinline__ uint32_t spread16(uint32_t v) {
@@ -73,10 +75,17 @@ __device__ __forceinline__ double wave_sum_to_lane63(double v) {
 // 2 % to spare, so that uneven buckets seldom spill a few terms into a second
 // pass: on 1e6 terms in 4096 buckets, ranges of 8.4 buckets took 2320 us, of 8
 // 1902 us), but no more than max_ranges ranges; `fixed`: max_ranges ranges.
-__device__ __forceinline__ int64_t dis_range_buckets(int64_t total, int64_t buckets, int max_ranges, int fixed) {
+// Where that leaves CUs without a run of candidates, the ranges are halved, to
+// 4 and to 2 terms a lane: then a workgroup's loads, not its candidates, are the
+// time (200,000 two-word terms x 16 candidates 54 us with 98 ranges, 30 with
+// 391; x 64, which fill the chip, 69 and 78).
+__device__ __forceinline__ int64_t dis_range_buckets(int64_t total, int64_t buckets, int max_ranges, int fixed,
+                                                     int64_t n_cand) {
   const int64_t least = (buckets + max_ranges - 1) / max_ranges;
   if (fixed || total <= 0) return least;
-  const int64_t fill = (int64_t)((double)buckets * (kDisPass / 1.02) / (double)total);
+  int pass = kDisPass;
+  while (pass > 2 * kDisB && (total / pass + 1) * ((n_cand + kDisRun - 1) / kDisRun) < kDisFill) pass /= 2;
+  const int64_t fill = (int64_t)((double)buckets * (pass / 1.02) / (double)total);
   return fill < least ? least : (fill > buckets ? buckets : fill);
 }
 
@@ -225,7 +234,7 @@ __device__ __forceinline__ void dis_pass(const StoreDev& st, DisShared<W>& sh, i
 // per qubit for the phase, 4 terms per lane, ranges of buckets by tiles) took
 // 2.38 ms plus 0.13 ms for the sum over ranges.  12,007 one-word terms x 13,472
 // candidates: 1113 -> 193 us (its ranges held 307 of 2048
-// terms).  233,001 terms x 5 candidates: 298 -> 22 us.
+// terms).  233,001 terms x 5 candidates: 298 -> 19 us.
 template <int W>
 __global__ __launch_bounds__(kDisB, W <= 2 ? 3 : 2) void k_dis_batched(StoreDev st, int nq, const double* __restrict__ theta,
                                                        const double* __restrict__ phi,
@@ -237,10 +246,10 @@ __global__ __launch_bounds__(kDisB, W <= 2 ? 3 : 2) void k_dis_batched(StoreDev 
   extern __shared__ __align__(16) unsigned char smem_dis[];
   DisShared<W>& sh = *reinterpret_cast<DisShared<W>*>(smem_dis);
   const int64_t B = 1ll << *st.m;
-  const int64_t per = dis_range_buckets(*st.total, B, max_ranges, fixed);
+  const int64_t per = dis_range_buckets(*st.total, B, max_ranges, fixed, n_cand);
   const int64_t nr = (B + per - 1) / per;
   int64_t run = (nr * n_cand + gridDim.x - 1) / gridDim.x;
-  const int64_t least = n_cand < 16 ? n_cand : 16;
+  const int64_t least = n_cand < kDisRun ? n_cand : kDisRun;
   if (run < least) run = least;
   int64_t at = blockIdx.x * run;
   int64_t end = at + run < nr * n_cand ? at + run : nr * n_cand;
@@ -348,7 +357,7 @@ int64_t dis_tile() { return kDisTile; }   // the largest tile the batched kernel
 __global__ __launch_bounds__(kBlock) void k_dis_reduce(StoreDev st, const double* partial, int max_ranges, int fixed,
                                                        int64_t n_cand, double* g) {
   __shared__ double red[16][17];
-  const int64_t B = 1ll << *st.m, per = dis_range_buckets(*st.total, B, max_ranges, fixed);
+  const int64_t B = 1ll << *st.m, per = dis_range_buckets(*st.total, B, max_ranges, fixed, n_cand);
   const int64_t nr = (B + per - 1) / per;
   const int t = threadIdx.x & 15, l = threadIdx.x >> 4;
   const int64_t a = blockIdx.x * 16ll + t;
