@@ -466,7 +466,7 @@ int launch_store_load_regions(int W, StoreDev st, const uint64_t* x, const uint6
 // into more than kSplit parts is several work items, which each place their
 // part.  (With a wavefront per destination bucket that selected its terms, the
 // source was read 2^(m - ms) times: 112 us to count and 218 us to place 1.1e6
-// two-word terms from 8192 into 2^17 buckets, now @C and @R.)  Bound: HBM,
+// two-word terms from 8192 into 2^17 buckets, now 15 and 71.)  Bound: HBM,
 // 40 bytes read a term and row writes shorter than a cache line.
 //
 // Fewer (m < ms): a wavefront per destination bucket d copies the source
