@@ -127,14 +127,15 @@ int iqcc_get_param(const iqcc_ctx *ctx, const char *name, int64_t *value);
  * `max_terms` terms as the output of a dressing step (the device arena holds
  * 2*max_terms rows because a step reserves, per bucket pair, the worst-case
  * output size 2*(n_b + n_b')).  Device memory: about
- * 2*max_terms*(16*W + 8) bytes plus the bucket table, allocated by the
- * library (synchronising). */
+ * 2*max_terms*(16*W + 8) bytes plus the bucket table and up to 136 KB for the
+ * sums of the step that writes the store, allocated by the library
+ * (synchronising). */
 int iqcc_store_create(iqcc_ctx *ctx, int n_qubits, int64_t max_terms, iqcc_store **store);
 /* As iqcc_store_create with store flags (0 or IQCC_STORE_INPLACE). */
 int iqcc_store_create_ex(iqcc_ctx *ctx, int n_qubits, int64_t max_terms, uint32_t flags,
                          iqcc_store **store);
 /* HOST only: *bytes = device memory a store of these parameters needs
- * (header, bucket table and arena in one block).  IQCC_ERR_INVALID_ARG for
+ * (header, bucket table, sums of a step and arena in one block).  IQCC_ERR_INVALID_ARG for
  * n_qubits < 1, max_terms outside 1..2^38 or unknown flags. */
 int iqcc_store_bytes(int n_qubits, int64_t max_terms, uint32_t flags, int64_t *bytes);
 /* Create a store inside caller-owned DEVICE memory `mem` of `bytes` bytes

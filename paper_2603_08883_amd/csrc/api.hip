@@ -71,6 +71,8 @@ struct iqcc_store {
   double floor = 0.0;     // every live |c| is >= floor (0: unknown)
   bool regions = false;   // contents laid out in bucket regions (in-place dressing allowed)
   int region_m = -1;      // their bucket bits (fixed while the layout lasts)
+  double* slot = nullptr; // finish slot of the calls that write the store, in its memory
+  int slot_words = 0;     // words it holds
 };
 
 namespace {
@@ -257,13 +259,23 @@ int ilog2_ceil(int64_t v) {
 namespace {
 
 // Device memory of a store, one block: a 256-byte header of device scalars,
-// the bucket table (off, cnt, lim) and the arena planes x[W][cap], z[W][cap],
-// c[cap]; every array starts on a 256-byte boundary.
+// the bucket table (off, cnt, lim), a finish slot and the arena planes
+// x[W][cap], z[W][cap], c[cap]; every array starts on a 256-byte boundary.
+//
+// The finish slot belongs to the call that writes the store.  A store has one
+// writer at a time, so steps that write different stores share nothing, in
+// whatever streams they run and however often a captured one is replayed.  (With
+// slots of the context taken in turn, a long step met the 32nd call after it.)
 struct StoreLayout {
-  int W = 0, mcap = 0;
+  int W = 0, mcap = 0, slot_words = 0;
   int64_t cap = 0;
-  size_t off = 0, cnt = 0, lim = 0, x = 0, z = 0, c = 0, bytes = 0;
+  size_t off = 0, cnt = 0, lim = 0, slot = 0, x = 0, z = 0, c = 0, bytes = 0;
 };
+
+// Four words for each workgroup of an out-of-place step, which has no more than
+// one per bucket; six for each of an in-place step, one per CU.
+constexpr int kStoreWords = 4 * kDressGrid;
+static_assert(kStoreWords >= 6 * kInplaceGrid, "a store's slot holds the words of an in-place step");
 
 constexpr size_t kHeaderBytes = 256;
 
@@ -290,6 +302,8 @@ bool store_layout(int n_qubits, int64_t max_terms, uint32_t flags, StoreLayout& 
   L.off = o; o = align256(o + 8 * B);
   L.cnt = o; o = align256(o + 8 * B);
   L.lim = o; o = align256(o + 8 * B);
+  L.slot_words = (flags & IQCC_STORE_INPLACE) || B >= kDressGrid ? kStoreWords : 4 * (int)B;
+  L.slot = o; o = align256(o + 8 * (size_t)(kFinishHead + L.slot_words));
   L.x = o; o = align256(o + 8 * (size_t)L.W * L.cap);
   L.z = o; o = align256(o + 8 * (size_t)L.W * L.cap);
   L.c = o; o = align256(o + 8 * (size_t)L.cap);
@@ -321,15 +335,19 @@ iqcc_store* store_from_memory(int n_qubits, int64_t max_terms, uint32_t flags, c
   st->d.c = (double*)(b + L.c);
   st->d.cap = L.cap;
   st->d.mcap = L.mcap;
+  st->slot = (double*)(b + L.slot);
+  st->slot_words = L.slot_words;
   return st;
 }
 
-// An empty store: every scalar 0 and bucket 0 (the only bucket at m = 0) empty.
+// An empty store: every scalar 0, bucket 0 (the only bucket at m = 0) empty and
+// the counters of the finish slot zero.
 hipError_t store_clear(iqcc_store* st, hipStream_t s) {
   hipError_t e = hipMemsetAsync(st->mem, 0, kHeaderBytes, s);
   if (e == hipSuccess) e = hipMemsetAsync(st->d.off, 0, 8, s);
   if (e == hipSuccess) e = hipMemsetAsync(st->d.cnt, 0, 8, s);
   if (e == hipSuccess) e = hipMemsetAsync(st->d.lim, 0, 8, s);
+  if (e == hipSuccess) e = hipMemsetAsync(st->slot, 0, 8 * (size_t)kFinishHead, s);
   return e;
 }
 
@@ -767,7 +785,7 @@ static int dress_impl(iqcc_ctx* ctx, const iqcc_store* in, const uint64_t* px, c
     cfg.energy_in = energy_in;
     cfg.energy_out = energy;
   }
-  cfg.slot = take_slot(ctx);
+  cfg.slot = out->slot;
   cfg.tape_self = tape_self;
   cfg.tape_partner = tape_partner;
   launch_dress(W, in->d, out->d, P, cfg, s);
@@ -775,7 +793,7 @@ static int dress_impl(iqcc_ctx* ctx, const iqcc_store* in, const uint64_t* px, c
   out->floor = eps;
   out->regions = false;
   if (want_e && !fused) {
-    energy_sum(ctx, out, theta, phi, take_slot(ctx), energy, s);
+    energy_sum(ctx, out, theta, phi, out->slot, energy, s);   // (after the step, in its stream)
     LAUNCH_CHECK(ctx);
   }
   return IQCC_OK;
@@ -836,14 +854,14 @@ int iqcc_dress_inplace(iqcc_ctx* ctx, iqcc_store* st, const uint64_t* px, const 
   cfg.nq = st->nq;
   const bool delta = fused && energy_in;
   cfg.delta = delta ? 1 : 0;
-  cfg.slot = take_slot(ctx);
+  cfg.slot = st->slot;
   cfg.energy_in = delta ? energy_in : nullptr;
   cfg.energy_out = fused ? energy_out : nullptr;
   launch_dress_inplace(W, st->d, P, cfg, grid, s);
   LAUNCH_CHECK(ctx);
   st->floor = eps;
   if (want_e && !fused) {
-    energy_sum(ctx, st, theta, phi, take_slot(ctx), energy_out, s);
+    energy_sum(ctx, st, theta, phi, st->slot, energy_out, s);
     LAUNCH_CHECK(ctx);
   }
   return IQCC_OK;
@@ -1440,7 +1458,7 @@ int iqcc_truncate_top(iqcc_ctx* ctx, const iqcc_store* in, int64_t max_terms, iq
   SelState* ss = (SelState*)(ctx->sel_hist + kSelHist);
   DevBuf keys, kcount;
   // (the output's rows and bucket counts are scratch until the copy)
-  launch_abs_select(in->d, ss, ctx->sel_hist, ctx->n_cu, max_terms, out->d, take_slot(ctx), s);
+  launch_abs_select(in->d, ss, ctx->sel_hist, ctx->n_cu, max_terms, out->d, out->slot, s);
   LAUNCH_CHECK(ctx);
   SelState h{};
   HIP_TRY(ctx, hipMemcpyAsync(&h, ss, sizeof(h), hipMemcpyDeviceToHost, s));
@@ -1450,7 +1468,7 @@ int iqcc_truncate_top(iqcc_ctx* ctx, const iqcc_store* in, int64_t max_terms, iq
   const int keep_all = h.n <= max_terms ? 1 : max_terms == 0 ? -1 : 0;
   if (keep_all == 0) {
     if (!h.done) {
-      launch_abs_select_rest(in->d, ss, ctx->sel_hist, ctx->n_cu, out->d, take_slot(ctx), s);
+      launch_abs_select_rest(in->d, ss, ctx->sel_hist, ctx->n_cu, out->d, out->slot, s);
       LAUNCH_CHECK(ctx);
       HIP_TRY(ctx, hipMemcpyAsync(&h, ss, sizeof(h), hipMemcpyDeviceToHost, s));
       HIP_TRY(ctx, hipStreamSynchronize(s));
@@ -1459,20 +1477,21 @@ int iqcc_truncate_top(iqcc_ctx* ctx, const iqcc_store* in, int64_t max_terms, iq
       // not every term equal to the threshold fits: the smaller canonical keys go first
       if (hipMalloc(&keys.p, (size_t)h.ties * 2 * W * sizeof(uint64_t)) != hipSuccess ||
           hipMalloc(&kcount.p, 64) != hipSuccess) {
-        launch_select_compact(W, in->d, out->d, ss, -1, 1, take_slot(ctx), s);   // leave a valid, empty store
+        launch_select_compact(W, in->d, out->d, ss, -1, 1, out->slot, s);   // leave a valid, empty store
         return fail(ctx, IQCC_ERR_HIP, "out of device memory for the keys of equal terms");
       }
       HIP_TRY(ctx, hipMemsetAsync(kcount.p, 0, 64, s));
       launch_collect_ties(W, in->d, ss, (uint64_t*)keys.p, h.ties, (unsigned long long*)kcount.p,
                           grid, s);
-      launch_key_select(W, (const uint64_t*)keys.p, h.ties, ss, ctx->sel_hist, take_slot(ctx), s);
+      launch_key_select(W, (const uint64_t*)keys.p, h.ties, ss, ctx->sel_hist, out->slot, s);
       const int one = 1;
       HIP_TRY(ctx, hipMemcpyAsync(&ss->key_mode, &one, sizeof(int), hipMemcpyHostToDevice, s));
       LAUNCH_CHECK(ctx);
     }
   }
-  const int cgrid = ctx->n_cu * 8 < 4 * kDressGrid ? ctx->n_cu * 8 : 4 * kDressGrid;
-  launch_select_compact(W, in->d, out->d, ss, keep_all, cgrid, take_slot(ctx), s);
+  // (a word per workgroup of the output's slot, four buckets per workgroup)
+  const int cgrid = ctx->n_cu * 8 < out->slot_words ? ctx->n_cu * 8 : out->slot_words;
+  launch_select_compact(W, in->d, out->d, ss, keep_all, cgrid, out->slot, s);
   out->regions = false;
   LAUNCH_CHECK(ctx);
   HIP_TRY(ctx, hipStreamSynchronize(s));

@@ -679,7 +679,7 @@ struct DressConfig {
                           //   output row is -1 when K^P is absent or dropped
   int unit_pairs;         // batched dressing: consecutive bucket pairs per work unit
 };
-// At most this many workgroups (their words fit a context's finish slot).
+// At most this many workgroups (their words fit a store's finish slot).
 constexpr int kDressGrid = 4096;
 void launch_dress(int W, const StoreDev& in, const StoreDev& out, const Entangler& P,
                   const DressConfig& cfg, hipStream_t s);
@@ -701,7 +701,7 @@ struct InplaceConfig {
 };
 size_t inplace_lds_bytes(int W, int cap, bool energy);
 int inplace_cap(int W, bool energy, size_t lds_budget);
-// At most this many workgroups (their words fit a finish slot).
+// At most this many workgroups (their words fit a store's finish slot).
 constexpr int kInplaceGrid = 4 * kDressGrid / 6;
 void launch_dress_inplace(int W, const StoreDev& st, const Entangler& P, const InplaceConfig& cfg, int grid,
                           hipStream_t s);
