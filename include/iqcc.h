@@ -37,6 +37,18 @@
  *     arguments leave every output untouched.
  *   - a context is bound to one device and must not be used by two threads
  *     at once.  Stores belong to the context that created them.
+ *   - calls of one context on different streams may run at the same time as
+ *     follows.  iqcc_dress, iqcc_dress_energy_update, iqcc_dress_taped,
+ *     iqcc_chain_forward, iqcc_dress_inplace and iqcc_batch_launch: any
+ *     number that write different stores, captured or not (their sums lie in the
+ *     memory of the store they write).  iqcc_qmf_energy, iqcc_qmf_energy_anti,
+ *     iqcc_dress_backward and iqcc_chain_backward: any number, beside those too,
+ *     on the first 16 streams that the context sees in such calls; captured
+ *     ones, and those of further streams, share 8 sets of sums taken in turn, and
+ *     two that meet in one set while they run may give a wrong sum (later
+ *     calls are not affected).  A stream is known by its handle: destroy it
+ *     only after such a call on it has ended.  All other calls use working
+ *     memory of the context and must not overlap each other.
  */
 #ifndef IQCC_H
 #define IQCC_H
@@ -396,15 +408,16 @@ int iqcc_qmf_energy(iqcc_ctx *ctx, const iqcc_store *h, const double *theta,
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * energy as iqcc_qmf_energy, from the same kernel, with no allocation of any
- * kind.  Its scratch (six sets of per-workgroup partial sums and arrival
- * counters, taken in turn) is a fixed array of device memory inside the
- * library, 120 KB per device, held until the process ends.  A grid (n_cu *
- * energy_grid_per_cu workgroups) above 8192 is refused with IQCC_ERR_CAPACITY
- * before any launch.  All calls on one device share that scratch, so more
- * than six calls that overlap on a device (other streams, other contexts or
- * threads) may race; calls in one stream are ordered.  Each call rewrites all
- * the partial sums it reads and leaves the counters zero. */
+ * energy as iqcc_qmf_energy (the same bits), from the same kernel and a second
+ * one that adds its sums, with no allocation of any kind.  Its scratch (six
+ * sets of per-workgroup partial sums, taken in turn) is a fixed array of device
+ * memory inside the library, 120 KB per device, held until the process ends.
+ * A grid (n_cu * energy_grid_per_cu workgroups) above 8192 is refused with
+ * IQCC_ERR_CAPACITY before any launch.  All calls on one device share that
+ * scratch, and a captured call keeps its set, so calls that overlap on a device
+ * (other streams, other contexts or threads) race; calls in one stream are
+ * ordered.  Each call rewrites all the scratch it reads, so a race spoils
+ * the calls that take part in it and no later one. */
 int iqcc_qmf_energy_noalloc(iqcc_ctx *ctx, const iqcc_store *h, const double *theta,
                             const double *phi, double *energy, void *stream);
 

@@ -8,6 +8,8 @@
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <thread>
+#include <utility>
 #include <vector>
 
 #include "../../include/iqcc.h"
@@ -39,8 +41,9 @@ struct iqcc_ctx {
   int64_t inplace_region_rows = 0;         // 0: regions share the arena minus the pool
   // device scratch
   double* lut = nullptr;        // kLutDoubles: 3-qubit group table (4 x 22 x 64)
-  double* slots = nullptr;      // kFinishSlots finish slots, taken in turn
-  unsigned next_slot = 0;
+  double* sums = nullptr;       // kSumStreams + kSumSpare slots of kSumWords words (see sum_slot)
+  std::vector<std::pair<hipStream_t, std::thread::id>> sum_streams;   // their streams, at most kSumStreams
+  unsigned next_spare = 0;
   unsigned* sel_hist = nullptr; // kSelHist digit counters, zero between calls, then a SelState
   double* partial = nullptr;    // n_partial
   int64_t n_partial = 0;
@@ -105,17 +108,38 @@ int fail(iqcc_ctx* ctx, int code, const char* fmt, ...) {
 
 hipStream_t as_stream(void* s) { return (hipStream_t)s; }
 
-// Finish slots of a context: consecutive calls take them in turn, so calls
-// that overlap on different streams have partial sums and a counter of their
-// own as long as fewer than kFinishSlots are in flight.
-constexpr int kFinishSlots = 32;
 constexpr int kLutDoubles = kMaxWords * kGroupsPerWord * kLutEntries;
 
-constexpr int kCtxSlot = kFinishHead + 4 * kDressGrid;   // words of the largest dressing grid
-static_assert(4 * kDressGrid >= kFinishWords && 4 * kDressGrid >= 6 * kInplaceGrid, "a slot holds every kernel's words");
+// Slots of the calls that only read a store.  Each of the first kSumStreams
+// streams a context sees has one, in which the workgroup that arrives last
+// finishes the sum: calls of one stream run one after another.  A call under
+// capture runs in whatever stream its graph is launched, and further streams
+// have no slot: these leave their words in one of kSumSpare sets, taken in turn,
+// which keep no state, and a second launch adds them.  Two of them that meet in
+// one set while they run can give a wrong sum, and nothing else.
+constexpr int kSumStreams = 16;
+constexpr int kSumSpare = 8;
+constexpr int kSumWords = 3 * kDressGrid;   // of the reverse step, the most
+constexpr int kSumSlot = kFinishHead + kSumWords;
+static_assert(kSumWords >= kFinishWords, "a slot holds the energy's words");
 
-double* take_slot(iqcc_ctx* ctx) {
-  return ctx->slots + (size_t)(__atomic_fetch_add(&ctx->next_slot, 1u, __ATOMIC_RELAXED) % kFinishSlots) * kCtxSlot;
+SumSlot sum_slot(iqcc_ctx* ctx, hipStream_t s) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    capture = hipStreamCaptureStatusActive;
+  }
+  if (capture == hipStreamCaptureStatusNone) {
+    // hipStreamPerThread is another stream in every thread
+    const std::pair<hipStream_t, std::thread::id> key{
+        s, s == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id()};
+    auto& seen = ctx->sum_streams;
+    size_t i = 0;
+    while (i < seen.size() && seen[i] != key) ++i;
+    if (i == seen.size() && i < kSumStreams) seen.push_back(key);
+    if (i < seen.size()) return {ctx->sums + i * kSumSlot, true};
+  }
+  return {ctx->sums + (kSumStreams + ctx->next_spare++ % kSumSpare) * (size_t)kSumSlot, false};
 }
 
 int ensure_scratch(iqcc_ctx* ctx, int64_t n) {
@@ -401,10 +425,12 @@ void inplace_geometry(const iqcc_ctx* ctx, const iqcc_store* st, int& m, int64_t
 }
 
 // ---- allocation-free QMF energy ----------------------------------------------
-// Device scratch of iqcc_qmf_energy_noalloc: kNoAllocSlots finish slots, taken
-// in turn, zero at start (the state finish_arrive leaves).  Every device the
-// library runs on holds its own copy until the process ends; host code reaches
-// it only through the per-device address from hipGetSymbolAddress.
+// Device scratch of iqcc_qmf_energy_noalloc: kNoAllocSlots sets of words, taken
+// in turn.  They keep no state (a second launch adds the words), so calls that
+// meet in one set, as replays of captured ones may, can give each other a wrong
+// sum but leave nothing behind.  Every device the library runs on holds its own
+// copy until the process ends; host code reaches it only through the per-device
+// address from hipGetSymbolAddress.
 constexpr int kNoAllocSlots = 6;
 constexpr int kNoAllocPartials = 8192;   // the largest grid the entry point accepts
 constexpr int kNoAllocDevices = 64;
@@ -440,6 +466,7 @@ int iqcc_ctx_create(iqcc_ctx** out, int device) {
   if (hipGetDeviceCount(&ndev) != hipSuccess || device < 0 || device >= ndev) return IQCC_ERR_HIP;
   iqcc_ctx* ctx = new iqcc_ctx();
   ctx->device = device;
+  ctx->sum_streams.reserve(kSumStreams);
   if (hipSetDevice(device) != hipSuccess) { delete ctx; return IQCC_ERR_HIP; }
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) != hipSuccess) { delete ctx; return IQCC_ERR_HIP; }
@@ -457,13 +484,13 @@ int iqcc_ctx_create(iqcc_ctx** out, int device) {
   }
   noalloc_setup(device);
   const size_t sel_bytes = sizeof(unsigned) * kSelHist + sizeof(SelState);
-  const size_t slot_bytes = sizeof(double) * kFinishSlots * kCtxSlot;
+  const size_t sum_bytes = sizeof(double) * (kSumStreams + kSumSpare) * kSumSlot;
   if (hipMalloc(&ctx->lut, sizeof(double) * kLutDoubles) != hipSuccess ||
-      hipMalloc(&ctx->slots, slot_bytes) != hipSuccess || hipMemset(ctx->slots, 0, slot_bytes) != hipSuccess ||
+      hipMalloc(&ctx->sums, sum_bytes) != hipSuccess || hipMemset(ctx->sums, 0, sum_bytes) != hipSuccess ||
       hipMalloc(&ctx->sel_hist, sel_bytes) != hipSuccess || hipMemset(ctx->sel_hist, 0, sel_bytes) != hipSuccess ||
       hipDeviceSynchronize() != hipSuccess) {
     if (ctx->lut) hipFree(ctx->lut);
-    if (ctx->slots) hipFree(ctx->slots);
+    if (ctx->sums) hipFree(ctx->sums);
     if (ctx->sel_hist) hipFree(ctx->sel_hist);
     delete ctx;
     return IQCC_ERR_HIP;
@@ -477,7 +504,7 @@ int iqcc_ctx_destroy(iqcc_ctx* ctx) {
   hipSetDevice(ctx->device);
   hipDeviceSynchronize();
   if (ctx->lut) hipFree(ctx->lut);
-  if (ctx->slots) hipFree(ctx->slots);
+  if (ctx->sums) hipFree(ctx->sums);
   if (ctx->sel_hist) hipFree(ctx->sel_hist);
   if (ctx->partial) hipFree(ctx->partial);
   if (ctx->scratch) hipFree(ctx->scratch);
@@ -733,8 +760,8 @@ int iqcc_store_export(iqcc_ctx* ctx, const iqcc_store* st, uint64_t* x, uint64_t
 // ---- dressing ---------------------------------------------------------------
 
 // *out = <h>; the caller checks the launch
-static void energy_sum(iqcc_ctx* ctx, const iqcc_store* h, const double* theta, const double* phi, double* slot,
-                       double* out, hipStream_t s) {
+static void energy_sum(iqcc_ctx* ctx, const iqcc_store* h, const double* theta, const double* phi,
+                       const SumSlot& slot, double* out, hipStream_t s) {
   launch_energy(h->W, h->nq, h->d, h->regions, ctx->n_cu, (int)ctx->energy_grid_per_cu, ctx->lds_per_cu, theta, phi,
                 slot, out, s);
 }
@@ -793,7 +820,7 @@ static int dress_impl(iqcc_ctx* ctx, const iqcc_store* in, const uint64_t* px, c
   out->floor = eps;
   out->regions = false;
   if (want_e && !fused) {
-    energy_sum(ctx, out, theta, phi, out->slot, energy, s);   // (after the step, in its stream)
+    energy_sum(ctx, out, theta, phi, {out->slot, true}, energy, s);   // (after the step, in its stream)
     LAUNCH_CHECK(ctx);
   }
   return IQCC_OK;
@@ -861,7 +888,7 @@ int iqcc_dress_inplace(iqcc_ctx* ctx, iqcc_store* st, const uint64_t* px, const 
   LAUNCH_CHECK(ctx);
   st->floor = eps;
   if (want_e && !fused) {
-    energy_sum(ctx, st, theta, phi, st->slot, energy_out, s);
+    energy_sum(ctx, st, theta, phi, {st->slot, true}, energy_out, s);
     LAUNCH_CHECK(ctx);
   }
   return IQCC_OK;
@@ -912,7 +939,7 @@ int iqcc_dress_backward(iqcc_ctx* ctx, const iqcc_store* in, const uint64_t* px,
   hipStream_t s = as_stream(stream);
   const int grid = (int)(ctx->n_cu * 4) < kDressGrid ? (int)(ctx->n_cu * 4) : kDressGrid;
   launch_dress_backward(in->W, in->d, std::cos(tau), std::sin(tau), tape_self, tape_partner,
-                        lambda_out, lambda_in, take_slot(ctx), dtau, grid, s);
+                        lambda_out, lambda_in, sum_slot(ctx, s), dtau, grid, s);
   LAUNCH_CHECK(ctx);
   return IQCC_OK;
 }
@@ -1181,7 +1208,8 @@ int iqcc_qmf_energy(iqcc_ctx* ctx, const iqcc_store* h, const double* theta, con
   int rc = check_ctx(ctx);
   if (rc) return rc;
   if (!h || !theta || !phi || !energy) return fail(ctx, IQCC_ERR_INVALID_ARG, "null argument");
-  energy_sum(ctx, h, theta, phi, take_slot(ctx), energy, as_stream(stream));
+  hipStream_t s = as_stream(stream);
+  energy_sum(ctx, h, theta, phi, sum_slot(ctx, s), energy, s);
   LAUNCH_CHECK(ctx);
   return IQCC_OK;
 }
@@ -1199,7 +1227,7 @@ int iqcc_qmf_energy_noalloc(iqcc_ctx* ctx, const iqcc_store* h, const double* th
                 "allocation-free energy holds %d workgroup partials, the grid needs %lld "
                 "(lower energy_grid_per_cu)", kNoAllocPartials, (long long)grid);
   double* slot = base + (size_t)(g_scratch_next.fetch_add(1, std::memory_order_relaxed) % kNoAllocSlots) * kFinishSlot;
-  energy_sum(ctx, h, theta, phi, slot, energy, as_stream(stream));
+  energy_sum(ctx, h, theta, phi, {slot, false}, energy, as_stream(stream));
   LAUNCH_CHECK(ctx);
   return IQCC_OK;
 }
@@ -1268,8 +1296,9 @@ int iqcc_qmf_energy_anti(iqcc_ctx* ctx, const iqcc_store* h, const uint64_t* px,
     return fail(ctx, IQCC_ERR_INVALID_ARG, "null argument");
   if (!padding_clear(h->nq, h->W, px, pz))
     return fail(ctx, IQCC_ERR_INVALID_ARG, "generator has bits beyond n_qubits");
-  launch_anti_sums(h->W, h->d, make_entangler(h->W, px, pz), h->nq, anti_grid(ctx), theta, phi, take_slot(ctx),
-                   energy_anti, nullptr, as_stream(stream));
+  hipStream_t s = as_stream(stream);
+  launch_anti_sums(h->W, h->d, make_entangler(h->W, px, pz), h->nq, anti_grid(ctx), theta, phi, sum_slot(ctx, s),
+                   energy_anti, nullptr, s);
   LAUNCH_CHECK(ctx);
   return IQCC_OK;
 }
@@ -1418,7 +1447,7 @@ int iqcc_qcc_iteration(iqcc_ctx* ctx, iqcc_store** h, iqcc_store** spare, const 
     uint64_t px[kMaxWords], pz[kMaxWords];
     std::memcpy(px, r + 1, sizeof(uint64_t) * W);
     std::memcpy(pz, r + 1 + W, sizeof(uint64_t) * W);
-    launch_anti_sums(W, (*h)->d, make_entangler(W, px, pz), (*h)->nq, anti_grid(ctx), theta, phi, take_slot(ctx),
+    launch_anti_sums(W, (*h)->d, make_entangler(W, px, pz), (*h)->nq, anti_grid(ctx), theta, phi, sum_slot(ctx, nullptr),
                      d_e + 2, d_e + 3, nullptr);
     LAUNCH_CHECK(ctx);
     HIP_TRY(ctx, hipMemcpy(sc, d_e, sizeof sc, hipMemcpyDeviceToHost));

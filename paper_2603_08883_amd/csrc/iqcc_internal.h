@@ -213,6 +213,11 @@ __device__ __forceinline__ FixedSum block_fixed_sum(FixedSum f, long long* tmp_h
 // workgroups meet at the root; more meet at the leaves first, because arrivals
 // at one address take their turns one by one.
 //
+// Two launches that may overlap must not arrive at one slot: their counts would
+// mix, and the counters would not come back to zero.  So a slot belongs to a
+// store that the launch writes, or to a stream; a launch that has neither leaves
+// its words and a second launch adds them (SumSlot).
+//
 // The words are agent-scope atomics, which go past the caches that other
 // workgroups do not share, and the arrival waits until they are written; it is
 // no release of everything else the workgroup wrote, which the end of the
@@ -253,6 +258,14 @@ __device__ __forceinline__ bool finish_arrive(double* slot, unsigned index, unsi
   asm volatile("" ::: "memory");
   return last != 0;
 }
+
+// Where a launch that writes no store leaves its workgroups' words.  single: in
+// a slot of its own stream, and the workgroup that arrives last adds them; else
+// a second launch does, in the same order, so both give the same bits.
+struct SumSlot {
+  double* slot;
+  bool single;
+};
 
 // Block-wide sum of doubles in a fixed order (lane tree, then waves in order).
 __device__ __forceinline__ double block_sum(double v, double* tmp) {
@@ -802,12 +815,12 @@ void launch_top_candidates(int W, const double* g, const uint64_t* cx, const uin
 // Sums over the terms that anticommute with P: c <K>, and (c_out not null) the
 // DIS gradient of P.  2 grid words of the slot.
 void launch_anti_sums(int W, const StoreDev& st, const Entangler& P, int nq, int grid, const double* theta,
-                      const double* phi, double* slot, double* b_out, double* c_out, hipStream_t s);
-// Stand-alone energy, one launch: *out = <st>.  per_cu: upper bound of the
-// workgroups per CU; slot: a finish slot (see finish_arrive); regions: rows in
+                      const double* phi, const SumSlot& slot, double* b_out, double* c_out, hipStream_t s);
+// Stand-alone energy: *out = <st>.  per_cu: upper bound of the workgroups per
+// CU; slot: at least kFinishWords words or one per bucket; regions: rows in
 // bucket regions.
 void launch_energy(int W, int nq, const StoreDev& st, bool regions, int n_cu, int per_cu, size_t lds_per_cu,
-                   const double* theta, const double* phi, double* slot, double* out, hipStream_t s);
+                   const double* theta, const double* phi, const SumSlot& slot, double* out, hipStream_t s);
 void launch_energy_backward(int W, int nq, const StoreDev& st, int grid, const double* theta, const double* phi,
                             const double* dE, double* lam /*null or [arena rows]*/, double* acc /*[3*nq][grid]*/,
                             double* dtheta, double* dphi, hipStream_t s);
@@ -824,8 +837,8 @@ int64_t dis_tile();   // candidates per workgroup of the batched kernel
 
 void launch_dress_backward(int W, const StoreDev& in, double C, double S,
                            const int32_t* tape_self, const int32_t* tape_partner,
-                           const double* lam_out, double* lam_in, double* slot /*3 grid words*/, double* dtau,
-                           int grid, hipStream_t s);
+                           const double* lam_out, double* lam_in, const SumSlot& slot /*3 grid words*/,
+                           double* dtau, int grid, hipStream_t s);
 void launch_expectations(int W, const StoreDev& st, const double* lut, const double* scale,
                          double* out, int grid, hipStream_t s);
 int64_t merge_scratch_len(int W, int64_t n, int m);

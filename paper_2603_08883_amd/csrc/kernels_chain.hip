@@ -23,12 +23,33 @@
 
 namespace iqcc {
 
+// dE/dt from the workgroups' parts, by one workgroup.
+__device__ __forceinline__ void dtau_total(const double* slot, unsigned active, long long* red_hi, long long* red_lo,
+                                           double* red_mag, double* dtau) {
+  FixedSum f;
+  for (unsigned i = threadIdx.x; i < active; i += kBlock) {
+    f.hi += __double_as_longlong(finish_get(slot, i));
+    f.lo += __double_as_longlong(finish_get(slot, active + i));
+    f.mag += finish_get(slot, 2 * active + i);
+  }
+  const FixedSum t = block_fixed_sum<kWaves>(f, red_hi, red_lo, red_mag);
+  if (threadIdx.x == 0) *dtau = fixed_value(t.hi, t.lo, t.mag);
+}
+
+// The second launch of a call without a slot of its stream.
+__global__ __launch_bounds__(kBlock) void k_dtau_total(StoreDev in, unsigned grid, const double* slot, double* dtau) {
+  __shared__ long long red_hi[kWaves], red_lo[kWaves];
+  __shared__ double red_mag[kWaves];
+  const int64_t B = 1ll << *in.m;
+  dtau_total(slot, B < grid ? (unsigned)B : grid, red_hi, red_lo, red_mag, dtau);
+}
+
 template <int W>
 __global__ __launch_bounds__(kBlock) void k_dress_backward(StoreDev in, double C,
                                                            double S, const int32_t* tape_self,
                                                            const int32_t* tape_partner,
                                                            const double* lam_out, double* lam_in,
-                                                           double* slot, double* dtau) {
+                                                           SumSlot sums, double* dtau) {
   __shared__ long long red_hi[kWaves], red_lo[kWaves];
   __shared__ double red_mag[kWaves];
   __shared__ int s_last;
@@ -56,31 +77,23 @@ __global__ __launch_bounds__(kBlock) void k_dress_backward(StoreDev in, double C
       fixed_add(acc, __dadd_rn(-__dmul_rn(__dmul_rn(S, c), la), s * __dmul_rn(__dmul_rn(C, c), lp)));
     }
   }
-  FixedSum t = block_fixed_sum<kWaves>(acc, red_hi, red_lo, red_mag);
+  const FixedSum t = block_fixed_sum<kWaves>(acc, red_hi, red_lo, red_mag);
   if (threadIdx.x < 64) {
     if (threadIdx.x == 0) {
-      finish_put(slot, blockIdx.x, __longlong_as_double(t.hi));
-      finish_put(slot, active + blockIdx.x, __longlong_as_double(t.lo));
-      finish_put(slot, 2 * active + blockIdx.x, t.mag);
+      finish_put(sums.slot, blockIdx.x, __longlong_as_double(t.hi));
+      finish_put(sums.slot, active + blockIdx.x, __longlong_as_double(t.lo));
+      finish_put(sums.slot, 2 * active + blockIdx.x, t.mag);
     }
-    const bool last = finish_arrive(slot, blockIdx.x, active);
+    const bool last = sums.single && finish_arrive(sums.slot, blockIdx.x, active);
     if (threadIdx.x == 0) s_last = last;
   }
   __syncthreads();
-  if (!s_last) return;
-  FixedSum f;
-  for (unsigned i = threadIdx.x; i < active; i += kBlock) {
-    f.hi += __double_as_longlong(finish_get(slot, i));
-    f.lo += __double_as_longlong(finish_get(slot, active + i));
-    f.mag += finish_get(slot, 2 * active + i);
-  }
-  t = block_fixed_sum<kWaves>(f, red_hi, red_lo, red_mag);
-  if (threadIdx.x == 0) *dtau = fixed_value(t.hi, t.lo, t.mag);
+  if (s_last) dtau_total(sums.slot, active, red_hi, red_lo, red_mag, dtau);
 }
 
 void launch_dress_backward(int W, const StoreDev& in, double C, double S,
                            const int32_t* tape_self, const int32_t* tape_partner,
-                           const double* lam_out, double* lam_in, double* slot, double* dtau, int grid,
+                           const double* lam_out, double* lam_in, const SumSlot& slot, double* dtau, int grid,
                            hipStream_t s) {
   switch (W) {
     case 1: hipLaunchKernelGGL(k_dress_backward<1>, dim3(grid), dim3(kBlock), 0, s, in, C, S, tape_self, tape_partner, lam_out, lam_in, slot, dtau); break;
@@ -88,6 +101,8 @@ void launch_dress_backward(int W, const StoreDev& in, double C, double S,
     case 3: hipLaunchKernelGGL(k_dress_backward<3>, dim3(grid), dim3(kBlock), 0, s, in, C, S, tape_self, tape_partner, lam_out, lam_in, slot, dtau); break;
     default: hipLaunchKernelGGL(k_dress_backward<4>, dim3(grid), dim3(kBlock), 0, s, in, C, S, tape_self, tape_partner, lam_out, lam_in, slot, dtau); break;
   }
+  if (!slot.single)
+    hipLaunchKernelGGL(k_dtau_total, dim3(1), dim3(kBlock), 0, s, in, (unsigned)grid, slot.slot, dtau);
 }
 
 // out[row] = scale * <K_row> for every live row of the store.

@@ -87,7 +87,8 @@ void launch_finalize_sum(const double* partial, int n, const double* scale, doub
 // with one workgroup per bucket, 10.4 with 512 rows, 10.3 with 1024, 11.5 with
 // 2048, 16 with stores below 16384 rows on one workgroup).
 // The active workgroups leave their sums in the finish slot; the last of them
-// to arrive adds them in a fixed order, so a call is one launch.
+// to arrive adds them in a fixed order, so a call is one launch (two without a
+// slot of the stream: 2 to 3 us more).
 //
 // Bound: HBM for large stores (40 bytes a two-word term), the chain of
 // latencies (bucket table, rows, table build, arrival) for small ones.
@@ -193,9 +194,38 @@ size_t energy_lds_bytes() {
          (size_t)(NT + 1) * 4;
 }
 
+// Workgroup g of the active ones takes the groups of G consecutive buckets g,
+// g + active, ... of the B buckets.
+struct EnergySplit {
+  int64_t B, G, ngroups;
+  unsigned active;
+};
+
+template <int NT>
+__device__ __forceinline__ EnergySplit energy_split(const StoreDev& st, unsigned grid) {
+  EnergySplit e;
+  e.B = 1ll << *st.m;
+  // at least kEMinRows rows per workgroup where the store has them
+  int64_t want = (*st.total + kEMinRows - 1) / kEMinRows;
+  want = want < 1 ? 1 : (want > grid ? grid : want);
+  e.G = (e.B + want - 1) / want;
+  e.G = e.G > NT ? NT : e.G;
+  e.ngroups = (e.B + e.G - 1) / e.G;
+  e.active = e.ngroups < want ? (unsigned)e.ngroups : (unsigned)want;
+  return e;
+}
+
+// The workgroups' sums in a fixed order, valid in thread 0.
+template <int NT>
+__device__ __forceinline__ double energy_total(const double* slot, unsigned active, double* red) {
+  double t = 0.0;
+  for (unsigned k = threadIdx.x; k < active; k += NT) t += finish_get(slot, k);
+  return block_sum_n<NT / 64>(t, red);
+}
+
 template <int W, int NT>
 __global__ __launch_bounds__(NT) void k_energy(StoreDev st, int nq, const double* theta, const double* phi,
-                                                     double* slot, double* out) {
+                                                     SumSlot sums, double* out) {
   extern __shared__ __align__(16) unsigned char smem_en[];
   double* lut = (double*)smem_en;
   double* tmp = lut + EnergyTable<W>::kEntries;                  // [kBuild]
@@ -204,14 +234,7 @@ __global__ __launch_bounds__(NT) void k_energy(StoreDev st, int nq, const double
   __shared__ double red[NT / 64];
   __shared__ uint64_t scan_tmp[NT / 64];
   __shared__ int s_last;
-  const int64_t B = 1ll << *st.m;
-  // at least kEMinRows rows per workgroup where the store has them
-  int64_t want = (*st.total + kEMinRows - 1) / kEMinRows;
-  want = want < 1 ? 1 : (want > gridDim.x ? gridDim.x : want);
-  int64_t G = (B + want - 1) / want;
-  G = G > NT ? NT : G;
-  const int64_t ngroups = (B + G - 1) / G;
-  const unsigned active = ngroups < want ? (unsigned)ngroups : (unsigned)want;
+  const auto [B, G, ngroups, active] = energy_split<NT>(st, gridDim.x);
   if (blockIdx.x >= active) return;
   // (the factors' chain of loads and sines beside that of the bucket table)
   build_factors<W, NT>(tmp, nq, theta, phi);
@@ -272,27 +295,37 @@ __global__ __launch_bounds__(NT) void k_energy(StoreDev st, int nq, const double
     } while (i0 < n);
   }
   const double s = block_sum_n<NT / 64>(acc, red);
+  if (!sums.single) {
+    if (threadIdx.x == 0) finish_put(sums.slot, blockIdx.x, s);
+    return;
+  }
   if (active == 1) {
     if (threadIdx.x == 0) *out = s;
     return;
   }
   if (threadIdx.x < 64) {
-    if (threadIdx.x == 0) finish_put(slot, blockIdx.x, s);
-    const bool last = finish_arrive(slot, blockIdx.x, active);
+    if (threadIdx.x == 0) finish_put(sums.slot, blockIdx.x, s);
+    const bool last = finish_arrive(sums.slot, blockIdx.x, active);
     if (threadIdx.x == 0) s_last = last;
   }
   __syncthreads();
   if (s_last) {
-    double t = 0.0;
-    for (unsigned k = threadIdx.x; k < active; k += NT) t += finish_get(slot, k);
-    t = block_sum_n<NT / 64>(t, red);
+    const double t = energy_total<NT>(sums.slot, active, red);
     if (threadIdx.x == 0) *out = t;
   }
 }
 
+// The second launch of a call without a slot of its stream.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_energy_total(StoreDev st, unsigned grid, const double* slot, double* out) {
+  __shared__ double red[NT / 64];
+  const double t = energy_total<NT>(slot, energy_split<NT>(st, grid).active, red);
+  if (threadIdx.x == 0) *out = t;
+}
+
 template <int W, int NT>
 static void launch_energy_w(int nq, const StoreDev& st, int n_cu, int per_cu, size_t lds_per_cu, const double* theta,
-                            const double* phi, double* slot, double* out, hipStream_t s) {
+                            const double* phi, const SumSlot& slot, double* out, hipStream_t s) {
   const size_t lds = energy_lds_bytes<W, NT>();
   // resident workgroups per CU: LDS (with the static part), 2048 threads
   int fit = (int)(lds_per_cu / (lds + 256));
@@ -301,6 +334,8 @@ static void launch_energy_w(int nq, const StoreDev& st, int n_cu, int per_cu, si
   if (grid > kFinishWords) grid = kFinishWords;
   (void)hipFuncSetAttribute((const void*)k_energy<W, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL((k_energy<W, NT>), dim3(grid), dim3(NT), lds, s, st, nq, theta, phi, slot, out);
+  if (!slot.single)
+    hipLaunchKernelGGL(k_energy_total<NT>, dim3(1), dim3(NT), 0, s, st, (unsigned)grid, slot.slot, out);
 }
 
 // A CU's LDS holds one table of two-word keys.  Where the rows of a store lie in
@@ -308,7 +343,7 @@ static void launch_energy_w(int nq, const StoreDev& st, int n_cu, int per_cu, si
 // 1024 threads, the waves of two (5.4e7 terms 552 us with 512, 499 with 1024);
 // loaded rows stream faster with 512 (1.6e7 terms 121 us, 125).
 void launch_energy(int W, int nq, const StoreDev& st, bool regions, int n_cu, int per_cu, size_t lds_per_cu, const double* theta,
-                   const double* phi, double* slot, double* out, hipStream_t s) {
+                   const double* phi, const SumSlot& slot, double* out, hipStream_t s) {
   switch (W) {
     case 1: launch_energy_w<1, 512>(nq, st, n_cu, per_cu, lds_per_cu, theta, phi, slot, out, s); break;
     case 2:

@@ -236,9 +236,32 @@ void launch_top_candidates(int W, const double* g, const uint64_t* cx, const uin
 // workgroup that arrives last adds the sums in a fixed order.  (Table, sum of
 // b, reduction, table, counter and the plain one-candidate gradient were six
 // launches: 49 us on 12,007 to 40,000 one-word terms, this takes 10 us.)
+__device__ __forceinline__ void anti_total(const double* slot, unsigned active, double* red, double* b_out,
+                                           double* c_out) {
+  double tb = 0.0, tc = 0.0;
+  for (unsigned i = threadIdx.x; i < active; i += kBlock) {
+    tb += finish_get(slot, i);
+    tc += finish_get(slot, active + i);
+  }
+  tb = block_sum(tb, red);
+  tc = block_sum(tc, red);
+  if (threadIdx.x == 0) {
+    *b_out = tb;
+    if (c_out) *c_out = tc;
+  }
+}
+
+// The second launch of a call without a slot of its stream.
+__global__ __launch_bounds__(kBlock) void k_anti_total(StoreDev st, unsigned grid, const double* slot, double* b_out,
+                                                       double* c_out) {
+  __shared__ double red[kWaves];
+  const int64_t B = 1ll << *st.m;
+  anti_total(slot, B < grid ? (unsigned)B : grid, red, b_out, c_out);
+}
+
 template <int W>
 __global__ __launch_bounds__(kBlock) void k_anti_sums(StoreDev st, Entangler P, int nq, const double* theta,
-                                                      const double* phi, double* slot, double* b_out, double* c_out) {
+                                                      const double* phi, SumSlot sums, double* b_out, double* c_out) {
   __shared__ double lut[W * kGroupsPerWord * kLutEntries];
   __shared__ double fq[256 * W];
   __shared__ double red[kWaves];
@@ -269,35 +292,26 @@ __global__ __launch_bounds__(kBlock) void k_anti_sums(StoreDev st, Entangler P, 
   sc = block_sum(sc, red);
   if (threadIdx.x < 64) {
     if (threadIdx.x == 0) {
-      finish_put(slot, blockIdx.x, sb);
-      finish_put(slot, active + blockIdx.x, sc);
+      finish_put(sums.slot, blockIdx.x, sb);
+      finish_put(sums.slot, active + blockIdx.x, sc);
     }
-    const bool last = finish_arrive(slot, blockIdx.x, active);
+    const bool last = sums.single && finish_arrive(sums.slot, blockIdx.x, active);
     if (threadIdx.x == 0) s_last = last;
   }
   __syncthreads();
-  if (!s_last) return;
-  double tb = 0.0, tc = 0.0;
-  for (unsigned i = threadIdx.x; i < active; i += kBlock) {
-    tb += finish_get(slot, i);
-    tc += finish_get(slot, active + i);
-  }
-  tb = block_sum(tb, red);
-  tc = block_sum(tc, red);
-  if (threadIdx.x == 0) {
-    *b_out = tb;
-    if (c_out) *c_out = tc;
-  }
+  if (s_last) anti_total(sums.slot, active, red, b_out, c_out);
 }
 
 void launch_anti_sums(int W, const StoreDev& st, const Entangler& P, int nq, int grid, const double* theta,
-                      const double* phi, double* slot, double* b_out, double* c_out, hipStream_t s) {
+                      const double* phi, const SumSlot& slot, double* b_out, double* c_out, hipStream_t s) {
   switch (W) {
     case 1: hipLaunchKernelGGL(k_anti_sums<1>, dim3(grid), dim3(kBlock), 0, s, st, P, nq, theta, phi, slot, b_out, c_out); break;
     case 2: hipLaunchKernelGGL(k_anti_sums<2>, dim3(grid), dim3(kBlock), 0, s, st, P, nq, theta, phi, slot, b_out, c_out); break;
     case 3: hipLaunchKernelGGL(k_anti_sums<3>, dim3(grid), dim3(kBlock), 0, s, st, P, nq, theta, phi, slot, b_out, c_out); break;
     default: hipLaunchKernelGGL(k_anti_sums<4>, dim3(grid), dim3(kBlock), 0, s, st, P, nq, theta, phi, slot, b_out, c_out); break;
   }
+  if (!slot.single)
+    hipLaunchKernelGGL(k_anti_total, dim3(1), dim3(kBlock), 0, s, st, (unsigned)grid, slot.slot, b_out, c_out);
 }
 
 }  // namespace iqcc

@@ -3,7 +3,10 @@
 Steps that write different stores share nothing: a long step on one stream
 with many short ones beside it, and a captured chain of steps replayed beside
 eager ones, leave what the same calls leave one after another (the sums of a
-step's workgroups lie in the memory of the store that it writes)."""
+step's workgroups lie in the memory of the store that it writes).  Sums over a
+store that is only read give the same bits on many streams, captured and
+replayed beside eager ones, and after all of these.  (Captured sums do not
+overlap each other here: that they may not is documented.)"""
 import numpy as np
 import pytest
 import torch
@@ -110,3 +113,103 @@ def test_captured_chain_beside_eager_steps(ctx):
         assert_same_terms(others[it].to_numpy(), ref)
     for o in (src, *outs, *others):
         o.close()
+
+
+class Sums:
+    """Every call that only reads stores, on a step of a small Hamiltonian."""
+
+    def __init__(self, ctx, nq=40, n=3000):
+        self.ctx = ctx
+        x, z, c = random_terms(nq, n, nq + n)
+        self.p = I.single_qubit_pauli(nq, "XYZ")
+        self.th, self.ph = (torch.from_numpy(a).cuda() for a in I.qmf_angles(nq, np.random.default_rng(2)))
+        self.h = iqcc.Store(ctx, nq, 2 * len(c)).load_numpy(x, z, c)
+        self.out = iqcc.Store(ctx, nq, 2 * len(c))
+        rows = iqcc.iqcc_store_rows(self.h.handle)
+        self.tapes = [torch.empty(rows, dtype=torch.int32, device="cuda") for _ in range(2)]
+        iqcc.iqcc_dress_taped(ctx.handle, self.h.handle, *self.p, 0.3, 0.0, self.out.handle, *self.tapes)
+        self.lam = torch.linspace(-1, 1, iqcc.iqcc_store_rows(self.out.handle), dtype=torch.float64, device="cuda")
+        self.oracle = O.qmf_energy(nq, x, z, c, self.th.cpu().numpy(), self.ph.cpu().numpy())
+        torch.cuda.synchronize()
+
+    def run(self, res, stream=None):
+        """energy, allocation-free energy, energy of the anticommuting terms, dE/dtau and the
+        cotangents of the step's input into res (a list of tensors)."""
+        a = (self.ctx.handle, self.h.handle)
+        iqcc.iqcc_qmf_energy(*a, self.th, self.ph, res[0], stream=stream)
+        iqcc.iqcc_qmf_energy_noalloc(*a, self.th, self.ph, res[1], stream=stream)
+        iqcc.iqcc_qmf_energy_anti(*a, *self.p, self.th, self.ph, res[2], stream=stream)
+        iqcc.iqcc_dress_backward(*a, *self.p, 0.3, *self.tapes, self.lam, res[4], res[3], stream=stream)
+
+    def buffers(self):
+        d = dict(dtype=torch.float64, device="cuda")
+        return [torch.full((), 7.0, **d) for _ in range(4)] + [torch.full((iqcc.iqcc_store_rows(self.h.handle),), 7.0, **d)]
+
+    def close(self):
+        self.h.close()
+        self.out.close()
+
+
+def same_bits(a, b):
+    return all(torch.equal(u, v) for u, v in zip(a, b))
+
+
+def test_sums_on_many_streams(ctx):
+    """More streams than have sums of their own, each a few calls ahead of the
+    others; streams beyond those one after another (see the header)."""
+    t = Sums(ctx)
+    ref = t.buffers()
+    t.run(ref)
+    torch.cuda.synchronize()
+    assert abs(ref[0].item() - t.oracle) <= 1e-10 and ref[0].item() == ref[1].item()
+    streams = [torch.cuda.Stream() for _ in range(20)]
+    handles = {s.cuda_stream for s in streams}
+    describe(0, "sums on many streams", n=t.h.count(), streams=len(handles))
+    for it in range(3):
+        got = {s: [t.buffers() for _ in range(12)] for s in streams}
+        torch.cuda.synchronize()
+        for k in range(12):
+            for s in streams[:12]:
+                a = (ctx.handle, t.h.handle)
+                r = got[s][k]
+                iqcc.iqcc_qmf_energy(*a, t.th, t.ph, r[0], stream=s.cuda_stream)
+                iqcc.iqcc_qmf_energy_anti(*a, *t.p, t.th, t.ph, r[2], stream=s.cuda_stream)
+                iqcc.iqcc_dress_backward(*a, *t.p, 0.3, *t.tapes, t.lam, r[4], r[3], stream=s.cuda_stream)
+        torch.cuda.synchronize()
+        for s in streams[:12]:
+            for r in got[s]:
+                assert same_bits(r[:1] + r[2:], ref[:1] + ref[2:])
+        for s in streams[12:]:
+            t.run(got[s][0], s.cuda_stream)
+            torch.cuda.synchronize()
+            assert same_bits(got[s][0], ref)
+    t.close()
+
+
+def test_captured_sums(ctx):
+    t = Sums(ctx)
+    ref, cap, eager = t.buffers(), t.buffers(), t.buffers()
+    t.run(ref)
+    t.run(cap)
+    torch.cuda.synchronize()
+    g, s, b = torch.cuda.CUDAGraph(), torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.graph(g, stream=s):
+        t.run(cap)
+    for it in range(6):
+        describe(it, "captured sums")
+        for r in cap + eager:
+            r.fill_(7.0)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            g.replay()
+        for _ in range(40):
+            a = (ctx.handle, t.h.handle)
+            iqcc.iqcc_qmf_energy(*a, t.th, t.ph, eager[0], stream=b.cuda_stream)
+            iqcc.iqcc_qmf_energy_anti(*a, *t.p, t.th, t.ph, eager[2], stream=b.cuda_stream)
+            iqcc.iqcc_dress_backward(*a, *t.p, 0.3, *t.tapes, t.lam, eager[4], eager[3], stream=b.cuda_stream)
+        torch.cuda.synchronize()
+        iqcc.iqcc_qmf_energy_noalloc(ctx.handle, t.h.handle, t.th, t.ph, eager[1])
+        torch.cuda.synchronize()
+        assert same_bits(cap, ref)
+        assert same_bits(eager, ref)
+    t.close()
