@@ -15,19 +15,14 @@
 // factors.  Plain form: one launch per candidate streaming all terms
 // (reference form).
 #include "iqcc_internal.h"
+#include "work_split.h"
 
 #pragma clang fp contract(off)
 
 namespace iqcc {
 
-constexpr int kDisB = 256;          // threads per workgroup of the batched kernel
 constexpr int kDisWaves = kDisB / 64;
-constexpr int kDisR = 8;            // terms per lane of a full pass
 constexpr int kDisTile = 256;       // candidates staged at once
-constexpr int kDisChunk = kDisB;    // buckets whose prefix sums are staged at once
-constexpr int kDisPass = kDisB * kDisR;
-constexpr int kDisRun = 16;     // least candidates of a workgroup's run, if there are as many
-constexpr int kDisFill = 256;   // workgroups that give every CU one
 
 // Spread the 16 bits of v to the even bits of a 32-bit word.
 __device__ __forceinline__ uint32_t spread16(uint32_t v) {
@@ -69,24 +64,6 @@ __device__ __forceinline__ double wave_sum_to_lane63(double v) {
   v += dpp_f64(v, 4);   // rows 1 and 3 add rows 0 and 2 (other rows add +0)
   v += dpp_f64(v, 5);   // rows 2 and 3 add rows 0..1
   return v;
-}
-
-// Buckets per term range of a batched launch: as many as fill one pass (with
-// 2 % to spare, so that uneven buckets seldom spill a few terms into a second
-// pass: on 1e6 terms in 4096 buckets, ranges of 8.4 buckets took 2320 us, of 8
-// 1902 us), but no more than max_ranges ranges; `fixed`: max_ranges ranges.
-// Where that leaves CUs without a run of candidates, the ranges are halved, to
-// 4 and to 2 terms a lane: then a workgroup's loads, not its candidates, are the
-// time (200,000 two-word terms x 16 candidates 54 us with 98 ranges, 30 with
-// 391; x 64, which fill the chip, 69 and 78).
-__device__ __forceinline__ int64_t dis_range_buckets(int64_t total, int64_t buckets, int max_ranges, int fixed,
-                                                     int64_t n_cand) {
-  const int64_t least = (buckets + max_ranges - 1) / max_ranges;
-  if (fixed || total <= 0) return least;
-  int pass = kDisPass;
-  while (pass > 2 * kDisB && (total / pass + 1) * ((n_cand + kDisRun - 1) / kDisRun) < kDisFill) pass /= 2;
-  const int64_t fill = (int64_t)((double)buckets * (pass / 1.02) / (double)total);
-  return fill < least ? least : (fill > buckets ? buckets : fill);
 }
 
 template <int W>
@@ -241,12 +218,12 @@ __global__ __launch_bounds__(kDisB, W <= 2 ? 3 : 2) void k_dis_batched(StoreDev 
                                                        const uint64_t* __restrict__ cx,
                                                        const uint64_t* __restrict__ cz, int64_t n_cand,
                                                        int64_t ld_cand, int tile_size, int max_ranges, int fixed,
-                                                       double* __restrict__ partial) {
+                                                       int n_cu, double* __restrict__ partial) {
   constexpr int NQ = 64 * W, NS = 4 * W;
   extern __shared__ __align__(16) unsigned char smem_dis[];
   DisShared<W>& sh = *reinterpret_cast<DisShared<W>*>(smem_dis);
   const int64_t B = 1ll << *st.m;
-  const int64_t per = dis_range_buckets(*st.total, B, max_ranges, fixed, n_cand);
+  const int64_t per = dis_range_buckets(*st.total, B, max_ranges, fixed, n_cand, n_cu);
   const int64_t nr = (B + per - 1) / per;
   int64_t run = (nr * n_cand + gridDim.x - 1) / gridDim.x;
   const int64_t least = n_cand < kDisRun ? n_cand : kDisRun;
@@ -355,9 +332,9 @@ int64_t dis_tile() { return kDisTile; }   // the largest tile the batched kernel
 // order.  (One thread per candidate walked all ranges alone: 243 us for 2048
 // ranges of 5 candidates.)
 __global__ __launch_bounds__(kBlock) void k_dis_reduce(StoreDev st, const double* partial, int max_ranges, int fixed,
-                                                       int64_t n_cand, double* g) {
+                                                       int n_cu, int64_t n_cand, double* g) {
   __shared__ double red[16][17];
-  const int64_t B = 1ll << *st.m, per = dis_range_buckets(*st.total, B, max_ranges, fixed, n_cand);
+  const int64_t B = 1ll << *st.m, per = dis_range_buckets(*st.total, B, max_ranges, fixed, n_cand, n_cu);
   const int64_t nr = (B + per - 1) / per;
   const int t = threadIdx.x & 15, l = threadIdx.x >> 4;
   const int64_t a = blockIdx.x * 16ll + t;
@@ -564,7 +541,7 @@ static void launch_dis_w(const StoreDev& st, const double* theta, const double* 
   // candidates: 1903 us with the resident ones alone, 1678 us with four times,
   // 1731 us with eight times as many: each builds its tables)
   hipLaunchKernelGGL(k_dis_batched<W>, dim3(n_cu * (W <= 2 ? 12 : 8)), dim3(kDisB), lds, s, st, nq, theta, phi, cx, cz,
-                     n_cand, ld_cand, tile, max_ranges, fixed, partial);
+                     n_cand, ld_cand, tile, max_ranges, fixed, n_cu, partial);
 }
 
 void launch_dis_batched(int W, const StoreDev& st, const double* theta, const double* phi, int nq, const uint64_t* cx,
@@ -579,7 +556,7 @@ void launch_dis_batched(int W, const StoreDev& st, const double* theta, const do
     default: launch_dis_w<4>(st, theta, phi, nq, cx, cz, n_cand, ld_cand, tile, n_cu, max_ranges, fixed, partial, s); break;
   }
   hipLaunchKernelGGL(k_dis_reduce, dim3((unsigned)((n_cand + 15) / 16)), dim3(kBlock), 0, s, st, partial, max_ranges,
-                     fixed, n_cand, g);
+                     fixed, n_cu, n_cand, g);
 }
 
 void launch_dis_plain(int W, const StoreDev& st, const double* lut, const uint64_t* cx, const uint64_t* cz,

@@ -8,6 +8,7 @@
 #include <cfloat>
 
 #include "iqcc_internal.h"
+#include "work_split.h"
 
 #pragma clang fp contract(off)
 
@@ -80,12 +81,10 @@ void launch_finalize_sum(const double* partial, int n, const double* scale, doub
 // leave few waves per CU.
 //
 // The grid holds what the CUs keep resident (more workgroups would only build
-// more tables), and of it one workgroup per kEMinRows rows of the store takes
-// part ("active"): with fewer rows a workgroup would spend its
-// time on its table and its arrival, with more on another round of bucket
-// searches and loads (a call over the stores of a 32-Hamiltonian batch: 17.1 us
-// with one workgroup per bucket, 10.4 with 512 rows, 10.3 with 1024, 11.5 with
-// 2048, 16 with stores below 16384 rows on one workgroup).
+// more tables), and of it as many workgroups take part ("active") as the rows
+// and the buckets ask for (energy_buckets): with fewer rows a workgroup would
+// spend its time on its table and its arrival, with more on another round of
+// bucket searches and loads.
 // The active workgroups leave their sums in the finish slot; the last of them
 // to arrive adds them in a fixed order, so a call is one launch (two without a
 // slot of the stream: 2 to 3 us more).
@@ -96,7 +95,6 @@ void launch_finalize_sum(const double* partial, int n, const double* scale, doub
 // launches: 168 us); 361 terms: 6.6 us (23 us).
 // ---------------------------------------------------------------------------
 constexpr int kEItems = 4;
-constexpr int64_t kEMinRows = 1024;
 constexpr int kNibbleEntries = 256;
 constexpr int kNibblesPerWord = 16;
 
@@ -194,25 +192,9 @@ size_t energy_lds_bytes() {
          (size_t)(NT + 1) * 4;
 }
 
-// Workgroup g of the active ones takes the groups of G consecutive buckets g,
-// g + active, ... of the B buckets.
-struct EnergySplit {
-  int64_t B, G, ngroups;
-  unsigned active;
-};
-
 template <int NT>
-__device__ __forceinline__ EnergySplit energy_split(const StoreDev& st, unsigned grid) {
-  EnergySplit e;
-  e.B = 1ll << *st.m;
-  // at least kEMinRows rows per workgroup where the store has them
-  int64_t want = (*st.total + kEMinRows - 1) / kEMinRows;
-  want = want < 1 ? 1 : (want > grid ? grid : want);
-  e.G = (e.B + want - 1) / want;
-  e.G = e.G > NT ? NT : e.G;
-  e.ngroups = (e.B + e.G - 1) / e.G;
-  e.active = e.ngroups < want ? (unsigned)e.ngroups : (unsigned)want;
-  return e;
+__device__ __forceinline__ BucketSplit energy_split(const StoreDev& st, unsigned grid) {
+  return energy_buckets(*st.total, 1ll << *st.m, grid, NT);
 }
 
 // The workgroups' sums in a fixed order, valid in thread 0.
@@ -234,7 +216,10 @@ __global__ __launch_bounds__(NT) void k_energy(StoreDev st, int nq, const double
   __shared__ double red[NT / 64];
   __shared__ uint64_t scan_tmp[NT / 64];
   __shared__ int s_last;
-  const auto [B, G, ngroups, active] = energy_split<NT>(st, gridDim.x);
+  const int64_t B = 1ll << *st.m;
+  const BucketSplit split = energy_split<NT>(st, gridDim.x);
+  const int64_t G = split.G, ngroups = split.ngroups;
+  const unsigned active = (unsigned)split.active;
   if (blockIdx.x >= active) return;
   // (the factors' chain of loads and sines beside that of the bucket table)
   build_factors<W, NT>(tmp, nq, theta, phi);
@@ -319,7 +304,7 @@ __global__ __launch_bounds__(NT) void k_energy(StoreDev st, int nq, const double
 template <int NT>
 __global__ __launch_bounds__(NT) void k_energy_total(StoreDev st, unsigned grid, const double* slot, double* out) {
   __shared__ double red[NT / 64];
-  const double t = energy_total<NT>(slot, energy_split<NT>(st, grid).active, red);
+  const double t = energy_total<NT>(slot, (unsigned)energy_split<NT>(st, grid).active, red);
   if (threadIdx.x == 0) *out = t;
 }
 
@@ -415,7 +400,6 @@ struct BwdGeom {
   static constexpr int kThreads = 64 * kTeamWaves * kTeams;
   static constexpr int kSplit = kTeamWaves / kBlocks;   // waves that share a block's terms
 };
-constexpr int kBwdGroup = 256;     // most buckets per group of one flat range
 constexpr int kDigits = 32;
 constexpr int kDigitStride = 80;   // bytes per digit row of 64 terms (padded: 16-byte reads of 8 lanes hit all banks)
 constexpr int kDigitBase = -186;   // log2 of the lowest digit's weight
@@ -441,13 +425,6 @@ struct BwdShared {
   static_assert(sizeof(lut) + sizeof(fac) + sizeof(bytes) + sizeof(dig) >= sizeof(int) * 96 * B::kBlocks * kDigits,
                 "the digit sums fit");
 };
-
-// Workgroups that take part: one per kThreads rows, at most grid and one per bucket.
-__device__ __forceinline__ int64_t bwd_active(int64_t total, int64_t buckets, int grid, int threads) {
-  int64_t a = (total + threads - 1) / threads;
-  a = a < 1 ? 1 : (a > grid ? grid : a);
-  return a > buckets ? buckets : a;
-}
 
 // Bytes of dword d (4 rows of 64 bytes, one byte per term) of every lane's key:
 // the 4 x 4 bytes of four lanes are transposed, and each lane writes the dword
@@ -522,7 +499,8 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
   extern __shared__ __align__(16) unsigned char smem_bwd[];
   BwdShared<W>& sh = *reinterpret_cast<BwdShared<W>*>(smem_bwd);
   const int64_t B = 1ll << *st.m;
-  const int64_t active = bwd_active(*st.total, B, (int)gridDim.x, NT);
+  const BucketSplit split = gradient_buckets(*st.total, B, gridDim.x, NT);
+  const int64_t active = split.active, G = split.G, ngroups = split.ngroups;
   if (blockIdx.x >= active) return;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -560,9 +538,6 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
   // Workgroup g takes the groups of G consecutive buckets g, g + active, ...;
   // a group's rows are one flat range, one term per thread and pass, the next
   // pass's term loaded while this one's bits are multiplied.
-  int64_t G = (B + active - 1) / active;
-  G = G > kBwdGroup ? kBwdGroup : G;
-  const int64_t ngroups = (B + G - 1) / G;
   for (int64_t grp = blockIdx.x; grp < ngroups; grp += active) {
     const int64_t b = grp * G + threadIdx.x;
     const bool mine = threadIdx.x < G && b < B;
@@ -738,7 +713,7 @@ __global__ __launch_bounds__(kBlock) void k_backward_finalize(StoreDev st, int t
                                                               const double* dE, double* dtheta, double* dphi) {
   __shared__ double red[kWaves];
   const int q = blockIdx.x;
-  const int active = (int)bwd_active(*st.total, 1ll << *st.m, grid, threads);
+  const int active = (int)gradient_buckets(*st.total, 1ll << *st.m, grid, threads).active;
   double S[3] = {0.0, 0.0, 0.0};
   for (int g = threadIdx.x; g < active; g += kBlock) {
 #pragma unroll

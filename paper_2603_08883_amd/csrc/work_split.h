@@ -1,0 +1,78 @@
+// How the kernels that walk a store's bucket table share it among workgroups.
+// Plain C++ (constexpr functions serve the device too), so that the rules can be
+// checked on the host over all sizes.
+//
+// A workgroup walks its buckets in groups of at most as many as it has threads
+// for, one group after another, and a group costs a chain of loads (about
+// 2.6 us) even where its buckets are empty.  So the rows alone do not decide: an
+// in-place store may have far more buckets than terms, and then there are as
+// many workgroups as groups.  1000 two-word terms in 2^16 / 2^19 buckets: energy
+// 32 / 39 us (393 / 3082 with the rows alone, and 48 / 50 with up to four groups a
+// workgroup), angle gradient 38 / 63 us (519 / 2713), DIS of 40
+// candidates 114 / 320 us (7540 / 25250).
+#pragma once
+
+#include <stdint.h>
+
+namespace iqcc {
+
+// Groups of G consecutive buckets; workgroup g of the `active` ones takes the
+// groups g, g + active, ...
+struct BucketSplit {
+  int64_t G, ngroups, active;
+};
+
+// One workgroup per rows_each rows or per group of `most` buckets, whichever
+// are more, at most grid.
+constexpr BucketSplit split_buckets(int64_t rows, int64_t buckets, int64_t grid, int64_t rows_each, int64_t most) {
+  const int64_t by_rows = (rows + rows_each - 1) / rows_each;
+  const int64_t by_buckets = (buckets + most - 1) / most;
+  int64_t want = by_rows > by_buckets ? by_rows : by_buckets;
+  want = want < 1 ? 1 : (want > grid ? grid : want);
+  want = want > buckets ? buckets : want;
+  int64_t G = (buckets + want - 1) / want;
+  G = G > most ? most : G;
+  const int64_t ngroups = (buckets + G - 1) / G;
+  return {G, ngroups, ngroups < want ? ngroups : want};
+}
+
+// Energy.  rows_each: a call over the stores of a 32-Hamiltonian batch takes
+// 10.4 us with 512 rows, 10.3 with 1024, 11.5 with 2048.
+constexpr int64_t kEnergyRows = 1024;
+constexpr BucketSplit energy_buckets(int64_t rows, int64_t buckets, int64_t grid, int threads) {
+  return split_buckets(rows, buckets, grid, kEnergyRows, threads);
+}
+
+// Angle gradient, a row per thread.
+constexpr int kBwdGroup = 256;     // most buckets per group of one flat range
+constexpr BucketSplit gradient_buckets(int64_t rows, int64_t buckets, int64_t grid, int threads) {
+  return split_buckets(rows, buckets, grid, threads, kBwdGroup);
+}
+
+constexpr int kDisB = 256;          // threads per workgroup of the batched DIS kernel
+constexpr int kDisR = 8;            // terms per lane of a full pass
+constexpr int kDisChunk = kDisB;    // buckets whose prefix sums are staged at once
+constexpr int kDisPass = kDisB * kDisR;
+constexpr int kDisRun = 16;         // least candidates of a workgroup's run, if there are as many
+
+// Buckets per term range of a batched DIS launch: as many as fill one pass (with
+// 2 % to spare, so that uneven buckets seldom spill a few terms into a second
+// pass: on 1e6 terms in 4096 buckets, ranges of 8.4 buckets took 2320 us, of 8
+// 1902 us), but no more than max_ranges ranges; `fixed`: max_ranges ranges.
+// Where that leaves CUs without a run of candidates, the ranges are halved, to
+// 4 and to 2 terms a lane: then a workgroup's loads, not its candidates, are the
+// time (200,000 two-word terms x 16 candidates 54 us with 98 ranges, 30 with
+// 391; x 64, which fill the chip, 69 and 78).  And no more than one chunk of
+// buckets.
+constexpr int64_t dis_range_buckets(int64_t rows, int64_t buckets, int max_ranges, int fixed, int64_t n_cand,
+                                    int n_cu) {
+  const int64_t least = (buckets + max_ranges - 1) / max_ranges;
+  if (fixed || rows <= 0) return least;
+  int pass = kDisPass;
+  while (pass > 2 * kDisB && (rows / pass + 1) * ((n_cand + kDisRun - 1) / kDisRun) < n_cu) pass /= 2;
+  int64_t fill = (int64_t)((double)buckets * (pass / 1.02) / (double)rows);
+  fill = fill > kDisChunk ? kDisChunk : fill;
+  return fill < least ? least : (fill > buckets ? buckets : fill);
+}
+
+}  // namespace iqcc
