@@ -235,16 +235,18 @@ void launch_top_candidates(int W, const double* g, const uint64_t* cx, const uin
 // groups P does not touch, the table is built in every workgroup, and the
 // workgroup that arrives last adds the sums in a fixed order.  (Table, sum of
 // b, reduction, table, counter and the plain one-candidate gradient were six
-// launches: 49 us on 12,007 to 40,000 one-word terms, this takes 10 us.)
+// launches: 49 us on 12,007 to 40,000 one-word terms, this takes 10 us.)  C: with
+// the second sum; without it only <K> is formed (3e6 one-word terms 64 -> 58 us,
+// 3e5 four-word terms in 2^15 bucket regions 401 -> 367).
 __device__ __forceinline__ void anti_total(const double* slot, unsigned active, double* red, double* b_out,
                                            double* c_out) {
   double tb = 0.0, tc = 0.0;
   for (unsigned i = threadIdx.x; i < active; i += kBlock) {
     tb += finish_get(slot, i);
-    tc += finish_get(slot, active + i);
+    if (c_out) tc += finish_get(slot, active + i);
   }
   tb = block_sum(tb, red);
-  tc = block_sum(tc, red);
+  if (c_out) tc = block_sum(tc, red);
   if (threadIdx.x == 0) {
     *b_out = tb;
     if (c_out) *c_out = tc;
@@ -259,7 +261,7 @@ __global__ __launch_bounds__(kBlock) void k_anti_total(StoreDev st, unsigned gri
   anti_total(slot, B < grid ? (unsigned)B : grid, red, b_out, c_out);
 }
 
-template <int W>
+template <int W, bool C>
 __global__ __launch_bounds__(kBlock) void k_anti_sums(StoreDev st, Entangler P, int nq, const double* theta,
                                                       const double* phi, SumSlot sums, double* b_out, double* c_out) {
   __shared__ double lut[W * kGroupsPerWord * kLutEntries];
@@ -280,20 +282,24 @@ __global__ __launch_bounds__(kBlock) void k_anti_sums(StoreDev st, Entangler P, 
         kx[w] = st.x[w * st.cap + off + i];
         kz[w] = st.z[w * st.cap + off + i];
       }
-      const double c = st.c[off + i];
       if (!anticommutes<W>(kx, kz, P.px, P.pz)) continue;
-      double ek, ekp;
-      expect_split<W>(lut, P, kx, kz, ek, ekp);
-      sb += c * ek;
-      sc += product_phase<W>(kx, kz, P.px, P.pz) == 1 ? c * ekp : -(c * ekp);
+      const double c = st.c[off + i];
+      if constexpr (C) {
+        double ek, ekp;
+        expect_split<W>(lut, P, kx, kz, ek, ekp);
+        sb += c * ek;
+        sc += product_phase<W>(kx, kz, P.px, P.pz) == 1 ? c * ekp : -(c * ekp);
+      } else {
+        sb += c * expect_lut<W>(lut, kx, kz);
+      }
     }
   }
   sb = block_sum(sb, red);
-  sc = block_sum(sc, red);
+  if (C) sc = block_sum(sc, red);
   if (threadIdx.x < 64) {
     if (threadIdx.x == 0) {
       finish_put(sums.slot, blockIdx.x, sb);
-      finish_put(sums.slot, active + blockIdx.x, sc);
+      if (C) finish_put(sums.slot, active + blockIdx.x, sc);
     }
     const bool last = sums.single && finish_arrive(sums.slot, blockIdx.x, active);
     if (threadIdx.x == 0) s_last = last;
@@ -302,13 +308,22 @@ __global__ __launch_bounds__(kBlock) void k_anti_sums(StoreDev st, Entangler P, 
   if (s_last) anti_total(sums.slot, active, red, b_out, c_out);
 }
 
+template <int W>
+static void launch_anti_w(const StoreDev& st, const Entangler& P, int nq, int grid, const double* theta,
+                          const double* phi, const SumSlot& slot, double* b_out, double* c_out, hipStream_t s) {
+  if (c_out)
+    hipLaunchKernelGGL((k_anti_sums<W, true>), dim3(grid), dim3(kBlock), 0, s, st, P, nq, theta, phi, slot, b_out, c_out);
+  else
+    hipLaunchKernelGGL((k_anti_sums<W, false>), dim3(grid), dim3(kBlock), 0, s, st, P, nq, theta, phi, slot, b_out, c_out);
+}
+
 void launch_anti_sums(int W, const StoreDev& st, const Entangler& P, int nq, int grid, const double* theta,
                       const double* phi, const SumSlot& slot, double* b_out, double* c_out, hipStream_t s) {
   switch (W) {
-    case 1: hipLaunchKernelGGL(k_anti_sums<1>, dim3(grid), dim3(kBlock), 0, s, st, P, nq, theta, phi, slot, b_out, c_out); break;
-    case 2: hipLaunchKernelGGL(k_anti_sums<2>, dim3(grid), dim3(kBlock), 0, s, st, P, nq, theta, phi, slot, b_out, c_out); break;
-    case 3: hipLaunchKernelGGL(k_anti_sums<3>, dim3(grid), dim3(kBlock), 0, s, st, P, nq, theta, phi, slot, b_out, c_out); break;
-    default: hipLaunchKernelGGL(k_anti_sums<4>, dim3(grid), dim3(kBlock), 0, s, st, P, nq, theta, phi, slot, b_out, c_out); break;
+    case 1: launch_anti_w<1>(st, P, nq, grid, theta, phi, slot, b_out, c_out, s); break;
+    case 2: launch_anti_w<2>(st, P, nq, grid, theta, phi, slot, b_out, c_out, s); break;
+    case 3: launch_anti_w<3>(st, P, nq, grid, theta, phi, slot, b_out, c_out, s); break;
+    default: launch_anti_w<4>(st, P, nq, grid, theta, phi, slot, b_out, c_out, s); break;
   }
   if (!slot.single)
     hipLaunchKernelGGL(k_anti_total, dim3(1), dim3(kBlock), 0, s, st, (unsigned)grid, slot.slot, b_out, c_out);
