@@ -38,6 +38,7 @@
 // the phase of a term looked up again in each pass, per-slot counters in LDS
 // and shuffled scans the step took 466 us.
 #include "iqcc_internal.h"
+#include "work_split.h"
 
 #pragma clang fp contract(off)
 
@@ -870,7 +871,12 @@ __global__ __launch_bounds__(kIPB) void k_dress_inplace(StoreDev st, Entangler P
     build_group_table<W, kIPB>(lut, (double*)(smem + lut_bytes), cfg.nq, cfg.theta, cfg.phi);
   }
   const Seg<W> g = carve_seg<W>(smem + lut_bytes + (size_t)wave * seg_bytes(W, cfg.cap), cfg.cap);
-  const int64_t gw = (int64_t)wave * gridDim.x + blockIdx.x;   // few items: one per CU first
+  // Waves are numbered across the CUs: few items lie one per CU.  Neighbouring
+  // items then lie on different XCDs, which read 2.3 % more bytes of a 124-qubit
+  // chain than with a CU's waves next to each other (616 and 602 MB a step), but
+  // its steps are faster: 20 of them 11.1 and 11.3 ms, ten with their copy and
+  // gradient 2350 and 2440 us.
+  const int64_t gw = (int64_t)wave * gridDim.x + blockIdx.x;
   double eacc = 0.0;
   WaveCounts wc;
   if (*st.err == 0) {
@@ -886,15 +892,9 @@ __global__ __launch_bounds__(kIPB) void k_dress_inplace(StoreDev st, Entangler P
     const int64_t pair_terms = G.selfp ? mean : 2 * mean;
     const int maxp = G.selfp ? kIPSlots : kIPSlots / 2;
     const int64_t nw = (int64_t)gridDim.x * kIPW;
-    // Pairs per item: what the stash holds, but at least two items a wave, since
-    // a wave's chain of loads, join and stores takes about as long for 6 terms
-    // as for 192 (4096 buckets of 3 terms: 64 items of 32 pairs on 64 waves 24
-    // to 38 us a step, 2048 of one pair 13 us; 2^18 buckets of 4 terms: 92 us
-    // with 4096 items for 3072 waves, 80 us with 8192)
-    int ppi = 1;
-    while (ppi * 2 <= maxp && (int64_t)ppi * 2 * pair_terms <= cfg.item_terms &&
-           G.npairs / (ppi * 2) >= 2 * nw)
-      ppi *= 2;
+    int most = 1;   // pairs that the stash holds
+    while (most * 2 <= maxp && (int64_t)most * 2 * pair_terms <= cfg.item_terms) most *= 2;
+    const int ppi = item_pairs(G.npairs, most, nw);
     G.ppi = ppi;
     G.nitems = (G.npairs + ppi - 1) / ppi;
     // bucket tables two items ahead, term slices one item ahead

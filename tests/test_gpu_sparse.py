@@ -1,6 +1,7 @@
 """In-place stores with far more buckets than terms: most of a workgroup's
 buckets, of its groups and of a term range are empty.  Energy, angle gradient
-and screening against the oracle."""
+and screening against the oracle, and in-place steps whose items are many empty
+pairs, or as many as there are waves."""
 import numpy as np
 import pytest
 import torch
@@ -11,6 +12,7 @@ from paper_2603_08883_amd import iqcc
 from tests.gpu_util import describe
 from tests.test_gpu_dis_sizes import candidates
 from tests.test_gpu_energy_sizes import random_terms
+from tests.test_gpu_inplace_items import test_inplace_items as inplace_steps
 
 pytestmark = pytest.mark.gpu
 
@@ -40,3 +42,9 @@ def test_sparse_store(nq, n, max_terms, n_cand):
         assert np.abs(g.cpu().numpy() - O.dis_gradients(nq, x, z, c, th, ph, cx, cz)).max() <= tol
     s.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("nq,n,max_terms", [(40, 2000, 1 << 24), (40, 1, 1 << 20), (100, 60_000, 1 << 24),
+                                            (150, 900, 1 << 22), (250, 3000, 1 << 21)])
+def test_sparse_inplace_steps(nq, n, max_terms):
+    inplace_steps(nq, n, max_terms)

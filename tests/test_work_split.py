@@ -20,6 +20,10 @@ int main() {
   long long rows, buckets, grid, threads, cand;
   char kind;
   while (std::scanf(" %c %lld %lld %lld %lld %lld", &kind, &rows, &buckets, &grid, &threads, &cand) == 6) {
+    if (kind == 'i') {   // pairs, most a stash holds, waves
+      std::printf("%d\n", item_pairs(rows, (int)buckets, grid));
+      continue;
+    }
     if (kind == 'd') {   // grid: most ranges; threads: compute units
       std::printf("%lld\n", (long long)dis_range_buckets(rows, buckets, (int)grid, 0, cand, (int)threads));
       continue;
@@ -80,3 +84,17 @@ def test_dis_ranges(split, n_cand):
         assert per <= max(256, ceil(b, most)), (r, b, per)   # one chunk of buckets, or the ranges run out
         if r >= 8 * b and per > ceil(b, most):               # dense: a pass of 512 to 2048 terms
             assert min(b, 512 / 1.02 * b / r - 1) <= per <= 2048 / 1.02 * b / r, (r, b, per)
+
+
+@pytest.mark.parametrize("waves", [12, 3072])
+def test_inplace_items(split, waves):
+    cases = [("i", 1 << p, 1 << m, waves, 0, 0) for p in range(0, 28) for m in range(0, 6)]
+    for (_, pairs, most, *_), (n,) in zip(cases, split(cases)):
+        assert 1 <= n <= most and n & (n - 1) == 0
+        items = ceil(pairs, n)
+        if ceil(pairs, most) <= waves:      # one item a wave, as small as that allows
+            assert items <= waves and (n == 1 or ceil(pairs, n // 2) > waves), (pairs, most, n)
+        elif n > 1:                         # at least two items a wave
+            assert items >= 2 * waves, (pairs, most, n)
+        if items >= 4 * waves:              # and no smaller than that needs
+            assert n == most, (pairs, most, n)
