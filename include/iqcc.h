@@ -432,9 +432,10 @@ int iqcc_qmf_energy_noalloc(iqcc_ctx *ctx, const iqcc_store *h, const double *th
  * buckets: the contributions are added as exact fixed-point integers
  * (resolution 2^-186 before a division by one qubit factor, at least 2^-86
  * after it; a contribution that holds a qubit factor below 2^-100 is left out),
- * and the per-workgroup sums are reduced in a fixed order.  The exact sums need every |c| < 2^31; past
- * that bound, or with a non-finite coefficient or angle, dtheta and dphi come
- * out NaN. */
+ * and the per-workgroup sums are reduced in a fixed order.  The exact sums need
+ * every |c| < 2^31 and fewer than 2^31 terms on each compute unit, which takes
+ * its share of the buckets; past these bounds, or with a non-finite coefficient
+ * or angle, dtheta and dphi come out NaN. */
 int iqcc_qmf_energy_backward(iqcc_ctx *ctx, const iqcc_store *h, const double *theta,
                              const double *phi, const double *dE_scale, double *dtheta,
                              double *dphi, double *lambda, void *stream);

@@ -216,18 +216,17 @@ __global__ __launch_bounds__(NT) void k_energy(StoreDev st, int nq, const double
   __shared__ double red[NT / 64];
   __shared__ uint64_t scan_tmp[NT / 64];
   __shared__ int s_last;
-  const int64_t B = 1ll << *st.m;
+  const int B = 1 << *st.m;
   const BucketSplit split = energy_split<NT>(st, gridDim.x);
-  const int64_t G = split.G, ngroups = split.ngroups;
-  const unsigned active = (unsigned)split.active;
-  if (blockIdx.x >= active) return;
+  const int G = split.G, ngroups = split.ngroups, active = split.active;
+  if ((int)blockIdx.x >= active) return;
   // (the factors' chain of loads and sines beside that of the bucket table)
   build_factors<W, NT>(tmp, nq, theta, phi);
   bool table = false;
   double acc = 0.0;
-  for (int64_t grp = blockIdx.x; grp < ngroups; grp += active) {
-    const int64_t b = grp * G + threadIdx.x;
-    const bool mine = threadIdx.x < G && b < B;
+  for (int grp = blockIdx.x; grp < ngroups; grp += active) {
+    const int b = grp * G + (int)threadIdx.x;
+    const bool mine = (int)threadIdx.x < G && b < B;
     const int64_t cnt = mine ? st.cnt[b] : 0;
     const int64_t off = mine ? st.off[b] : 0;
     uint64_t total;
@@ -359,11 +358,13 @@ void launch_energy(int W, int nq, const StoreDev& st, bool regions, int n_cu, in
 // depend on the order of the rows: v_k is taken as a fixed-point number
 // (resolution 2^-186, |v| < 2^31) of 32 digits of 7 bits, and the matrix cores
 // add the digits of all terms per key bit (v_mfma_i32_32x32x32_i8: 32 qubits x
-// 32 terms x 32 digits), exactly in 32-bit integers for up to 2^24 terms per
-// workgroup.  Sums over exactly one of X, Z, Y are integer differences of
+// 32 terms x 32 digits), exactly in 32-bit integers: every kCarryTerms terms the
+// digits' carries move up one digit, so no sum passes 2^31; the top digit, which
+// holds the signs and the carries out of the others, is below the number of
+// terms.  Sums over exactly one of X, Z, Y are integer differences of
 // those.  Per workgroup the 32 digit sums turn into one double, and the
 // workgroups' doubles are added in a fixed order.  A workgroup that meets a
-// non-finite coefficient or angle, |c| >= 2^31, or 2^24 terms writes NaN.
+// non-finite coefficient or angle, |c| >= 2^31, or 2^31 terms writes NaN.
 //
 // Work split: a team of TW waves takes 64 TW terms at a time.  Each wave makes
 // v and its digits, and writes the bytes of its 64 terms' keys to LDS by byte
@@ -403,6 +404,14 @@ struct BwdGeom {
 constexpr int kDigits = 32;
 constexpr int kDigitStride = 80;   // bytes per digit row of 64 terms (padded: 16-byte reads of 8 lanes hit all banks)
 constexpr int kDigitBase = -186;   // log2 of the lowest digit's weight
+// Rows of an arena from which a workgroup may hold so many terms that its digit
+// sums need carries: 127 x 2^24 is below 2^31.  (The kernel without them is 1 to
+// 2 % faster with wide keys.)
+constexpr int64_t kCarryRows = 1ll << 24;
+// Terms of a workgroup after which its digit sums are carried: a sum stays below
+// 127 x 2 kCarryTerms of new digits and what a carry leaves, 127 + 2 kCarryTerms in
+// each wave.
+constexpr uint32_t kCarryTerms = 1u << 22;
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
@@ -473,6 +482,18 @@ __device__ __forceinline__ void put_digits(uint8_t* dig, int lane, double v) {
   at[8 * kDigitStride] = (uint8_t)(hi >> 24);
 }
 
+// Moves the carry of each digit sum to the next digit, in the next lane; the top
+// digit keeps what it has.
+__device__ __forceinline__ void carry_digits(v16i& s, int lane) {
+  const int d = lane & (kDigits - 1);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int c = d < kDigits - 1 ? s[i] >> 7 : 0;
+    const int up = __shfl_up(c, 1, kDigits);
+    s[i] += (d ? up : 0) - c * 128;
+  }
+}
+
 // Barrier of one team's `waves` waves, in two halves, between which a wave does
 // what needs no other wave: an arrival counter in LDS that only grows (`target`
 // is the wave's own count of what it has to reach).  All waves of a workgroup
@@ -490,7 +511,7 @@ __device__ __forceinline__ void team_wait(const unsigned* arrived, unsigned targ
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-template <int W>
+template <int W, bool CARRY>
 __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st, int nq, const double* theta,
                                                                      const double* phi, const double* dE,
                                                                      double* lam, double* acc_g) {
@@ -498,10 +519,10 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
   constexpr int NT = BG::kThreads, NB = BG::kBlocks, TW = BG::kTeamWaves;
   extern __shared__ __align__(16) unsigned char smem_bwd[];
   BwdShared<W>& sh = *reinterpret_cast<BwdShared<W>*>(smem_bwd);
-  const int64_t B = 1ll << *st.m;
+  const int B = 1 << *st.m;
   const BucketSplit split = gradient_buckets(*st.total, B, gridDim.x, NT);
-  const int64_t active = split.active, G = split.G, ngroups = split.ngroups;
-  if (blockIdx.x >= active) return;
+  const int active = split.active, G = split.G, ngroups = split.ngroups;
+  if ((int)blockIdx.x >= active) return;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int team = wave / TW, tw = wave % TW, block = tw % NB, part = tw / NB;
@@ -530,17 +551,17 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
   uint32_t sel1, sel2;
   byte_selectors(lane, sel1, sel2);
   const double scale = dE ? *dE : 1.0;
-  bool ok = true;   // every coefficient finite and below 2^31 in magnitude
-  int64_t nwg = 0;   // terms of the workgroup
+  bool ok = true;   // every coefficient finite and below 2^31 in magnitude, below 2^31 terms
+  uint32_t nwg = 0;   // terms of the workgroup
   v16i sx, sz, sy;
 #pragma unroll
   for (int i = 0; i < 16; ++i) sx[i] = sz[i] = sy[i] = 0;
   // Workgroup g takes the groups of G consecutive buckets g, g + active, ...;
   // a group's rows are one flat range, one term per thread and pass, the next
   // pass's term loaded while this one's bits are multiplied.
-  for (int64_t grp = blockIdx.x; grp < ngroups; grp += active) {
-    const int64_t b = grp * G + threadIdx.x;
-    const bool mine = threadIdx.x < G && b < B;
+  for (int grp = blockIdx.x; grp < ngroups; grp += active) {
+    const int b = grp * G + (int)threadIdx.x;
+    const bool mine = (int)threadIdx.x < G && b < B;
     const int64_t cnt = mine ? st.cnt[b] : 0;
     const int64_t off = mine ? st.off[b] : 0;
     uint64_t total;
@@ -555,7 +576,6 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
     const int64_t base = sh.s_off[0];   // one range of rows, as in the energy
     const bool contig = __syncthreads_and(!mine || off - (int64_t)ex == base) != 0;
     const uint32_t n = (uint32_t)total;
-    nwg += n;
     uint64_t kx[W], kz[W];
     double c;
     int64_t row;
@@ -582,7 +602,10 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
       }
     };
     load(threadIdx.x);
-    for (uint32_t i0 = 0; i0 < n; i0 += NT) {
+    for (uint32_t i0 = 0; i0 < n;) {
+     constexpr uint32_t kPart = kCarryTerms / NT * NT;
+     const uint32_t part_n = !CARRY || n - i0 < kPart ? n - i0 : kPart;
+     for (const uint32_t stop = i0 + part_n; i0 < stop; i0 += NT) {
       const bool live = i0 + threadIdx.x < n;
       const bool has_terms = i0 + 64 * wave < n;   // of the wave
       double v = 0.0, all = 1.0;
@@ -652,11 +675,21 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
         }
       }
       team_arrive(&sh.arrived[team], target, TW);
+     }
+     if (CARRY) {
+       if (((nwg + part_n) ^ nwg) / kCarryTerms) {
+         carry_digits(sx, lane);
+         carry_digits(sz, lane);
+         carry_digits(sy, lane);
+       }
+       nwg += part_n;
+       ok = ok && nwg < 1u << 31;
+     }
     }
   }
   if (!ok) sh.bad = 1;
   __syncthreads();
-  const bool in_range = sh.bad == 0 && nwg < (1ll << 24);
+  const bool in_range = sh.bad == 0;
   // digit sums of all waves (x or z alone: less the sums over both), over the
   // table and what follows it; then one double per (qubit, sigma).  Column d of
   // row r sits at d ^ (r mod 32): both the adds (one row, all columns) and the
@@ -684,7 +717,7 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
     int carry = 0;
 #pragma unroll
     for (int d = 0; d < kDigits; ++d) {
-      const int t = dg[d] + carry;   // below 2^31: 127 * 2^24 + 2^24
+      const int t = dg[d] + carry;   // below 2^31
       dg[d] = t & 127;
       carry = t >> 7;
     }
@@ -695,14 +728,21 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
   }
 }
 
+template <int W, bool CARRY>
+static int launch_bwd_t(int nq, const StoreDev& st, int grid, const double* theta, const double* phi,
+                        const double* dE, double* lam, double* acc, hipStream_t s) {
+  const size_t lds = sizeof(BwdShared<W>);
+  (void)hipFuncSetAttribute((const void*)k_energy_bwd<W, CARRY>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((k_energy_bwd<W, CARRY>), dim3(grid), dim3(BwdGeom<W>::kThreads), lds, s, st, nq, theta, phi, dE,
+                     lam, acc);
+  return BwdGeom<W>::kThreads;
+}
+
 template <int W>
 static int launch_bwd_w(int nq, const StoreDev& st, int grid, const double* theta, const double* phi,
                         const double* dE, double* lam, double* acc, hipStream_t s) {
-  const size_t lds = sizeof(BwdShared<W>);
-  (void)hipFuncSetAttribute((const void*)k_energy_bwd<W>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(k_energy_bwd<W>, dim3(grid), dim3(BwdGeom<W>::kThreads), lds, s, st, nq, theta, phi, dE, lam,
-                     acc);
-  return BwdGeom<W>::kThreads;
+  return st.cap < kCarryRows ? launch_bwd_t<W, false>(nq, st, grid, theta, phi, dE, lam, acc, s)
+                             : launch_bwd_t<W, true>(nq, st, grid, theta, phi, dE, lam, acc, s);
 }
 
 // One workgroup per qubit: S[q][sigma] summed over the workgroups in a fixed

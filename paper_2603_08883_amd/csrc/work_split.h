@@ -17,9 +17,9 @@
 namespace iqcc {
 
 // Groups of G consecutive buckets; workgroup g of the `active` ones takes the
-// groups g, g + active, ...
+// groups g, g + active, ...  (a store has at most 2^28 buckets)
 struct BucketSplit {
-  int64_t G, ngroups, active;
+  int G, ngroups, active;
 };
 
 // One workgroup per rows_each rows or per group of `most` buckets, whichever
@@ -33,7 +33,7 @@ constexpr BucketSplit split_buckets(int64_t rows, int64_t buckets, int64_t grid,
   int64_t G = (buckets + want - 1) / want;
   G = G > most ? most : G;
   const int64_t ngroups = (buckets + G - 1) / G;
-  return {G, ngroups, ngroups < want ? ngroups : want};
+  return {(int)G, (int)ngroups, (int)(ngroups < want ? ngroups : want)};
 }
 
 // Energy.  rows_each: a call over the stores of a 32-Hamiltonian batch takes
