@@ -1473,6 +1473,30 @@ int iqcc_qcc_iteration(iqcc_ctx* ctx, iqcc_store** h, iqcc_store** spare, const 
 
 // ---- term-limit compression -------------------------------------------------
 
+// The selection of the max_terms largest |c| (its state in h, and on the device
+// for the copy), with the output's rows and bucket counts as scratch.
+static int select_top(iqcc_ctx* ctx, const iqcc_store* in, int64_t max_terms, const iqcc_store* out, SelState& h,
+                      hipStream_t s) {
+  SelState* ss = (SelState*)(ctx->sel_hist + kSelHist);
+  launch_abs_select(in->d, ss, ctx->sel_hist, ctx->n_cu, max_terms, out->d, out->slot, s);
+  LAUNCH_CHECK(ctx);
+  HIP_TRY(ctx, hipMemcpyAsync(&h, ss, sizeof(h), hipMemcpyDeviceToHost, s));
+  HIP_TRY(ctx, hipStreamSynchronize(s));
+  if (h.err || h.skip) return IQCC_OK;
+  if (!h.done) {
+    launch_abs_select_rest(in->d, ss, ctx->sel_hist, ctx->n_cu, out->d, out->slot, s);
+    LAUNCH_CHECK(ctx);
+    HIP_TRY(ctx, hipMemcpyAsync(&h, ss, sizeof(h), hipMemcpyDeviceToHost, s));
+    HIP_TRY(ctx, hipStreamSynchronize(s));
+  }
+  if (h.need < h.ties) {
+    // not every term equal to the threshold fits: the smaller canonical keys go first
+    launch_select_ties(in->W, in->d, out->d, h.ties, ss, ctx->sel_hist, ctx->n_cu, out->slot, s);
+    LAUNCH_CHECK(ctx);
+  }
+  return IQCC_OK;
+}
+
 int iqcc_truncate_top(iqcc_ctx* ctx, const iqcc_store* in, int64_t max_terms, iqcc_store* out,
                       void* stream) {
   int rc = check_ctx(ctx);
@@ -1482,46 +1506,21 @@ int iqcc_truncate_top(iqcc_ctx* ctx, const iqcc_store* in, int64_t max_terms, iq
   if (out->d.cap < in->d.cap || out->d.mcap < in->d.mcap)
     return fail(ctx, IQCC_ERR_CAPACITY, "output store is smaller than the input store");
   hipStream_t s = as_stream(stream);
-  const int W = in->W;
-  const int grid = (int)(ctx->n_cu * 4);
-  SelState* ss = (SelState*)(ctx->sel_hist + kSelHist);
-  DevBuf keys, kcount;
-  // (the output's rows and bucket counts are scratch until the copy)
-  launch_abs_select(in->d, ss, ctx->sel_hist, ctx->n_cu, max_terms, out->d, out->slot, s);
-  LAUNCH_CHECK(ctx);
-  SelState h{};
-  HIP_TRY(ctx, hipMemcpyAsync(&h, ss, sizeof(h), hipMemcpyDeviceToHost, s));
-  HIP_TRY(ctx, hipStreamSynchronize(s));
-  rc = store_error(ctx, h.err);
-  if (rc) return rc;
-  const int keep_all = h.n <= max_terms ? 1 : max_terms == 0 ? -1 : 0;
-  if (keep_all == 0) {
-    if (!h.done) {
-      launch_abs_select_rest(in->d, ss, ctx->sel_hist, ctx->n_cu, out->d, out->slot, s);
-      LAUNCH_CHECK(ctx);
-      HIP_TRY(ctx, hipMemcpyAsync(&h, ss, sizeof(h), hipMemcpyDeviceToHost, s));
-      HIP_TRY(ctx, hipStreamSynchronize(s));
-    }
-    if (h.need < h.ties) {
-      // not every term equal to the threshold fits: the smaller canonical keys go first
-      if (hipMalloc(&keys.p, (size_t)h.ties * 2 * W * sizeof(uint64_t)) != hipSuccess ||
-          hipMalloc(&kcount.p, 64) != hipSuccess) {
-        launch_select_compact(W, in->d, out->d, ss, -1, 1, out->slot, s);   // leave a valid, empty store
-        return fail(ctx, IQCC_ERR_HIP, "out of device memory for the keys of equal terms");
-      }
-      HIP_TRY(ctx, hipMemsetAsync(kcount.p, 0, 64, s));
-      launch_collect_ties(W, in->d, ss, (uint64_t*)keys.p, h.ties, (unsigned long long*)kcount.p,
-                          grid, s);
-      launch_key_select(W, (const uint64_t*)keys.p, h.ties, ss, ctx->sel_hist, out->slot, s);
-      const int one = 1;
-      HIP_TRY(ctx, hipMemcpyAsync(&ss->key_mode, &one, sizeof(int), hipMemcpyHostToDevice, s));
-      LAUNCH_CHECK(ctx);
-    }
-  }
-  // (a word per workgroup of the output's slot, four buckets per workgroup)
-  const int cgrid = ctx->n_cu * 8 < out->slot_words ? ctx->n_cu * 8 : out->slot_words;
-  launch_select_compact(W, in->d, out->d, ss, keep_all, cgrid, out->slot, s);
+  // from here on the output's rows and bucket counts are scratch, unless the
+  // input is invalid; a call that fails leaves it empty
+  const bool regions = out->regions;
   out->regions = false;
+  SelState h{};
+  rc = select_top(ctx, in, max_terms, out, h, s);
+  if (!rc && h.err) {
+    out->regions = regions;
+    return store_error(ctx, h.err);
+  }
+  const int keep_all = rc || max_terms == 0 ? -1 : h.n <= max_terms ? 1 : 0;
+  // (a word per workgroup of the output's slot, four buckets per workgroup)
+  const int grid = ctx->n_cu * 8 < out->slot_words ? ctx->n_cu * 8 : out->slot_words;
+  launch_select_compact(in->W, in->d, out->d, (SelState*)(ctx->sel_hist + kSelHist), keep_all, grid, out->slot, s);
+  if (rc) return rc;
   LAUNCH_CHECK(ctx);
   HIP_TRY(ctx, hipStreamSynchronize(s));
   return IQCC_OK;

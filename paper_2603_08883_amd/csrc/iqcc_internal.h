@@ -720,7 +720,7 @@ void launch_dress_inplace(int W, const StoreDev& st, const Entangler& P, const I
                           hipStream_t s);
 // Bucket regions: bucket b gets max(R, 2 cnt_b rounded up to 16) rows; the
 // pool starts after the last region.  Load of flat rows (as launch_store_load;
-// scratch 3 B + B/1024 + 16 + n) and copy of a store (deterministic: each
+// scratch 2 B + B/1024 + 16 + n) and copy of a store (deterministic: each
 // destination bucket takes its rows in source order).  Both set err = 1 when
 // the regions do not fit the arena.
 int launch_store_load_regions(int W, StoreDev st, const uint64_t* x, const uint64_t* z, const double* c,
@@ -766,7 +766,7 @@ struct SelState {
   uint64_t T;                    // |c| bits of the M-th largest term
   int64_t ties;                  // terms with |c| bits == T
   int64_t at;                    // terms in the digit picked last
-  int64_t listed;                // |c| values listed by the finish in one launch
+  int64_t listed;                // |c| values listed by the finish in one launch, then ties' keys
   int key_mode;                  // 1: keep only ties with canonical key <= kthr
   int done;                      // T, ties and need are settled
   int64_t n;                     // live terms of the store
@@ -782,10 +782,10 @@ void launch_abs_select(const StoreDev& st, SelState* ss, unsigned* hist, int n_c
                        double* slot, hipStream_t s);
 void launch_abs_select_rest(const StoreDev& st, SelState* ss, unsigned* hist, int n_cu, const StoreDev& tmp,
                             double* slot, hipStream_t s);
-void launch_collect_ties(int W, const StoreDev& st, const SelState* ss, uint64_t* keys, int64_t cap,
-                         unsigned long long* count, int grid, hipStream_t s);
-void launch_key_select(int W, const uint64_t* keys, int64_t n, SelState* ss, unsigned* hist, double* slot,
-                       hipStream_t s);
+// Canonical key threshold of the n ties (terms with |c| bits == T), whose keys go
+// to the first rows of `keys`.
+void launch_select_ties(int W, const StoreDev& st, const StoreDev& keys, int64_t n, SelState* ss, unsigned* hist,
+                        int n_cu, double* slot, hipStream_t s);
 // keep_all: 1 every term, 0 the selection in ss, -1 none; grid words of the slot
 void launch_select_compact(int W, const StoreDev& in, const StoreDev& out, const SelState* ss, int keep_all, int grid,
                            double* slot, hipStream_t s);

@@ -14,9 +14,9 @@
 // alone.  If the second digit leaves few terms, one workgroup settles the other
 // four from a list of them.  That fixes the threshold T (the M-th largest |c|),
 // the number of terms above it and the number to take among the terms equal to
-// T.  When not all ties are taken, the tie keys are collected and the same
-// selection runs on their canonical key words (x words, then z words, most
-// significant first), from the bottom.  A last pass copies every bucket's kept
+// T.  When not all ties are taken, the tie keys are collected (in the output's
+// arena too) and the same selection runs on their canonical key words (x words,
+// then z words, most significant first), from the bottom.  A last pass copies every bucket's kept
 // terms, in input order, to the same rows of the output arena.
 //
 // A pass is one launch: the workgroup that adds its histogram last picks the
@@ -132,6 +132,7 @@ __device__ void add_and_pick(const unsigned* h, const PickArgs& a) {
       ss->ties = p.at;
     } else {
       ss->kthr[a.key_word] = chosen;
+      ss->key_mode = 1;
     }
   }
 }
@@ -283,6 +284,7 @@ __global__ __launch_bounds__(kSelBlock) void k_cand_finish(StoreDev st, const ui
   ss->at = ss->ties = at;
   ss->T = prefix;
   ss->prefix = 0;
+  ss->listed = 0;   // (counts the ties' keys next)
   ss->done = 1;
 }
 
@@ -308,38 +310,42 @@ __device__ __forceinline__ uint64_t canon_word(const StoreDev& st, int64_t row, 
   return q < W ? st.x[(W - 1 - q) * st.cap + row] : st.z[(2 * W - 1 - q) * st.cap + row];
 }
 
-// Keys of the terms with |c| bits == T, as rows of 2W canonical words.
+// Keys of the terms with |c| bits == T, as the first rows of `keys`.
 template <int W>
-__global__ __launch_bounds__(kBlock) void k_collect_ties(StoreDev st, const SelState* ss,
-                                                         uint64_t* keys, int64_t cap,
-                                                         unsigned long long* count) {
+__global__ __launch_bounds__(kBlock) void k_collect_ties(StoreDev st, SelState* ss, StoreDev keys) {
   const uint64_t T = ss->T;
   const int64_t B = 1ll << *st.m;
   for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
     const int64_t n = st.cnt[b], off = st.off[b];
     for (int64_t i = threadIdx.x; i < n; i += kBlock) {
       if (abs_bits(st.c[off + i]) != T) continue;
-      const int64_t r = (int64_t)atomicAdd(count, 1ull);
-      if (r < cap)
-        for (int q = 0; q < 2 * W; ++q) keys[r * 2 * W + q] = canon_word<W>(st, off + i, q);
+      const int64_t r = (int64_t)atomicAdd((unsigned long long*)&ss->listed, 1ull);
+      if (r < keys.cap) {
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          keys.x[w * keys.cap + r] = st.x[w * st.cap + off + i];
+          keys.z[w * keys.cap + r] = st.z[w * st.cap + off + i];
+        }
+      }
     }
   }
 }
 
 // Digit of key word q over the tie keys whose earlier words equal kthr[0..q)
 // and whose bits of word q above shift + width equal the prefix.
-__global__ __launch_bounds__(kSelBlock) void k_key_hist(const uint64_t* keys, int64_t n, int nw, int q, int shift,
-                                                        int first, PickArgs a) {
+template <int W>
+__global__ __launch_bounds__(kSelBlock) void k_key_hist(StoreDev keys, int64_t n, int q, int shift, int first,
+                                                        PickArgs a) {
   __shared__ unsigned h[kSelBins];
   for (int i = threadIdx.x; i < kSelBins; i += kSelBlock) h[i] = 0;
   __syncthreads();
   const uint64_t dmask = (1ull << a.width) - 1;
   for (int64_t i = blockIdx.x * (int64_t)kSelBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kSelBlock) {
-    const uint64_t* k = keys + i * nw;
     bool match = true;
-    for (int p = 0; p < q; ++p) match = match && k[p] == a.ss->kthr[p];
-    if (match && (first || (k[q] >> (shift + a.width)) == a.ss->prefix))
-      atomicAdd(&h[(k[q] >> shift) & dmask], 1u);
+    for (int p = 0; p < q; ++p) match = match && canon_word<W>(keys, i, p) == a.ss->kthr[p];
+    const uint64_t word = canon_word<W>(keys, i, q);
+    if (match && (first || (word >> (shift + a.width)) == a.ss->prefix))
+      atomicAdd(&h[(word >> shift) & dmask], 1u);
   }
   add_and_pick(h, a);
 }
@@ -447,26 +453,28 @@ void launch_abs_select_rest(const StoreDev& st, SelState* ss, unsigned* hist, in
   }
 }
 
-void launch_collect_ties(int W, const StoreDev& st, const SelState* ss, uint64_t* keys, int64_t cap,
-                         unsigned long long* count, int grid, hipStream_t s) {
-  switch (W) {
-    case 1: hipLaunchKernelGGL(k_collect_ties<1>, dim3(grid), dim3(kBlock), 0, s, st, ss, keys, cap, count); break;
-    case 2: hipLaunchKernelGGL(k_collect_ties<2>, dim3(grid), dim3(kBlock), 0, s, st, ss, keys, cap, count); break;
-    case 3: hipLaunchKernelGGL(k_collect_ties<3>, dim3(grid), dim3(kBlock), 0, s, st, ss, keys, cap, count); break;
-    default: hipLaunchKernelGGL(k_collect_ties<4>, dim3(grid), dim3(kBlock), 0, s, st, ss, keys, cap, count); break;
-  }
-}
-
-void launch_key_select(int W, const uint64_t* keys, int64_t n, SelState* ss, unsigned* hist, double* slot,
-                       hipStream_t s) {
-  int64_t g = (n + kSelBlock - 1) / kSelBlock;
+template <int W>
+static void launch_ties_w(const StoreDev& st, const StoreDev& keys, int64_t n, SelState* ss, unsigned* hist, int n_cu,
+                          double* slot, hipStream_t s) {
+  hipLaunchKernelGGL(k_collect_ties<W>, dim3(4 * n_cu), dim3(kBlock), 0, s, st, ss, keys);
+  const int64_t g = (n + kSelBlock - 1) / kSelBlock;
   const int grid = (int)(g < 1 ? 1 : g > 256 ? 256 : g);
   for (int q = 0; q < 2 * W; ++q)
     for (int p = 0; p < 6; ++p) {
       // (need goes on from the number of ties to take; the prefix starts anew per word)
       const PickArgs a{ss, hist, slot, -1, kDigitWidth[p], 0, p == 5, q};
-      hipLaunchKernelGGL(k_key_hist, dim3(grid), dim3(kSelBlock), 0, s, keys, n, 2 * W, q, kDigitShift[p], p == 0, a);
+      hipLaunchKernelGGL(k_key_hist<W>, dim3(grid), dim3(kSelBlock), 0, s, keys, n, q, kDigitShift[p], p == 0, a);
     }
+}
+
+void launch_select_ties(int W, const StoreDev& st, const StoreDev& keys, int64_t n, SelState* ss, unsigned* hist,
+                        int n_cu, double* slot, hipStream_t s) {
+  switch (W) {
+    case 1: launch_ties_w<1>(st, keys, n, ss, hist, n_cu, slot, s); break;
+    case 2: launch_ties_w<2>(st, keys, n, ss, hist, n_cu, slot, s); break;
+    case 3: launch_ties_w<3>(st, keys, n, ss, hist, n_cu, slot, s); break;
+    default: launch_ties_w<4>(st, keys, n, ss, hist, n_cu, slot, s); break;
+  }
 }
 
 void launch_select_compact(int W, const StoreDev& in, const StoreDev& out, const SelState* ss, int keep_all, int grid,
