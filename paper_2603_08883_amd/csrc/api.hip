@@ -1473,27 +1473,29 @@ int iqcc_qcc_iteration(iqcc_ctx* ctx, iqcc_store** h, iqcc_store** spare, const 
 
 // ---- term-limit compression -------------------------------------------------
 
-// The selection of the max_terms largest |c| (its state in h, and on the device
-// for the copy), with the output's rows and bucket counts as scratch.
+// The max_terms terms of largest |c| into out, whose rows and bucket counts are
+// the selection's scratch; its state in h.
 static int select_top(iqcc_ctx* ctx, const iqcc_store* in, int64_t max_terms, const iqcc_store* out, SelState& h,
-                      hipStream_t s) {
+                      int grid, hipStream_t s) {
   SelState* ss = (SelState*)(ctx->sel_hist + kSelHist);
   launch_abs_select(in->d, ss, ctx->sel_hist, ctx->n_cu, max_terms, out->d, out->slot, s);
+  launch_select_compact(in->W, in->d, out->d, ss, kKeepAuto, grid, out->slot, s);
   LAUNCH_CHECK(ctx);
   HIP_TRY(ctx, hipMemcpyAsync(&h, ss, sizeof(h), hipMemcpyDeviceToHost, s));
   HIP_TRY(ctx, hipStreamSynchronize(s));
-  if (h.err || h.skip) return IQCC_OK;
+  if (sel_settled(h)) return IQCC_OK;
   if (!h.done) {
     launch_abs_select_rest(in->d, ss, ctx->sel_hist, ctx->n_cu, out->d, out->slot, s);
     LAUNCH_CHECK(ctx);
     HIP_TRY(ctx, hipMemcpyAsync(&h, ss, sizeof(h), hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
   }
-  if (h.need < h.ties) {
-    // not every term equal to the threshold fits: the smaller canonical keys go first
+  // not every term equal to the threshold fits: the smaller canonical keys go first
+  if (h.need < h.ties)
     launch_select_ties(in->W, in->d, out->d, h.ties, ss, ctx->sel_hist, ctx->n_cu, out->slot, s);
-    LAUNCH_CHECK(ctx);
-  }
+  launch_select_compact(in->W, in->d, out->d, ss, 0, grid, out->slot, s);
+  LAUNCH_CHECK(ctx);
+  HIP_TRY(ctx, hipStreamSynchronize(s));
   return IQCC_OK;
 }
 
@@ -1510,19 +1512,18 @@ int iqcc_truncate_top(iqcc_ctx* ctx, const iqcc_store* in, int64_t max_terms, iq
   // input is invalid; a call that fails leaves it empty
   const bool regions = out->regions;
   out->regions = false;
+  // (a word per workgroup of the output's slot, four buckets per workgroup)
+  const int grid = ctx->n_cu * 8 < out->slot_words ? ctx->n_cu * 8 : out->slot_words;
   SelState h{};
-  rc = select_top(ctx, in, max_terms, out, h, s);
-  if (!rc && h.err) {
+  rc = select_top(ctx, in, max_terms, out, h, grid, s);
+  if (rc) {
+    launch_select_compact(in->W, in->d, out->d, nullptr, -1, grid, out->slot, s);
+    return rc;
+  }
+  if (h.keep == kKeepInvalid) {
     out->regions = regions;
     return store_error(ctx, h.err);
   }
-  const int keep_all = rc || max_terms == 0 ? -1 : h.n <= max_terms ? 1 : 0;
-  // (a word per workgroup of the output's slot, four buckets per workgroup)
-  const int grid = ctx->n_cu * 8 < out->slot_words ? ctx->n_cu * 8 : out->slot_words;
-  launch_select_compact(in->W, in->d, out->d, (SelState*)(ctx->sel_hist + kSelHist), keep_all, grid, out->slot, s);
-  if (rc) return rc;
-  LAUNCH_CHECK(ctx);
-  HIP_TRY(ctx, hipStreamSynchronize(s));
   return IQCC_OK;
 }
 

@@ -770,24 +770,31 @@ struct SelState {
   int key_mode;                  // 1: keep only ties with canonical key <= kthr
   int done;                      // T, ties and need are settled
   int64_t n;                     // live terms of the store
-  int err, skip;                 // its error flag; nothing selected
+  int err;                       // its error flag
+  int keep;                      // 0: select; 1 every term, -1 none, kKeepInvalid: no selection
   uint64_t kthr[2 * kMaxWords];  // canonical key threshold among the ties
 };
+constexpr int kKeepInvalid = 2;   // the store is invalid
 constexpr int kSelHist = 2048;   // digit counters, zero between passes
 // The need-th largest |c| of st: T, ties and need (ties to take) of ss, if done
-// is set then; else launch_abs_select_rest settles them.  skip: the store is
-// invalid (err), or need is 0 or not below its n terms.  tmp: a store at least
-// as large, whose rows and bucket counts are scratch.
+// is set then; else launch_abs_select_rest settles them.  tmp: a store at least as
+// large, whose rows and bucket counts are scratch unless keep says no selection.
 void launch_abs_select(const StoreDev& st, SelState* ss, unsigned* hist, int n_cu, int64_t need, const StoreDev& tmp,
                        double* slot, hipStream_t s);
 void launch_abs_select_rest(const StoreDev& st, SelState* ss, unsigned* hist, int n_cu, const StoreDev& tmp,
                             double* slot, hipStream_t s);
+// True when ss holds all that the copy needs (on the device and on the host).
+__host__ __device__ __forceinline__ bool sel_settled(const SelState& ss) {
+  return ss.keep != 0 || (ss.done && ss.need == ss.ties);
+}
 // Canonical key threshold of the n ties (terms with |c| bits == T), whose keys go
 // to the first rows of `keys`.
 void launch_select_ties(int W, const StoreDev& st, const StoreDev& keys, int64_t n, SelState* ss, unsigned* hist,
                         int n_cu, double* slot, hipStream_t s);
-// keep_all: 1 every term, 0 the selection in ss, -1 none; grid words of the slot
-void launch_select_compact(int W, const StoreDev& in, const StoreDev& out, const SelState* ss, int keep_all, int grid,
+// keep: 1 every term, 0 the selection in ss, -1 none, kKeepAuto: what ss says, nothing if
+// the store is invalid or the selection not settled; grid words of the slot
+constexpr int kKeepAuto = 3;
+void launch_select_compact(int W, const StoreDev& in, const StoreDev& out, const SelState* ss, int keep, int grid,
                            double* slot, hipStream_t s);
 
 // A Pauli key passed by value to a kernel.
