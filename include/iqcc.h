@@ -98,14 +98,15 @@ const char *iqcc_version(void);
  *   "batch_unit_pairs"   consecutive bucket pairs of one Hamiltonian per work
  *                        unit of a batch (1 .. 65536); read when the batch is
  *                        created
- *   "energy_grid_per_cu" workgroups per compute unit of the stand-alone energy
- *                        kernel (1 .. 32)
+ *   "energy_grid_per_cu" most workgroups per compute unit of the stand-alone
+ *                        energy kernel (1 .. 32); it takes as many as the LDS
+ *                        holds at once, and as the terms and buckets ask for
  *   "fuse_energy"        1: dressing evaluates the energy of its output in the
  *                        same pass when angles are given; 0: separate pass
  *   "dis_tile"           DIS candidates held per workgroup tile (1 .. 256)
- *   "dis_bucket_ranges"  bucket ranges (workgroups along the terms) of the
- *                        batched DIS launch; 0 = about 8 workgroups per CU
- *                        in total (0 .. 4096)
+ *   "dis_bucket_ranges"  bucket ranges of the batched DIS launch; 0 = as many
+ *                        as the terms fill, 512 to 2048 terms each, at most
+ *                        about 8 per CU and 256 candidates (0 .. 4096)
  *   "inplace_bucket_terms" mean bucket size of an IQCC_STORE_INPLACE store
  *                        when it holds max_terms terms (1 .. 16384)
  *   "inplace_item_terms" input terms per work item of iqcc_dress_inplace
@@ -411,12 +412,11 @@ int iqcc_qmf_energy(iqcc_ctx *ctx, const iqcc_store *h, const double *theta,
  * energy as iqcc_qmf_energy (the same bits), from the same kernel and a second
  * one that adds its sums, with no allocation of any kind.  Its scratch (six
  * sets of per-workgroup partial sums, taken in turn) is a fixed array of device
- * memory inside the library, 120 KB per device, held until the process ends.
- * A grid (n_cu * energy_grid_per_cu workgroups) above 8192 is refused with
- * IQCC_ERR_CAPACITY before any launch.  All calls on one device share that
- * scratch, and a captured call keeps its set, so calls that overlap on a device
- * (other streams, other contexts or threads) race; calls in one stream are
- * ordered.  Each call rewrites all the scratch it reads, so a race spoils
+ * memory inside the library, 120 KB per device, held until the process ends; no
+ * value of "energy_grid_per_cu" asks for more.  All calls on one device share
+ * that scratch, and a captured call keeps its set, so calls that overlap on a
+ * device (other streams, other contexts or threads) race; calls in one stream
+ * are ordered.  Each call rewrites all the scratch it reads, so a race spoils
  * the calls that take part in it and no later one. */
 int iqcc_qmf_energy_noalloc(iqcc_ctx *ctx, const iqcc_store *h, const double *theta,
                             const double *phi, double *energy, void *stream);

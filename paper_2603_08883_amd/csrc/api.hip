@@ -34,7 +34,7 @@ struct iqcc_ctx {
   int64_t energy_grid_per_cu = 16;         // stand-alone energy kernel
   int64_t fuse_energy = 1;
   int64_t dis_tile = 256;
-  int64_t dis_bucket_ranges = 0;           // 0: about 8 workgroups per CU in total
+  int64_t dis_bucket_ranges = 0;           // 0: as many as the terms fill
   int64_t inplace_bucket_terms = 256;      // mean bucket of an in-place store at max_terms
   int64_t inplace_item_terms = 0;          // 0: from the stash capacity
   int64_t inplace_cap = 0;                 // 0: as many stash entries as the LDS holds
@@ -432,7 +432,6 @@ void inplace_geometry(const iqcc_ctx* ctx, const iqcc_store* st, int& m, int64_t
 // copy until the process ends; host code reaches it only through the per-device
 // address from hipGetSymbolAddress.
 constexpr int kNoAllocSlots = 6;
-constexpr int kNoAllocPartials = 8192;   // the largest grid the entry point accepts
 constexpr int kNoAllocDevices = 64;
 static __device__ __align__(256) double scratch[kNoAllocSlots * kFinishSlot];
 std::atomic<unsigned> g_scratch_next{0};
@@ -1221,11 +1220,6 @@ int iqcc_qmf_energy_noalloc(iqcc_ctx* ctx, const iqcc_store* h, const double* th
   if (!h || !theta || !phi || !energy) return fail(ctx, IQCC_ERR_INVALID_ARG, "null argument");
   double* base = (ctx->device >= 0 && ctx->device < kNoAllocDevices) ? g_scratch[ctx->device] : nullptr;
   if (!base) return fail(ctx, IQCC_ERR_HIP, "the device scratch of the allocation-free entry point is unavailable");
-  const int64_t grid = ctx->n_cu * ctx->energy_grid_per_cu;
-  if (grid > kNoAllocPartials)
-    return fail(ctx, IQCC_ERR_CAPACITY,
-                "allocation-free energy holds %d workgroup partials, the grid needs %lld "
-                "(lower energy_grid_per_cu)", kNoAllocPartials, (long long)grid);
   double* slot = base + (size_t)(g_scratch_next.fetch_add(1, std::memory_order_relaxed) % kNoAllocSlots) * kFinishSlot;
   energy_sum(ctx, h, theta, phi, {slot, false}, energy, as_stream(stream));
   LAUNCH_CHECK(ctx);

@@ -28,7 +28,7 @@ IQCC_ERR_UNSUPPORTED = -4
 IQCC_DIS_BATCHED = 0
 IQCC_DIS_PLAIN = 1
 IQCC_STORE_INPLACE = 1
-NOALLOC_MAX_PARTIALS = 8192   # workgroup partials the allocation-free energy holds
+NOALLOC_MAX_PARTIALS = 8192   # the largest energy_grid_per_cu on every CU: no grid is refused
 
 _lib = None
 
