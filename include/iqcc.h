@@ -500,7 +500,8 @@ int iqcc_qmf_energy_anti(iqcc_ctx *ctx, const iqcc_store *h, const uint64_t *px,
  * (most significant word first), written to the HOST array fx as rows of
  * n_words words.  *n receives the count; IQCC_ERR_CAPACITY (fx untouched) when
  * it exceeds cap.  Matching a flip set of H is the second DIS condition of
- * App. A. */
+ * App. A.  Working memory: 16 to 32 bytes and 8 W a term, 25 % more; the context
+ * keeps up to 128 MB of it for the next call. */
 int iqcc_flip_sets(iqcc_ctx *ctx, const iqcc_store *h, int w_max, uint64_t *fx, int64_t cap,
                    int64_t *n);
 
@@ -521,7 +522,9 @@ int iqcc_flip_sets(iqcc_ctx *ctx, const iqcc_store *h, int w_max, uint64_t *fx, 
  * HOST outputs: sel_x, sel_z [n_select][n_words] (applied generators), sel_g
  * [n_select] (their screening gradients), sel_tau [n_select], energy
  * [n_select + 1] (energy before the first step and after each), the number of
- * candidates and the number of generators applied (<= n_select). */
+ * candidates and the number of generators applied (<= n_select).  Working
+ * memory: that of iqcc_flip_sets, and 16 W + 8 bytes a candidate, 25 % more, of
+ * which the context keeps up to 128 MB too. */
 int iqcc_qcc_iteration(iqcc_ctx *ctx, iqcc_store **h, iqcc_store **spare, const double *theta,
                        const double *phi, int w_max, int n_select, double eps, uint64_t *sel_x,
                        uint64_t *sel_z, double *sel_g, double *sel_tau, double *energy,

@@ -49,8 +49,10 @@ struct iqcc_ctx {
   int64_t n_partial = 0;
   int64_t* scratch = nullptr;   // n_scratch
   int64_t n_scratch = 0;
-  char* work = nullptr;         // n_work bytes: flip sets and candidates of an iteration
+  char* work = nullptr;         // n_work bytes: flip sets of an iteration
   int64_t n_work = 0;
+  char* cand = nullptr;         // n_cand bytes: its candidates
+  int64_t n_cand = 0;
 };
 
 struct iqcc_batch {
@@ -153,17 +155,37 @@ int ensure_scratch(iqcc_ctx* ctx, int64_t n) {
   return IQCC_OK;
 }
 
-int ensure_work(iqcc_ctx* ctx, int64_t bytes) {
-  if (bytes <= ctx->n_work) return IQCC_OK;
+// A block of an iteration's working memory (p, n bytes) of at least `bytes`.
+int ensure_block(iqcc_ctx* ctx, char*& p, int64_t& n, int64_t bytes) {
+  if (bytes <= n) return IQCC_OK;
   HIP_TRY(ctx, hipDeviceSynchronize());
-  if (ctx->work) HIP_TRY(ctx, hipFree(ctx->work));
-  ctx->work = nullptr;
-  ctx->n_work = 0;
+  if (p) HIP_TRY(ctx, hipFree(p));
+  p = nullptr;
+  n = 0;
   bytes += bytes / 4;   // a Hamiltonian that grows from call to call
-  HIP_TRY(ctx, hipMalloc(&ctx->work, (size_t)bytes));
-  ctx->n_work = bytes;
+  HIP_TRY(ctx, hipMalloc(&p, (size_t)bytes));
+  n = bytes;
   return IQCC_OK;
 }
+
+// At the end of a call, the blocks that it filled: a large one (16 to 32 bytes
+// and 8 W a term) is given back, a small one, whose allocation would be a good
+// part of the call, stays.
+constexpr int64_t kKeptBlock = 128ll << 20;
+
+struct BlockTrim {
+  iqcc_ctx* ctx;
+  ~BlockTrim() {
+    trim(ctx->work, ctx->n_work);
+    trim(ctx->cand, ctx->n_cand);
+  }
+  static void trim(char*& p, int64_t& n) {
+    if (n <= kKeptBlock) return;
+    hipFree(p);   // (waits for what still uses it)
+    p = nullptr;
+    n = 0;
+  }
+};
 
 int ensure_partial(iqcc_ctx* ctx, int64_t n) {
   if (n <= ctx->n_partial) return IQCC_OK;
@@ -508,6 +530,7 @@ int iqcc_ctx_destroy(iqcc_ctx* ctx) {
   if (ctx->partial) hipFree(ctx->partial);
   if (ctx->scratch) hipFree(ctx->scratch);
   if (ctx->work) hipFree(ctx->work);
+  if (ctx->cand) hipFree(ctx->cand);
   delete ctx;
   return IQCC_OK;
 }
@@ -1326,7 +1349,7 @@ int flip_sets_device(iqcc_ctx* ctx, const iqcc_store* h, int w_max, FlipSets& F)
   int64_t table = 64;
   while (table < 2 * F.live) table <<= 1;
   F.ld = F.live;
-  rc = ensure_work(ctx, 64 + 8 * table + 8 * (int64_t)h->W * F.ld);
+  rc = ensure_block(ctx, ctx->work, ctx->n_work, 64 + 8 * table + 8 * (int64_t)h->W * F.ld);
   if (rc) return rc;
   F.count = (unsigned long long*)ctx->work;
   unsigned long long* tab = F.count + 8;
@@ -1347,6 +1370,7 @@ int iqcc_flip_sets(iqcc_ctx* ctx, const iqcc_store* h, int w_max, uint64_t* fx, 
   int rc = check_ctx(ctx);
   if (rc) return rc;
   if (!h || !n || w_max < 1 || cap < 0) return fail(ctx, IQCC_ERR_INVALID_ARG, "bad flip-set arguments");
+  const BlockTrim trim{ctx};
   FlipSets F;
   rc = flip_sets_device(ctx, h, w_max, F);
   if (rc) return rc;
@@ -1389,29 +1413,18 @@ int iqcc_qcc_iteration(iqcc_ctx* ctx, iqcc_store** h, iqcc_store** spare, const 
   *n_applied = 0;
   *n_candidates = 0;
   // 1. flip sets
+  const BlockTrim trim{ctx};
   FlipSets F;
   rc = flip_sets_device(ctx, *h, w_max, F);
   if (rc) return rc;
   const int64_t nc = F.qubits;
   *n_candidates = nc;
-  // Work memory past the flip sets: candidates, gradients, selection, scalars.
-  // The flip sets move to the front of the new block when it has to grow.
   const int k = (int)(n_select < nc ? n_select : nc);
   const int64_t row = 1 + 2 * W;
-  const int64_t head = F.ld ? (int64_t)((char*)(F.fx + (size_t)W * F.ld) - ctx->work) : 64;
-  int64_t need = head + 8 * ((2 * W + 1) * nc + row * k + 8);
-  if (need > ctx->n_work) {
-    need += need / 4;
-    char* bigger = nullptr;
-    HIP_TRY(ctx, hipMalloc(&bigger, (size_t)need));
-    if (F.ld) HIP_TRY(ctx, hipMemcpy(bigger, ctx->work, (size_t)head, hipMemcpyDeviceToDevice));
-    if (F.ld) F.fx = (uint64_t*)(bigger + ((char*)F.fx - ctx->work));
-    F.count = (unsigned long long*)bigger;
-    if (ctx->work) hipFree(ctx->work);
-    ctx->work = bigger;
-    ctx->n_work = need;
-  }
-  uint64_t* dcx = (uint64_t*)(ctx->work + head);
+  // candidates, gradients, selection, scalars
+  rc = ensure_block(ctx, ctx->cand, ctx->n_cand, 8 * ((2 * W + 1) * nc + row * k + 8));
+  if (rc) return rc;
+  uint64_t* dcx = (uint64_t*)ctx->cand;
   uint64_t* dcz = dcx + (size_t)W * nc;
   double* dg = (double*)(dcz + (size_t)W * nc);
   double* dsel = dg + nc;
