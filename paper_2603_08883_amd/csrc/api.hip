@@ -1399,6 +1399,37 @@ int iqcc_flip_sets(iqcc_ctx* ctx, const iqcc_store* h, int w_max, uint64_t* fx, 
   return IQCC_OK;
 }
 
+// The k candidates of largest |g| on the host, zero and NaN gradients left out, as
+// rows {g, x words, z words} in sel.
+static int rank_candidates(iqcc_ctx* ctx, int W, const double* dg, const uint64_t* dcx, int64_t nc, int k,
+                           std::vector<double>& sel) {
+  std::vector<double> g(nc);
+  std::vector<uint64_t> key(2 * (size_t)W * nc);   // x planes, then z planes
+  HIP_TRY(ctx, hipMemcpy(g.data(), dg, sizeof(double) * nc, hipMemcpyDeviceToHost));
+  HIP_TRY(ctx, hipMemcpy(key.data(), dcx, sizeof(uint64_t) * key.size(), hipMemcpyDeviceToHost));
+  std::vector<int64_t> idx;
+  for (int64_t i = 0; i < nc; ++i)
+    if (std::fabs(g[i]) > 0.0) idx.push_back(i);
+  const size_t n = idx.size() < (size_t)k ? idx.size() : (size_t)k;
+  std::partial_sort(idx.begin(), idx.begin() + n, idx.end(), [&](int64_t a, int64_t b) {
+    const double ga = std::fabs(g[a]), gb = std::fabs(g[b]);
+    if (ga != gb) return ga > gb;
+    for (int half = 0; half < 2; ++half)   // canonical order: x words from the most significant down, then z
+      for (int w = W - 1; w >= 0; --w) {
+        const uint64_t* plane = &key[(size_t)(half * W + w) * nc];
+        if (plane[a] != plane[b]) return plane[a] < plane[b];
+      }
+    return false;
+  });
+  sel.resize((1 + 2 * W) * n);
+  for (size_t j = 0; j < n; ++j) {
+    double* r = &sel[(1 + 2 * W) * j];
+    r[0] = g[idx[j]];
+    for (int q = 0; q < 2 * W; ++q) std::memcpy(r + 1 + q, &key[(size_t)q * nc + idx[j]], sizeof(uint64_t));
+  }
+  return IQCC_OK;
+}
+
 int iqcc_qcc_iteration(iqcc_ctx* ctx, iqcc_store** h, iqcc_store** spare, const double* theta,
                        const double* phi, int w_max, int n_select, double eps, uint64_t* sel_x,
                        uint64_t* sel_z, double* sel_g, double* sel_tau, double* energy,
@@ -1422,13 +1453,14 @@ int iqcc_qcc_iteration(iqcc_ctx* ctx, iqcc_store** h, iqcc_store** spare, const 
   const int k = (int)(n_select < nc ? n_select : nc);
   const int64_t row = 1 + 2 * W;
   // candidates, gradients, selection, scalars
-  rc = ensure_block(ctx, ctx->cand, ctx->n_cand, 8 * ((2 * W + 1) * nc + row * k + 8));
+  const bool on_device = k <= kTopCandidates;
+  rc = ensure_block(ctx, ctx->cand, ctx->n_cand, 8 * ((2 * W + 1) * nc + row * kTopCandidates + 8));
   if (rc) return rc;
   uint64_t* dcx = (uint64_t*)ctx->cand;
   uint64_t* dcz = dcx + (size_t)W * nc;
   double* dg = (double*)(dcz + (size_t)W * nc);
   double* dsel = dg + nc;
-  double* d_e = dsel + row * k;   // [0] energy, [1] next energy, [2] b, [3] c
+  double* d_e = dsel + (on_device ? row * k : 0);   // [0] energy, [1] next energy, [2] b, [3] c
   rc = iqcc_qmf_energy(ctx, *h, theta, phi, d_e, nullptr);
   if (rc) return rc;
   double sc[4];
@@ -1441,14 +1473,22 @@ int iqcc_qcc_iteration(iqcc_ctx* ctx, iqcc_store** h, iqcc_store** spare, const 
   launch_candidates(W, F.fx, F.ld, F.sets, dcx, dcz, nc, F.count, nullptr);
   rc = iqcc_dis_gradients(ctx, *h, theta, phi, dcx, dcz, nc, nc, IQCC_DIS_BATCHED, dg, nullptr);
   if (rc) return rc;
-  launch_top_candidates(W, dg, dcx, dcz, nc, k, dsel, nullptr);
-  LAUNCH_CHECK(ctx);
-  std::vector<double> sel((size_t)row * k + 1);
-  HIP_TRY(ctx, hipMemcpy(sel.data(), dsel, sizeof(double) * sel.size(), hipMemcpyDeviceToHost));
-  energy[0] = sel[(size_t)row * k];
+  std::vector<double> sel;
+  if (on_device) {
+    launch_top_candidates(W, dg, dcx, dcz, nc, k, dsel, nullptr);
+    LAUNCH_CHECK(ctx);
+    sel.resize((size_t)row * k + 1);   // and the energy
+    HIP_TRY(ctx, hipMemcpy(sel.data(), dsel, sizeof(double) * sel.size(), hipMemcpyDeviceToHost));
+    energy[0] = sel.back();
+  } else {
+    rc = rank_candidates(ctx, W, dg, dcx, nc, k, sel);
+    if (rc) return rc;
+    HIP_TRY(ctx, hipMemcpy(energy, d_e, 8, hipMemcpyDeviceToHost));
+  }
+  const int ranked = (int)(sel.size() / row);
   // 4. one closed-form step per selected generator, in rank order; zero
   // gradients are never taken
-  for (int j = 0; j < k; ++j) {
+  for (int j = 0; j < ranked; ++j) {
     const double* r = &sel[(size_t)row * j];
     if (!(std::fabs(r[0]) > 0.0)) break;
     uint64_t px[kMaxWords], pz[kMaxWords];

@@ -816,7 +816,9 @@ void launch_flip_unique(int W, const StoreDev& st, int w_max, unsigned long long
 // One candidate per qubit of each of the nf sets, nc in all (planes of nc).
 void launch_candidates(int W, const uint64_t* fx, int64_t ld, int64_t nf, uint64_t* cx, uint64_t* cz, int64_t nc,
                        unsigned long long* count, hipStream_t s);
-// The k <= nc candidates of largest |g|, as rows {g, x words, z words}.
+// The k <= nc candidates of largest |g|, as rows {g, x words, z words}; meant for
+// few (see there).
+constexpr int kTopCandidates = 32;
 void launch_top_candidates(int W, const double* g, const uint64_t* cx, const uint64_t* cz, int64_t nc, int k,
                            double* out, hipStream_t s);
 // Sums over the terms that anticommute with P: c <K>, and (c_out not null) the

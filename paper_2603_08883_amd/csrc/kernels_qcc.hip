@@ -138,11 +138,13 @@ void launch_candidates(int W, const uint64_t* fx, int64_t ld, int64_t nf, uint64
 }
 
 // The k candidates of largest |g| (equal |g|: ascending canonical key; a
-// gradient that is no number ranks last), one workgroup: every thread keeps
+// gradient that is no number ranks last), for few of them, one workgroup: every thread keeps
 // the best of its share that has not been taken, a tree over the workgroup
 // finds the best of those, and only the thread that held it looks for its
 // next.  The order is total (candidates are distinct), so "not taken" is
-// "after the last one taken".  out: k rows {g, x words, z words}.
+// "after the last one taken".  out: k rows {g, x words, z words}.  A pick takes
+// 8 us among 12,000 candidates, so more than kTopCandidates are ranked by the
+// host.
 constexpr int kTopBlock = 1024;
 static_assert(kTopBlock / 64 == 16, "the second tree spans 16 waves");
 
@@ -282,15 +284,16 @@ __global__ __launch_bounds__(kBlock) void k_anti_sums(StoreDev st, Entangler P, 
         kx[w] = st.x[w * st.cap + off + i];
         kz[w] = st.z[w * st.cap + off + i];
       }
+      double c = 0.0;
+      if (C) c = st.c[off + i];   // (beside the key's test)
       if (!anticommutes<W>(kx, kz, P.px, P.pz)) continue;
-      const double c = st.c[off + i];
       if constexpr (C) {
         double ek, ekp;
         expect_split<W>(lut, P, kx, kz, ek, ekp);
         sb += c * ek;
         sc += product_phase<W>(kx, kz, P.px, P.pz) == 1 ? c * ekp : -(c * ekp);
       } else {
-        sb += c * expect_lut<W>(lut, kx, kz);
+        sb += st.c[off + i] * expect_lut<W>(lut, kx, kz);
       }
     }
   }
