@@ -892,9 +892,9 @@ __global__ __launch_bounds__(kIPB) void k_dress_inplace(StoreDev st, Entangler P
     const int64_t pair_terms = G.selfp ? mean : 2 * mean;
     const int maxp = G.selfp ? kIPSlots : kIPSlots / 2;
     const int64_t nw = (int64_t)gridDim.x * kIPW;
-    int most = 1;   // pairs that the stash holds
+    int most = 1;   // pairs that the stash is expected to hold
     while (most * 2 <= maxp && (int64_t)most * 2 * pair_terms <= cfg.item_terms) most *= 2;
-    const int ppi = item_pairs(G.npairs, most, nw);
+    const int ppi = item_pairs(n_in, G.npairs, most, cfg.cap, nw);
     G.ppi = ppi;
     G.nitems = (G.npairs + ppi - 1) / ppi;
     // bucket tables two items ahead, term slices one item ahead

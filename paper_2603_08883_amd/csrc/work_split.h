@@ -75,18 +75,27 @@ constexpr int64_t dis_range_buckets(int64_t rows, int64_t buckets, int max_range
   return fill < least ? least : (fill > buckets ? buckets : fill);
 }
 
-// Pairs per item of an in-place step, a power of two up to `most` (what the stash
-// of a wave holds), for nw waves.  A wave's chain of loads, join and stores takes
-// about as long for 6 terms as for 192.  So where one item a wave is enough, the
-// smallest such items are taken (4096 buckets of 3 terms: 64 items of 32 pairs on
-// 64 waves 24 to 38 us a step, 2048 of one pair 13 us; 65536 buckets of 3 two-word
-// terms: 8192 items 51 us with the host's part, 2048 of 16 pairs 39), else at
-// least two items a wave (2^18 buckets of 4 terms: 92 us with 4096 items for
+// Pairs per item of an in-place step of `rows` terms, a power of two up to `most`
+// (whose anticommuting terms the stash of `cap` entries of a wave is expected to
+// hold), for nw waves.  A wave's chain of loads, join and stores takes about as
+// long for 6 terms as for the 128 that it loads at once.  So where items of at most
+// that many, and of half the stash if all of them anticommute (a larger set goes
+// to the store's pool, which costs more than a round), make one round of the
+// waves, the smallest such are taken: 4096 buckets of 3 terms: 64 items of 32
+// pairs on 64 waves 24 to 38 us a step, 2048 of one pair 13 us; 65536 buckets of 3
+// two-word terms: 8192 items 51 us with the host's part, 2048 of 16 pairs 39.  Else
+// at least two items a wave (2^18 buckets of 4 terms: 92 us with 4096 items for
 // 3072 waves, 80 us with 8192).
-constexpr int item_pairs(int64_t npairs, int most, int64_t nw) {
-  const bool one = (npairs + most - 1) / most <= nw;
+constexpr int item_pairs(int64_t rows, int64_t npairs, int most, int cap, int64_t nw) {
+  const int64_t terms = cap / 2 < 128 ? cap / 2 : 128;
+  int one = 1;
+  while (one * 2 <= most && rows * one * 2 <= terms * npairs) one *= 2;
   int n = 1;
-  while (n < most && (one ? (npairs + n - 1) / n > nw : npairs / (n * 2) >= 2 * nw)) n *= 2;
+  if ((npairs + one - 1) / one <= nw) {
+    while ((npairs + n - 1) / n > nw) n *= 2;
+  } else {
+    while (n < most && npairs / (n * 2) >= 2 * nw) n *= 2;
+  }
   return n;
 }
 

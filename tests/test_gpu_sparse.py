@@ -48,3 +48,29 @@ def test_sparse_store(nq, n, max_terms, n_cand):
                                             (150, 900, 1 << 22), (250, 3000, 1 << 21)])
 def test_sparse_inplace_steps(nq, n, max_terms):
     inplace_steps(nq, n, max_terms)
+
+
+@pytest.mark.parametrize("nq,n,max_terms", [(40, 60_000, 1 << 22), (100, 300_000, 1 << 22), (170, 300_000, 9_000_000),
+                                            (250, 300_000, 9_000_000), (250, 30_000, 1 << 22)])
+@pytest.mark.parametrize("energy", [False, True])
+def test_items_fit_the_stash(nq, n, max_terms, energy):
+    """Wide keys leave little stash: items are not made so large, to be few, that
+    their anticommuting terms have to go to the store's pool."""
+    ctx = iqcc.Context(0)
+    g = torch.Generator(device="cuda").manual_seed(nq)
+    W = (nq + 63) // 64
+    x, z = (torch.randint(0, 1 << (nq % 64 or 62), (W, n), dtype=torch.int64, device="cuda", generator=g) for _ in range(2))
+    c = torch.randn(n, dtype=torch.float64, device="cuda", generator=g)
+    th, ph = (torch.from_numpy(a).cuda() for a in I.qmf_angles(nq, np.random.default_rng(nq)))
+    s = iqcc.Store(ctx, nq, max_terms, iqcc.IQCC_STORE_INPLACE)
+    iqcc.iqcc_store_load(ctx.handle, s.handle, x, z, c)
+    assert len(torch.unique(x[0])) == n      # distinct keys
+    p = I.single_qubit_pauli(nq, "XYZ")
+    e = torch.zeros(1, dtype=torch.float64, device="cuda")
+    for step in range(4):                    # the second step finds every image: two thirds anticommute
+        describe(step, "items fit the stash", nq=nq, n=n, max_terms=max_terms, energy=energy)
+        iqcc.iqcc_dress_inplace(ctx.handle, s.handle, *p, 0.1, 0.0, *((th, ph, None, e) if energy else ()))
+        assert iqcc.iqcc_store_inplace_stats(ctx.handle, s.handle)["relocated"] == 0
+    s.count()
+    s.close()
+    ctx.close()

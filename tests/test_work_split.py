@@ -20,8 +20,8 @@ int main() {
   long long rows, buckets, grid, threads, cand;
   char kind;
   while (std::scanf(" %c %lld %lld %lld %lld %lld", &kind, &rows, &buckets, &grid, &threads, &cand) == 6) {
-    if (kind == 'i') {   // pairs, most a stash holds, waves
-      std::printf("%d\n", item_pairs(rows, (int)buckets, grid));
+    if (kind == 'i') {   // rows, pairs, most pairs of an item, stash, waves
+      std::printf("%d\n", item_pairs(rows, buckets, (int)grid, (int)threads, cand));
       continue;
     }
     if (kind == 'd') {   // grid: most ranges; threads: compute units
@@ -87,14 +87,24 @@ def test_dis_ranges(split, n_cand):
 
 
 @pytest.mark.parametrize("waves", [12, 3072])
-def test_inplace_items(split, waves):
-    cases = [("i", 1 << p, 1 << m, waves, 0, 0) for p in range(0, 28) for m in range(0, 6)]
-    for (_, pairs, most, *_), (n,) in zip(cases, split(cases)):
+@pytest.mark.parametrize("cap", [40, 200, 400])
+def test_inplace_items(split, waves, cap):
+    cases = []
+    for p in range(0, 28):
+        for per in (0.01, 0.3, 1, 6, 20, 60, 300):      # terms a pair
+            most = 1
+            while most * 2 <= 32 and most * 2 * max(per, 2) <= 1.5 * cap:
+                most *= 2
+            cases.append(("i", int(per * (1 << p)), 1 << p, most, cap, waves))
+    for (_, rows, pairs, most, *_), (n,) in zip(cases, split(cases)):
         assert 1 <= n <= most and n & (n - 1) == 0
-        items = ceil(pairs, n)
-        if ceil(pairs, most) <= waves:      # one item a wave, as small as that allows
-            assert items <= waves and (n == 1 or ceil(pairs, n // 2) > waves), (pairs, most, n)
-        elif n > 1:                         # at least two items a wave
-            assert items >= 2 * waves, (pairs, most, n)
-        if items >= 4 * waves:              # and no smaller than that needs
-            assert n == most, (pairs, most, n)
+        items, per = ceil(pairs, n), rows / pairs
+        fits = [m for m in (1, 2, 4, 8, 16, 32) if m <= most and (m == 1 or m * per <= min(128, cap / 2))]
+        if ceil(pairs, fits[-1]) <= waves:      # one round, of items as small as that allows
+            assert items <= waves and (n == 1 or ceil(pairs, n // 2) > waves), (rows, pairs, most, n)
+        elif n > 1:                             # at least two items a wave
+            assert items >= 2 * waves, (rows, pairs, most, n)
+        if items < 2 * waves and n > 1:         # never by items that may pass the stash
+            assert n * per <= cap / 2, (rows, pairs, most, n)
+        if items >= 4 * waves:                  # and no smaller than that needs
+            assert n == most, (rows, pairs, most, n)
