@@ -501,7 +501,7 @@ int iqcc_qmf_energy_anti(iqcc_ctx *ctx, const iqcc_store *h, const uint64_t *px,
  * n_words words.  *n receives the count; IQCC_ERR_CAPACITY (fx untouched) when
  * it exceeds cap.  Matching a flip set of H is the second DIS condition of
  * App. A.  Working memory: 16 to 32 bytes and 8 W a term, 25 % more; the context
- * keeps up to 128 MB of it for the next call. */
+ * keeps up to 1 GiB of it for the next call. */
 int iqcc_flip_sets(iqcc_ctx *ctx, const iqcc_store *h, int w_max, uint64_t *fx, int64_t cap,
                    int64_t *n);
 
@@ -524,7 +524,7 @@ int iqcc_flip_sets(iqcc_ctx *ctx, const iqcc_store *h, int w_max, uint64_t *fx, 
  * [n_select + 1] (energy before the first step and after each), the number of
  * candidates and the number of generators applied (<= n_select).  Working
  * memory: that of iqcc_flip_sets, and 16 W + 8 bytes a candidate, 25 % more, of
- * which the context keeps up to 128 MB too. */
+ * which the context keeps up to 1 GiB too. */
 int iqcc_qcc_iteration(iqcc_ctx *ctx, iqcc_store **h, iqcc_store **spare, const double *theta,
                        const double *phi, int w_max, int n_select, double eps, uint64_t *sel_x,
                        uint64_t *sel_z, double *sel_g, double *sel_tau, double *energy,

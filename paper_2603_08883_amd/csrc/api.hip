@@ -170,8 +170,9 @@ int ensure_block(iqcc_ctx* ctx, char*& p, int64_t& n, int64_t bytes) {
 
 // At the end of a call, the blocks that it filled: a large one (16 to 32 bytes
 // and 8 W a term) is given back, a small one, whose allocation would be a good
-// part of the call, stays.
-constexpr int64_t kKeptBlock = 128ll << 20;
+// part of the call, stays (144 MB for 3e6 two-word terms: 142 us a call, 825 with
+// the block freed each time).
+constexpr int64_t kKeptBlock = 1ll << 30;
 
 struct BlockTrim {
   iqcc_ctx* ctx;
