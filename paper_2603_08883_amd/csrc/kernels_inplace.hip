@@ -890,13 +890,12 @@ __global__ __launch_bounds__(kIPB) void k_dress_inplace(StoreDev st, Entangler P
     G.npairs = G.f ? (1ll << (m - 1)) : (1ll << m);
     const int64_t mean = (n_in >> m) > 0 ? (n_in >> m) : 1;
     const int64_t pair_terms = G.selfp ? mean : 2 * mean;
-    const int maxp = G.selfp ? kIPSlots : kIPSlots / 2;
+    const int maxp = log2_floor(G.selfp ? kIPSlots : kIPSlots / 2);
     const int64_t nw = (int64_t)gridDim.x * kIPW;
-    int most = 1;   // pairs that the stash is expected to hold
-    while (most * 2 <= maxp && (int64_t)most * 2 * pair_terms <= cfg.item_terms) most *= 2;
-    const int ppi = item_pairs(n_in, G.npairs, most, cfg.cap, nw);
-    G.ppi = ppi;
-    G.nitems = (G.npairs + ppi - 1) / ppi;
+    const int fit = doublings(pair_terms, cfg.item_terms);   // (the stash is expected to hold)
+    const int e = item_pairs_log2(n_in, G.npairs, fit < maxp ? fit : maxp, cfg.cap, nw);
+    G.ppi = 1 << e;
+    G.nitems = (G.npairs + G.ppi - 1) >> e;
     // bucket tables two items ahead, term slices one item ahead
     SlotDesc d_next;
     if (gw + nw < G.nitems) d_next = load_desc(st, G, gw + nw);

@@ -27,12 +27,13 @@ struct BucketSplit {
 constexpr BucketSplit split_buckets(int64_t rows, int64_t buckets, int64_t grid, int64_t rows_each, int64_t most) {
   const int64_t by_rows = (rows + rows_each - 1) / rows_each;
   const int64_t by_buckets = (buckets + most - 1) / most;
-  int64_t want = by_rows > by_buckets ? by_rows : by_buckets;
-  want = want < 1 ? 1 : (want > grid ? grid : want);
-  want = want > buckets ? buckets : want;
-  int64_t G = (buckets + want - 1) / want;
-  G = G > most ? most : G;
-  const int64_t ngroups = (buckets + G - 1) / G;
+  int64_t want64 = by_rows > by_buckets ? by_rows : by_buckets;
+  want64 = want64 < 1 ? 1 : (want64 > grid ? grid : want64);
+  // (32 bits: a 64-bit division is a good part of a microsecond on the device)
+  const uint32_t B = (uint32_t)buckets, want = want64 > buckets ? B : (uint32_t)want64;
+  uint32_t G = (B + want - 1) / want;
+  G = G > (uint32_t)most ? (uint32_t)most : G;
+  const uint32_t ngroups = (B + G - 1) / G;
   return {(int)G, (int)ngroups, (int)(ngroups < want ? ngroups : want)};
 }
 
@@ -75,9 +76,19 @@ constexpr int64_t dis_range_buckets(int64_t rows, int64_t buckets, int max_range
   return fill < least ? least : (fill > buckets ? buckets : fill);
 }
 
-// Pairs per item of an in-place step of `rows` terms, a power of two up to `most`
-// (whose anticommuting terms the stash of `cap` entries of a wave is expected to
-// hold), for nw waves.  A wave's chain of loads, join and stores takes about as
+// floor(log2(v)), v >= 1
+constexpr int log2_floor(uint64_t v) { return 63 - __builtin_clzll(v); }
+
+// The largest e >= 0 with a 2^e <= b (0 if there is none); a, b >= 1 below 2^62.
+constexpr int doublings(uint64_t a, uint64_t b) {
+  int e = log2_floor(b) - log2_floor(a);
+  if (e > 0 && a << e > b) --e;
+  return e > 0 ? e : 0;
+}
+
+// Pairs per item of an in-place step of `rows` terms in `npairs` pairs (a power of
+// two), as a power of two up to 2^most (whose anticommuting terms the stash of
+// `cap` entries of a wave is expected to hold), for nw waves.  A wave's chain of loads, join and stores takes about as
 // long for 6 terms as for the 128 that it loads at once.  So where items of at most
 // that many, and of half the stash if all of them anticommute (a larger set goes
 // to the store's pool, which costs more than a round), make one round of the
@@ -86,17 +97,16 @@ constexpr int64_t dis_range_buckets(int64_t rows, int64_t buckets, int max_range
 // two-word terms: 8192 items 51 us with the host's part, 2048 of 16 pairs 39.  Else
 // at least two items a wave (2^18 buckets of 4 terms: 92 us with 4096 items for
 // 3072 waves, 80 us with 8192).
-constexpr int item_pairs(int64_t rows, int64_t npairs, int most, int cap, int64_t nw) {
+// (No loops: every wave works this out before its first load.)
+constexpr int item_pairs_log2(int64_t rows, int64_t npairs, int most, int cap, int64_t nw) {
+  const int p = log2_floor(npairs);
   const int64_t terms = cap / 2 < 128 ? cap / 2 : 128;
-  int one = 1;
-  while (one * 2 <= most && rows * one * 2 <= terms * npairs) one *= 2;
-  int n = 1;
-  if ((npairs + one - 1) / one <= nw) {
-    while ((npairs + n - 1) / n > nw) n *= 2;
-  } else {
-    while (n < most && npairs / (n * 2) >= 2 * nw) n *= 2;
-  }
-  return n;
+  int one = doublings(rows > 0 ? rows : 1, terms * npairs);
+  one = one < most ? one : most;
+  const int round = p - log2_floor(nw);             // so that the items are no more than the waves
+  if (round <= one) return round > 0 ? round : 0;
+  const int two = p - log2_floor(2 * nw - 1) - 1;   // twice the waves or more
+  return two < 0 ? 0 : (two < most ? two : most);
 }
 
 }  // namespace iqcc

@@ -20,8 +20,12 @@ int main() {
   long long rows, buckets, grid, threads, cand;
   char kind;
   while (std::scanf(" %c %lld %lld %lld %lld %lld", &kind, &rows, &buckets, &grid, &threads, &cand) == 6) {
+    if (kind == 'l') {
+      std::printf("%d\n", doublings(rows, buckets));
+      continue;
+    }
     if (kind == 'i') {   // rows, pairs, most pairs of an item, stash, waves
-      std::printf("%d\n", item_pairs(rows, buckets, (int)grid, (int)threads, cand));
+      std::printf("%d\n", 1 << item_pairs_log2(rows, buckets, log2_floor(grid), (int)threads, cand));
       continue;
     }
     if (kind == 'd') {   // grid: most ranges; threads: compute units
@@ -108,3 +112,9 @@ def test_inplace_items(split, waves, cap):
             assert n * per <= cap / 2, (rows, pairs, most, n)
         if items >= 4 * waves:                  # and no smaller than that needs
             assert n == most, (rows, pairs, most, n)
+
+
+def test_doublings(split):
+    cases = [("l", a, b, 0, 0, 0) for a in (1, 2, 3, 5, 8, 100, 12_345_678) for b in (1, 2, 3, 4, 7, 300, 301, 1 << 40)]
+    for (_, a, b, *_), (e,) in zip(cases, split(cases)):
+        assert e >= 0 and (e == 0 or a << e <= b) and a << (e + 1) > b, (a, b, e)
