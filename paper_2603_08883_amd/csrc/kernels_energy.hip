@@ -559,7 +559,9 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
   // Workgroup g takes the groups of G consecutive buckets g, g + active, ...;
   // a group's rows are one flat range, one term per thread and pass, the next
   // pass's term loaded while this one's bits are multiplied.
-  for (int grp = blockIdx.x; grp < ngroups; grp += active) {
+  // A group of more than kCarryTerms rows is walked in parts, i_first the first row.
+  uint32_t i_first = 0;
+  for (int grp = blockIdx.x; grp < ngroups;) {
     const int b = grp * G + (int)threadIdx.x;
     const bool mine = (int)threadIdx.x < G && b < B;
     const int64_t cnt = mine ? st.cnt[b] : 0;
@@ -575,7 +577,8 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
     __syncthreads();
     const int64_t base = sh.s_off[0];   // one range of rows, as in the energy
     const bool contig = __syncthreads_and(!mine || off - (int64_t)ex == base) != 0;
-    const uint32_t n = (uint32_t)total;
+    constexpr uint32_t kPart = kCarryTerms / NT * NT;
+    const uint32_t n = !CARRY || (uint32_t)total - i_first < kPart ? (uint32_t)total : i_first + kPart;
     uint64_t kx[W], kz[W];
     double c;
     int64_t row;
@@ -601,11 +604,8 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
         c = __builtin_nontemporal_load(&st.c[row]);
       }
     };
-    load(threadIdx.x);
-    for (uint32_t i0 = 0; i0 < n;) {
-     constexpr uint32_t kPart = kCarryTerms / NT * NT;
-     const uint32_t part_n = !CARRY || n - i0 < kPart ? n - i0 : kPart;
-     for (const uint32_t stop = i0 + part_n; i0 < stop; i0 += NT) {
+    load(i_first + threadIdx.x);
+    for (uint32_t i0 = i_first; i0 < n; i0 += NT) {
       const bool live = i0 + threadIdx.x < n;
       const bool has_terms = i0 + 64 * wave < n;   // of the wave
       double v = 0.0, all = 1.0;
@@ -675,17 +675,19 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
         }
       }
       team_arrive(&sh.arrived[team], target, TW);
-     }
-     if (CARRY) {
-       if (((nwg + part_n) ^ nwg) / kCarryTerms) {
-         carry_digits(sx, lane);
-         carry_digits(sz, lane);
-         carry_digits(sy, lane);
-       }
-       nwg += part_n;
-       ok = ok && nwg < 1u << 31;
-     }
     }
+    if (CARRY) {
+      const uint32_t done = nwg + (n - i_first);
+      if ((done ^ nwg) / kCarryTerms) {
+        carry_digits(sx, lane);
+        carry_digits(sz, lane);
+        carry_digits(sy, lane);
+      }
+      nwg = done;
+      ok = ok && nwg < 1u << 31;
+      i_first = n < (uint32_t)total ? n : 0u;
+    }
+    if (i_first == 0) grp += active;
   }
   if (!ok) sh.bad = 1;
   __syncthreads();
