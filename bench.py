@@ -113,7 +113,7 @@ def profiled_traffic(ctx):
             k, v = line.split(":", 1)
             fields[k.strip()] = v.strip()
     h = hashlib.sha256()
-    for f in ("kernels_inplace.hip", "iqcc_internal.h"):
+    for f in ("kernels_inplace.hip", "iqcc_internal.h", "work_split.h"):
         with open(os.path.join(here, "paper_2603_08883_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     knobs = " ".join(f"{k}={iqcc.iqcc_get_param(ctx.handle, k)}"
@@ -141,9 +141,11 @@ def dis_ops_per_pair():
         if ":" in line and not line.startswith(" "):
             k, v = line.split(":", 1)
             fields[k.strip()] = v.strip()
-    with open(os.path.join(here, "paper_2603_08883_amd", "csrc", "kernels_dis.hip"), "rb") as fh:
-        sha = hashlib.sha256(fh.read()).hexdigest()
-    if fields.get("kernel_source_sha256") != sha:
+    h = hashlib.sha256()
+    for f in ("kernels_dis.hip", "work_split.h"):
+        with open(os.path.join(here, "paper_2603_08883_amd", "csrc", f), "rb") as fh:
+            h.update(fh.read())
+    if fields.get("kernel_source_sha256") != h.hexdigest():
         return None
     try:
         return float(fields["valu_lane_ops_per_pair"])

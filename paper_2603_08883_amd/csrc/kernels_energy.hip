@@ -389,7 +389,7 @@ void launch_energy(int W, int nq, const StoreDev& st, bool regions, int n_cu, in
 // Bound: VALU issue (about 510 instructions per 64 two-word terms: 128 for the
 // product, 100 for digits and bytes, 160 for the bit operands) and the waits of
 // three waves per SIMD; 24 matrix products of 32 cycles run beside.  4e6
-// two-word terms: 94 us; with every (term, group) value added to integer tables
+// two-word terms: 88 us; with every (term, group) value added to integer tables
 // in LDS by two 64-bit atomics 203 us.  1.1e6 one-word terms: 26 us (67 us).
 // acc layout: [3 * nq][workgroups] with sigma order X, Z, Y.
 // ---------------------------------------------------------------------------
@@ -404,10 +404,6 @@ struct BwdGeom {
 constexpr int kDigits = 32;
 constexpr int kDigitStride = 80;   // bytes per digit row of 64 terms (padded: 16-byte reads of 8 lanes hit all banks)
 constexpr int kDigitBase = -186;   // log2 of the lowest digit's weight
-// Rows of an arena from which a workgroup may hold so many terms that its digit
-// sums need carries: 127 x 2^24 is below 2^31.  (The kernel without them is 1 to
-// 2 % faster with wide keys.)
-constexpr int64_t kCarryRows = 1ll << 24;
 // Terms of a workgroup after which its digit sums are carried: a sum stays below
 // 127 x 2 kCarryTerms of new digits and what a carry leaves, 127 + 2 kCarryTerms in
 // each wave.
@@ -511,7 +507,7 @@ __device__ __forceinline__ void team_wait(const unsigned* arrived, unsigned targ
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-template <int W, bool CARRY>
+template <int W>
 __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st, int nq, const double* theta,
                                                                      const double* phi, const double* dE,
                                                                      double* lam, double* acc_g) {
@@ -578,7 +574,7 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
     const int64_t base = sh.s_off[0];   // one range of rows, as in the energy
     const bool contig = __syncthreads_and(!mine || off - (int64_t)ex == base) != 0;
     constexpr uint32_t kPart = kCarryTerms / NT * NT;
-    const uint32_t n = !CARRY || (uint32_t)total - i_first < kPart ? (uint32_t)total : i_first + kPart;
+    const uint32_t n = (uint32_t)total - i_first < kPart ? (uint32_t)total : i_first + kPart;
     uint64_t kx[W], kz[W];
     double c;
     int64_t row;
@@ -676,17 +672,15 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
       }
       team_arrive(&sh.arrived[team], target, TW);
     }
-    if (CARRY) {
-      const uint32_t done = nwg + (n - i_first);
-      if ((done ^ nwg) / kCarryTerms) {
-        carry_digits(sx, lane);
-        carry_digits(sz, lane);
-        carry_digits(sy, lane);
-      }
-      nwg = done;
-      ok = ok && nwg < 1u << 31;
-      i_first = n < (uint32_t)total ? n : 0u;
+    const uint32_t done = nwg + (n - i_first);
+    if ((done ^ nwg) / kCarryTerms) {
+      carry_digits(sx, lane);
+      carry_digits(sz, lane);
+      carry_digits(sy, lane);
     }
+    nwg = done;
+    ok = ok && nwg < 1u << 31;
+    i_first = n < (uint32_t)total ? n : 0u;
     if (i_first == 0) grp += active;
   }
   if (!ok) sh.bad = 1;
@@ -730,21 +724,14 @@ __global__ __launch_bounds__(BwdGeom<W>::kThreads) void k_energy_bwd(StoreDev st
   }
 }
 
-template <int W, bool CARRY>
-static int launch_bwd_t(int nq, const StoreDev& st, int grid, const double* theta, const double* phi,
-                        const double* dE, double* lam, double* acc, hipStream_t s) {
-  const size_t lds = sizeof(BwdShared<W>);
-  (void)hipFuncSetAttribute((const void*)k_energy_bwd<W, CARRY>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((k_energy_bwd<W, CARRY>), dim3(grid), dim3(BwdGeom<W>::kThreads), lds, s, st, nq, theta, phi, dE,
-                     lam, acc);
-  return BwdGeom<W>::kThreads;
-}
-
 template <int W>
 static int launch_bwd_w(int nq, const StoreDev& st, int grid, const double* theta, const double* phi,
                         const double* dE, double* lam, double* acc, hipStream_t s) {
-  return st.cap < kCarryRows ? launch_bwd_t<W, false>(nq, st, grid, theta, phi, dE, lam, acc, s)
-                             : launch_bwd_t<W, true>(nq, st, grid, theta, phi, dE, lam, acc, s);
+  const size_t lds = sizeof(BwdShared<W>);
+  (void)hipFuncSetAttribute((const void*)k_energy_bwd<W>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL(k_energy_bwd<W>, dim3(grid), dim3(BwdGeom<W>::kThreads), lds, s, st, nq, theta, phi, dE, lam,
+                     acc);
+  return BwdGeom<W>::kThreads;
 }
 
 // One workgroup per qubit: S[q][sigma] summed over the workgroups in a fixed
